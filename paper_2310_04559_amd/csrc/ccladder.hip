@@ -28,6 +28,7 @@
 #include "ccladder.h"
 #include "gemm.hpp"
 #include "gemm_direct.hpp"
+#include "gemm_wave.hpp"
 #include "plan.h"
 #include "split.hpp"
 
@@ -73,49 +74,45 @@ bool vec_ok(const T* p, long long ld) {
   return (reinterpret_cast<uintptr_t>(p) % 16) == 0 && (ld % per16) == 0;
 }
 
-// Products with both operands K-contiguous and 16-byte aligned rows take the
-// direct-to-LDS kernel (128 x 256 tiles, 8 waves); everything else the
-// register-staged family.
-template <class Tr, int EPI>
-bool launch_kc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, int* rc) {
-  if (!vec_ok(g0.A, g0.lda) || !vec_ok(g0.B, g0.ldb)) return false;
+// One launch of the K-contiguous direct-to-LDS kernel on BM x BN tiles.
+template <class Tr, int EPI, int BM, int BN>
+void launch_kc_tiles(const GemmArgs<typename Tr::T>& g0, hipStream_t stream) {
   GemmArgs<typename Tr::T> g = g0;
-  // the tiling whose grids finish first: 160-row tiles (float64), or 128-row
-  // tiles plus a 64-row launch over the remainder rows (plain or pair-mirrored
-  // accumulation, whose rows can be offset)
-  constexpr bool kTall = !Tr::kDrain;
-  constexpr bool kSplit = EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM;
-  long long main_rows = g.M;
-  const int bm = choose_kc_tiling(g.M, g.N, kTall, kSplit, &main_rows);
-  auto launch = [&](auto kernel, const GemmArgs<typename Tr::T>& a, int rows_per_tile) {
-    GemmArgs<typename Tr::T> b = a;
-    b.tiles_m = (b.M + rows_per_tile - 1) / rows_per_tile;
-    b.tiles_n = (b.N + kDBN - 1) / kDBN;
-    b.group_m = b.tiles_m < 16 ? b.tiles_m : 16;
-    const long long tiles = (long long)b.tiles_m * b.tiles_n;
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(tiles)), dim3(kDThreads), 0, stream, b);
-  };
-  if ((long long)((g.M + 63) / 64) * ((g.N + kDBN - 1) / kDBN) > 0x7fffffffLL) return false;
-  if (bm == 160) {
-    if constexpr (kTall) launch(gemm_kc_direct_kernel<Tr, EPI, 160>, g, 160);
-  } else if (bm == 64) {
-    if constexpr (kSplit) {
+  g.tiles_m = (g.M + BM - 1) / BM;
+  g.tiles_n = (g.N + BN - 1) / BN;
+  g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
+  hipLaunchKernelGGL((gemm_kc_direct_kernel<Tr, EPI, BM, BN>),
+                     dim3(static_cast<unsigned>((long long)g.tiles_m * g.tiles_n)), dim3(kDThreads),
+                     0, stream, g);
+}
+
+// Products with both operands K-contiguous and 16-byte aligned rows, on the tiles
+// that pick_tiles chose.
+template <class Tr, int EPI>
+int launch_kc_direct(const GemmArgs<typename Tr::T>& g0, const TilePick& pick, hipStream_t stream) {
+  GemmArgs<typename Tr::T> g = g0;
+  if ((long long)((g.M + 63) / 64) * ((g.N + 63) / 64) > 0x7fffffffLL) return CC_LADDER_EINVAL;
+  if (pick.bm == 160) {
+    if constexpr (!Tr::kDrain) launch_kc_tiles<Tr, EPI, 160, 256>(g, stream);
+  } else if (pick.bn == 64) {
+    launch_kc_tiles<Tr, EPI, 64, 64>(g, stream);
+  } else if (pick.bn == 128) {
+    launch_kc_tiles<Tr, EPI, 64, 128>(g, stream);
+  } else {
+    if (pick.main_rows < g.M) {  // 64-row tiles over the remainder rows
       GemmArgs<typename Tr::T> rest = g;
-      g.M = static_cast<int>(main_rows);
+      g.M = static_cast<int>(pick.main_rows);
       rest.M -= g.M;
-      rest.A += main_rows * g.lda;
+      rest.A += pick.main_rows * g.lda;
       if constexpr (EPI == EPI_PAIR || EPI == EPI_PM)
         rest.m_off = g.m_off + g.M;  // the mirrored store needs the global (i,j) row
       else
-        rest.C = static_cast<double*>(g.C) + main_rows * g.ldc;
-      launch(gemm_kc_direct_kernel<Tr, EPI>, g, kDBM);
-      launch(gemm_kc_direct_kernel<Tr, EPI, 64>, rest, 64);
+        rest.C = static_cast<double*>(g.C) + pick.main_rows * g.ldc;
+      launch_kc_tiles<Tr, EPI, 64, 256>(rest, stream);
     }
-  } else {
-    launch(gemm_kc_direct_kernel<Tr, EPI>, g, kDBM);
+    launch_kc_tiles<Tr, EPI, 128, 256>(g, stream);
   }
-  *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
-  return true;
+  return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
 // Offsets of the packed build's compact grid: row_tiles[tm] = number of needed
@@ -133,11 +130,15 @@ __global__ void pack_rows_kernel(int* row_tiles, int tiles_m, int tiles_n, int v
 
 // Integral builds (both operands row-contiguous, permuted or packed store) take
 // the direct-to-LDS RC kernel when rows are whole 16-byte chunks and aligned.
+template <class Tr>
+bool rc_direct_ok(const GemmArgs<typename Tr::T>& g) {
+  return vec_ok(g.A, g.lda) && vec_ok(g.B, g.ldb) && g.M % Tr::CH == 0 && g.N % Tr::CH == 0 &&
+         g.K > 0;
+}
+
 template <class Tr, int EPI>
 bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, int* rc) {
-  constexpr int CH = Tr::CH;
-  if (!vec_ok(g0.A, g0.lda) || !vec_ok(g0.B, g0.ldb)) return false;
-  if (g0.M % CH != 0 || g0.N % CH != 0 || g0.K <= 0) return false;
+  if (!rc_direct_ok<Tr>(g0)) return false;
   GemmArgs<typename Tr::T> g = g0;
   g.tiles_m = (g.M + kDBM - 1) / kDBM;
   g.tiles_n = (g.N + kDBN - 1) / kDBN;
@@ -183,11 +184,29 @@ bool launch_kr_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, in
   return true;
 }
 
+template <class Tr, int LA, int LB, int EPI, int SIDE>
+int launch_wave_side(const GemmArgs<typename Tr::T>& g0, int wk, hipStream_t stream) {
+  GemmArgs<typename Tr::T> g = g0;
+  constexpr int T = kWTile * SIDE;
+  g.tiles_m = (g.M + T - 1) / T;
+  g.tiles_n = (g.N + T - 1) / T;
+  const long long tiles = (long long)g.tiles_m * g.tiles_n;
+  if (tiles > 0x7fffffffLL) return CC_LADDER_EINVAL;
+  g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
+  hipLaunchKernelGGL((gemm_wave_kernel<Tr, LA, LB, EPI, SIDE, SIDE>),
+                     dim3(static_cast<unsigned>(tiles)), dim3(64 * SIDE * SIDE * wk),
+                     wave_lds_bytes(SIDE * SIDE, wk), stream, g);
+  return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+}
+
+// mt, nt: rows and columns of the whole output when this launch computes one
+// block of it (0: M, N).
 template <class Tr, int LA, int LB, int EPI>
 int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B, long long ldb,
                 void* C, long long ldc, int M, int N, int K, int v, int drain_steps,
                 hipStream_t stream, int o = 0, int a0 = 0, int* row_tiles = nullptr,
-                double alpha = 1.0, int pm = 0, int kband = 0, int m_keep = 0) {
+                double alpha = 1.0, int pm = 0, int kband = 0, int m_keep = 0, int mt = 0,
+                int nt = 0) {
   if (M <= 0 || N <= 0 || K <= 0) return CC_LADDER_OK;
   GemmArgs<typename Tr::T> g;
   g.alpha = alpha;
@@ -208,6 +227,31 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
                 Tr::kDirectRC) {
     int rc = CC_LADDER_OK;
     if (launch_rc_direct<Tr, EPI>(g, stream, &rc)) return rc;
+  }
+  // The tiles, by the whole output's extents and the kernels that the operands
+  // suit.  (Float32 row-contiguous products on the direct kernel, above, deal k to
+  // the MFMA slots in another order: a switch of kernels would change their sums.)
+  // The register-direct kernel has no K bands, and loads row-contiguous operands
+  // by pairs of rows.
+  constexpr bool kKC = LA == KC && LB == KC && Tr::kDirectKC;
+  constexpr bool kKR = LA == KC && LB == RC && EPI == EPI_ACC && Tr::kDirectKR;
+  const bool aligned = vec_ok(A, lda) && vec_ok(B, ldb);
+  const bool direct = aligned && (kKC || (kKR && N % Tr::CH == 0));
+  const int nk = (K + Tr::BK - 1) / Tr::BK;
+  const TilePick pick =
+      pick_tiles(!direct ? kTilesStaged : kKC ? kTilesKC : kTilesKR, M, N, K, mt ? mt : M,
+                 nt ? nt : N, Tr::kDrain ? (nk + g.drain_steps - 1) / g.drain_steps : nk,
+                 sizeof(typename Tr::T), !Tr::kDrain,
+                 EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM);
+  if (pick.side && !kband && (LA == KC || M >= 2) && (LB == KC || N >= 2))
+    return pick.side == 1 ? launch_wave_side<Tr, LA, LB, EPI, 1>(g, pick.wk, stream)
+                          : launch_wave_side<Tr, LA, LB, EPI, 2>(g, pick.wk, stream);
+  if constexpr (kKC) {
+    if (direct) return launch_kc_direct<Tr, EPI>(g, pick, stream);
+  }
+  if constexpr (kKR) {
+    int rc = CC_LADDER_OK;
+    if (direct && launch_kr_direct<Tr>(g, stream, &rc)) return rc;
   }
   g.tiles_m = (M + kBM - 1) / kBM;
   g.tiles_n = (N + kBN - 1) / kBN;
@@ -230,20 +274,8 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
                        g.tiles_n, v, kBM, kBN);
     grid = dim3(static_cast<unsigned>(needed));
   }
-  if constexpr (LA == KC && LB == KC && (EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM) &&
-                Tr::kDirectKC) {
-    int rc = CC_LADDER_OK;
-    if (launch_kc_direct<Tr, EPI>(g, stream, &rc)) return rc;
-  }
-  if constexpr (LA == KC && LB == RC && EPI == EPI_ACC && Tr::kDirectKR) {
-    int rc = CC_LADDER_OK;
-    if (launch_kr_direct<Tr>(g, stream, &rc)) return rc;
-  }
   const dim3 block(kThreads);
-  if (vec_ok(A, lda) && vec_ok(B, ldb))
-    hipLaunchKernelGGL((gemm_kernel<Tr, LA, LB, EPI, true>), grid, block, 0, stream, g);
-  else
-    hipLaunchKernelGGL((gemm_kernel<Tr, LA, LB, EPI, false>), grid, block, 0, stream, g);
+  hipLaunchKernelGGL((gemm_kernel<Tr, LA, LB, EPI>), grid, block, 0, stream, g);
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
@@ -263,16 +295,18 @@ __global__ __launch_bounds__(256) void part_reduce_kernel(const double* __restri
 
 // C[m*ldc + n] += sum_k A[m*lda + k] B[n*ldb + k] with K cut into `splits`
 // ranges of whole K-steps, one workgroup per (tile, range), float64 partials in
-// `part` (splits * M * N) and an ordered reduction.  For products whose tile grid
+// `part` (splits * M * N) and an ordered reduction (nt: columns of the whole
+// output, as in launch_gemm).  For products whose tile grid
 // alone leaves compute units idle (small M x N, long K).  Falls back to the plain
 // product when there is one range or the operands do not suit the direct kernel.
 template <class Tr>
 int launch_contract_split(const typename Tr::T* A, long long lda, const typename Tr::T* B,
                           long long ldb, double* C, long long ldc, int M, int N, int K, int splits,
-                          double* part, int drain_steps, hipStream_t stream) {
+                          double* part, int drain_steps, int nt, hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0) return CC_LADDER_OK;
   if (splits <= 1 || !part || !vec_ok(A, lda) || !vec_ok(B, ldb))
-    return launch_gemm<Tr, KC, KC, EPI_ACC>(A, lda, B, ldb, C, ldc, M, N, K, 0, drain_steps, stream);
+    return launch_gemm<Tr, KC, KC, EPI_ACC>(A, lda, B, ldb, C, ldc, M, N, K, 0, drain_steps, stream,
+                                            0, 0, nullptr, 1.0, 0, 0, 0, M, nt);
   GemmArgs<typename Tr::T> g;
   g.alpha = 1.0;
   g.A = A; g.lda = lda;
@@ -932,6 +966,7 @@ int forward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::T
                    const typename Tr::T* Lp = nullptr, typename Tr::T* G = nullptr) {
   const int o = pl.o, v = pl.v, P = pl.P;
   const long long v2 = (long long)v * v;
+  const int iv2 = v * v;
   const int drain = Tr::kDrain ? pl.k_chunk / Tr::BK : 0;
   if (pl.gsym) {
     const int rc = build_pair_integral<Tr>(pl, Lp, G, row_tiles, tr, s);
@@ -952,13 +987,16 @@ int forward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::T
                                                 static_cast<typename Tr::T*>(nullptr), 0, s)
                        : launch_gemm<Tr, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
                                                            static_cast<int>((long long)(v - a0) * v),
-                                                           P, v, drain, s, o, a0, row_tiles);
+                                                           P, v, drain, s, o, a0, row_tiles, 1.0, 0,
+                                                           0, 0, iv2, iv2);
       tr(CC_LADDER_PHASE_BUILD, blk, 1);
       if (rc) return rc;
       // R[(ij)][(ab)] and R[(ji)][(ba)] += t[(ij)][(cd)] . V_A[pair(a,b)][(cd)]
       tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
       rc = launch_gemm<Tr, KC, KC, EPI_PAIR>(t, v2, V, v2, R, v2, o * o, static_cast<int>(npairs),
-                                             static_cast<int>(v2), v, drain, s, o, a0);
+                                             static_cast<int>(v2), v, drain, s, o, a0, nullptr, 1.0,
+                                             0, 0, 0, o * o,
+                                             static_cast<int>((long long)v * (v + 1) / 2));
       tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
       if (rc) return rc;
       continue;
@@ -966,13 +1004,15 @@ int forward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::T
     // V_A[a][b][c][d]: rows (a,c) of L's block, columns (b,d) of L, K = x
     tr(CC_LADDER_PHASE_BUILD, blk, 0);
     int rc = launch_gemm<Tr, RC, RC, EPI_PERM>(L + (long long)a0 * v, v2, L, v2, V, 0, na * v,
-                                               static_cast<int>(v2), P, v, drain, s);
+                                               static_cast<int>(v2), P, v, drain, s, 0, 0, nullptr,
+                                               1.0, 0, 0, 0, iv2, iv2);
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
     // R[(ij)][a0*v + (a,b)] += t[(ij)][(cd)] . V_A[(ab)][(cd)]
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
     rc = launch_gemm<Tr, KC, KC, EPI_ACC>(t, v2, V, v2, R + (long long)a0 * v, v2, o * o, na * v,
-                                          static_cast<int>(v2), v, drain, s);
+                                          static_cast<int>(v2), v, drain, s, 0, 0, nullptr, 1.0, 0, 0,
+                                          0, o * o, iv2);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }
@@ -992,6 +1032,7 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
                       typename Tr::T* G = nullptr) {
   const int o = pl.o, v = pl.v, P = pl.P;
   const long long v2 = (long long)v * v;
+  const int iv2 = v * v;
   const int drain = Tr::kDrain ? pl.k_chunk / Tr::BK : 0;
   const int mp = o * (o + 1) / 2, mm = o * (o - 1) / 2;
   const int kp = static_cast<int>((long long)v * (v + 1) / 2);
@@ -1015,7 +1056,7 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     } else {
       rc = launch_gemm<Tr, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
                                              static_cast<int>((long long)(v - a0) * v), P, v,
-                                             drain, s, o, a0, row_tiles);
+                                             drain, s, o, a0, row_tiles, 1.0, 0, 0, 0, iv2, iv2);
       if (!rc)
         rc = pm_rows<PM_INTS>(V, np, v, a0, v, Vp, pl.ldp, Vm, pl.ldm, 2.0, 1.0, s);
     }
@@ -1023,10 +1064,10 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     if (rc) return rc;
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
     rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tp, pl.ldp, Vp, pl.ldp, R, v2, mp, static_cast<int>(np), kp,
-                                         v, drain, s, o, a0, nullptr, 0.5, 1);
+                                         v, drain, s, o, a0, nullptr, 0.5, 1, 0, 0, mp, kp);
     if (!rc)
       rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tm, pl.ldm, Vm, pl.ldm, R, v2, mm, static_cast<int>(nm),
-                                           km, v, drain, s, o, a0, nullptr, 0.5, 2);
+                                           km, v, drain, s, o, a0, nullptr, 0.5, 2, 0, 0, mm, km);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }
@@ -1041,6 +1082,7 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
   using T = typename Tr::T;
   const int o = pl.o, v = pl.v, P = pl.P;
   const long long v2 = (long long)v * v;
+  const int iv2 = v * v;
   const int drain = Tr::kDrain ? pl.k_chunk / Tr::BK : 0;
   T* V = reinterpret_cast<T*>(base + pl.off_V);
   T* W = reinterpret_cast<T*>(base + pl.off_W);
@@ -1069,7 +1111,8 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
                                             static_cast<T*>(nullptr), 0, s)
                    : launch_gemm<Tr, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
                                                        static_cast<int>((long long)(v - a0) * v), P,
-                                                       v, drain, s, o, a0, row_tiles);
+                                                       v, drain, s, o, a0, row_tiles, 1.0, 0, 0, 0,
+                                                       iv2, iv2);
       tr(CC_LADDER_PHASE_BUILD, blk, 1);
       if (rc) return rc;
       // B[(ij)][(cd)] += sum_(ab packed) w lam[(ij)][(ab)] V_A[pair(a,b)][(cd)]
@@ -1088,7 +1131,8 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
     } else {
       tr(CC_LADDER_PHASE_BUILD, blk, 0);
       rc = launch_gemm<Tr, RC, RC, EPI_PERM>(L + off, v2, L, v2, V, 0, na * v,
-                                             static_cast<int>(v2), P, v, drain, s);
+                                             static_cast<int>(v2), P, v, drain, s, 0, 0, nullptr, 1.0,
+                                             0, 0, 0, iv2, iv2);
       tr(CC_LADDER_PHASE_BUILD, blk, 1);
       if (rc) return rc;
       // dt[(ij)][(cd)] += lam[(ij)][a0*v + (ab)] . V_A[(ab)][(cd)]
@@ -1116,7 +1160,8 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
                                                  nullptr, 1.0, 0, 0, static_cast<int>(npairs));
     } else {
       rc = launch_gemm<Tr, RC, RC, EPI_PERM>(lam + off, v2, t, v2, W, 0, na * v,
-                                             static_cast<int>(v2), o * o, v, drain, s);
+                                             static_cast<int>(v2), o * o, v, drain, s, 0, 0, nullptr,
+                                             1.0, 0, 0, 0, iv2, iv2);
     }
     tr(CC_LADDER_PHASE_W, blk, 1);
     if (rc) return rc;
@@ -1179,13 +1224,13 @@ int intermediate_blocks(const Plan& pl, const typename Tr::T* Lrow, long long ld
     const int np = (n_first - p0) < pl.n_a ? (n_first - p0) : pl.n_a;
     tr(CC_LADDER_PHASE_BUILD, blk, 0);
     int rc = launch_gemm<Tr, RC, RC, EPI_PERM>(Lrow + (long long)p0 * v, ld_row, Lov,
-                                               (long long)o * v, V, 0, np * v, o * v, P, v, drain,
-                                               s);
+                                               (long long)o * v, V, 0, np * v, o * v, P, v, drain, s,
+                                               0, 0, nullptr, 1.0, 0, 0, 0, n_first * v, o * v);
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
     rc = launch_contract_split<Tr>(t, v2, V, v2, Z + (long long)p0 * o, ld_out, o * o, np * o,
-                                   static_cast<int>(v2), pl.k_splits, part, drain, s);
+                                   static_cast<int>(v2), pl.k_splits, part, drain, n_first * o, s);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }
@@ -1205,12 +1250,14 @@ int hole_blocks(const Plan& pl, const typename Tr::T* Loo, const typename Tr::T*
     const int ni = (o - i0) < pl.n_a ? (o - i0) : pl.n_a;
     tr(CC_LADDER_PHASE_BUILD, blk, 0);
     int rc = launch_gemm<Tr, RC, RC, EPI_PERM>(Loo + (long long)i0 * o, o2, Loo, o2, W, 0, ni * o,
-                                               static_cast<int>(o2), P, o, drain, s);
+                                               static_cast<int>(o2), P, o, drain, s, 0, 0, nullptr,
+                                               1.0, 0, 0, 0, o * o, o * o);
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
     rc = launch_gemm<Tr, KC, RC, EPI_ACC>(W, o2, t, v2, R + (long long)i0 * o * v2, v2, ni * o,
-                                          static_cast<int>(v2), static_cast<int>(o2), v, drain, s);
+                                          static_cast<int>(v2), static_cast<int>(o2), v, drain, s, 0, 0,
+                                          nullptr, 1.0, 0, 0, 0, o * o, static_cast<int>(v2));
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }

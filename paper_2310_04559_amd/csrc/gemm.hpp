@@ -327,11 +327,16 @@ struct TileIO {
 
   __device__ static inline void advance(Cursor& cu) { cu.p += cu.kstep; }
 
-  // Whole tile in bounds and 16-byte aligned: one vector load per chunk.
+  // Whole tile in bounds: one 16-byte load per chunk at the element's alignment
+  // (global vector loads need whole dwords only), so rows of any length take it.
+  typedef T ChunkU __attribute__((ext_vector_type(CH), aligned(sizeof(T))));
   __device__ static inline void load_full(Chunk (&r)[NCH], const Cursor& cu) {
 #pragma unroll
-    for (int c = 0; c < NCH; ++c)
-      r[c] = *reinterpret_cast<const Chunk*>(cu.p + c * cu.cstride);
+    for (int c = 0; c < NCH; ++c) {
+      const ChunkU x = *reinterpret_cast<const ChunkU*>(cu.p + c * cu.cstride);
+#pragma unroll
+      for (int e = 0; e < CH; ++e) r[c][e] = x[e];
+    }
   }
 
   // Any tile: element loads, zero outside [0, nrows) x [0, K).
@@ -413,9 +418,9 @@ __device__ inline void tile_of_banded(int kband, int bid, int nwg, int tiles_m, 
   tile_from_linear(kband == 2 ? nwg - 1 - bid : bid, nwg, tiles_m, group_m, tm, tn);
 }
 
-// K loop of one tile.  FAST: the tile lies inside M x N and its operands are
-// 16-byte aligned, so every full K-step is one vector load per chunk with no
-// test; only a ragged last K-step is masked.  Otherwise every load is masked.
+// K loop of one tile.  FAST: the tile lies inside M x N, so every full K-step is
+// one vector load per chunk with no test; only a ragged last K-step is masked.
+// Otherwise every load is masked.
 template <class Tr, int LA, int LB, bool FAST>
 __device__ __forceinline__ void tile_mainloop(const GemmArgs<typename Tr::T>& g, int m0, int n0,
                                               int ks0, int ks1,
@@ -527,7 +532,7 @@ __device__ __forceinline__ void tile_mainloop(const GemmArgs<typename Tr::T>& g,
   }
 }
 
-template <class Tr, int LA, int LB, int EPI, bool VEC>
+template <class Tr, int LA, int LB, int EPI>
 __global__ __launch_bounds__(kThreads, Tr::kWaves) void gemm_kernel(GemmArgs<typename Tr::T> g) {
   using T = typename Tr::T;
   using Acc = typename Tr::Acc;
@@ -581,7 +586,7 @@ __global__ __launch_bounds__(kThreads, Tr::kWaves) void gemm_kernel(GemmArgs<typ
   int ks0, ks1;
   k_band(g, n0, kBN, Tr::BK, ks0, ks1);
   const bool interior = (m0 + kBM <= g.M) && (n0 + kBN <= g.N);
-  if (VEC && interior)
+  if (interior)
     tile_mainloop<Tr, LA, LB, true>(g, m0, n0, ks0, ks1, sA[0], sA[1], sB[0], sB[1], acc, acc64);
   else
     tile_mainloop<Tr, LA, LB, false>(g, m0, n0, ks0, ks1, sA[0], sA[1], sB[0], sB[1], acc, acc64);

@@ -34,7 +34,7 @@ __device__ __forceinline__ void d_wait_vm(int n) {
   case N:          \
     __builtin_amdgcn_s_waitcnt(((N)&15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14)); \
     break;
-    CCL_DVM(0) CCL_DVM(5) CCL_DVM(6) CCL_DVM(7)
+    CCL_DVM(0) CCL_DVM(2) CCL_DVM(3) CCL_DVM(5) CCL_DVM(6) CCL_DVM(7)
 #undef CCL_DVM
     default:
       __builtin_amdgcn_s_waitcnt(7 << 4 | 15 << 8);
@@ -45,8 +45,18 @@ __device__ __forceinline__ void d_wait_vm(int n) {
 // blocks per wave, 156 KB of LDS), whose tiles divide o^2 = 1600 exactly and pad
 // 900 and 3600 less; and 64 (2 x 4 blocks per wave) for the remainder rows of a
 // product whose last 128-row tile row would be at most half full.
-template <class Tr, int EPI, int BM = kDBM>
-__global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<typename Tr::T> g) {
+// BN = 256; with BM = 64 also 128 and 64 (two workgroups per compute unit), for
+// products whose 256-wide tiles leave compute units idle: one 128 x 256 tile takes
+// its compute unit 4 us per 16 k (two waves per SIMD, 64 float64 MFMAs of 64 cycles
+// each), so a short grid is bound by that serial loop.  169 x 4753 x 4753 float64:
+// 1.17 ms on 128 x 256 tiles (38 workgroups), 0.19 ms on 64 x 64 (225); 800 x 4950 x
+// 4950: 1.23 -> 0.63 ms on 64 x 128.
+template <int BM, int BN>
+constexpr int kc_groups() { return BM == 64 && BN < 256 ? 2 : 1; }  // per compute unit
+
+template <class Tr, int EPI, int BM = kDBM, int BN = kDBN>
+__global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_direct_kernel(
+    GemmArgs<typename Tr::T> g) {
   static_assert(EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PART || EPI == EPI_PM,
                 "K-contiguous epilogues");
   static_assert(BM == kDBM || BM == 64 || (BM == 160 && !Tr::kDrain), "tile heights");
@@ -56,8 +66,9 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
   constexpr int CH = Tr::CH;                 // elements per 16 bytes
   constexpr int BK = kDRow / sizeof(T);      // K per step (16 float64 / 32 float32)
   constexpr int MI = BM / 32;                // row blocks per wave (2 wave rows)
+  constexpr int NJ = BN / 64;                // column blocks per wave (4 wave columns)
   constexpr int A_BYTES = BM * kDRow;        // 8, 16 or 20 KB
-  constexpr int B_BYTES = kDBN * kDRow;      // 32 KB
+  constexpr int B_BYTES = BN * kDRow;        // 8, 16 or 32 KB
   constexpr int STAGE = A_BYTES + B_BYTES;
   constexpr int A_SLABS = BM / 8, JA = (A_SLABS + 7) / 8;  // 8-row slabs of A; per wave at most JA
   static_assert(kDStages * STAGE <= 160 * 1024, "LDS");
@@ -67,11 +78,11 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 2) * (BM / 2);
-  const int wn = (wave & 3) * 64;
-  // slabs this wave loads per stage: A slabs wave + 8j < A_SLABS, and 4 of B
-  // (compile-time 5 or 6 when the A slabs split evenly over the 8 waves)
+  const int wn = (wave & 3) * (16 * NJ);
+  // slabs this wave loads per stage: A slabs wave + 8j < A_SLABS, and NJ of B
+  // (a compile-time count when the A slabs split evenly over the 8 waves)
   constexpr bool A_EVEN = A_SLABS % 8 == 0;
-  const int LOADS = A_EVEN ? A_SLABS / 8 + 4 : (A_SLABS - wave + 7) / 8 + 4;
+  const int LOADS = A_EVEN ? A_SLABS / 8 + NJ : (A_SLABS - wave + 7) / 8 + NJ;
   int tm, tn;
   const int nk_all = (g.K + BK - 1) / BK;
   int ks0 = 0, ks1 = nk_all;  // K-steps of this workgroup
@@ -89,17 +100,17 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
   } else {
     tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
   }
-  const int m0 = tm * BM, n0 = tn * kDBN;
-  if (EPI != EPI_PART && g.kband) k_band(g, n0, kDBN, BK, ks0, ks1);
+  const int m0 = tm * BM, n0 = tn * BN;
+  if (EPI != EPI_PART && g.kband) k_band(g, n0, BN, BK, ks0, ks1);
 
-  // Slabs: A rows 8*(wave + 8*j), j < JA; B rows 8*(wave + 8*j), j < 4.  The
+  // Slabs: A rows 8*(wave + 8*j), j < JA; B rows 8*(wave + 8*j), j < NJ.  The
   // swizzle of a lane depends on the slab's parity only (slab origin 8*s rows).
   const int lrow = lane >> 3;
   const int sw_even = ((lane & 7) ^ ((lane >> 4) & 7)) * CH;        // slab index even
   const int sw_odd = ((lane & 7) ^ ((4 + (lane >> 4)) & 7)) * CH;   // slab index odd
   const int my_sw = (wave & 1) ? sw_odd : sw_even;  // slabs wave + 8j share the wave's parity
   const T* pa[JA];
-  const T* pb[4];
+  const T* pb[NJ];
 #pragma unroll
   for (int j = 0; j < JA; ++j) {
     int row = m0 + 8 * (wave + 8 * j) + lrow;
@@ -107,7 +118,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
     pa[j] = g.A + (long long)row * g.lda + my_sw;
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     int row = n0 + 8 * (wave + 8 * j) + lrow;
     row = row < g.N ? row : g.N - 1;
     pb[j] = g.B + (long long)row * g.ldb + my_sw;
@@ -121,7 +132,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
         __builtin_amdgcn_global_load_lds((const void*)(pa[j] + ko),
                                          (lds_void*)(st + 8 * (wave + 8 * j) * kDRow), 16, 0, 0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
       __builtin_amdgcn_global_load_lds((const void*)(pb[j] + ko),
                                        (lds_void*)(st + A_BYTES + 8 * (wave + 8 * j) * kDRow), 16,
                                        0, 0);
@@ -141,16 +152,16 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
     for (int j = 0; j < JA; ++j)
       if (A_EVEN || wave + 8 * j < A_SLABS) one(pa[j], st + 8 * (wave + 8 * j) * kDRow);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) one(pb[j], st + A_BYTES + 8 * (wave + 8 * j) * kDRow);
+    for (int j = 0; j < NJ; ++j) one(pb[j], st + A_BYTES + 8 * (wave + 8 * j) * kDRow);
     __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14));  // lgkmcnt(0): the LDS writes landed
   };
 
-  Acc acc[MI][4];
-  f64x4 acc64[MI][4];
+  Acc acc[MI][NJ];
+  f64x4 acc64[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       acc[i][j] = Acc{0, 0, 0, 0};
       acc64[i][j] = f64x4{0, 0, 0, 0};
     }
@@ -182,26 +193,26 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
 #pragma unroll
       for (int gi = 0; gi < 2; ++gi) {
         const int chunk = ((4 * gi + (lane >> 4)) ^ fsw) * 16;
-        Chunk fa[MI], fb[4];
+        Chunk fa[MI], fb[NJ];
 #pragma unroll
         for (int i = 0; i < MI; ++i)
           fa[i] = *reinterpret_cast<const Chunk*>(st + (wm + 16 * i) * kDRow + frow + chunk);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
           fb[j] = *reinterpret_cast<const Chunk*>(st + A_BYTES + (wn + 16 * j) * kDRow + frow + chunk);
 #pragma unroll
         for (int e = 0; e < CH; ++e)
 #pragma unroll
           for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = Tr::mfma(fa[i][e], fb[j][e], acc[i][j]);
+            for (int j = 0; j < NJ; ++j) acc[i][j] = Tr::mfma(fa[i][e], fb[j][e], acc[i][j]);
       }
     }
     if (Tr::kDrain) {
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             acc64[i][j][r] += static_cast<double>(acc[i][j][r]);
@@ -213,7 +224,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kc_direct_kernel(GemmArgs<t
 
   const int col = lane & 15;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     const int n = n0 + wn + 16 * j + col;
     if (n >= g.N) continue;
     const EpiCol ec = epi_col<T, EPI>(g, n);

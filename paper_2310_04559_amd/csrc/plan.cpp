@@ -460,6 +460,93 @@ int choose_k_splits(long long M, long long N, long long K, int bk) {
   return best;
 }
 
+namespace {
+
+// Time of a launch per unit of K, in multiply-adds of one compute unit: rounds of
+// the grid over the 256 compute units times the tile, over the share of the matrix
+// cores' rate that the tile reaches.  The shares are float64 measurements on
+// products that fill whole rounds: 128 x 256 (and 160) 0.88 (o=40 v=360 P=1200
+// contraction), 64 x 128 0.84 (225 x 16290 x 16290: 2.05 ms against 2.17 on 64 x 256),
+// 64 x 64 0.80 (400 x 16290 x 16290: 3.66 ms).  The smaller tiles win where the larger ones would leave part of a
+// round idle: 169 x 4753 x 4753 0.19 ms on 64 x 64 against 1.17 on 128 x 256,
+// 800 x 4950 x 4950 0.63 on 64 x 128 against 1.23.
+double tile_cost(long long M, long long N, int bm, int bn, double rate) {
+  const long long tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  return static_cast<double>((tiles + 255) / 256) * bm * bn / rate;
+}
+
+// The register-direct kernel reaches 0.62 of the rate while its operands stay in
+// the 256 MB last-level cache (400 x 4950 x 4950: 0.40 ms on 32 x 32, 0.49 on 64 x
+// 64 direct-to-LDS tiles) and 0.42 beyond (400 x 16290 x 16290: 6.7 ms against 3.7);
+// a compute unit needs eight waves to cover the latency of their loads.
+double wave_cost(long long M, long long N, double bytes, int side, int wk) {
+  const long long t = 32 * side;
+  const long long tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
+  const long long rounds = (tiles + 255) / 256;
+  const long long waves = rounds * side * side * wk;
+  const double busy = waves >= 8 ? 1.0 : static_cast<double>(waves) / 8;
+  const double rate = bytes > 256e6 ? 0.42 : 0.62;
+  return static_cast<double>(rounds) * t * t / (rate * busy);
+}
+
+// Waves along K: each with at least two pieces, at most eight per compute unit.
+int waves_along_k(long long M, long long N, long long units, int side) {
+  const long long t = 32 * side;
+  const long long rounds = (((M + t - 1) / t) * ((N + t - 1) / t) + 255) / 256;
+  int wk = 1;
+  while (2 * wk * side * side <= 16 && units >= 4LL * wk && rounds * wk * side * side < 8) wk *= 2;
+  return wk;
+}
+
+TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long long units, int es,
+                     bool tall, bool split) {
+  TilePick p;
+  double best = 0.0;
+  auto take = [&](int bm, int bn, long long main_rows, double cost) {
+    if (p.bm && cost >= best) return;
+    best = cost;
+    p.bm = bm;
+    p.bn = bn;
+    p.main_rows = main_rows;
+  };
+  if (cls == kTilesKC) {
+    long long main_rows = M;
+    const int bm = choose_kc_tiling(M, N, tall, split, &main_rows);
+    const double cost = bm == 64 ? tile_cost(main_rows, N, 128, 256, 0.88) +
+                                       tile_cost(M - main_rows, N, 64, 256, 0.88)
+                                 : tile_cost(M, N, bm, 256, 0.88);
+    take(bm == 64 ? 128 : bm, 256, main_rows, cost);
+    take(64, 128, M, tile_cost(M, N, 64, 128, 0.84));
+    take(64, 64, M, tile_cost(M, N, 64, 64, 0.80));
+  } else if (cls == kTilesKR) {
+    take(128, 256, M, tile_cost(M, N, 128, 256, 0.88));
+  } else {
+    take(128, 128, M, tile_cost(M, N, 128, 128, 0.80));
+  }
+  const double bytes = (static_cast<double>(M) + static_cast<double>(N)) * K * es;
+  for (int side = 2; side >= 1; --side) {
+    const int wk = waves_along_k(M, N, units, side);
+    const double cost = wave_cost(M, N, bytes, side, wk);
+    if (cost < best) {
+      best = cost;
+      p.side = side;
+      p.wk = wk;
+    }
+  }
+  return p;
+}
+
+}  // namespace
+
+TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long long mt,
+                    long long nt, long long units, int es, bool tall, bool split) {
+  const TilePick whole = pick_launch(cls, mt, nt, K, units, es, tall, split);
+  if (whole.side && whole.wk > 1) return whole;
+  // one wave along K or a big tile: the same order of the sums, so the launch's own
+  // extents decide
+  return pick_launch(cls, M, N, K, 1, es, tall, split);
+}
+
 int layout_intermediate(int which, int o, int v, int P, int precision, int n_p, int k_chunk,
                         Plan* plan) {
   const int n_first = which == CC_INTERMEDIATE_IJBK ? v : o;

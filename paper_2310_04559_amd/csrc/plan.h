@@ -105,6 +105,32 @@ int choose_kc_tiling(long long M, long long N, bool tall, bool split, long long*
 // that minimises the waves per unit of work (at least 64 K-steps per range).
 int choose_k_splits(long long M, long long N, long long K, int bk);
 
+// The kernel family that a float64 or float32 product C[M][N] (K contracted)
+// suits by the layout and alignment of its operands; each has its big tiles, and
+// all can run on the register-direct kernel (gemm_wave.hpp).
+enum TileClass {
+  kTilesKC,     // K-contiguous direct-to-LDS kernel: 128 or 160 x 256, 64 x 128, 64 x 64
+  kTilesKR,     // mixed direct-to-LDS kernel: 128 x 256
+  kTilesStaged  // register-staged kernel: 128 x 128
+};
+
+// How one launch is cut over the chip.
+struct TilePick {
+  int bm = 0, bn = 0;       // tile
+  long long main_rows = 0;  // kTilesKC: rows on bm-row tiles when the rest takes 64-row tiles
+  int side = 0;             // > 0: register-direct kernel, side x side sub-tiles of 32 x 32 ...
+  int wk = 1;               // ... with wk waves along K
+};
+
+// Picks the cut of a launch that computes M x N of a whole output of mt x nt.
+// `units` is the number of pieces of K that the waves of the register-direct
+// kernel can share (K-steps; float32: drain chunks), `es` the element size.
+// `tall`, `split` as in choose_kc_tiling (kTilesKC).  wk alone decides the order
+// in which an element's sum is formed and depends on the whole output only, so
+// results do not depend on the blocks.
+TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long long mt,
+                    long long nt, long long units, int es, bool tall, bool split);
+
 int layout_intermediate(int which, int o, int v, int P, int precision, int n_p, int k_chunk,
                         Plan* plan);
 int make_plan_intermediate(int which, int o, int v, int P, int precision, size_t budget,
