@@ -242,7 +242,7 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
       pick_tiles(!direct ? kTilesStaged : kKC ? kTilesKC : kTilesKR, M, N, K, mt ? mt : M,
                  nt ? nt : N, Tr::kDrain ? (nk + g.drain_steps - 1) / g.drain_steps : nk,
                  sizeof(typename Tr::T), !Tr::kDrain,
-                 EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM);
+                 EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM || EPI == EPI_FOLD);
   if (pick.side && !kband && (LA == KC || M >= 2) && (LB == KC || N >= 2))
     return pick.side == 1 ? launch_wave_side<Tr, LA, LB, EPI, 1>(g, pick.wk, stream)
                           : launch_wave_side<Tr, LA, LB, EPI, 2>(g, pick.wk, stream);
@@ -544,11 +544,12 @@ int mirror_add(const double* B, double* dt, int o, int v, hipStream_t s) {
 // prefix_{v-1}(c) + d - c - 1 the pairs c < d.  Rows:
 //   AMPS: the pairs (i, j), i <= j, of o; X = t[i][j]; rp = the pair index, rm
 //         its index among the pairs i < j (none for i = j)
+//   ALL:  every row (i, j); X = t[i][j]; rp = rm = the row
 //   INTS: the packed integral rows (a, b), a <= b, a from a0; X = row r of the
 //         block; rp = r, rm = the local index among the pairs a < b (none for a = b)
 // One workgroup per (row, tile pair C <= D of 32 x 32 tiles): both tiles X[C][D]
 // and X[D][C] go through LDS, so reads and writes run along contiguous d.
-enum { PM_AMPS = 0, PM_INTS = 1 };
+enum { PM_AMPS = 0, PM_INTS = 1, PM_ALL = 2 };
 
 template <int MODE, typename In, typename Out>
 __global__ __launch_bounds__(256) void pm_rows_kernel(const In* __restrict__ X, long long nrows,
@@ -572,6 +573,8 @@ __global__ __launch_bounds__(256) void pm_rows_kernel(const In* __restrict__ X, 
       const int j = i + static_cast<int>(r - pair_prefix_d(i, n));
       src = (long long)i * n + j;
       rm = i < j ? pair_prefix_d(i, n - 1) + (j - i - 1) : -1;
+    } else if (MODE == PM_ALL) {
+      src = rm = r;
     } else {
       const long long q = pair_prefix_d(a0, v) + r;
       const int a = pair_row(q, v);
@@ -1074,6 +1077,70 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
   return CC_LADDER_OK;
 }
 
+// The float64 forward folded over the exchange of both virtual pairs (FoldPlan):
+// t+ and t- of every row (of the pairs i <= j, i < j when t is pair-symmetric), then
+// per block the packed build, V+ and V-, and the two half-sized contractions, whose
+// results are added to R[i][j][a][b] and +- to R[i][j][b][a] (and their mirrors).
+// Bound by the matrix cores like the direct route, with half its multiply-adds
+// (P v^4 + o^2 v^4 instead of twice that) for the same bytes: the packed block is
+// written, read and rewritten combined where the direct route writes all of V_A.
+// o=40 v=360 P=1200: 1366 -> 778 ms; o=20 v=180 P=600: 34.2 -> 21.1 ms.
+int forward_fold(const Plan& pl, const FoldPlan& f, const double* L, const double* t, double* R,
+                 char* base, const Tracer& tr, hipStream_t s) {
+  const int o = pl.o, v = pl.v, P = pl.P;
+  const long long v2 = (long long)v * v;
+  const int iv2 = v * v;
+  const int kp = static_cast<int>((long long)v * (v + 1) / 2);
+  const int km = static_cast<int>((long long)v * (v - 1) / 2);
+  double* Tp = reinterpret_cast<double*>(base + f.off_Tp);
+  double* Tm = reinterpret_cast<double*>(base + f.off_Tm);
+  double* V = reinterpret_cast<double*>(base + f.off_V);
+  double* Vp = reinterpret_cast<double*>(base + f.off_Vp);
+  double* Vm = reinterpret_cast<double*>(base + f.off_Vm);
+  int* row_tiles = reinterpret_cast<int*>(base + f.off_tiles);
+  // the exchange partner's amplitudes (c and d swapped) give t+ and -t-
+  const double sm = pl.exchange ? -1.0 : 1.0;
+  tr(CC_LADDER_PHASE_PREP, 0, 0);
+  int rc = pl.pairsym ? pm_rows<PM_AMPS>(t, f.rows_p, o, 0, v, Tp, f.ldp, Tm, f.ldm, 1.0, sm, s)
+                      : pm_rows<PM_ALL>(t, f.rows_p, o, 0, v, Tp, f.ldp, Tm, f.ldm, 1.0, sm, s);
+  tr(CC_LADDER_PHASE_PREP, 0, 1);
+  if (rc) return rc;
+  for (int blk = 0; blk < f.nb; ++blk) {
+    const int a0 = pair_block_start(v, f.nb, blk);
+    const int na = pair_block_start(v, f.nb, blk + 1) - a0;
+    if (na <= 0) continue;
+    const long long off = (long long)a0 * v;
+    const long long np = pair_prefix(a0 + na, v) - pair_prefix(a0, v);
+    const long long nm = np - na;
+    tr(CC_LADDER_PHASE_BUILD, blk, 0);
+    rc = launch_gemm<TrF64, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
+                                              static_cast<int>((long long)(v - a0) * v), P, v, 0, s,
+                                              o, a0, row_tiles, 1.0, 0, 0, 0, iv2, iv2);
+    if (!rc) rc = pm_rows<PM_INTS>(V, np, v, a0, v, Vp, f.ldp, Vm, f.ldm, 2.0, 1.0, s);
+    tr(CC_LADDER_PHASE_BUILD, blk, 1);
+    if (rc) return rc;
+    tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
+    const int mp = static_cast<int>(f.rows_p), mm = static_cast<int>(f.rows_m);
+    const int inp = static_cast<int>(np), inm = static_cast<int>(nm);
+    if (pl.pairsym) {
+      rc = launch_gemm<TrF64, KC, KC, EPI_PM>(Tp, f.ldp, Vp, f.ldp, R, v2, mp, inp, kp, v, 0, s, o,
+                                              a0, nullptr, 0.5, 1, 0, 0, mp, kp);
+      if (!rc)
+        rc = launch_gemm<TrF64, KC, KC, EPI_PM>(Tm, f.ldm, Vm, f.ldm, R, v2, mm, inm, km, v, 0, s,
+                                                o, a0, nullptr, 0.5, 2, 0, 0, mm, km);
+    } else {
+      rc = launch_gemm<TrF64, KC, KC, EPI_FOLD>(Tp, f.ldp, Vp, f.ldp, R, v2, mp, inp, kp, v, 0, s,
+                                                o, a0, nullptr, 0.5, 1, 0, 0, mp, kp);
+      if (!rc)
+        rc = launch_gemm<TrF64, KC, KC, EPI_FOLD>(Tm, f.ldm, Vm, f.ldm, R, v2, mm, inm, km, v, 0,
+                                                  s, o, a0, nullptr, 0.5, 2, 0, 0, mm, km);
+    }
+    tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
+    if (rc) return rc;
+  }
+  return CC_LADDER_OK;
+}
+
 template <class Tr>
 int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::T* t,
                     const typename Tr::T* lam, double* dL, double* dt, char* base,
@@ -1404,6 +1471,8 @@ int residual_body(const Plan& pl, const double* L, const double* t, double* R, i
                                     reinterpret_cast<int*>(base + pl.off_tiles), tr, stream, Lp,
                                     pl.gsym ? reinterpret_cast<float*>(base + pl.off_G) : nullptr);
   }
+  FoldPlan fold;
+  if (plan_fold(pl, &fold)) return forward_fold(pl, fold, L, t, R, base, tr, stream);
   if (pl.exchange && precision != CC_LADDER_FP32) {
     // the exchange partner is the ladder of the swapped amplitudes
     double* tx = reinterpret_cast<double*>(base + pl.off_tx);

@@ -31,6 +31,10 @@
 //             a0, a <= b (a < b for pm = 2): val = alpha * acc is added to the set
 //             {R[i,j,a,b], R[j,i,b,a]} and, as +val (pm = 1) or -val (pm = 2), to
 //             {R[i,j,b,a], R[j,i,a,b]}, each distinct element once
+//   EPI_FOLD: the combinations of EPI_PM for any amplitudes: rows m = (i,j) as they are,
+//             columns n = pair (a,b) as in EPI_PM: val = alpha * acc is added to
+//             C[m*ldc + a*v + b] and, for a != b, +val (pm = 1) or -val (pm = 2) to
+//             C[m*ldc + b*v + a]
 //   EPI_PART: split K: workgroup s of a tile sums K-steps [s*split_steps, (s+1)*split_steps)
 //             and stores C[s*part_stride + m*ldc + n] = acc (float64 partials, summed
 //             in order of s by a separate pass)
@@ -74,7 +78,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;
 enum { KC = 0, RC = 1 };
 enum { EPI_ACC = 0, EPI_PERM = 1, EPI_PACK = 2, EPI_PAIR = 3, EPI_PART = 4, EPI_PM = 5,
-       EPI_UNPACK = 6, EPI_SYM = 7 };
+       EPI_UNPACK = 6, EPI_SYM = 7, EPI_FOLD = 8 };
 
 // float64 operands on v_mfma_f64_16x16x4_f64.
 struct TrF64 {
@@ -135,7 +139,7 @@ struct GemmArgs {
   long long part_stride; // EPI_PART: elements between consecutive splits' partials
   double alpha;          // EPI_ACC: C += alpha * acc (1, or 2 for a term counted twice)
   int m_off = 0;         // EPI_PAIR/PM: global row of this launch's row 0 (a remainder launch)
-  int pm = 0;            // EPI_PM: 1 = symmetric pairs (i <= j, a <= b), 2 = antisymmetric (<)
+  int pm = 0;            // EPI_PM/FOLD: 1 = symmetric pairs (i <= j, a <= b), 2 = antisymmetric (<)
   int kband = 0;         // K bands of a half-written B operand (0 = the whole K range)
   int m_keep = 0;        // EPI_UNPACK: rows stored (M may be padded to whole 16-byte chunks)
 };
@@ -210,7 +214,7 @@ __device__ __forceinline__ EpiCol epi_col(const GemmArgs<T>& g, int n) {
     c.x = a;
     c.y = b;
     c.off = (long long)a * v + b;
-  } else if (EPI == EPI_PM) {
+  } else if (EPI == EPI_PM || EPI == EPI_FOLD) {
     // pairs a < b of v are the pairs a <= b' = b - 1 of v - 1
     const int s = g.pm == 2 ? 1 : 0;
     const long long q = pair_prefix_d(g.a0, v - s) + n;
@@ -267,6 +271,11 @@ __device__ __forceinline__ void epi_store(const GemmArgs<T>& g, int m, int n, co
       C[rji + ba] += w;
       if (c.x != c.y) C[rji + ab] += x;
     }
+  } else if (EPI == EPI_FOLD) {
+    double* row = static_cast<double*>(g.C) + (long long)m * g.ldc;
+    const double w = g.alpha * val;
+    row[c.off] += w;
+    if (c.x != c.y) row[(long long)c.y * v + c.x] += g.pm == 2 ? -w : w;
   } else {  // EPI_PAIR
     double* C = static_cast<double*>(g.C);
     const int mg = m + g.m_off;

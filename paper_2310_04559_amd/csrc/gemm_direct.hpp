@@ -1,7 +1,8 @@
 // Amplitude-contraction GEMM with direct global->LDS operand loads (gfx950).
 //
 //   C[m][n] (+)= sum_k A[m*lda + k] B[n*ldb + k]   (both operands KC; EPI_ACC, EPI_PAIR,
-//                                                   or EPI_PART: one K-range per workgroup)
+//                                                   EPI_PM, EPI_FOLD, or EPI_PART: one
+//                                                   K-range per workgroup)
 //
 // 512 threads = 8 wave64s in a 2 x 4 grid over a BM x 256 tile (BM = 128; the
 // K-contiguous kernel also 64 and, for float64, 160); each wave owns (BM/2) x 64 =
@@ -57,7 +58,8 @@ constexpr int kc_groups() { return BM == 64 && BN < 256 ? 2 : 1; }  // per compu
 template <class Tr, int EPI, int BM = kDBM, int BN = kDBN>
 __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_direct_kernel(
     GemmArgs<typename Tr::T> g) {
-  static_assert(EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PART || EPI == EPI_PM,
+  static_assert(EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PART || EPI == EPI_PM ||
+                    EPI == EPI_FOLD,
                 "K-contiguous epilogues");
   static_assert(BM == kDBM || BM == 64 || (BM == 160 && !Tr::kDrain), "tile heights");
   using T = typename Tr::T;

@@ -533,6 +533,7 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
       p.wk = wk;
     }
   }
+  p.cost = best;
   return p;
 }
 
@@ -545,6 +546,82 @@ TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long l
   // one wave along K or a big tile: the same order of the sums, so the launch's own
   // extents decide
   return pick_launch(cls, M, N, K, 1, es, tall, split);
+}
+
+namespace {
+
+// Layout for nb pair-balanced blocks; bytes is 0 when nb exceeds v.
+FoldPlan layout_fold(const Plan& pl, int nb) {
+  FoldPlan f;
+  const int v = pl.v;
+  if (nb < 1 || nb > v) return f;
+  const size_t v2 = static_cast<size_t>(v) * v;
+  f.nb = nb;
+  f.ldp = static_cast<long long>((static_cast<size_t>(v) * (v + 1) / 2 + 3) / 4 * 4);
+  f.ldm = static_cast<long long>((static_cast<size_t>(v) * (v - 1) / 2 + 3) / 4 * 4);
+  f.rows_p = pl.pairsym ? (long long)pl.o * (pl.o + 1) / 2 : (long long)pl.o * pl.o;
+  f.rows_m = pl.pairsym ? (long long)pl.o * (pl.o - 1) / 2 : (long long)pl.o * pl.o;
+  size_t np = 0, nm = 0, na_max = 0;
+  for (int k = 0; k < nb; ++k) {
+    const int a0 = pair_block_start(v, nb, k), a1 = pair_block_start(v, nb, k + 1);
+    const size_t n = static_cast<size_t>(pair_prefix(a1, v) - pair_prefix(a0, v));
+    const size_t na = static_cast<size_t>(a1 - a0);
+    np = n > np ? n : np;
+    nm = n - na > nm ? n - na : nm;
+    na_max = na > na_max ? na : na_max;
+  }
+  size_t cur = 0;
+  f.off_Tp = take(&cur, f.rows_p * f.ldp * sizeof(double));
+  f.off_Tm = take(&cur, f.rows_m * f.ldm * sizeof(double));
+  f.off_V = take(&cur, np * v2 * sizeof(double));
+  f.off_Vp = take(&cur, np * f.ldp * sizeof(double));
+  f.off_Vm = take(&cur, nm * f.ldm * sizeof(double));
+  f.off_tiles = take(&cur, ((na_max * v + 127) / 128 + 1) * sizeof(int));
+  f.bytes = cur;
+  return f;
+}
+
+}  // namespace
+
+bool plan_fold(const Plan& pl, FoldPlan* f) {
+  // Below 64 virtuals the extra launches (the combinations and a second product
+  // per block) take what the products save.
+  if (pl.op != kOpLadder || pl.precision != CC_LADDER_FP64 || pl.backward || pl.pm || pl.gsym ||
+      pl.v < 64)
+    return false;
+  const int v = pl.v;
+  const size_t room = pl.bytes - (pl.check_sym ? kAlign : 0);  // the same choice with the check
+  if (layout_fold(pl, v).bytes > room) return false;
+  int lo = 1, hi = v;  // the footprint shrinks as the block count grows
+  while (lo < hi) {
+    const int mid = lo + (hi - lo) / 2;
+    if (layout_fold(pl, mid).bytes <= room) hi = mid; else lo = mid + 1;
+  }
+  *f = layout_fold(pl, lo);
+  // Both routes in multiply-adds of one compute unit at the matrix rate (0.14e12 per
+  // second): builds at the register-staged kernel's share, contractions as tiled,
+  // memory passes at 4 TB/s, launches at 6 us.
+  constexpr double kLaunch = 6e-6 * 0.14e12, kByte = 0.14e12 / 4e12, kBuildRate = 256 * 0.80;
+  const double v2 = static_cast<double>(v) * v;
+  const double pairs = 0.5 * v * (v + 1.0);
+  const long long o2 = (long long)pl.o * pl.o;
+  auto contract = [](long long M, double N, long long K) {
+    const long long n = static_cast<long long>(N + 0.5);
+    if (M <= 0 || n <= 0 || K <= 0) return 0.0;
+    return pick_launch(kTilesKC, M, n, K, (K + 15) / 16, sizeof(double), true, true).cost * K;
+  };
+  double direct, fold;
+  if (pl.pairsym)
+    direct = pairs * v2 * pl.P / kBuildRate +
+             pl.nblocks * (contract(o2, pairs / pl.nblocks, (long long)v * v) + 2 * kLaunch);
+  else
+    direct = v2 * v2 * pl.P / kBuildRate +
+             pl.nblocks * (contract(o2, v2 / pl.nblocks, (long long)v * v) + 2 * kLaunch);
+  fold = pairs * v2 * pl.P / kBuildRate +
+         f->nb * (contract(f->rows_p, pairs / f->nb, (long long)v * (v + 1) / 2) +
+                  contract(f->rows_m, (pairs - v) / f->nb, (long long)v * (v - 1) / 2) + 4 * kLaunch) +
+         16.0 * (pairs + f->rows_p) * v2 * kByte + kLaunch;
+  return fold < direct;
 }
 
 int layout_intermediate(int which, int o, int v, int P, int precision, int n_p, int k_chunk,

@@ -120,6 +120,7 @@ struct TilePick {
   long long main_rows = 0;  // kTilesKC: rows on bm-row tiles when the rest takes 64-row tiles
   int side = 0;             // > 0: register-direct kernel, side x side sub-tiles of 32 x 32 ...
   int wk = 1;               // ... with wk waves along K
+  double cost = 0.0;        // its time per unit of K, in multiply-adds of one compute unit
 };
 
 // Picks the cut of a launch that computes M x N of a whole output of mt x nt.
@@ -130,6 +131,25 @@ struct TilePick {
 // results do not depend on the blocks.
 TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long long mt,
                     long long nt, long long units, int es, bool tall, bool split);
+
+// The float64 forward folded over the exchange of both virtual pairs, inside the
+// scratch of a plan for the direct forward.  (ac|bd) = (bd|ac) for any vectors, so
+// the map t -> R commutes with swapping (c,d) and (a,b) together and splits into its
+// symmetric and antisymmetric parts: with t+- = t[i][j][c][d] +- t[i][j][d][c] and
+// V+-[ab][cd] = (ac|bd) +- (ad|bc),
+//   R[i][j][a][b] +- R[i][j][b][a] = sum over pairs c <= d (c < d) of V+- t+-
+// for every i, j and any t: half the build (pairs a <= b) and half the contraction.
+// Pair-symmetric amplitudes (pl.pairsym) restrict the rows to i <= j as well.
+struct FoldPlan {
+  int nb = 0;                     // pair-balanced blocks of virtuals a
+  long long rows_p = 0, rows_m = 0;  // rows of t+, t-
+  long long ldp = 0, ldm = 0;     // row strides: pairs c <= d and c < d, rounded to 4
+  size_t off_Tp = 0, off_Tm = 0, off_V = 0, off_Vp = 0, off_Vm = 0, off_tiles = 0;
+  size_t bytes = 0;
+};
+
+// True when the folded forward fits the plan's scratch and is the faster route.
+bool plan_fold(const Plan& pl, FoldPlan* f);
 
 int layout_intermediate(int which, int o, int v, int P, int precision, int n_p, int k_chunk,
                         Plan* plan);
