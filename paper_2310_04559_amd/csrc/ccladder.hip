@@ -167,21 +167,19 @@ bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, in
 }
 
 // K-contiguous A times row-contiguous B, float64 accumulation: the mixed
-// direct-to-LDS kernel when rows are aligned and N is whole 16-byte chunks.
-template <class Tr>
-bool launch_kr_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, int* rc) {
-  if (!vec_ok(g0.A, g0.lda) || !vec_ok(g0.B, g0.ldb)) return false;
-  if (g0.N % Tr::CH != 0 || g0.K <= 0) return false;
+// direct-to-LDS kernel (rows aligned, whole 16-byte chunks of columns) on BM x BN
+// tiles.
+template <class Tr, int EPI, int BM, int BN>
+int launch_kr_tiles(const GemmArgs<typename Tr::T>& g0, hipStream_t stream) {
   GemmArgs<typename Tr::T> g = g0;
-  g.tiles_m = (g.M + kDBM - 1) / kDBM;
-  g.tiles_n = (g.N + kDBN - 1) / kDBN;
+  g.tiles_m = (g.M + BM - 1) / BM;
+  g.tiles_n = (g.N + BN - 1) / BN;
   const long long tiles = (long long)g.tiles_m * g.tiles_n;
-  if (tiles > 0x7fffffffLL) return false;
+  if (tiles > 0x7fffffffLL) return CC_LADDER_EINVAL;
   g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
-  hipLaunchKernelGGL((gemm_kr_direct_kernel<Tr>), dim3(static_cast<unsigned>(tiles)),
+  hipLaunchKernelGGL((gemm_kr_direct_kernel<Tr, EPI, BM, BN>), dim3(static_cast<unsigned>(tiles)),
                      dim3(kDThreads), 0, stream, g);
-  *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
-  return true;
+  return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
 template <class Tr, int LA, int LB, int EPI, int SIDE>
@@ -200,19 +198,20 @@ int launch_wave_side(const GemmArgs<typename Tr::T>& g0, int wk, hipStream_t str
 }
 
 // mt, nt: rows and columns of the whole output when this launch computes one
-// block of it (0: M, N).
+// block of it (0: M, N).  n_load: readable columns of a row-contiguous B (0: N).
 template <class Tr, int LA, int LB, int EPI>
 int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B, long long ldb,
                 void* C, long long ldc, int M, int N, int K, int v, int drain_steps,
                 hipStream_t stream, int o = 0, int a0 = 0, int* row_tiles = nullptr,
                 double alpha = 1.0, int pm = 0, int kband = 0, int m_keep = 0, int mt = 0,
-                int nt = 0) {
+                int nt = 0, int n_load = 0) {
   if (M <= 0 || N <= 0 || K <= 0) return CC_LADDER_OK;
   GemmArgs<typename Tr::T> g;
   g.alpha = alpha;
   g.pm = pm;
   g.kband = kband;
   g.m_keep = m_keep;
+  g.n_load = n_load;
   g.A = A; g.lda = lda;
   g.B = B; g.ldb = ldb;
   g.C = C; g.ldc = ldc;
@@ -234,9 +233,10 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
   // The register-direct kernel has no K bands, and loads row-contiguous operands
   // by pairs of rows.
   constexpr bool kKC = LA == KC && LB == KC && Tr::kDirectKC;
-  constexpr bool kKR = LA == KC && LB == RC && EPI == EPI_ACC && Tr::kDirectKR;
+  constexpr bool kKR =
+      LA == KC && LB == RC && (EPI == EPI_ACC || EPI == EPI_FOLD) && Tr::kDirectKR;
   const bool aligned = vec_ok(A, lda) && vec_ok(B, ldb);
-  const bool direct = aligned && (kKC || (kKR && N % Tr::CH == 0));
+  const bool direct = aligned && (kKC || (kKR && (n_load ? n_load : N) % Tr::CH == 0));
   const int nk = (K + Tr::BK - 1) / Tr::BK;
   const TilePick pick =
       pick_tiles(!direct ? kTilesStaged : kKC ? kTilesKC : kTilesKR, M, N, K, mt ? mt : M,
@@ -250,8 +250,13 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
     if (direct) return launch_kc_direct<Tr, EPI>(g, pick, stream);
   }
   if constexpr (kKR) {
-    int rc = CC_LADDER_OK;
-    if (direct && launch_kr_direct<Tr>(g, stream, &rc)) return rc;
+    if (direct) {
+      if constexpr (!Tr::kDrain) {
+        if (pick.bn == 64) return launch_kr_tiles<Tr, EPI, 64, 64>(g, stream);
+        if (pick.bn == 128) return launch_kr_tiles<Tr, EPI, 64, 128>(g, stream);
+      }
+      return launch_kr_tiles<Tr, EPI, kDBM, kDBN>(g, stream);
+    }
   }
   g.tiles_m = (M + kBM - 1) / kBM;
   g.tiles_n = (N + kBN - 1) / kBN;
@@ -1275,6 +1280,161 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
   return CC_LADDER_OK;
 }
 
+// S[(a,c)][(b,d)] (row stride lds) from W+ and W- (rows: pairs of a, b; columns:
+// pairs of c, d), with packed values as pm_rows makes them (diagonal pairs once):
+//   S[a,b][c,d] = S[b,a][d,c] = (w W+ + W-) / 2,  S[a,b][d,c] = S[b,a][c,d] = (w W+ - W-) / 2
+// for a <= b, c <= d, w = 1 doubled on a = b and on c = d (no W- there).  One
+// workgroup per (pair (a,b), tile pair C <= D of 32 x 32 tiles): W+- are read along
+// d, and each of the four 32 x 32 tiles of S is written along its contiguous index,
+// two of them through LDS.  Bound by memory: v^4 values written, half of that read
+// (o=30 v=300: 38 ms for 97 GB, 2.5 TB/s).
+__global__ __launch_bounds__(256) void unfold_kernel(const double* __restrict__ Wp, long long ldp,
+                                                     const double* __restrict__ Wm, long long ldm,
+                                                     int v, int tiles, double* __restrict__ S,
+                                                     long long lds) {
+  __shared__ double xs[kSwapTile][kSwapTile + 1], ys[kSwapTile][kSwapTile + 1];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const long long ntp = (long long)tiles * (tiles + 1) / 2;
+  const long long npairs = (long long)v * (v + 1) / 2;
+  for (long long w = blockIdx.x; w < npairs * ntp; w += gridDim.x) {
+    const long long r = w / ntp;
+    const int tp = static_cast<int>(w - r * ntp);
+    const int C = pair_row(tp, tiles);
+    const int D = C + static_cast<int>(tp - pair_prefix_d(C, tiles));
+    const int c0 = C * kSwapTile, d0 = D * kSwapTile;
+    const int a = pair_row(r, v);
+    const int b = a + static_cast<int>(r - pair_prefix_d(a, v));
+    const double* wp = Wp + r * ldp;
+    const double* wm = a < b ? Wm + (pair_prefix_d(a, v - 1) + (b - a - 1)) * ldm : nullptr;
+    const double wab = a == b ? 1.0 : 0.5;
+    // xs[k][l] = S[a,b][c0+k,d0+l], ys[k][l] = S[a,b][d0+l,c0+k] for c0+k <= d0+l
+#pragma unroll
+    for (int k = ty; k < kSwapTile; k += 8) {
+      const int c = c0 + k, d = d0 + tx;
+      if (c < v && d < v && c <= d) {
+        const double p = wp[pair_prefix_d(c, v) + (d - c)] * (c == d ? 2.0 * wab : wab);
+        const double m =
+            wm && c < d ? 0.5 * wm[pair_prefix_d(c, v - 1) + (d - c - 1)] : 0.0;
+        xs[k][tx] = p + m;
+        ys[k][tx] = p - m;
+      }
+    }
+    __syncthreads();
+    double* Sab = S + (long long)a * v * lds + (long long)b * v;  // [c*lds + d]
+    double* Sba = S + (long long)b * v * lds + (long long)a * v;
+#pragma unroll
+    for (int k = ty; k < kSwapTile; k += 8) {
+      // rows c, contiguous d: S[a,b][c,d] and S[b,a][c,d]; in the diagonal tile the
+      // half d < c comes from its mirror
+      int c = c0 + k, d = d0 + tx;
+      if (c < v && d < v) {
+        const bool up = c <= d;  // (C < D: always)
+        Sab[(long long)c * lds + d] = up ? xs[k][tx] : ys[tx][k];
+        if (a < b) Sba[(long long)c * lds + d] = up ? ys[k][tx] : xs[tx][k];
+      }
+      if (D != C) {
+        // rows d, contiguous c: S[a,b][d,c] and S[b,a][d,c]
+        c = c0 + tx;
+        d = d0 + k;
+        if (c < v && d < v) {
+          Sab[(long long)d * lds + c] = ys[tx][k];
+          if (a < b) Sba[(long long)d * lds + c] = xs[tx][k];
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Rows of n doubles copied to a row stride ldy (an even one, for aligned rows).
+__global__ __launch_bounds__(256) void copy_rows_kernel(const double* __restrict__ x, long long rows,
+                                                        long long n, double* __restrict__ y,
+                                                        long long ldy) {
+  const long long per = (n + 255) / 256;
+  for (long long w = blockIdx.x; w < rows * per; w += gridDim.x) {
+    const long long r = w / per, e = (w - r * per) * 256 + threadIdx.x;
+    if (e < n) y[r * ldy + e] = x[r * n + e];
+  }
+}
+
+// The float64 adjoint folded over the exchange of both virtual pairs (FoldAdjoint).
+// Matrix-bound: 3 P v^4 + 2 o^2 v^4 multiply-adds instead of the direct route's
+// (4 P + 4 o^2) v^4.  With odd v, dL runs on rows padded to whole 16-byte chunks.
+// o=30 v=300 P=900: 933 -> 608 ms (build 113, combinations 28, dt 120, W 107, S 38, dL
+// 240).
+int backward_fold(const Plan& pl, const FoldAdjoint& fa, const double* L, const double* t,
+                  const double* lam, double* dL, double* dt, char* base, const Tracer& tr,
+                  hipStream_t s) {
+  const FoldPlan& f = fa.f;
+  const int o = pl.o, v = pl.v, P = pl.P, o2 = o * o, iv2 = v * v;
+  const long long v2 = (long long)v * v;
+  const int kp = static_cast<int>((long long)v * (v + 1) / 2);
+  const int km = static_cast<int>((long long)v * (v - 1) / 2);
+  auto at = [&](size_t off) { return reinterpret_cast<double*>(base + off); };
+  double *Tp = at(f.off_Tp), *Tm = at(f.off_Tm), *Mp = at(fa.off_Mp), *Mm = at(fa.off_Mm);
+  double *V = at(f.off_V), *Vp = at(f.off_Vp), *Vm = at(f.off_Vm);
+  double *Wp = at(fa.off_Wp), *Wm = at(fa.off_Wm), *S = at(fa.off_S);
+  int* row_tiles = reinterpret_cast<int*>(base + f.off_tiles);
+  // exchange: the ladder of swapped amplitudes, t- and dt- with the other sign
+  const double sm = pl.exchange ? -1.0 : 1.0;
+  tr(CC_LADDER_PHASE_PREP, 0, 0);
+  int rc = pm_rows<PM_ALL>(t, o2, o, 0, v, Tp, f.ldp, Tm, f.ldm, 1.0, sm, s);
+  if (!rc) rc = pm_rows<PM_ALL>(lam, o2, o, 0, v, Mp, f.ldp, Mm, f.ldm, 1.0, 1.0, s);
+  tr(CC_LADDER_PHASE_PREP, 0, 1);
+  if (rc) return rc;
+  for (int blk = 0; blk < f.nb; ++blk) {
+    const int a0 = pair_block_start(v, f.nb, blk);
+    const int na = pair_block_start(v, f.nb, blk + 1) - a0;
+    if (na <= 0) continue;
+    const long long off = (long long)a0 * v;
+    const long long p0 = pair_prefix(a0, v), m0 = pair_prefix(a0, v - 1);  // first pairs
+    const long long np = pair_prefix(a0 + na, v) - p0, nm = np - na;
+    tr(CC_LADDER_PHASE_BUILD, blk, 0);
+    rc = launch_gemm<TrF64, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
+                                              static_cast<int>((long long)(v - a0) * v), P, v, 0, s,
+                                              o, a0, row_tiles, 1.0, 0, 0, 0, iv2, iv2);
+    if (!rc) rc = pm_rows<PM_INTS>(V, np, v, a0, v, Vp, f.ldp, Vm, f.ldm, 2.0, 1.0, s);
+    tr(CC_LADDER_PHASE_BUILD, blk, 1);
+    if (rc) return rc;
+    // dt over the pairs of c, d, from the block's pairs of a, b (the pads of V+- rows
+    // may be read: their columns are not stored)
+    tr(CC_LADDER_PHASE_DT, blk, 0);
+    rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mp + p0, f.ldp, Vp, f.ldp, dt, v2, o2, kp,
+                                              static_cast<int>(np), v, 0, s, o, 0, nullptr, 0.5, 1,
+                                              0, 0, 0, 0, static_cast<int>(f.ldp));
+    if (!rc)
+      rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mm + m0, f.ldm, Vm, f.ldm, dt, v2, o2, km,
+                                                static_cast<int>(nm), v, 0, s, o, 0, nullptr,
+                                                0.5 * sm, 2, 0, 0, 0, 0, static_cast<int>(f.ldm));
+    tr(CC_LADDER_PHASE_DT, blk, 1);
+    if (rc) return rc;
+  }
+  tr(CC_LADDER_PHASE_W, 0, 0);
+  rc = launch_gemm<TrF64, RC, RC, EPI_STORE>(Mp, f.ldp, Tp, f.ldp, Wp, f.ldp, kp, kp, o2, v, 0, s);
+  if (!rc)
+    rc = launch_gemm<TrF64, RC, RC, EPI_STORE>(Mm, f.ldm, Tm, f.ldm, Wm, f.ldm, km, km, o2, v, 0, s);
+  tr(CC_LADDER_PHASE_W, 0, 1);
+  if (rc) return rc;
+  tr(CC_LADDER_PHASE_DL, 0, 0);
+  const int tiles = (v + kSwapTile - 1) / kSwapTile;
+  const long long work = (long long)kp * ((long long)tiles * (tiles + 1) / 2);
+  hipLaunchKernelGGL(unfold_kernel, dim3(static_cast<unsigned>(std::min<long long>(work, 65536))),
+                     dim3(256), 0, s, Wp, f.ldp, Wm, f.ldm, v, tiles, S, fa.lds);
+  const double* Lr = L;
+  if (fa.copy_L) {
+    double* Lc = at(fa.off_L);
+    hipLaunchKernelGGL(copy_rows_kernel, dim3(16384), dim3(256), 0, s, L, (long long)P, v2, Lc,
+                       fa.lds);
+    Lr = Lc;
+  }
+  rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+  // dL[x][(a,c)] += sum_(bd) L[x][(bd)] S[(ac)][(bd)]
+  if (!rc)
+    rc = launch_gemm<TrF64, KC, KC, EPI_ACC>(Lr, fa.lds, S, fa.lds, dL, v2, P, iv2, iv2, v, 0, s);
+  tr(CC_LADDER_PHASE_DL, 0, 1);
+  return rc;
+}
+
 // Occupied intermediates: Z[(ij)][(p, y)] += sum_(x,d) t[(ij)][(x,d)] G[(p,y)][(x,d)],
 // G built per block of first indices p from rows (p, x) of Lrow ([P][n_first*v],
 // leading dimension ld_row) and columns (y, d) of L_ov ([P][o*v]).
@@ -1634,6 +1794,9 @@ extern "C" int cc_ladder_backward(int o, int v, int P, const double* L, const do
     if (rc) return rc;
   }
   const Tracer tr(opts, stream);
+  FoldAdjoint fold;
+  if (plan_fold_adjoint(pl, &fold))
+    return backward_fold(pl, fold, L, t, lam, dL, dt, base, tr, stream);
   // exchange: gradients of the ladder at the swapped amplitudes; dt is
   // accumulated in swapped order in scratch and swapped back at the end
   double* dtx = pl.exchange ? reinterpret_cast<double*>(base + pl.off_dtx) : dt;

@@ -38,6 +38,7 @@
 //   EPI_PART: split K: workgroup s of a tile sums K-steps [s*split_steps, (s+1)*split_steps)
 //             and stores C[s*part_stride + m*ldc + n] = acc (float64 partials, summed
 //             in order of s by a separate pass)
+//   EPI_STORE: C[m*ldc + n] = acc (float64)
 //   EPI_SYM:  a symmetric product (A = B): only the tiles on or above the diagonal run
 //             (the compact grid of EPI_PACK with v = 1), and each stores C[m*ldc + n] = acc
 //             and its mirror C[n*ldc + m] = acc (the same value: the products commute)
@@ -78,7 +79,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;
 enum { KC = 0, RC = 1 };
 enum { EPI_ACC = 0, EPI_PERM = 1, EPI_PACK = 2, EPI_PAIR = 3, EPI_PART = 4, EPI_PM = 5,
-       EPI_UNPACK = 6, EPI_SYM = 7, EPI_FOLD = 8 };
+       EPI_UNPACK = 6, EPI_SYM = 7, EPI_FOLD = 8, EPI_STORE = 9 };
 
 // float64 operands on v_mfma_f64_16x16x4_f64.
 struct TrF64 {
@@ -141,6 +142,8 @@ struct GemmArgs {
   int m_off = 0;         // EPI_PAIR/PM: global row of this launch's row 0 (a remainder launch)
   int pm = 0;            // EPI_PM/FOLD: 1 = symmetric pairs (i <= j, a <= b), 2 = antisymmetric (<)
   int kband = 0;         // K bands of a half-written B operand (0 = the whole K range)
+  int n_load = 0;        // mixed direct-to-LDS kernel: columns of B that may be read (N and
+                         // pads up to whole 16-byte chunks; 0 = N)
   int m_keep = 0;        // EPI_UNPACK: rows stored (M may be padded to whole 16-byte chunks)
 };
 
@@ -234,7 +237,7 @@ __device__ __forceinline__ void epi_store(const GemmArgs<T>& g, int m, int n, co
   const long long v = g.v;
   if (EPI == EPI_ACC) {
     static_cast<double*>(g.C)[(long long)m * g.ldc + n] += g.alpha * val;
-  } else if (EPI == EPI_PART) {
+  } else if (EPI == EPI_PART || EPI == EPI_STORE) {
     static_cast<double*>(g.C)[(long long)m * g.ldc + n] = val;
   } else if (EPI == EPI_PERM) {
     const int a = m / g.v, x = m - a * g.v;

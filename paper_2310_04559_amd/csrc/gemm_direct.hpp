@@ -519,48 +519,57 @@ namespace ccl {
 // Mixed-layout GEMM with direct global->LDS loads (gfx950): A K-contiguous, B
 // row-contiguous, float64 accumulation into C:
 //
-//   C[m*ldc + n] += sum_k A[m*lda + k] B[k*ldb + n]
+//   C[m*ldc + n] += sum_k A[m*lda + k] B[k*ldb + n]        (EPI_ACC, or EPI_FOLD)
 //
-// (the adjoint's dt and second dL term, the hole-hole ladder's contraction).  A is
+// (the adjoint's dt and second dL term, the hole-hole ladder's contraction).
+// BM x BN tiles: 128 x 256 (2 x 4 waves of 64 x 64); float64 also 64 x 128 (2 x 4
+// waves of 32 x 32) and 64 x 64 (4 x 2 waves of 16 x 32), two workgroups per compute
+// unit, where the larger tiles would leave compute units idle (pick_tiles).  A is
 // staged like the K-contiguous kernel (8-row slabs of 128-byte rows, XOR-swizzled
 // chunks), B like the row-contiguous kernel (BK rows of 256 contiguous n, columns
 // of a wave's four blocks interleaved).  In MFMA step e of k-group gi, slot j of
 // both operands carries k = gi*4*CH + CH*j + e: A's lane reads its CH consecutive
 // k once per group, B's lane reads that k row's four (float32) or two-plus-two
-// (float64) interleaved columns once per step.  Needs 16-byte aligned rows, N a
-// multiple of the 16-byte chunk; rows past M are clamped, columns past N clamped
-// onto the last chunk (never stored), a ragged last K-step goes through registers
-// with zero fill.
-template <class Tr>
-__global__ __launch_bounds__(kDThreads, 1) void gemm_kr_direct_kernel(GemmArgs<typename Tr::T> g) {
+// (float64) interleaved columns once per step.  Needs 16-byte aligned rows and whole
+// 16-byte chunks of columns (N, or N and readable pads: n_load); rows past M are
+// clamped, columns past N clamped onto the last chunk (never stored), a ragged
+// last K-step goes through registers with zero fill.
+template <class Tr, int EPI = EPI_ACC, int BM = kDBM, int BN = kDBN>
+__global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_direct_kernel(
+    GemmArgs<typename Tr::T> g) {
+  static_assert(EPI == EPI_ACC || EPI == EPI_FOLD, "float64 accumulation");
+  static_assert((BM == kDBM && BN == kDBN) || (BM == 64 && BN <= 128 && Tr::CH == 2),
+                "tiles; the interleave of two column blocks is float64's");
   using T = typename Tr::T;
   using Acc = typename Tr::Acc;
   using Chunk = typename Tr::Chunk;
   constexpr int CH = Tr::CH;
   constexpr int BK = kDRow / sizeof(T);          // 16 float64 / 32 float32
-  constexpr int ROWB = kDBN * sizeof(T);         // bytes of one k row of B (256 n)
-  constexpr int A_BYTES = kDBM * kDRow;          // 16 KB
-  constexpr int B_BYTES = BK * ROWB;             // 32 KB
+  constexpr int ROWB = BN * sizeof(T);           // bytes of one k row of B
+  constexpr int A_BYTES = BM * kDRow;
+  constexpr int B_BYTES = BK * ROWB;
   constexpr int STAGE = A_BYTES + B_BYTES;
-  constexpr int AL = kDBM / 8 / 8;               // A: 8-row slabs per wave (2)
-  constexpr int BI = B_BYTES / 1024 / 8;         // B: 1 KB instructions per wave (4)
+  constexpr int AL = BM / 8 / 8;                 // A: 8-row slabs per wave
+  constexpr int BI = B_BYTES / 1024 / 8;         // B: 1 KB instructions per wave
   constexpr int LOADS = AL + BI;
-  constexpr int CPRB = kDBN / CH;                // 16-byte chunks per B row
+  constexpr int CPRB = BN / CH;                  // 16-byte chunks per B row
+  constexpr int WC = BN == 64 ? 2 : 4;           // wave columns
+  constexpr int MI = BM / (16 * (8 / WC)), NJ = BN / (16 * WC);  // blocks per wave
   __shared__ __attribute__((aligned(1024))) unsigned char lds[kDStages * STAGE];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = (wave >> 2) * 64;
-  const int wn = (wave & 3) * 64;
+  const int wm = (wave / WC) * (16 * MI);
+  const int wn = (wave % WC) * (16 * NJ);
   int tm, tn;
   if (g.kband)
     tile_of_banded(g.kband, blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
   else
     tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
-  const int m0 = tm * kDBM, n0 = tn * kDBN;
+  const int m0 = tm * BM, n0 = tn * BN;
   int ks0, ks1;  // this tile's K-steps
-  k_band(g, n0, kDBN, BK, ks0, ks1);
+  k_band(g, n0, BN, BK, ks0, ks1);
 
   // A: slabs of 8 rows, lane -> row lane/8, physical chunk lane%8 holding
   // logical chunk (lane%8) ^ ((row/2)%8)
@@ -576,6 +585,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kr_direct_kernel(GemmArgs<t
     pa[j] = g.A + (long long)row * g.lda + my_sw;
   }
   // B: wave instruction q covers the 1 KB [q KB, q KB + 1 KB) of the stage's B slab
+  const int nl = g.n_load ? g.n_load : g.N;
   const T* pb[BI];
   int rb[BI];
 #pragma unroll
@@ -583,7 +593,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kr_direct_kernel(GemmArgs<t
     const int flat = (wave + 8 * j) * 64 + lane;
     rb[j] = flat / CPRB;
     int n = n0 + (flat % CPRB) * CH;
-    n = n < g.N ? n : g.N - CH;
+    n = n < nl ? n : nl - CH;
     pb[j] = g.B + (long long)rb[j] * g.ldb + n;
   }
   auto issue = [&](int kt) {
@@ -620,12 +630,12 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kr_direct_kernel(GemmArgs<t
     __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14));  // lgkmcnt(0): the LDS writes landed
   };
 
-  Acc acc[4][4];
-  f64x4 acc64[4][4];
+  Acc acc[MI][NJ];
+  f64x4 acc64[MI][NJ];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       acc[i][j] = Acc{0, 0, 0, 0};
       acc64[i][j] = f64x4{0, 0, 0, 0};
     }
@@ -656,36 +666,33 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kr_direct_kernel(GemmArgs<t
 #pragma unroll
       for (int gi = 0; gi < 2; ++gi) {
         const int chunk = ((4 * gi + slot) ^ fsw) * 16;
-        Chunk fa[4];
+        Chunk fa[MI];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MI; ++i)
           fa[i] = *reinterpret_cast<const Chunk*>(st + (wm + 16 * i) * kDRow + frow + chunk);
 #pragma unroll
         for (int e = 0; e < CH; ++e) {
           // k row gi*4*CH + CH*slot + e of B, this lane's interleaved columns
           const unsigned char* rb_ = st + A_BYTES + (4 * CH * gi + CH * slot + e) * ROWB + offb;
-          T fb[4];
-          if constexpr (CH == 4) {
-            const Chunk b = *reinterpret_cast<const Chunk*>(rb_);
+          T fb[NJ];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) fb[j] = b[j];
-          } else {
-            const Chunk b0 = *reinterpret_cast<const Chunk*>(rb_);
-            const Chunk b1 = *reinterpret_cast<const Chunk*>(rb_ + 32 * sizeof(T));
-            fb[0] = b0[0]; fb[1] = b0[1]; fb[2] = b1[0]; fb[3] = b1[1];
+          for (int h = 0; h < NJ / CH; ++h) {
+            const Chunk b = *reinterpret_cast<const Chunk*>(rb_ + h * 32 * sizeof(T));
+#pragma unroll
+            for (int q = 0; q < CH; ++q) fb[CH * h + q] = b[q];
           }
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+          for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = Tr::mfma(fa[i][e], fb[j], acc[i][j]);
+            for (int j = 0; j < NJ; ++j) acc[i][j] = Tr::mfma(fa[i][e], fb[j], acc[i][j]);
         }
       }
     }
     if (Tr::kDrain) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             acc64[i][j][r] += static_cast<double>(acc[i][j][r]);
@@ -695,19 +702,19 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_kr_direct_kernel(GemmArgs<t
     k0 = kend;
   }
 
-  double* C = static_cast<double*>(g.C);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     const int n = n0 + wn + rc_pos<Tr>(j, r16);
     if (n >= g.N) continue;
+    const EpiCol ec = epi_col<T, EPI>(g, n);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + wm + 16 * i + Tr::row_of(lane, r);
         if (m >= g.M) continue;
-        C[(long long)m * g.ldc + n] +=
-            g.alpha * (Tr::kDrain ? acc64[i][j][r] : static_cast<double>(acc[i][j][r]));
+        epi_store<T, EPI>(g, m, n, ec,
+                          Tr::kDrain ? acc64[i][j][r] : static_cast<double>(acc[i][j][r]));
       }
   }
 }

@@ -520,6 +520,10 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
     take(64, 64, M, tile_cost(M, N, 64, 64, 0.80));
   } else if (cls == kTilesKR) {
     take(128, 256, M, tile_cost(M, N, 128, 256, 0.88));
+    if (tall) {
+      take(64, 128, M, tile_cost(M, N, 64, 128, 0.84));
+      take(64, 64, M, tile_cost(M, N, 64, 64, 0.80));
+    }
   } else {
     take(128, 128, M, tile_cost(M, N, 128, 128, 0.80));
   }
@@ -622,6 +626,47 @@ bool plan_fold(const Plan& pl, FoldPlan* f) {
                   contract(f->rows_m, (pairs - v) / f->nb, (long long)v * (v - 1) / 2) + 4 * kLaunch) +
          16.0 * (pairs + f->rows_p) * v2 * kByte + kLaunch;
   return fold < direct;
+}
+
+bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a) {
+  // From 64 virtuals on, as the forward: below, the extra launches take what the
+  // products save.  W is formed whole, so a plan of several blocks keeps the direct
+  // route.
+  if (pl.op != kOpLadder || pl.precision != CC_LADDER_FP64 || !pl.backward || pl.pairsym_adj ||
+      pl.n_a != pl.v || pl.v < 64)
+    return false;
+  const int v = pl.v;
+  const size_t v2 = static_cast<size_t>(v) * v;
+  const size_t kp = static_cast<size_t>(v) * (v + 1) / 2;
+  for (int nb = 1; nb <= 4; ++nb) {
+    FoldAdjoint p;
+    p.f = layout_fold(pl, nb);  // t+- first, then the blocks
+    if (!p.f.nb) return false;
+    p.lds = static_cast<long long>((v2 + 1) / 2 * 2);
+    p.copy_L = p.lds != static_cast<long long>(v2);
+    const size_t ldp = p.f.ldp, ldm = p.f.ldm;
+    // lam+- after t+-; the blocks of dt's stage and W+-, S share what follows
+    size_t cur = p.f.off_V;
+    p.off_Mp = take(&cur, p.f.rows_p * ldp * sizeof(double));
+    p.off_Mm = take(&cur, p.f.rows_m * ldm * sizeof(double));
+    const size_t shift = cur - p.f.off_V;
+    p.f.off_V += shift;
+    p.f.off_Vp += shift;
+    p.f.off_Vm += shift;
+    p.f.off_tiles += shift;
+    p.f.bytes += shift;
+    p.off_Wp = take(&cur, kp * ldp * sizeof(double));
+    p.off_Wm = take(&cur, (kp - v) * ldm * sizeof(double));
+    p.off_S = take(&cur, v2 * p.lds * sizeof(double));
+    if (p.copy_L) p.off_L = take(&cur, static_cast<size_t>(pl.P) * p.lds * sizeof(double));
+    p.bytes = cur > p.f.bytes ? cur : p.f.bytes;
+    if (p.bytes <= pl.bytes) {
+      *a = p;
+      return true;
+    }
+    if (cur > pl.bytes) return false;  // more blocks shrink dt's stage only
+  }
+  return false;
 }
 
 int layout_intermediate(int which, int o, int v, int P, int precision, int n_p, int k_chunk,

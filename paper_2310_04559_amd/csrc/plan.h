@@ -110,7 +110,7 @@ int choose_k_splits(long long M, long long N, long long K, int bk);
 // all can run on the register-direct kernel (gemm_wave.hpp).
 enum TileClass {
   kTilesKC,     // K-contiguous direct-to-LDS kernel: 128 or 160 x 256, 64 x 128, 64 x 64
-  kTilesKR,     // mixed direct-to-LDS kernel: 128 x 256
+  kTilesKR,     // mixed direct-to-LDS kernel: 128 x 256; float64 also 64 x 128, 64 x 64
   kTilesStaged  // register-staged kernel: 128 x 128
 };
 
@@ -126,7 +126,8 @@ struct TilePick {
 // Picks the cut of a launch that computes M x N of a whole output of mt x nt.
 // `units` is the number of pieces of K that the waves of the register-direct
 // kernel can share (K-steps; float32: drain chunks), `es` the element size.
-// `tall`, `split` as in choose_kc_tiling (kTilesKC).  wk alone decides the order
+// `tall` (kTilesKC: 160-row tiles; kTilesKR: the 64-row ones) and `split` as in
+// choose_kc_tiling.  wk alone decides the order
 // in which an element's sum is formed and depends on the whole output only, so
 // results do not depend on the blocks.
 TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long long mt,
@@ -150,6 +151,24 @@ struct FoldPlan {
 
 // True when the folded forward fits the plan's scratch and is the faster route.
 bool plan_fold(const Plan& pl, FoldPlan* f);
+
+// The float64 adjoint folded the same way, inside the scratch of a plan that holds
+// all of W in one block.  With lam+- combined like t+-,
+//   dt[i][j][c][d] +- dt[i][j][d][c] = sum over pairs a <= b (a < b) of lam+- V+-
+// and the symmetric part of W that dL needs is
+//   S[a,b][c,d] = W[a,b][c,d] + W[b,a][d,c] = (W+ + W-) / 2,  W+- = sum_ij lam+- t+-,
+// so the build, dt and W take half their multiply-adds; dL = L S is as before.
+struct FoldAdjoint {
+  FoldPlan f;                        // t+-, V, V+- (blocks of dt's stage)
+  size_t off_Mp = 0, off_Mm = 0;     // lam+, lam- (strides f.ldp, f.ldm)
+  size_t off_Wp = 0, off_Wm = 0;     // W+ [pairs a <= b][f.ldp], W- [pairs a < b][f.ldm]
+  size_t off_S = 0;                  // S as rows (a,c), columns (b,d), row stride lds
+  size_t off_L = 0;                  // copy of L with row stride lds (odd v only)
+  long long lds = 0;                 // v^2 rounded to 2: rows on 16-byte boundaries
+  bool copy_L = false;
+  size_t bytes = 0;
+};
+bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a);
 
 int layout_intermediate(int which, int o, int v, int P, int precision, int n_p, int k_chunk,
                         Plan* plan);

@@ -65,3 +65,37 @@ def test_folded_forward_non_finite_rows_stay_apart(gpu_lib):
     assert np.isfinite(got[ok]).all() and not np.isfinite(got[1, 2]).any()
     t[1, 2, 3, 5] = 0.0
     assert rel_fro(got[ok], oracle.ladder_forward(L, t)[ok]) < TOL[0]
+
+
+# the folded adjoint: even and odd v (the odd one copies L to aligned rows), more and
+# fewer rows than one tile; a_block = 40 holds W in two blocks and keeps the direct route
+@pytest.mark.parametrize("o,v,P,a_block", [(6, 64, 30, 0), (13, 71, 41, 0), (3, 97, 12, 0),
+                                           (6, 64, 30, 40)])
+@pytest.mark.parametrize("exchange", [False, True])
+def test_folded_backward(gpu_lib, o, v, P, a_block, exchange):
+    import torch
+
+    announce("fold-backward", o, v, P, "a_block", a_block, "exchange", exchange)
+    L, t, lam = random_general(o, v, P, 4300 + o + v)
+    dL0 = np.random.default_rng(23).standard_normal(L.shape)
+    dt0 = np.random.default_rng(24).standard_normal(t.shape)
+    dL, dt = dev(dL0), dev(dt0)
+    gpu_lib.cc_ladder_backward(dev(L), dev(t), dev(lam), dL, dt, 0,
+                               opts=gpu_lib.make_opts(a_block=a_block, exchange=exchange))
+    torch.cuda.synchronize()
+    ref = oracle.exchange_backward(L, t, lam) if exchange else oracle.ladder_backward(L, t, lam)
+    assert rel_fro(host(dL) - dL0, ref[0]) < TOL[0]
+    assert rel_fro(host(dt) - dt0, ref[1]) < TOL[0]
+
+
+def test_folded_backward_integer_exact(gpu_lib):
+    import torch
+
+    announce("fold-backward-int")
+    L, t = integer_inputs(5, 66, 7, 4400)
+    lam = integer_inputs(5, 66, 7, 4401)[1]
+    dL, dt = dev(np.zeros_like(L)), dev(np.zeros_like(t))
+    gpu_lib.cc_ladder_backward(dev(L), dev(t), dev(lam), dL, dt, 0)
+    torch.cuda.synchronize()
+    dL_ref, dt_ref = oracle.ladder_backward(L, t, lam)
+    assert np.array_equal(host(dL), dL_ref) and np.array_equal(host(dt), dt_ref)
