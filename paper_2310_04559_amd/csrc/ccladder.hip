@@ -1633,6 +1633,9 @@ int residual_body(const Plan& pl, const double* L, const double* t, double* R, i
   }
   FoldPlan fold;
   if (plan_fold(pl, &fold)) return forward_fold(pl, fold, L, t, R, base, tr, stream);
+  StackedPlan stacked;
+  if (plan_stacked_i8(pl, &stacked))
+    return split_i8_stacked(pl, stacked, L, t, R, base, tr, stream);
   if (pl.exchange && precision != CC_LADDER_FP32) {
     // the exchange partner is the ladder of the swapped amplitudes
     double* tx = reinterpret_cast<double*>(base + pl.off_tx);
@@ -1689,6 +1692,10 @@ int gather_pair_rows(const double* G, long long ldg, long long nrows, int a0, in
                      hipStream_t s) {
   return pm_gather<GATHER_ROWS>(G, ldg, nrows, a0, v, rows, (long long)v * v,
                                 static_cast<double*>(nullptr), 0, s);
+}
+
+int swap_amplitudes(const double* x, double* y, int o, int v, hipStream_t s) {
+  return swap_cd(x, y, o, v, s);
 }
 
 int ladder_forward_planned(const Plan& pl, const double* L, const double* t, double* R,

@@ -628,6 +628,55 @@ bool plan_fold(const Plan& pl, FoldPlan* f) {
   return fold < direct;
 }
 
+namespace {
+
+StackedPlan layout_stacked_i8(const Plan& pl, int nb) {
+  StackedPlan q;
+  const int v = pl.v;
+  if (nb < 1 || nb > v) return q;
+  const size_t v2 = static_cast<size_t>(v) * v, o2 = static_cast<size_t>(pl.o) * pl.o;
+  size_t np = 0, na_max = 0;
+  for (int k = 0; k < nb; ++k) {
+    const int a0 = pair_block_start(v, nb, k), a1 = pair_block_start(v, nb, k + 1);
+    const size_t n = static_cast<size_t>(pair_prefix(a1, v) - pair_prefix(a0, v));
+    np = n > np ? n : np;
+    na_max = static_cast<size_t>(a1 - a0) > na_max ? static_cast<size_t>(a1 - a0) : na_max;
+  }
+  q.nb = nb;
+  q.npk = static_cast<long long>(np);
+  const size_t s = static_cast<size_t>(pl.slices);
+  const SliceDims dL = slice_dims(static_cast<long long>(v2), pl.P);
+  const SliceDims dt = slice_dims(static_cast<long long>(2 * o2), static_cast<int>(v2));
+  const SliceDims dV = slice_dims(q.npk, static_cast<int>(v2));
+  size_t cur = 0;
+  q.off_L = take(&cur, s * dL.rows_pad * dL.k_pad);
+  q.off_Lexp = take(&cur, static_cast<size_t>(dL.rows_pad) * i8_chunks(dL.k_pad) * sizeof(int));
+  q.off_t = take(&cur, s * dt.rows_pad * dt.k_pad);
+  q.off_texp = take(&cur, static_cast<size_t>(dt.rows_pad) * i8_chunks(dt.k_pad) * sizeof(int));
+  q.off_V = take(&cur, (np > o2 ? np : o2) * v2 * sizeof(double));
+  q.off_Vs = take(&cur, s * dV.rows_pad * dV.k_pad);
+  q.off_Vexp = take(&cur, static_cast<size_t>(dV.rows_pad) * i8_chunks(dV.k_pad) * sizeof(int));
+  q.off_tiles = take(&cur, ((na_max * v + 127) / 128 + 1) * sizeof(int));
+  q.bytes = cur;
+  return q;
+}
+
+}  // namespace
+
+bool plan_stacked_i8(const Plan& pl, StackedPlan* q) {
+  // From 64 virtuals on; below, a call is launches rather than digit products.  At
+  // most twice the direct plan's blocks: smaller ones would leave the contraction's
+  // grid short.
+  if (pl.op != kOpLadder || pl.precision != CC_LADDER_SPLIT_INT8 || pl.backward || pl.pairsym ||
+      pl.v < 64)
+    return false;
+  for (int nb = 1; nb <= 2 * pl.nblocks && nb <= pl.v; ++nb) {
+    *q = layout_stacked_i8(pl, nb);
+    if (q->bytes <= pl.bytes) return true;
+  }
+  return false;
+}
+
 bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a) {
   // From 64 virtuals on, as the forward: below, the extra launches take what the
   // products save.  W is formed whole, so a plan of several blocks keeps the direct

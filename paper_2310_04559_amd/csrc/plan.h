@@ -152,6 +152,23 @@ struct FoldPlan {
 // True when the folded forward fits the plan's scratch and is the faster route.
 bool plan_fold(const Plan& pl, FoldPlan* f);
 
+// The split-int8 general forward over the pairs a <= b, inside the scratch of its
+// direct plan.  R[i][j][b][a] is the ladder of the amplitudes with c and d swapped at
+// column (a,b), since (bc|ad) = (ad|bc): the packed rows a <= b of the integral,
+// contracted with t and with its swapped copy stacked as 2 o^2 rows, give all of R.
+// Half the build and half the re-cut integral rows; the contraction is the same size.
+// Within a chunk of contracted indices the order of the indices does not matter to
+// the digits or to the exact sums.
+struct StackedPlan {
+  int nb = 0;  // pair-balanced blocks
+  long long npk = 0;  // packed rows of the largest
+  size_t off_L = 0, off_Lexp = 0, off_t = 0, off_texp = 0, off_V = 0, off_Vs = 0, off_Vexp = 0;
+  size_t off_tiles = 0;
+  size_t bytes = 0;
+};
+// True when it fits the plan's scratch (V must also hold the swapped copy of t).
+bool plan_stacked_i8(const Plan& pl, StackedPlan* q);
+
 // The float64 adjoint folded the same way, inside the scratch of a plan that holds
 // all of W in one block.  With lam+- combined like t+-,
 //   dt[i][j][c][d] +- dt[i][j][d][c] = sum over pairs a <= b (a < b) of lam+- V+-

@@ -48,8 +48,13 @@ int pack_pair_vectors(const double* L, double* Lp, int P, int v, long long ldg, 
 int gather_pair_rows(const double* G, long long ldg, long long nrows, int a0, int v, double* rows,
                      hipStream_t s);
 
+// x with its last two indices swapped, over o x o matrices of v x v.
+int swap_amplitudes(const double* x, double* y, int o, int v, hipStream_t s);
+
 int split_forward(const Plan& pl, const double* L, const double* t, double* R, char* ws,
                   const Tracer& tr, hipStream_t stream);
+int split_i8_stacked(const Plan& pl, const StackedPlan& q, const double* L, const double* t,
+                     double* R, char* ws, const Tracer& tr, hipStream_t stream);
 int split_i8_forward(const Plan& pl, const double* L, const double* t, double* R, char* ws,
                      const Tracer& tr, hipStream_t stream);
 

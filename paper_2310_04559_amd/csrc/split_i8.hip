@@ -193,14 +193,18 @@ struct I8Args {
   int M, N, Kp;
   double* C;             // EPI_ACC: C[m*ldc + n] +=; EPI_PERM: float64 integral block;
                          // EPI_PACK: packed rows a <= b of the block; EPI_PAIR: R (both mirrors);
-                         // EPI_SYM: the symmetric product C[m*ldc + n] of one operand with itself
+                         // EPI_SYM: the symmetric product C[m*ldc + n] of one operand with itself;
+                         // EPI_STACK: rows m of t, then of t with c and d swapped (o2 each),
+                         // columns packed pairs (a,b): R[m][a][b], R[m - o2][b][a]
   long long ldc;
   int v;
-  int o;                 // EPI_PAIR: occupied count (rows are (i,j))
-  int a0;                // EPI_PACK/PAIR: first virtual of the integral block
+  int o;                 // EPI_PAIR/STACK: occupied count (rows are (i,j))
+  int a0;                // EPI_PACK/PAIR/STACK: first virtual of the integral block
   const int* row_tiles;  // EPI_PACK/EPI_SYM compact grid: first linear tile of each tile row
   int tiles_m, tiles_n, group_m;
 };
+
+constexpr int EPI_STACK = 16;  // this file's own epilogue, beside those of gemm.hpp
 
 __device__ __forceinline__ void i8_wait_vm0() {
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
@@ -396,7 +400,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void i8_gemm_kernel(I8Args g) {
         } else if (EPI == EPI_PACK) {
           pa = n / g.v;
           pb = n - pa * g.v;
-        } else if (EPI == EPI_PAIR) {
+        } else if (EPI == EPI_PAIR || EPI == EPI_STACK) {
           const long long q = pair_prefix_d(g.a0, v) + n;
           pa = pair_row(q, g.v);
           pb = pa + static_cast<int>(q - pair_prefix_d(pa, v));
@@ -438,6 +442,12 @@ __global__ __launch_bounds__(64 * WAVES, 1) void i8_gemm_kernel(I8Args g) {
                 double* d2 = C + (long long)n * g.ldc + m;
                 *d2 = first ? val : *d2 + val;
               }
+            } else if (EPI == EPI_STACK) {
+              const int o2 = g.o * g.o;
+              if (m < o2)
+                C[(long long)m * g.ldc + (long long)pa * v + pb] += val;
+              else if (pa != pb)
+                C[(long long)(m - o2) * g.ldc + (long long)pb * v + pa] += val;
             } else {  // EPI_PAIR: R[i][j][a][b] and, for a != b, R[j][i][b][a]
               C[(long long)m * g.ldc + (long long)pa * v + pb] += val;
               if (pa != pb) {
@@ -511,15 +521,23 @@ int launch_i8_gemm(const I8Args& a0, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
+// `rows` digit rows are written for R source rows (the others as zeros), on rows
+// of out and ex whose exponents of consecutive chunks are ex_stride apart.
+template <int S>
+int i8_slice_kc_rows(const double* X, long long ld, int R, int rows, int K, int Kp, int ex_stride,
+                     signed char* out, int* ex, hipStream_t s) {
+  const int nch = i8_chunks(Kp);
+  const long long grid = (long long)rows * nch;
+  if (grid > 0x7fffffffLL) return CC_LADDER_EINVAL;
+  hipLaunchKernelGGL((i8_slice_kc_kernel<S>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, X,
+                     ld, R, K, Kp, nch, out, ex, ex_stride);
+  return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+}
+
 template <int S>
 int i8_slice_kc(const double* X, long long ld, int R, int K, const SliceDims& d, signed char* out,
                 int* ex, hipStream_t s) {
-  const int nch = i8_chunks(d.k_pad);
-  const long long grid = (long long)d.rows_pad * nch;
-  if (grid > 0x7fffffffLL) return CC_LADDER_EINVAL;
-  hipLaunchKernelGGL((i8_slice_kc_kernel<S>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, X,
-                     ld, R, K, d.k_pad, nch, out, ex, d.rows_pad);
-  return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+  return i8_slice_kc_rows<S>(X, ld, R, d.rows_pad, K, d.k_pad, d.rows_pad, out, ex, s);
 }
 
 template <int S>
@@ -641,7 +659,87 @@ int i8_forward_s(const Plan& pl, const double* L, const double* t, double* R, ch
   return CC_LADDER_OK;
 }
 
+// The general forward over the pairs a <= b with t and its swapped copy stacked
+// (StackedPlan).  Bound by the integer matrix cores; against the direct route it
+// builds and re-cuts half the integral rows and leaves no half-empty tile row
+// (2 o^2 = 3200 rows at o = 40).  o=40 v=360 P=1200: 553 -> 469 ms.
+template <int S, int D>
+int i8_stacked_s(const Plan& pl, const StackedPlan& q, const double* L, const double* t, double* R,
+                 char* ws, const Tracer& tr, hipStream_t s) {
+  const int o = pl.o, v = pl.v, P = pl.P, o2 = o * o;
+  const long long v2 = (long long)v * v;
+  const SliceDims dL = slice_dims(v2, P);
+  const SliceDims dt = slice_dims(2LL * o2, static_cast<int>(v2));
+  const SliceDims dV = slice_dims(q.npk, static_cast<int>(v2));
+  signed char* Ls = reinterpret_cast<signed char*>(ws + q.off_L);
+  int* Le = reinterpret_cast<int*>(ws + q.off_Lexp);
+  signed char* ts = reinterpret_cast<signed char*>(ws + q.off_t);
+  int* te = reinterpret_cast<int*>(ws + q.off_texp);
+  double* V = reinterpret_cast<double*>(ws + q.off_V);
+  signed char* Vs = reinterpret_cast<signed char*>(ws + q.off_Vs);
+  int* Ve = reinterpret_cast<int*>(ws + q.off_Vexp);
+  const int iv2 = static_cast<int>(v2);
+  tr(CC_LADDER_PHASE_PREP, 0, 0);
+  int rc = i8_slice_rc<S>(L, v2, iv2, P, dL, Ls, Le, s);
+  // the swapped copy lies in the integral block's place until it is cut; the
+  // exchange partner's amplitudes are the swapped ones, so the halves trade places
+  if (!rc) rc = swap_amplitudes(t, V, o, v, s);
+  const double* first = pl.exchange ? V : t;
+  const double* second = pl.exchange ? t : V;
+  if (!rc) rc = i8_slice_kc_rows<S>(first, v2, o2, o2, iv2, dt.k_pad, dt.rows_pad, ts, te, s);
+  if (!rc)
+    rc = i8_slice_kc_rows<S>(second, v2, o2, dt.rows_pad - o2, iv2, dt.k_pad, dt.rows_pad,
+                             ts + (long long)o2 * dt.k_pad * S, te + o2, s);
+  tr(CC_LADDER_PHASE_PREP, 0, 1);
+  if (rc) return rc;
+  const long long Lrow = (long long)dL.k_pad * S;
+  for (int blk = 0; blk < q.nb; ++blk) {
+    const int a0 = pair_block_start(v, q.nb, blk);
+    const int na = pair_block_start(v, q.nb, blk + 1) - a0;
+    if (na <= 0) continue;
+    const long long r0 = (long long)a0 * v;
+    const long long np = pair_prefix(a0 + na, v) - pair_prefix(a0, v);
+    I8Args b{};
+    b.A = b.B = Ls + r0 * Lrow;
+    b.ea = b.eb = Le + r0;
+    b.ea_stride = b.eb_stride = dL.rows_pad;
+    b.M = na * v; b.N = static_cast<int>((long long)(v - a0) * v); b.Kp = dL.k_pad;
+    b.C = V; b.v = v; b.a0 = a0;
+    b.row_tiles = reinterpret_cast<const int*>(ws + q.off_tiles);
+    tr(CC_LADDER_PHASE_BUILD, blk, 0);
+    rc = launch_i8_gemm<S, D, EPI_PACK>(b, s);
+    tr(CC_LADDER_PHASE_BUILD, blk, 1);
+    if (rc) return rc;
+    tr(CC_LADDER_PHASE_SLICE, blk, 0);
+    rc = i8_slice_kc<S>(V, v2, static_cast<int>(np), iv2, dV, Vs, Ve, s);
+    tr(CC_LADDER_PHASE_SLICE, blk, 1);
+    if (rc) return rc;
+    I8Args c{};
+    c.A = ts; c.ea = te;
+    c.B = Vs; c.eb = Ve;
+    c.ea_stride = dt.rows_pad;
+    c.eb_stride = dV.rows_pad;
+    c.M = 2 * o2; c.N = static_cast<int>(np); c.Kp = dt.k_pad;
+    c.C = R; c.ldc = v2; c.v = v; c.o = o; c.a0 = a0;
+    tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
+    rc = launch_i8_gemm<S, D, EPI_STACK>(c, s);
+    tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
+    if (rc) return rc;
+  }
+  return CC_LADDER_OK;
+}
+
 }  // namespace
+
+int split_i8_stacked(const Plan& pl, const StackedPlan& q, const double* L, const double* t,
+                     double* R, char* ws, const Tracer& tr, hipStream_t stream) {
+  switch (pl.slices * 10 + pl.split_depth) {
+    case 41: return i8_stacked_s<4, 1>(pl, q, L, t, R, ws, tr, stream);
+    case 42: return i8_stacked_s<4, 2>(pl, q, L, t, R, ws, tr, stream);
+    case 51: return i8_stacked_s<5, 1>(pl, q, L, t, R, ws, tr, stream);
+    default: return CC_LADDER_EINVAL;
+  }
+}
 
 int split_i8_forward(const Plan& pl, const double* L, const double* t, double* R, char* ws,
                      const Tracer& tr, hipStream_t stream) {
