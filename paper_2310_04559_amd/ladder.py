@@ -37,9 +37,16 @@ def _with_workspace(opts, o, v, P, precision, backward, device):
     if opts is not None and opts.workspace:
         return opts
     base = opts if opts is not None else native.make_opts()
-    budget = base.hbm_budget or _budget(device)
+    budget = base.hbm_budget
     nbytes, _ = native.cc_ladder_workspace_query(o, v, P, precision, backward=backward,
                                                  hbm_budget=budget, opts=base)
+    # The unlimited plan is the budget's plan whenever it fits the budget, which is at
+    # least half the free memory; only a plan that does not fit that needs PyTorch's
+    # allocator statistics (75 us a call, against 3 for the free memory: they were
+    # most of a small ladder's time).
+    if not budget and nbytes > min(_BUDGET_CAP, torch.cuda.mem_get_info(device)[0] // 2):
+        nbytes, _ = native.cc_ladder_workspace_query(o, v, P, precision, backward=backward,
+                                                     hbm_budget=_budget(device), opts=base)
     ws = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
     return native.copy_opts(base, workspace=ws)
 
