@@ -130,15 +130,15 @@ __global__ void pack_rows_kernel(int* row_tiles, int tiles_m, int tiles_n, int v
 
 // Integral builds (both operands row-contiguous, permuted or packed store) take
 // the direct-to-LDS RC kernel when rows are whole 16-byte chunks and aligned.
-template <class Tr>
-bool rc_direct_ok(const GemmArgs<typename Tr::T>& g) {
-  return vec_ok(g.A, g.lda) && vec_ok(g.B, g.ldb) && g.M % Tr::CH == 0 && g.N % Tr::CH == 0 &&
-         g.K > 0;
-}
-
 template <class Tr, int EPI>
 bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, int* rc) {
-  if (!rc_direct_ok<Tr>(g0)) return false;
+  if (!vec_ok(g0.A, g0.lda) || !vec_ok(g0.B, g0.ldb) || g0.K <= 0) return false;
+  // rows that end in a part of a 16-byte chunk: readable pads, and the order of k that
+  // these products have on the register-staged kernel
+  const bool whole = g0.M % Tr::CH == 0 && g0.N % Tr::CH == 0;
+  if (!whole && (EPI != EPI_PERM || !g0.m_load || g0.m_load % Tr::CH || !g0.n_load ||
+                 g0.n_load % Tr::CH))
+    return false;
   GemmArgs<typename Tr::T> g = g0;
   g.tiles_m = (g.M + kDBM - 1) / kDBM;
   g.tiles_n = (g.N + kDBN - 1) / kDBN;
@@ -159,6 +159,15 @@ bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, in
     hipLaunchKernelGGL(pack_rows_kernel, dim3(1), dim3(1), 0, stream,
                        const_cast<int*>(g.row_tiles), g.tiles_m, g.tiles_n, g.v, kDBM, kDBN);
     grid = needed;
+  }
+  if constexpr (EPI == EPI_PERM) {
+    if (g.sym) grid = sym_tiles_before(g.tiles_m, g.tiles_n);
+    if (!whole) {
+      hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI, 1>), dim3(static_cast<unsigned>(grid)),
+                         dim3(kDThreads), 0, stream, g);
+      *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+      return true;
+    }
   }
   hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI>), dim3(static_cast<unsigned>(grid)),
                      dim3(kDThreads), 0, stream, g);
@@ -198,13 +207,16 @@ int launch_wave_side(const GemmArgs<typename Tr::T>& g0, int wk, hipStream_t str
 }
 
 // mt, nt: rows and columns of the whole output when this launch computes one
-// block of it (0: M, N).  n_load: readable columns of a row-contiguous B (0: N).
+// block of it (0: M, N).  m_load, n_load: readable rows of a row-contiguous A and
+// columns of a row-contiguous B (0: M, N).  ldv: EPI_PERM's row stride (0: v^2).  sym:
+// the product of one operand with itself over all its columns (half of it formed where
+// the direct kernel takes it).
 template <class Tr, int LA, int LB, int EPI>
 int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B, long long ldb,
                 void* C, long long ldc, int M, int N, int K, int v, int drain_steps,
                 hipStream_t stream, int o = 0, int a0 = 0, int* row_tiles = nullptr,
                 double alpha = 1.0, int pm = 0, int kband = 0, int m_keep = 0, int mt = 0,
-                int nt = 0, int n_load = 0) {
+                int nt = 0, int n_load = 0, int m_load = 0, long long ldv = 0, int sym = 0) {
   if (M <= 0 || N <= 0 || K <= 0) return CC_LADDER_OK;
   GemmArgs<typename Tr::T> g;
   g.alpha = alpha;
@@ -212,6 +224,9 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
   g.kband = kband;
   g.m_keep = m_keep;
   g.n_load = n_load;
+  g.m_load = m_load;
+  g.ldv = ldv ? ldv : (long long)v * v;
+  g.sym = sym;
   g.A = A; g.lda = lda;
   g.B = B; g.ldb = ldb;
   g.C = C; g.ldc = ldc;
@@ -343,6 +358,17 @@ int launch_contract_split(const typename Tr::T* A, long long lda, const typename
 // operand preparation and reductions
 // ---------------------------------------------------------------------------
 
+// Rows of n values converted to a row stride ldy.
+__global__ __launch_bounds__(256) void to_f32_rows_kernel(const double* __restrict__ x,
+                                                          long long rows, long long n,
+                                                          float* __restrict__ y, long long ldy) {
+  const long long per = (n + 255) / 256;
+  for (long long w = blockIdx.x; w < rows * per; w += gridDim.x) {
+    const long long r = w / per, e = (w - r * per) * 256 + threadIdx.x;
+    if (e < n) y[r * ldy + e] = static_cast<float>(x[r * n + e]);
+  }
+}
+
 __global__ __launch_bounds__(256) void to_f32_kernel(const double* __restrict__ x,
                                                      float* __restrict__ y, long long n) {
   const long long stride = (long long)gridDim.x * blockDim.x;
@@ -358,6 +384,16 @@ int to_f32(const double* x, float* y, size_t n, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
+int to_f32_rows(const double* x, float* y, long long rows, long long n, long long ldy,
+                hipStream_t s) {
+  if (ldy == n) return to_f32(x, y, static_cast<size_t>(rows) * n, s);
+  const long long blocks = std::min<long long>(rows * ((n + 255) / 256), 16384);
+  if (blocks <= 0) return CC_LADDER_OK;
+  hipLaunchKernelGGL(to_f32_rows_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, x,
+                     rows, n, y, ldy);
+  return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+}
+
 // y[m][d][c] = x[m][c][d] for o^2 matrices m of v x v, through a 32 x 32 LDS
 // tile so that both the read and the write of a tile row are coalesced.  One
 // workgroup per (matrix, tile) pair, grid-stride.  Out is double or float
@@ -367,7 +403,7 @@ constexpr int kSwapTile = 32;
 template <typename Out>
 __global__ __launch_bounds__(256) void swap_cd_kernel(const double* __restrict__ x,
                                                       Out* __restrict__ y, int v, long long nmat,
-                                                      int tiles) {
+                                                      int tiles, long long ldy) {
   __shared__ double tile[kSwapTile][kSwapTile + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 8 rows of 32 lanes
   const long long per_mat = (long long)tiles * tiles;
@@ -377,7 +413,7 @@ __global__ __launch_bounds__(256) void swap_cd_kernel(const double* __restrict__
     const int r = static_cast<int>(w - m * per_mat);
     const int c0 = (r / tiles) * kSwapTile, d0 = (r % tiles) * kSwapTile;
     const double* xm = x + m * v2;
-    Out* ym = y + m * v2;
+    Out* ym = y + m * ldy;
 #pragma unroll
     for (int k = ty; k < kSwapTile; k += 8) {
       const int c = c0 + k, d = d0 + tx;
@@ -394,13 +430,13 @@ __global__ __launch_bounds__(256) void swap_cd_kernel(const double* __restrict__
 }
 
 template <typename Out>
-int swap_cd(const double* x, Out* y, int o, int v, hipStream_t s) {
+int swap_cd(const double* x, Out* y, int o, int v, hipStream_t s, long long ldy = 0) {
   const long long nmat = (long long)o * o;
   const int tiles = (v + kSwapTile - 1) / kSwapTile;
   const long long work = nmat * tiles * tiles;
   const long long blocks = std::min<long long>(work, 16384);
   hipLaunchKernelGGL(swap_cd_kernel<Out>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, x,
-                     y, v, nmat, tiles);
+                     y, v, nmat, tiles, ldy ? ldy : (long long)v * v);
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
@@ -491,12 +527,13 @@ __global__ __launch_bounds__(256) void mirror_add_kernel(const double* __restric
   }
 }
 
-// In place W <- W + W^T for a square n x n matrix (row stride n): one workgroup
+// In place W <- W + W^T for a square n x n matrix (row stride ld): one workgroup
 // per pair of 32 x 32 tiles P <= Q reads both tiles through LDS and writes both
 // sums, so every element is read and written once and no two workgroups touch
 // the same element.
 template <typename T>
-__global__ __launch_bounds__(256) void sym_add_kernel(T* __restrict__ W, long long n, int tiles) {
+__global__ __launch_bounds__(256) void sym_add_kernel(T* __restrict__ W, long long n, long long ld,
+                                                      int tiles) {
   __shared__ double a[kSwapTile][kSwapTile + 1], b[kSwapTile][kSwapTile + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const long long npairs = (long long)tiles * (tiles + 1) / 2;
@@ -507,28 +544,28 @@ __global__ __launch_bounds__(256) void sym_add_kernel(T* __restrict__ W, long lo
 #pragma unroll
     for (int k = ty; k < kSwapTile; k += 8) {
       // a[k][tx] = W[p0+k][q0+tx], b[k][tx] = W[q0+k][p0+tx]
-      a[k][tx] = (p0 + k < n && q0 + tx < n) ? static_cast<double>(W[(p0 + k) * n + q0 + tx]) : 0.0;
-      b[k][tx] = (q0 + k < n && p0 + tx < n) ? static_cast<double>(W[(q0 + k) * n + p0 + tx]) : 0.0;
+      a[k][tx] = (p0 + k < n && q0 + tx < n) ? static_cast<double>(W[(p0 + k) * ld + q0 + tx]) : 0.0;
+      b[k][tx] = (q0 + k < n && p0 + tx < n) ? static_cast<double>(W[(q0 + k) * ld + p0 + tx]) : 0.0;
     }
     __syncthreads();
 #pragma unroll
     for (int k = ty; k < kSwapTile; k += 8) {
       // W[p0+k][q0+tx] = a[k][tx] + b[tx][k]; W[q0+k][p0+tx] = b[k][tx] + a[tx][k]
-      if (p0 + k < n && q0 + tx < n) W[(p0 + k) * n + q0 + tx] = static_cast<T>(a[k][tx] + b[tx][k]);
+      if (p0 + k < n && q0 + tx < n) W[(p0 + k) * ld + q0 + tx] = static_cast<T>(a[k][tx] + b[tx][k]);
       if (P != Q && q0 + k < n && p0 + tx < n)
-        W[(q0 + k) * n + p0 + tx] = static_cast<T>(b[k][tx] + a[tx][k]);
+        W[(q0 + k) * ld + p0 + tx] = static_cast<T>(b[k][tx] + a[tx][k]);
     }
     __syncthreads();
   }
 }
 
 template <typename T>
-int sym_add(T* W, long long n, hipStream_t s) {
+int sym_add(T* W, long long n, long long ld, hipStream_t s) {
   const int tiles = static_cast<int>((n + kSwapTile - 1) / kSwapTile);
   const long long work = (long long)tiles * (tiles + 1) / 2;
   const long long blocks = std::min<long long>(work, 65536);
   hipLaunchKernelGGL((sym_add_kernel<T>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, W, n,
-                     tiles);
+                     ld, tiles);
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
@@ -974,6 +1011,7 @@ int forward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::T
                    const typename Tr::T* Lp = nullptr, typename Tr::T* G = nullptr) {
   const int o = pl.o, v = pl.v, P = pl.P;
   const long long v2 = (long long)v * v;
+  const long long ldk = pl.ldk;  // row stride of L, t and V (lam and W)
   const int iv2 = v * v;
   const int drain = Tr::kDrain ? pl.k_chunk / Tr::BK : 0;
   if (pl.gsym) {
@@ -1011,14 +1049,16 @@ int forward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::T
     }
     // V_A[a][b][c][d]: rows (a,c) of L's block, columns (b,d) of L, K = x
     tr(CC_LADDER_PHASE_BUILD, blk, 0);
-    int rc = launch_gemm<Tr, RC, RC, EPI_PERM>(L + (long long)a0 * v, v2, L, v2, V, 0, na * v,
-                                               static_cast<int>(v2), P, v, drain, s, 0, 0, nullptr,
-                                               1.0, 0, 0, 0, iv2, iv2);
+    // (with every virtual in the block, the integral is one symmetric product)
+    int rc = launch_gemm<Tr, RC, RC, EPI_PERM>(
+        L + (long long)a0 * v, ldk, L, ldk, V, 0, na * v, iv2, P, v, drain, s, 0, 0, nullptr, 1.0,
+        0, 0, 0, iv2, iv2, static_cast<int>(ldk), na == v ? static_cast<int>(ldk) : 0, ldk,
+        na == v);
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
     // R[(ij)][a0*v + (a,b)] += t[(ij)][(cd)] . V_A[(ab)][(cd)]
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
-    rc = launch_gemm<Tr, KC, KC, EPI_ACC>(t, v2, V, v2, R + (long long)a0 * v, v2, o * o, na * v,
+    rc = launch_gemm<Tr, KC, KC, EPI_ACC>(t, ldk, V, ldk, R + (long long)a0 * v, v2, o * o, na * v,
                                           static_cast<int>(v2), v, drain, s, 0, 0, nullptr, 1.0, 0, 0,
                                           0, o * o, iv2);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
@@ -1154,6 +1194,7 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
   using T = typename Tr::T;
   const int o = pl.o, v = pl.v, P = pl.P;
   const long long v2 = (long long)v * v;
+  const long long ldk = pl.ldk;  // row stride of L, t, lam, V and W (v^2 when pair-symmetric)
   const int iv2 = v * v;
   const int drain = Tr::kDrain ? pl.k_chunk / Tr::BK : 0;
   T* V = reinterpret_cast<T*>(base + pl.off_V);
@@ -1202,15 +1243,16 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
       if (rc) return rc;
     } else {
       tr(CC_LADDER_PHASE_BUILD, blk, 0);
-      rc = launch_gemm<Tr, RC, RC, EPI_PERM>(L + off, v2, L, v2, V, 0, na * v,
-                                             static_cast<int>(v2), P, v, drain, s, 0, 0, nullptr, 1.0,
-                                             0, 0, 0, iv2, iv2);
+      rc = launch_gemm<Tr, RC, RC, EPI_PERM>(
+          L + off, ldk, L, ldk, V, 0, na * v, iv2, P, v, drain, s, 0, 0, nullptr, 1.0, 0, 0, 0, iv2,
+          iv2, static_cast<int>(ldk), na == v ? static_cast<int>(ldk) : 0, ldk, na == v);
       tr(CC_LADDER_PHASE_BUILD, blk, 1);
       if (rc) return rc;
       // dt[(ij)][(cd)] += lam[(ij)][a0*v + (ab)] . V_A[(ab)][(cd)]
       tr(CC_LADDER_PHASE_DT, blk, 0);
-      rc = launch_gemm<Tr, KC, RC, EPI_ACC>(lam + off, v2, V, v2, dt, v2, o * o,
-                                            static_cast<int>(v2), na * v, v, drain, s);
+      rc = launch_gemm<Tr, KC, RC, EPI_ACC>(lam + off, ldk, V, ldk, dt, v2, o * o, iv2, na * v, v,
+                                            drain, s, 0, 0, nullptr, 1.0, 0, 0, 0, 0, 0,
+                                            static_cast<int>(ldk));
       tr(CC_LADDER_PHASE_DT, blk, 1);
       if (rc) return rc;
     }
@@ -1231,9 +1273,10 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
                                                  static_cast<int>(v2), o * o, v, drain, s, 0, a0,
                                                  nullptr, 1.0, 0, 0, static_cast<int>(npairs));
     } else {
-      rc = launch_gemm<Tr, RC, RC, EPI_PERM>(lam + off, v2, t, v2, W, 0, na * v,
-                                             static_cast<int>(v2), o * o, v, drain, s, 0, 0, nullptr,
-                                             1.0, 0, 0, 0, iv2, iv2);
+      rc = launch_gemm<Tr, RC, RC, EPI_PERM>(lam + off, ldk, t, ldk, W, 0, na * v, iv2, o * o, v,
+                                             drain, s, 0, 0, nullptr, 1.0, 0, 0, 0, iv2, iv2,
+                                             static_cast<int>(ldk),
+                                             na == v ? static_cast<int>(ldk) : 0, ldk);
     }
     tr(CC_LADDER_PHASE_W, blk, 1);
     if (rc) return rc;
@@ -1254,18 +1297,19 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
     } else if (na == v) {
       // one block holds all of W' = [(ac)][(bd)]: the two terms are one product
       // with its symmetric part, dL[x][p] += sum_q L[x][q] (W'[p][q] + W'[q][p])
-      rc = sym_add(W, v2, s);
+      rc = sym_add(W, v2, ldk, s);
       if (!rc)
-        rc = launch_gemm<Tr, KC, KC, EPI_ACC>(L, v2, W, v2, dL, v2, P, static_cast<int>(v2),
+        rc = launch_gemm<Tr, KC, KC, EPI_ACC>(L, ldk, W, ldk, dL, v2, P, static_cast<int>(v2),
                                               static_cast<int>(v2), v, drain, s);
     } else {
       // dL[x][a0*v + (ac)] += L[x][(bd)] . W'_A[(ac)][(bd)]
-      rc = launch_gemm<Tr, KC, KC, EPI_ACC>(L, v2, W, v2, dL + off, v2, P, na * v,
+      rc = launch_gemm<Tr, KC, KC, EPI_ACC>(L, ldk, W, ldk, dL + off, v2, P, na * v,
                                             static_cast<int>(v2), v, drain, s);
       // dL[x][(bd)] += L[x][a0*v + (ac)] . W'_A[(ac)][(bd)]
       if (!rc)
-        rc = launch_gemm<Tr, KC, RC, EPI_ACC>(L + off, v2, W, v2, dL, v2, P, static_cast<int>(v2),
-                                              na * v, v, drain, s);
+        rc = launch_gemm<Tr, KC, RC, EPI_ACC>(L + off, ldk, W, ldk, dL, v2, P, static_cast<int>(v2),
+                                              na * v, v, drain, s, 0, 0, nullptr, 1.0, 0, 0, 0, 0, 0,
+                                              static_cast<int>(ldk));
     }
     tr(CC_LADDER_PHASE_DL, blk, 1);
     if (rc) return rc;
@@ -1664,9 +1708,11 @@ int residual_body(const Plan& pl, const double* L, const double* t, double* R, i
       float* t32 = reinterpret_cast<float*>(base + pl.off_t);
       float* Lp = pl.gsym ? reinterpret_cast<float*>(base + pl.off_Lp) : nullptr;
       tr(CC_LADDER_PHASE_PREP, 0, 0);
-      rc = pl.gsym ? pack_sym(L, Lp, P, v, pl.ldg, stream) : to_f32(L, L32, (size_t)P * v * v, stream);
+      const long long v2 = (long long)v * v;
+      rc = pl.gsym ? pack_sym(L, Lp, P, v, pl.ldg, stream) : to_f32_rows(L, L32, P, v2, pl.ldk, stream);
       if (!rc)
-        rc = pl.exchange ? swap_cd(t, t32, o, v, stream) : to_f32(t, t32, (size_t)o * o * v * v, stream);
+        rc = pl.exchange ? swap_cd(t, t32, o, v, stream, pl.ldk)
+                         : to_f32_rows(t, t32, (long long)o * o, v2, pl.ldk, stream);
       tr(CC_LADDER_PHASE_PREP, 0, 1);
       if (rc) return rc;
       return forward_blocks<TrF32>(pl, L32, t32, R, reinterpret_cast<float*>(base + pl.off_V),
@@ -1833,10 +1879,12 @@ extern "C" int cc_ladder_backward(int o, int v, int P, const double* L, const do
     float* lam32 = reinterpret_cast<float*>(base + pl.off_lam);
     float* Lp = pl.gsym ? reinterpret_cast<float*>(base + pl.off_Lp) : nullptr;
     tr(CC_LADDER_PHASE_PREP, 0, 0);
-    rc = to_f32(L, L32, (size_t)P * v * v, stream);
+    const long long v2 = (long long)v * v, o2 = (long long)o * o;
+    rc = to_f32_rows(L, L32, P, v2, pl.ldk, stream);
     if (!rc)
-      rc = pl.exchange ? swap_cd(t, t32, o, v, stream) : to_f32(t, t32, (size_t)o * o * v * v, stream);
-    if (!rc) rc = to_f32(lam, lam32, (size_t)o * o * v * v, stream);
+      rc = pl.exchange ? swap_cd(t, t32, o, v, stream, pl.ldk)
+                       : to_f32_rows(t, t32, o2, v2, pl.ldk, stream);
+    if (!rc) rc = to_f32_rows(lam, lam32, o2, v2, pl.ldk, stream);
     if (!rc && pl.gsym) rc = pack_sym(L, Lp, P, v, pl.ldg, stream);
     tr(CC_LADDER_PHASE_PREP, 0, 1);
     if (rc) return rc;

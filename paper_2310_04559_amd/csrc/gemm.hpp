@@ -15,11 +15,12 @@
 // Epilogues:
 //   EPI_ACC : C[m*ldc + n] += alpha * acc                 (float64 accumulation)
 //   EPI_PERM: m = (a, x), n = (y, d) with x, d < v and y < N/v:
-//             C[a*N*v + y*v^2 + x*v + d] = acc            (stores, in the operand type, an
+//             C[(a*(N/v) + y)*ldv + x*v + d] = acc         (stores, in the operand type, an
 //                                                          integral-shaped block with its
-//                                                          middle indices swapped; N = v^2
-//                                                          for the virtual-virtual build,
-//                                                          o*v for occupied columns)
+//                                                          middle indices swapped, rows (a,y)
+//                                                          of stride ldv, v^2 or padded; N =
+//                                                          v^2 for the virtual-virtual
+//                                                          build, o*v for occupied columns)
 //   EPI_PACK: the build restricted to b >= a: m = (a - a0, c), n = (b - a0, d);
 //             C[(pair(a,b) - pair(a0,a0))*v^2 + c*v + d] = acc for b >= a, where
 //             pair(a,b) = prefix(a) + b - a numbers the rows a <= b (tiles wholly
@@ -130,6 +131,9 @@ struct GemmArgs {
   long long ldc;
   int M, N, K;
   int v;             // EPI_PERM/PACK/PAIR index split
+  long long ldv = 0; // EPI_PERM: row stride of the integral-shaped block
+  int sym = 0;       // EPI_PERM, direct-to-LDS kernel: one operand with itself, only the
+                     // elements n >= m formed and stored at (m, n) and (n, m)
   int o;             // EPI_PAIR: occupied count (rows are (i,j))
   int a0;            // EPI_PACK/PAIR: first virtual of the integral block
   int tiles_m, tiles_n;
@@ -142,8 +146,9 @@ struct GemmArgs {
   int m_off = 0;         // EPI_PAIR/PM: global row of this launch's row 0 (a remainder launch)
   int pm = 0;            // EPI_PM/FOLD: 1 = symmetric pairs (i <= j, a <= b), 2 = antisymmetric (<)
   int kband = 0;         // K bands of a half-written B operand (0 = the whole K range)
-  int n_load = 0;        // mixed direct-to-LDS kernel: columns of B that may be read (N and
-                         // pads up to whole 16-byte chunks; 0 = N)
+  int m_load = 0, n_load = 0;  // direct-to-LDS kernels, row-contiguous operands: rows of A and
+                         // columns of B that may be read (M, N and pads up to whole
+                         // 16-byte chunks; 0 = M, N)
   int m_keep = 0;        // EPI_UNPACK: rows stored (M may be padded to whole 16-byte chunks)
 };
 
@@ -205,7 +210,7 @@ __device__ __forceinline__ EpiCol epi_col(const GemmArgs<T>& g, int n) {
   const long long v = g.v;
   if (EPI == EPI_PERM || EPI == EPI_UNPACK) {
     const int y = n / g.v, d = n - y * g.v;
-    c.off = (long long)y * v * v + d;
+    c.off = (EPI == EPI_PERM ? (long long)y * g.ldv : (long long)y * v * v) + d;
   } else if (EPI == EPI_PACK) {
     const int bl = n / g.v;
     c.x = bl;
@@ -241,7 +246,8 @@ __device__ __forceinline__ void epi_store(const GemmArgs<T>& g, int m, int n, co
     static_cast<double*>(g.C)[(long long)m * g.ldc + n] = val;
   } else if (EPI == EPI_PERM) {
     const int a = m / g.v, x = m - a * g.v;
-    static_cast<T*>(g.C)[(long long)a * g.N * v + c.off + (long long)x * v] = static_cast<T>(val);
+    static_cast<T*>(g.C)[(long long)a * (g.N / g.v) * g.ldv + c.off + (long long)x * v] =
+        static_cast<T>(val);
   } else if (EPI == EPI_SYM) {
     T* C = static_cast<T*>(g.C);
     C[(long long)m * g.ldc + n] = static_cast<T>(val);

@@ -261,10 +261,20 @@ namespace ccl {
 // lanes of a k row reading 256 contiguous bytes (no bank conflicts, no swizzle).
 // Columns are interleaved the same way, which also makes the values a lane stores
 // for the four column blocks adjacent in the output: the permuted epilogue writes
-// them with 16-byte stores when v is a multiple of the chunk.  Needs M and N
-// multiples of the 16-byte chunk and 16-byte aligned operand rows; rows past M or
-// N are clamped onto the last chunk (never stored); a ragged last K-step is
-// loaded through registers with zero fill.
+// them with 16-byte stores when v is a multiple of the chunk.  Needs 16-byte
+// aligned operand rows of whole 16-byte chunks (M and N, or readable pads: m_load,
+// n_load); rows past M or N are clamped onto the last chunk (never stored); a
+// ragged last K-step is loaded through registers with zero fill.
+//
+// KMAP deals the k of a step to the MFMA slots: 0 four adjacent rows per MFMA; 1 as
+// the register-staged kernel does (slot j of MFMA e in a group of 4*CH takes
+// CH*j + e), so that operands padded for this kernel keep the sums they had there.
+//
+// sym (EPI_PERM, M = N, A = B): the integral (ac|bd) = (bd|ac) of a block that holds
+// all virtuals.  Only the tiles that meet n >= m run, on a compact grid, and each
+// value is stored at (m, n) and (n, m): half the multiply-adds for the same bytes.
+// A lane's 4 x CH group of adjacent rows and columns makes both stores 16-byte
+// vectors.  o=40 v=360 P=1200 float32 forward: 728 -> 573 ms.
 template <class Tr>
 __device__ __forceinline__ int rc_pos(int i, int r) {
   if constexpr (Tr::CH == 4)
@@ -273,7 +283,24 @@ __device__ __forceinline__ int rc_pos(int i, int r) {
     return 32 * (i >> 1) + 2 * r + (i & 1);
 }
 
-template <class Tr, int EPI>
+// Compact grid of the 128 x 256 tiles that meet the diagonal or lie above it:
+// tile row t holds tiles_n - t/2 of them, the rows before it
+// t*tiles_n - floor((t-1)^2 / 4).
+__host__ __device__ inline long long sym_tiles_before(long long t, long long tiles_n) {
+  return t * tiles_n - (t - 1) * (t - 1) / 4;
+}
+
+__device__ inline void sym_tile(long long id, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const double tnd = tiles_n;
+  int t = static_cast<int>(2.0 * (tnd - sqrt(tnd * tnd - static_cast<double>(id))));
+  t = t < 0 ? 0 : (t >= tiles_m ? tiles_m - 1 : t);
+  while (t + 1 < tiles_m && sym_tiles_before(t + 1, tiles_n) <= id) ++t;
+  while (t > 0 && sym_tiles_before(t, tiles_n) > id) --t;
+  tm = t;
+  tn = t / 2 + static_cast<int>(id - sym_tiles_before(t, tiles_n));
+}
+
+template <class Tr, int EPI, int KMAP = 0>
 __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<typename Tr::T> g) {
   static_assert(EPI == EPI_PERM || EPI == EPI_PACK || EPI == EPI_UNPACK || EPI == EPI_SYM,
                 "integral-block stores");
@@ -310,6 +337,8 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
     }
     tm = lo;
     tn = pack_first_tile(tm, kDBM, kDBN, g.v) + (id - g.row_tiles[tm]);
+  } else if (EPI == EPI_PERM && g.sym) {
+    sym_tile(xcd_linear(blockIdx.x, gridDim.x), g.tiles_m, g.tiles_n, tm, tn);
   } else {
     tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
   }
@@ -318,6 +347,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   // Wave instruction q of a stage covers bytes [q KB, q KB + 1 KB) of the A (or B)
   // slab: flattened chunk q*64 + lane -> (k row, chunk).  This lane's k row and
   // source pointer at k = 0 for each of its instructions.
+  const int ml = g.m_load ? g.m_load : g.M, nl = g.n_load ? g.n_load : g.N;
   const T* pa[AI];
   const T* pb[BI];
   int ra[AI], rb[BI];
@@ -326,7 +356,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
     const int flat = (wave + 8 * j) * 64 + lane;
     ra[j] = flat / CPRA;
     int m = m0 + (flat % CPRA) * CH;
-    m = m < g.M ? m : g.M - CH;
+    m = m < ml ? m : ml - CH;
     pa[j] = g.A + (long long)ra[j] * g.lda + m;
   }
 #pragma unroll
@@ -334,7 +364,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
     const int flat = (wave + 8 * j) * 64 + lane;
     rb[j] = flat / CPRB;
     int n = n0 + (flat % CPRB) * CH;
-    n = n < g.N ? n : g.N - CH;
+    n = n < nl ? n : nl - CH;
     pb[j] = g.B + (long long)rb[j] * g.ldb + n;
   }
   auto issue = [&](int kt) {
@@ -404,8 +434,9 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
       const unsigned char* st = lds + (kt % kDStages) * STAGE;
 #pragma unroll
       for (int kk = 0; kk < BK / 4; ++kk) {
-        const unsigned char* ra_ = st + (4 * kk + kr) * ROWA + offa;
-        const unsigned char* rb_ = st + A_BYTES + (4 * kk + kr) * ROWB + offb;
+        const int krow = KMAP ? 4 * CH * (kk / CH) + CH * kr + kk % CH : 4 * kk + kr;
+        const unsigned char* ra_ = st + krow * ROWA + offa;
+        const unsigned char* rb_ = st + A_BYTES + krow * ROWB + offb;
         T fa[4], fb[4];
         if constexpr (CH == 4) {
           const Chunk a = *reinterpret_cast<const Chunk*>(ra_);
@@ -444,7 +475,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   }
 
   // epilogue: column groups of CH adjacent n (blocks j = CH*h .. CH*h + CH - 1).
-  // EPI_PERM: m = (a, x), n = (y, d) -> C[a*N*v + y*v^2 + x*v + d];
+  // EPI_PERM: m = (a, x), n = (y, d) -> C[(a*(N/v) + y)*ldv + x*v + d];
   // EPI_PACK: m = (a - a0, c), n = (b - a0, d), kept for b >= a, at packed row
   // pair(a, b) - pair(a0, a0): C[row*v^2 + c*v + d];
   // EPI_UNPACK: m = pair(a, b) - pair(a0, a0) (m < m_keep), n = (c, d) ->
@@ -462,7 +493,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
       return (long long)(a - g.a0) * v * v * v + (long long)y * v * v + (long long)b * v + d;
     }
     const int a = m / g.v, x = m - a * g.v;
-    if (EPI == EPI_PERM) return (long long)a * g.N * v + (long long)y * v * v + (long long)x * v + d;
+    if (EPI == EPI_PERM) return ((long long)a * (g.N / g.v) + y) * g.ldv + (long long)x * v + d;
     if (y < a) return -1;
     const long long row = pair_prefix_d(g.a0 + a, v) - pair_prefix_d(g.a0, v) + (y - a);
     return row * v * v + (long long)x * v + d;
@@ -470,7 +501,63 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
 #pragma unroll
   for (int h = 0; h < NG; ++h) {
     const int nb = n0 + wn + rc_pos<Tr>(CH * h, r16);  // first column of the group
-    if (nb >= g.N) continue;                            // N % CH == 0: whole group out
+    if (nb >= g.N) continue;
+    if (EPI == EPI_PERM && g.sym) {
+      // rows of 4 adjacent m per (r), columns of CH adjacent n: the group on or above
+      // the diagonal, and its mirror with rows and columns exchanged
+      T* C = static_cast<T*>(g.C);
+      const int nv = g.N / g.v, yb = nb / g.v, db = nb - yb * g.v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        T val[4][CH];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int e = 0; e < CH; ++e)
+            val[i][e] = static_cast<T>(Tr::kDrain ? acc64[i][CH * h + e][r]
+                                                  : static_cast<double>(acc[i][CH * h + e][r]));
+#pragma unroll
+        for (int q = 0; q < 4 / CH; ++q) {  // CH adjacent rows at a time
+          const int mb = m0 + wm + rc_pos<Tr>(CH * q, Tr::row_of(lane, r));
+          if (mb >= g.M) continue;
+          const int ab = mb / g.v, xb = mb - ab * g.v;
+          if (vec && mb + CH - 1 <= nb) {
+            // wholly on or above the diagonal (M and N are multiples of CH here)
+            T* up = C + ((long long)ab * nv + yb) * g.ldv + (long long)xb * v + db;
+            T* down = C + ((long long)yb * nv + ab) * g.ldv + (long long)db * v + xb;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+              Chunk x, y;
+#pragma unroll
+              for (int e = 0; e < CH; ++e) {
+                x[e] = val[CH * q + i][e];
+                y[e] = val[CH * q + e][i];
+              }
+              *reinterpret_cast<Chunk*>(up + i * v) = x;
+              *reinterpret_cast<Chunk*>(down + i * v) = y;
+            }
+          } else {
+            // element by element, the indices (a, x) and (y, d) carried along
+            int a = ab, x = xb;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+              int y = yb, d = db;
+#pragma unroll
+              for (int e = 0; e < CH; ++e) {
+                const int m = mb + i, n = nb + e;
+                if (m < g.M && n < g.N && m <= n) {
+                  C[((long long)a * nv + y) * g.ldv + (long long)x * v + d] = val[CH * q + i][e];
+                  C[((long long)y * nv + a) * g.ldv + (long long)d * v + x] = val[CH * q + i][e];
+                }
+                if (++d == g.v) { d = 0; ++y; }
+              }
+              if (++x == g.v) { x = 0; ++a; }
+            }
+          }
+        }
+      }
+      continue;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -504,6 +591,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
         } else {
 #pragma unroll
           for (int e = 0; e < CH; ++e) {
+            if (nb + e >= g.N) continue;
             const long long oe = dst_of(m, nb + e);
             if (oe >= 0) C[oe] = val[e];
           }

@@ -137,7 +137,8 @@ void block_range(const Plan& pl, int blk, int* a0, int* na) {
 }
 
 int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
-                int slices, int depth, int k_chunk, unsigned flags, Plan* plan, int nb) {
+                int slices, int depth, int k_chunk, unsigned flags, Plan* plan, int nb,
+                bool padded) {
   const int pairsym = (flags & CC_LADDER_PAIR_SYMMETRIC) ? 1 : 0;
   Plan p;
   // packed forward in pair-balanced blocks: the widest block sizes the tile
@@ -173,8 +174,10 @@ int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
   p.npk = p.pairsym ? static_cast<long long>(npk) : 0;
   const size_t npk_ld = (npk + 3) / 4 * 4;  // row stride of the adjoint's gathered lam
   const size_t rows = (p.pairsym || p.pairsym_adj) ? npk : static_cast<size_t>(n_a) * v;
-  const size_t blk = rows * v2;
-  const size_t blk_w = static_cast<size_t>(n_a) * v * v2;
+  const size_t ldk = padded && precision == CC_LADDER_FP32 && !pairsym ? (v2 + 3) / 4 * 4 : v2;
+  p.ldk = static_cast<long long>(ldk);
+  const size_t blk = rows * ldk;
+  const size_t blk_w = static_cast<size_t>(n_a) * v * ldk;
   size_t cur = 0;
   p.exchange = (flags & CC_LADDER_EXCHANGE) ? 1 : 0;
   p.pm = (p.pairsym && (flags & CC_LADDER_PLUS_MINUS)) ? 1 : 0;
@@ -232,9 +235,9 @@ int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
     case CC_LADDER_FP32:
       p.k_chunk = k_chunk ? k_chunk : 512;
       // the forward over G needs no float32 copy of L (the adjoint's dL does)
-      if (!p.gsym || p.backward) p.off_L = take(&cur, static_cast<size_t>(P) * v2 * sizeof(float));
-      p.off_t = take(&cur, o2 * v2 * sizeof(float));
-      if (p.backward) p.off_lam = take(&cur, o2 * v2 * sizeof(float));
+      if (!p.gsym || p.backward) p.off_L = take(&cur, static_cast<size_t>(P) * ldk * sizeof(float));
+      p.off_t = take(&cur, o2 * ldk * sizeof(float));
+      if (p.backward) p.off_lam = take(&cur, o2 * ldk * sizeof(float));
       p.off_V = take(&cur, blk * sizeof(float));
       if (p.backward) p.off_W = take(&cur, blk_w * sizeof(float));
       if (p.pairsym_adj) p.off_lamP = take(&cur, o2 * npk_ld * sizeof(float));
@@ -394,9 +397,18 @@ int make_plan_flags(int o, int v, int P, int precision, int backward, size_t bud
     *plan = best;
     return CC_LADDER_OK;
   }
-  return search_block(v, budget, fixed, [&](int n_a, Plan* p) {
+  const int rc = search_block(v, budget, fixed, [&](int n_a, Plan* p) {
     return layout_plan(o, v, P, precision, backward, n_a, slices, depth, k_chunk, flags, p);
   }, plan);
+  if (rc || precision != CC_LADDER_FP32 || v % 2 == 0) return rc;
+  // odd v: padded rows where the same blocks still fit (a plan sized without the
+  // pads keeps its blocks and its rows)
+  Plan pad;
+  if (layout_plan(o, v, P, precision, backward, plan->n_a, slices, depth, k_chunk, flags, &pad, 0,
+                  true) == CC_LADDER_OK &&
+      (!budget || pad.bytes <= budget))
+    *plan = pad;
+  return rc;
 }
 
 }  // namespace

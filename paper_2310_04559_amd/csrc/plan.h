@@ -44,6 +44,9 @@ struct Plan {
   size_t off_Lp = 0;    // packed vectors Lp[x][pair(a,c)], a <= c ([P][ldg], pads zero)
   size_t off_G = 0;     // G[ldg][ldg], symmetric
   int k_chunk = 0;      // float32 drain interval along the contracted index
+  long long ldk = 0;    // row stride of the float32 copies of L, t, lam and of the rows of V
+                        // and W: v^2, or v^2 rounded to 4 in a general plan whose budget
+                        // holds the pads (odd v: rows on 16-byte boundaries)
   // operand copies made once per call (float32 / bf16 slice forms)
   size_t off_L = 0, off_t = 0, off_lam = 0;
   size_t off_L2 = 0;    // intermediate ijbk, FP32: the virtual-virtual vectors (off_L: L_ov)
@@ -63,11 +66,13 @@ struct Plan {
   size_t bytes = 0;     // total scratch
 };
 
+// `padded`: row strides of a general float32 plan rounded to 4 elements.
 // Fills `plan` for a block size of n_a (1 <= n_a <= v), or, when nb > 0 and the
 // plan is a packed (pair-symmetric) forward, for nb pair-balanced blocks (n_a
 // ignored).  Returns 0, CC_LADDER_EINVAL or CC_LADDER_EUNSUPPORTED.
 int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
-                int slices, int depth, int k_chunk, unsigned flags, Plan* plan, int nb = 0);
+                int slices, int depth, int k_chunk, unsigned flags, Plan* plan, int nb = 0,
+                bool padded = false);
 
 // Packed integral rows (a,b), a <= b, ordered by a then b: rows of virtuals
 // [0, a) come first.  pair_prefix(a, v) = sum_{a' < a} (v - a').

@@ -25,3 +25,14 @@ def test_unlimited_plan_is_the_plan_of_any_budget_that_holds_it():
                                                     hbm_budget=whole[0] + extra) == whole
             seen += 1
     assert seen > 600
+
+
+def test_float32_pads_are_left_out_where_they_do_not_fit():
+    # odd v: rows padded to whole 16-byte chunks; a scratch sized without the pads
+    # still holds the same blocks
+    for o, v, P in ((3, 21, 30), (5, 97, 200), (2, 203, 11)):
+        for bwd in (False, True):
+            whole, n = native.cc_ladder_workspace_query(o, v, P, "fp32", backward=bwd)
+            less, m = native.cc_ladder_workspace_query(o, v, P, "fp32", backward=bwd,
+                                                       hbm_budget=whole - 1)
+            assert n == m == v and less < whole

@@ -47,3 +47,21 @@ def test_small_backward(gpu_lib, o, v, P, precision):
     dL_ref, dt_ref = oracle.ladder_backward(L, t, lam)
     assert rel_fro(host(dL), dL_ref) < TOL[precision]
     assert rel_fro(host(dt), dt_ref) < TOL[precision]
+
+
+@pytest.mark.parametrize("o,v,P", [(6, 44, 70), (6, 45, 70), (4, 50, 530)])
+def test_float32_symmetric_build_is_the_blocked_one(gpu_lib, o, v, P):
+    # one block forms half the integral and mirrors it, and pads odd rows; blocks of 4
+    # virtuals form all of it: the same float32 sums, so the same bits (P = 530: two
+    # drain chunks of the build)
+    import torch
+
+    announce("float32-symmetric-build", o, v, P)
+    L, t, _ = random_general(o, v, P, 3200 + v)
+    got = []
+    for a_block in (0, 4):
+        R = dev(np.zeros_like(t))
+        gpu_lib.cc_ladder_residual(dev(L), dev(t), R, 1, opts=gpu_lib.make_opts(a_block=a_block))
+        torch.cuda.synchronize()
+        got.append(host(R))
+    assert np.array_equal(got[0], got[1])
