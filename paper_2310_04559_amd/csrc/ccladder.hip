@@ -662,6 +662,151 @@ int pm_rows(const In* X, long long nrows, int n, int a0, int v, Out* plus, long 
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
+// Adds the +- products of a block's pairs (a,b), a <= b, a from a0 (na virtuals), into
+// R: with p = half the sum of the first product's `splits` partials and m = half the
+// second's (0 on a = b, and on i = j where rows are pairs i <= j),
+//   R[i,j,a,b] += p + m, R[i,j,b,a] += p - m   (a < b; R[i,j,a,a] += p)
+// and, for rows i < j of pairs (o > 0), R[j,i,b,a] += p + m, R[j,i,a,b] += p - m.
+// One workgroup per (row, 32 x 32 tile of (a,b) with some a <= b): the partials and
+// R[..][a][b] run along b, the transposed elements along a through LDS, so that all
+// of it is coalesced; R's elements are each touched once.
+__global__ __launch_bounds__(256) void pm_combine_kernel(const double* __restrict__ Pp, long long sp,
+                                                         int np, const double* __restrict__ Pm,
+                                                         long long sm, int nm, int splits, int rows,
+                                                         int o, int v, int a0, int na,
+                                                         double* __restrict__ R) {
+  __shared__ double xs[kSwapTile][kSwapTile + 1], ys[kSwapTile][kSwapTile + 1];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int ta = (na + kSwapTile - 1) / kSwapTile;           // tiles of a, from a0
+  const int tb = (v - a0 + kSwapTile - 1) / kSwapTile;       // tiles of b, from a0
+  const long long per = (long long)ta * tb, v2 = (long long)v * v;
+  for (long long w = blockIdx.x; w < rows * per; w += gridDim.x) {
+    const int r = static_cast<int>(w / per);
+    const int q = static_cast<int>(w - r * per);
+    const int A = q / tb, B = q - A * tb;
+    if (B < A) continue;
+    const int as = a0 + A * kSwapTile, bs = a0 + B * kSwapTile;
+    int rm = r;
+    long long rij = r, rji = -1;
+    if (o > 0) {
+      const int i = pair_row(r, o), j = i + static_cast<int>(r - pair_prefix_d(i, o));
+      rij = (long long)i * o + j;
+      rji = i < j ? (long long)j * o + i : -1;
+      rm = i < j ? static_cast<int>(pair_prefix_d(i, o - 1)) + (j - i - 1) : -1;
+    }
+    double* Rij = R + rij * v2;
+    double* Rji = R + rji * v2;
+#pragma unroll
+    for (int k = ty; k < kSwapTile; k += 8) {
+      const int a = as + k, b = bs + tx;
+      if (a >= a0 + na || b >= v || a > b) continue;
+      const long long cp = pair_prefix_d(a, v) - pair_prefix_d(a0, v) + (b - a);
+      double p = 0.0, m = 0.0;
+      for (int s = 0; s < splits; ++s) p += Pp[s * sp + (long long)r * np + cp];
+      if (rm >= 0 && a < b) {
+        const long long cm = pair_prefix_d(a, v - 1) - pair_prefix_d(a0, v - 1) + (b - a - 1);
+        for (int s = 0; s < splits; ++s) m += Pm[s * sm + (long long)rm * nm + cm];
+      }
+      const double x = 0.5 * p + 0.5 * m, y = 0.5 * p - 0.5 * m;
+      xs[k][tx] = x;
+      ys[k][tx] = y;
+      Rij[(long long)a * v + b] += x;
+      if (rji >= 0 && a < b) Rji[(long long)a * v + b] += y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = ty; k < kSwapTile; k += 8) {
+      const int b = bs + k, a = as + tx;
+      if (a >= a0 + na || b >= v || a > b) continue;
+      if (a < b) Rij[(long long)b * v + a] += ys[tx][k];
+      if (rji >= 0) Rji[(long long)b * v + a] += xs[tx][k];
+    }
+    __syncthreads();
+  }
+}
+
+// Both +- contractions of a block, R from T+ V+ and T- V- (rows of all (i,j), or pairs
+// i <= j and i < j when pairs is set).  `part`: scratch that holds nothing any more and
+// takes `max_splits` partials of both products (null: none, whatever the blocks).  With
+// it the two products run in one launch, K split where their grids leave compute units
+// idle, and one coalesced pass adds both to R; without, one after the other into R,
+// whose transposed elements are then scattered read-modify-writes of 8 bytes.
+// o=13 v=97, two blocks: 860 -> 395 us; o=9 v=71: 114 -> 57 us; o=40 v=360 forward: 778 ->
+// 768 ms.
+template <class Tr>
+int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ldp,
+                const typename Tr::T* Tm, const typename Tr::T* Vm, long long ldm, double* R, int o,
+                int v, int a0, int na, bool pairs, double* part, long long max_splits, int drain,
+                hipStream_t s) {
+  using T = typename Tr::T;
+  const long long v2 = (long long)v * v;
+  const int kp = static_cast<int>((long long)v * (v + 1) / 2), km = kp - v;
+  const int mp = pairs ? o * (o + 1) / 2 : o * o, mm = pairs ? o * (o - 1) / 2 : o * o;
+  const int np = static_cast<int>(pair_prefix(a0 + na, v) - pair_prefix(a0, v)), nm = np - na;
+  const PairPick pick =
+      pick_pair_products(PairExtents{mp, kp, mm, km}, PairExtents{mp, np, mm, nm}, kp, sizeof(T),
+                         Tr::kDrain ? drain : 1, part ? max_splits : 0);
+  if (pick.splits == 0) {
+    int rc;
+    if (pairs) {
+      rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tp, ldp, Vp, ldp, R, v2, mp, np, kp, v, drain, s, o, a0,
+                                           nullptr, 0.5, 1, 0, 0, mp, kp);
+      if (!rc)
+        rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tm, ldm, Vm, ldm, R, v2, mm, nm, km, v, drain, s, o,
+                                             a0, nullptr, 0.5, 2, 0, 0, mm, km);
+    } else {
+      rc = launch_gemm<Tr, KC, KC, EPI_FOLD>(Tp, ldp, Vp, ldp, R, v2, mp, np, kp, v, drain, s, o,
+                                             a0, nullptr, 0.5, 1, 0, 0, mp, kp);
+      if (!rc)
+        rc = launch_gemm<Tr, KC, KC, EPI_FOLD>(Tm, ldm, Vm, ldm, R, v2, mm, nm, km, v, drain, s, o,
+                                               a0, nullptr, 0.5, 2, 0, 0, mm, km);
+    }
+    return rc;
+  }
+  constexpr int BK = kDRow / static_cast<int>(sizeof(T));
+  const int chunk = Tr::kDrain ? drain : 1;
+  auto args = [&](const T* A, const T* B, long long ld, int M, int N, int K, double* C) {
+    GemmArgs<T> g;
+    g.A = A; g.lda = ld;
+    g.B = B; g.ldb = ld;
+    g.C = C; g.ldc = N;
+    g.M = M; g.N = N; g.K = K;
+    g.v = v; g.o = 0; g.a0 = 0; g.row_tiles = nullptr;
+    g.alpha = 1.0;
+    g.drain_steps = drain > 0 ? drain : 1;
+    g.tiles_m = (M + pick.bm - 1) / pick.bm;
+    g.tiles_n = (N + pick.bn - 1) / pick.bn;
+    g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
+    const int nk = (kp + BK - 1) / BK;  // the longer product's, so both have the same ranges
+    g.split_steps = ((nk + pick.splits - 1) / pick.splits + chunk - 1) / chunk * chunk;
+    g.part_stride = (long long)M * N;
+    return g;
+  };
+  double* Pm = part + (long long)pick.splits * mp * np;
+  const GemmArgs<T> g = args(Tp, Vp, ldp, mp, np, kp, part);
+  const GemmArgs<T> h = args(Tm, Vm, ldm, mm, nm, km, Pm);
+  const long long n1 = (long long)g.tiles_m * g.tiles_n * pick.splits;
+  const long long n2 = mm > 0 && nm > 0 ? (long long)h.tiles_m * h.tiles_n * pick.splits : 0;
+  if (n1 + n2 > 0x7fffffffLL) return CC_LADDER_EINVAL;
+  const dim3 grid(static_cast<unsigned>(n1 + n2)), block(kDThreads);
+  const int in1 = static_cast<int>(n1);
+  if (pick.bn == 64)
+    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 64>), grid, block, 0, s, g, h, in1);
+  else if (pick.bn == 128)
+    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 128>), grid, block, 0, s, g, h, in1);
+  else if (pick.bm == 128)
+    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 128, 256>), grid, block, 0, s, g, h, in1);
+  else if constexpr (!Tr::kDrain)
+    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 160, 256>), grid, block, 0, s, g, h, in1);
+  const long long ta = (na + kSwapTile - 1) / kSwapTile, tb = (v - a0 + kSwapTile - 1) / kSwapTile;
+  const long long blocks = std::min<long long>(mp * ta * tb, 65536);
+  hipLaunchKernelGGL(pm_combine_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s,
+                     static_cast<const double*>(part), g.part_stride, np,
+                     static_cast<const double*>(Pm), h.part_stride, nm, pick.splits, mp,
+                     pairs ? o : 0, v, a0, na, R);
+  return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+}
+
 // Symmetric vectors: Lp[x][pair(a,c)] = L[x][a][c] for a <= c (pair(a,c) =
 // prefix_v(a) + c - a), row stride ldg, the pad columns [v(v+1)/2, ldg) zero.
 // One workgroup per (x, a): contiguous reads and writes along c.
@@ -1082,9 +1227,6 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
   const long long v2 = (long long)v * v;
   const int iv2 = v * v;
   const int drain = Tr::kDrain ? pl.k_chunk / Tr::BK : 0;
-  const int mp = o * (o + 1) / 2, mm = o * (o - 1) / 2;
-  const int kp = static_cast<int>((long long)v * (v + 1) / 2);
-  const int km = static_cast<int>((long long)v * (v - 1) / 2);
   if (pl.gsym) {
     const int rc = build_pair_integral<Tr>(pl, Lp, G, row_tiles, tr, s);
     if (rc) return rc;
@@ -1095,7 +1237,6 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     if (na <= 0) continue;
     const long long off = (long long)a0 * v;
     const long long np = pair_prefix(a0 + na, v) - pair_prefix(a0, v);
-    const long long nm = np - na;
     tr(CC_LADDER_PHASE_BUILD, blk, 0);
     int rc;
     if (pl.gsym) {
@@ -1111,11 +1252,19 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
-    rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tp, pl.ldp, Vp, pl.ldp, R, v2, mp, static_cast<int>(np), kp,
-                                         v, drain, s, o, a0, nullptr, 0.5, 1, 0, 0, mp, kp);
-    if (!rc)
-      rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tm, pl.ldm, Vm, pl.ldm, R, v2, mm, static_cast<int>(nm),
-                                           km, v, drain, s, o, a0, nullptr, 0.5, 2, 0, 0, mm, km);
+    // partial sums in the packed block's room (np rows of v^2, np columns of o^2 rows),
+    // or, after the only block's gather, G's
+    double* part = nullptr;
+    long long bytes = 0;  // per column
+    if (!pl.gsym) {
+      part = reinterpret_cast<double*>(V);
+      bytes = v2 * static_cast<long long>(sizeof(typename Tr::T));
+    } else if (pl.nblocks == 1) {
+      part = reinterpret_cast<double*>(G);
+      bytes = pl.ldg * static_cast<long long>(sizeof(typename Tr::T));
+    }
+    rc = pm_products<Tr>(Tp, Vp, pl.ldp, Tm, Vm, pl.ldm, R, o, v, a0, na, true, part,
+                         bytes / ((long long)o * o * 8), drain, s);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }
@@ -1135,8 +1284,6 @@ int forward_fold(const Plan& pl, const FoldPlan& f, const double* L, const doubl
   const int o = pl.o, v = pl.v, P = pl.P;
   const long long v2 = (long long)v * v;
   const int iv2 = v * v;
-  const int kp = static_cast<int>((long long)v * (v + 1) / 2);
-  const int km = static_cast<int>((long long)v * (v - 1) / 2);
   double* Tp = reinterpret_cast<double*>(base + f.off_Tp);
   double* Tm = reinterpret_cast<double*>(base + f.off_Tm);
   double* V = reinterpret_cast<double*>(base + f.off_V);
@@ -1156,7 +1303,6 @@ int forward_fold(const Plan& pl, const FoldPlan& f, const double* L, const doubl
     if (na <= 0) continue;
     const long long off = (long long)a0 * v;
     const long long np = pair_prefix(a0 + na, v) - pair_prefix(a0, v);
-    const long long nm = np - na;
     tr(CC_LADDER_PHASE_BUILD, blk, 0);
     rc = launch_gemm<TrF64, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
                                               static_cast<int>((long long)(v - a0) * v), P, v, 0, s,
@@ -1164,22 +1310,10 @@ int forward_fold(const Plan& pl, const FoldPlan& f, const double* L, const doubl
     if (!rc) rc = pm_rows<PM_INTS>(V, np, v, a0, v, Vp, f.ldp, Vm, f.ldm, 2.0, 1.0, s);
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
+    // (the packed block's room takes the partial sums)
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
-    const int mp = static_cast<int>(f.rows_p), mm = static_cast<int>(f.rows_m);
-    const int inp = static_cast<int>(np), inm = static_cast<int>(nm);
-    if (pl.pairsym) {
-      rc = launch_gemm<TrF64, KC, KC, EPI_PM>(Tp, f.ldp, Vp, f.ldp, R, v2, mp, inp, kp, v, 0, s, o,
-                                              a0, nullptr, 0.5, 1, 0, 0, mp, kp);
-      if (!rc)
-        rc = launch_gemm<TrF64, KC, KC, EPI_PM>(Tm, f.ldm, Vm, f.ldm, R, v2, mm, inm, km, v, 0, s,
-                                                o, a0, nullptr, 0.5, 2, 0, 0, mm, km);
-    } else {
-      rc = launch_gemm<TrF64, KC, KC, EPI_FOLD>(Tp, f.ldp, Vp, f.ldp, R, v2, mp, inp, kp, v, 0, s,
-                                                o, a0, nullptr, 0.5, 1, 0, 0, mp, kp);
-      if (!rc)
-        rc = launch_gemm<TrF64, KC, KC, EPI_FOLD>(Tm, f.ldm, Vm, f.ldm, R, v2, mm, inm, km, v, 0,
-                                                  s, o, a0, nullptr, 0.5, 2, 0, 0, mm, km);
-    }
+    rc = pm_products<TrF64>(Tp, Vp, f.ldp, Tm, Vm, f.ldm, R, o, v, a0, na, pl.pairsym, V,
+                            v2 / (f.rows_p + f.rows_m), 0, s);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }

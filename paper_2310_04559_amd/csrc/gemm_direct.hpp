@@ -55,9 +55,10 @@ __device__ __forceinline__ void d_wait_vm(int n) {
 template <int BM, int BN>
 constexpr int kc_groups() { return BM == 64 && BN < 256 ? 2 : 1; }  // per compute unit
 
-template <class Tr, int EPI, int BM = kDBM, int BN = kDBN>
-__global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_direct_kernel(
-    GemmArgs<typename Tr::T> g) {
+// The workgroup `bid` of `nwg` of one product.
+template <class Tr, int EPI, int BM, int BN>
+__device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const int bid,
+                                               const int nwg) {
   static_assert(EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PART || EPI == EPI_PM ||
                     EPI == EPI_FOLD,
                 "K-contiguous epilogues");
@@ -91,16 +92,16 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_
   if (EPI == EPI_PART) {
     // grid = tiles x splits; the split is the outer index of the linear id
     const int ntiles = g.tiles_m * g.tiles_n;
-    const int id = xcd_linear(blockIdx.x, gridDim.x);
+    const int id = xcd_linear(bid, nwg);
     const int split = id / ntiles;
     tile_from_linear(id - split * ntiles, ntiles, g.tiles_m, g.group_m, tm, tn);
     ks0 = split * g.split_steps;
     ks1 = ks0 + g.split_steps < nk_all ? ks0 + g.split_steps : nk_all;
     g.C = static_cast<double*>(g.C) + split * g.part_stride;
   } else if (g.kband) {
-    tile_of_banded(g.kband, blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
+    tile_of_banded(g.kband, bid, nwg, g.tiles_m, g.group_m, tm, tn);
   } else {
-    tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
+    tile_of(bid, nwg, g.tiles_m, g.group_m, tm, tn);
   }
   const int m0 = tm * BM, n0 = tn * BN;
   if (EPI != EPI_PART && g.kband) k_band(g, n0, BN, BK, ks0, ks1);
@@ -240,6 +241,22 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_
         epi_store<T, EPI>(g, m, n, ec, val);
       }
   }
+}
+
+template <class Tr, int EPI, int BM = kDBM, int BN = kDBN>
+__global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_direct_kernel(
+    GemmArgs<typename Tr::T> g) {
+  kc_direct_body<Tr, EPI, BM, BN>(g, blockIdx.x, gridDim.x);
+}
+
+// Two products in one launch, workgroups [0, n1) of the first: what the last rounds of
+// one leave idle, the other fills.
+template <class Tr, int BM, int BN>
+__global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_two_kernel(
+    GemmArgs<typename Tr::T> g, GemmArgs<typename Tr::T> h, int n1) {
+  const bool second = static_cast<int>(blockIdx.x) >= n1;
+  kc_direct_body<Tr, EPI_PART, BM, BN>(second ? h : g, second ? blockIdx.x - n1 : blockIdx.x,
+                                       second ? gridDim.x - n1 : n1);
 }
 
 }  // namespace ccl

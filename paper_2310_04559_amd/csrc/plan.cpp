@@ -564,6 +564,51 @@ TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long l
   return pick_launch(cls, M, N, K, 1, es, tall, split);
 }
 
+PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, long long kp, int es,
+                            int chunk, long long max_splits) {
+  PairPick pick;
+  const int bk = 128 / es;
+  const long long nk = (kp + bk - 1) / bk;
+  if (whole.mp <= 0 || whole.np <= 0 || nk <= 0 || max_splits < 1) return pick;
+  auto steps_of = [&](int s) {
+    const long long n = (nk + s - 1) / s;
+    return (n + chunk - 1) / chunk * chunk;
+  };
+  // multiply-adds of one compute unit, as tile_cost; a partial is written and read
+  // (16 bytes at 4 TB/s)
+  const double kPartial = 16.0 * 0.14e12 / 4e12 * (es == 4 ? 2.0 : 1.0);
+  const struct { int bm, bn; double rate; } tiles[] = {
+      {160, 256, 0.86}, {128, 256, 0.86}, {64, 128, 0.82}, {64, 64, 0.78}};
+  auto best_tile = [&](const PairExtents& e, int s, PairPick* p) {
+    double best = 0.0;
+    for (const auto& t : tiles) {
+      if (t.bm == 160 && es == 4) continue;
+      const long long n = ((e.mp + t.bm - 1) / t.bm) * ((e.np + t.bn - 1) / t.bn) +
+                          ((e.mm + t.bm - 1) / t.bm) * ((e.nm + t.bn - 1) / t.bn);
+      const double cost =
+          static_cast<double>((n * s + 255) / 256) * t.bm * t.bn * steps_of(s) * bk / t.rate;
+      if (best == 0.0 || cost < best) {
+        best = cost;
+        p->bm = t.bm;
+        p->bn = t.bn;
+      }
+    }
+    return best + (static_cast<double>(e.mp) * e.np + static_cast<double>(e.mm) * e.nm) * s * kPartial;
+  };
+  double best = 0.0;
+  for (int s = 1; s <= 16 && s <= max_splits; ++s) {
+    if (s > 1 && (steps_of(s) < 8 || (nk + steps_of(s) - 1) / steps_of(s) != s)) continue;
+    PairPick p;
+    const double cost = best_tile(whole, s, &p);
+    if (pick.splits == 0 || cost < 0.99 * best) {
+      best = cost;
+      pick.splits = s;
+    }
+  }
+  best_tile(block, pick.splits, &pick);
+  return pick;
+}
+
 namespace {
 
 // Layout for nb pair-balanced blocks; bytes is 0 when nb exceeds v.
@@ -633,10 +678,11 @@ bool plan_fold(const Plan& pl, FoldPlan* f) {
   else
     direct = v2 * v2 * pl.P / kBuildRate +
              pl.nblocks * (contract(o2, v2 / pl.nblocks, (long long)v * v) + 2 * kLaunch);
+  // the folded contraction keeps to whole rounds by splitting K: its multiply-adds at
+  // the tiles' share of the rate
   fold = pairs * v2 * pl.P / kBuildRate +
-         f->nb * (contract(f->rows_p, pairs / f->nb, (long long)v * (v + 1) / 2) +
-                  contract(f->rows_m, (pairs - v) / f->nb, (long long)v * (v - 1) / 2) + 4 * kLaunch) +
-         16.0 * (pairs + f->rows_p) * v2 * kByte + kLaunch;
+         (static_cast<double>(f->rows_p) + 63) * pairs * v2 / (256 * 0.72) +
+         f->nb * 4 * kLaunch + 16.0 * (pairs + f->rows_p) * v2 * kByte + kLaunch;
   return fold < direct;
 }
 

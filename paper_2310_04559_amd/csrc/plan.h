@@ -192,6 +192,22 @@ struct FoldAdjoint {
 };
 bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a);
 
+// The two products of a +- contraction in one launch of float64 partials that a
+// pass combines into R: K cut into `splits` ranges of whole drain chunks (`chunk`
+// K-steps; 1 in float64), tiles of bm x bn.
+struct PairExtents {
+  long long mp = 0, np = 0, mm = 0, nm = 0;  // rows and columns of the + and - products
+};
+struct PairPick {
+  int bm = 0, bn = 0;
+  int splits = 0;  // 0: no room for one partial of each
+};
+// `whole` are the extents over all pairs (a,b), which alone decide the order of the
+// sums (splits), so that results do not depend on the blocks; `block` those of this
+// launch.  kp: contracted pairs c <= d; max_splits: what the scratch holds.
+PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, long long kp, int es,
+                            int chunk, long long max_splits);
+
 int layout_intermediate(int which, int o, int v, int P, int precision, int n_p, int k_chunk,
                         Plan* plan);
 int make_plan_intermediate(int which, int o, int v, int P, int precision, size_t budget,
