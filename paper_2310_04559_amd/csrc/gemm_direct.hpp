@@ -346,7 +346,9 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   int tm, tn;
   if (EPI == EPI_PACK || EPI == EPI_SYM) {
     // compact grid over the tiles on or above the a = b diagonal
-    const int id = blockIdx.x;
+    // (each XCD a contiguous run of them, which shares row panels: o=40 v=360 float64
+    // forward 768 -> 764 ms)
+    const int id = xcd_linear(blockIdx.x, gridDim.x);
     int lo = 0, hi = g.tiles_m - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
