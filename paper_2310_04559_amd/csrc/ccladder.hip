@@ -841,6 +841,7 @@ __global__ __launch_bounds__(256) void pack_sym_kernel(const double* __restrict_
 // when d >= b; along c in row {b,d} when d < b and c >= a; otherwise (c < a,
 // d < b) element by element, where neighbouring rows b share the cache lines.
 enum { GATHER_PM = 0, GATHER_ROWS = 1 };
+constexpr size_t kGatherLds = 64 * 1024;  // bytes of X_ab that the row kernel holds
 
 template <int MODE, typename T>
 __global__ __launch_bounds__(256) void pm_gather_kernel(const T* __restrict__ G, long long ldg,
@@ -916,10 +917,91 @@ __global__ __launch_bounds__(256) void pm_gather_kernel(const T* __restrict__ G,
   }
 }
 
+// The same gather for matrices that fit a workgroup's LDS whole: one workgroup per
+// row (a, b) reads X_ab once and writes its outputs as contiguous runs.  The tiled kernel is
+// bound there by its latency per 32 x 32 tile pair (index arithmetic, a read, a
+// barrier, a write) and by tiles that overhang: o=9 v=71: 118 -> 62 us (87 with the reads one at
+// a time).
+template <int MODE, typename T>
+__global__ __launch_bounds__(256) void pm_gather_row_kernel(const T* __restrict__ G, int ldg,
+                                                            int a0, int v,
+                                                            T* __restrict__ plus, long long ldp,
+                                                            T* __restrict__ minus, long long ldm) {
+  extern __shared__ double gather_lds[];
+  T* X = reinterpret_cast<T*>(gather_lds);  // X[c*ls + d]
+  const int ls = v | 1;                     // odd: columns are read without bank conflicts
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto pp = [&](int x) { return x * v - x * (x - 1) / 2; };
+  const int r = xcd_linear(blockIdx.x, gridDim.x);
+  const int q = pp(a0) + r;
+  const int a = pair_row(q, v), b = a + (q - pp(a));
+  // The v^2 elements in three runs, each along G's rows: (c < a, all d), (c >= a,
+  // d >= b) along d, (c >= a, d < b) along c; eight reads of a thread in flight.
+  const int n1 = a * v, wd = v - b, n2 = n1 + (v - a) * wd, wc = v - a, n3 = v * v;
+  const float r1 = 1.0f / v, r2 = 1.0f / wd, r3 = 1.0f / wc;
+  for (int e0 = threadIdx.x; e0 < n3; e0 += 8 * 256) {
+    T x[8];
+    int at[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = e0 + 256 * u;
+      at[u] = -1;
+      if (e >= n3) continue;
+      // quotients of e < 2^14 by the widths: (e + 0.5) / w is at least 0.5 / w from an
+      // integer, far more than the float32 error
+      int c, d;
+      if (e < n1) {
+        c = static_cast<int>((e + 0.5f) * r1);
+        d = e - c * v;
+      } else if (e < n2) {
+        const int i = static_cast<int>((e - n1 + 0.5f) * r2);
+        c = a + i;
+        d = b + (e - n1 - i * wd);
+      } else {
+        d = static_cast<int>((e - n2 + 0.5f) * r3);
+        c = a + (e - n2 - d * wc);
+      }
+      const int p = c < a ? pp(c) + a - c : pp(a) + c - a;
+      const int q2 = d < b ? pp(d) + b - d : pp(b) + d - b;
+      const bool along_c = e >= n2;
+      x[u] = G[(long long)(along_c ? q2 : p) * ldg + (along_c ? p : q2)];
+      at[u] = c * ls + d;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (at[u] >= 0) X[at[u]] = x[u];
+  }
+  __syncthreads();
+  if (MODE == GATHER_ROWS) {
+    T* out = plus + r * ldp;
+    for (int c = wave; c < v; c += 4)
+      for (int d = lane; d < v; d += 64) out[c * v + d] = X[c * ls + d];
+  } else {
+    const long long rm =
+        a < b ? pair_prefix_d(a, v - 1) - pair_prefix_d(a0, v - 1) + (b - a - 1) : -1;
+    T* up = plus + r * ldp;
+    T* um = minus + rm * ldm;
+    for (int c = wave; c < v; c += 4) {
+      const int kp = pp(c) - c, km = kp - c - 1;  // pairs c <= d, c < d: prefix_{v-1}(c) = pp(c) - c
+      for (int d = c + lane; d < v; d += 64) {
+        const double x = X[c * ls + d], y = X[d * ls + c];
+        up[kp + d] = static_cast<T>(c == d ? 2.0 * x : x + y);
+        if (rm >= 0 && c < d) um[km + d] = static_cast<T>(x - y);
+      }
+    }
+  }
+}
+
 template <int MODE, typename T>
 int pm_gather(const T* G, long long ldg, long long nrows, int a0, int v, T* plus, long long ldp,
               T* minus, long long ldm, hipStream_t s) {
   if (nrows <= 0) return CC_LADDER_OK;
+  const size_t whole = static_cast<size_t>(v) * (v | 1) * sizeof(T);
+  if (whole <= kGatherLds) {  // v <= 90 in float64, 127 in float32
+    hipLaunchKernelGGL((pm_gather_row_kernel<MODE, T>), dim3(static_cast<unsigned>(nrows)),
+                       dim3(256), static_cast<unsigned>(whole), s, G, static_cast<int>(ldg), a0, v, plus, ldp, minus, ldm);
+    return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+  }
   const int tiles = (v + kSwapTile - 1) / kSwapTile;
   const long long work = nrows * ((long long)tiles * (tiles + 1) / 2);
   const long long blocks = std::min<long long>(work, 65536);
