@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void swap_cd_kernel(const double* __restrict__
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 8 rows of 32 lanes
   const long long per_mat = (long long)tiles * tiles;
   const long long v2 = (long long)v * v;
-  for (long long w = blockIdx.x; w < nmat * per_mat; w += gridDim.x) {
+  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < nmat * per_mat; w += gridDim.x) {
     const long long m = w / per_mat;
     const int r = static_cast<int>(w - m * per_mat);
     const int c0 = (r / tiles) * kSwapTile, d0 = (r % tiles) * kSwapTile;
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(256) void mirror_add_kernel(const double* __restric
   const long long per_mat = (long long)tiles * tiles;
   const long long nmat = (long long)o * o;
   const long long v2 = (long long)v * v;
-  for (long long w = blockIdx.x; w < nmat * per_mat; w += gridDim.x) {
+  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < nmat * per_mat; w += gridDim.x) {
     const long long m = w / per_mat;
     const int i = static_cast<int>(m / o), j = static_cast<int>(m - (long long)i * o);
     const long long mp = (long long)j * o + i;
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256) void sym_add_kernel(T* __restrict__ W, long lo
   __shared__ double a[kSwapTile][kSwapTile + 1], b[kSwapTile][kSwapTile + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const long long npairs = (long long)tiles * (tiles + 1) / 2;
-  for (long long w = blockIdx.x; w < npairs; w += gridDim.x) {
+  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < npairs; w += gridDim.x) {
     const int P = pair_row(w, tiles);
     const int Q = P + static_cast<int>(w - pair_prefix_d(P, tiles));
     const long long p0 = (long long)P * kSwapTile, q0 = (long long)Q * kSwapTile;
@@ -590,7 +590,11 @@ int mirror_add(const double* B, double* dt, int o, int v, hipStream_t s) {
 //   INTS: the packed integral rows (a, b), a <= b, a from a0; X = row r of the
 //         block; rp = r, rm = the local index among the pairs a < b (none for a = b)
 // One workgroup per (row, tile pair C <= D of 32 x 32 tiles): both tiles X[C][D]
-// and X[D][C] go through LDS, so reads and writes run along contiguous d.
+// and X[D][C] go through LDS, so reads and writes run along contiguous d.  Bound by
+// memory.  Each XCD takes a contiguous run of the work: a tile's rows of 32 pairs end
+// inside 128-byte lines, whose other part the next tile of the same row writes, and
+// only in one XCD's L2 do the two meet before the line leaves it (o=40 v=360, one of
+// two blocks: 27.4 -> 19.6 ms for 67 GB).
 enum { PM_AMPS = 0, PM_INTS = 1, PM_ALL = 2 };
 
 template <int MODE, typename In, typename Out>
@@ -603,7 +607,7 @@ __global__ __launch_bounds__(256) void pm_rows_kernel(const In* __restrict__ X, 
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const long long ntp = (long long)tiles * (tiles + 1) / 2;
   const long long v2 = (long long)v * v;
-  for (long long w = blockIdx.x; w < nrows * ntp; w += gridDim.x) {
+  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < nrows * ntp; w += gridDim.x) {
     const long long r = w / ntp;
     const int tp = static_cast<int>(w - r * ntp);
     const int C = pair_row(tp, tiles);
@@ -834,13 +838,19 @@ __global__ __launch_bounds__(256) void pack_sym_kernel(const double* __restrict_
 // (GATHER_ROWS: plus[r][c*v + d], the packed block of the pair-symmetric
 // forward and adjoint) or combined into plus/minus exactly as in pm_rows
 // (GATHER_PM: wdiag 2, sm 1).
-// Work item w = (tile pair C <= D, row r), the row inner: workgroups that run
-// together on one XCD take consecutive rows, the same a with consecutive b.
+// Work items walk kGatherRows rows at a time, tile pair C <= D by tile pair, the row
+// inner: workgroups that run together on one XCD take consecutive rows, the same a
+// with consecutive b, and the tiles next to each other.
 // Every element of the two 32 x 32 tiles is read in an orientation of G that
 // keeps 32 lanes on one contiguous run where one exists: along d in row {a,c}
 // when d >= b; along c in row {b,d} when d < b and c >= a; otherwise (c < a,
 // d < b) element by element, where neighbouring rows b share the cache lines.
 enum { GATHER_PM = 0, GATHER_ROWS = 1 };
+// Rows whose tile pairs a compute die walks before the next rows: their output lines
+// meet in its L2 (a tile's runs end inside a line) and neighbouring rows share what
+// they read.  o=40 v=360 in three blocks: 68.5 ms with all rows of a tile pair first,
+// 60.3 with 4, 57.0 with 8, 58.1 with 16, 63.1 with 64.
+constexpr long long kGatherRows = 8;
 constexpr size_t kGatherLds = 64 * 1024;  // bytes of X_ab that the row kernel holds
 
 template <int MODE, typename T>
@@ -854,7 +864,13 @@ __global__ __launch_bounds__(256) void pm_gather_kernel(const T* __restrict__ G,
   const long long work = nrows * ntp;
   auto pp = [&](long long x) { return pair_prefix_d(x, v); };
   for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < work; w += gridDim.x) {
-    const long long tp = w / nrows, r = w - tp * nrows;
+    // blocks of kGatherRows rows: tile pairs outer, rows inner
+    const long long chunk = w / (kGatherRows * ntp);
+    const long long first = chunk * kGatherRows;
+    const int in_chunk = static_cast<int>(nrows - first < kGatherRows ? nrows - first : kGatherRows);
+    const int wl = static_cast<int>(w - first * ntp);
+    const int tp = wl / in_chunk;
+    const long long r = first + (wl - tp * in_chunk);
     const int C = pair_row(tp, tiles);
     const int D = C + static_cast<int>(tp - pair_prefix_d(C, tiles));
     const int c0 = C * kSwapTile, d0 = D * kSwapTile;
@@ -1547,7 +1563,7 @@ int backward_blocks(const Plan& pl, const typename Tr::T* L, const typename Tr::
 // workgroup per (pair (a,b), tile pair C <= D of 32 x 32 tiles): W+- are read along
 // d, and each of the four 32 x 32 tiles of S is written along its contiguous index,
 // two of them through LDS.  Bound by memory: v^4 values written, half of that read
-// (o=30 v=300: 38 ms for 97 GB, 2.5 TB/s).
+// (o=30 v=300: 30.6 ms for 97 GB; 38.3 before each XCD took a contiguous run).
 __global__ __launch_bounds__(256) void unfold_kernel(const double* __restrict__ Wp, long long ldp,
                                                      const double* __restrict__ Wm, long long ldm,
                                                      int v, int tiles, double* __restrict__ S,
@@ -1556,7 +1572,7 @@ __global__ __launch_bounds__(256) void unfold_kernel(const double* __restrict__ 
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const long long ntp = (long long)tiles * (tiles + 1) / 2;
   const long long npairs = (long long)v * (v + 1) / 2;
-  for (long long w = blockIdx.x; w < npairs * ntp; w += gridDim.x) {
+  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < npairs * ntp; w += gridDim.x) {
     const long long r = w / ntp;
     const int tp = static_cast<int>(w - r * ntp);
     const int C = pair_row(tp, tiles);
