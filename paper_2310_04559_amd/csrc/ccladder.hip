@@ -226,6 +226,7 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
   g.n_load = n_load;
   g.m_load = m_load;
   g.ldv = ldv ? ldv : (long long)v * v;
+  g.lda_v = v > 0 ? N / v * g.ldv : 0;
   g.sym = sym;
   g.A = A; g.lda = lda;
   g.B = B; g.ldb = ldb;
@@ -317,14 +318,17 @@ __global__ __launch_bounds__(256) void part_reduce_kernel(const double* __restri
 // ranges of whole K-steps, one workgroup per (tile, range), float64 partials in
 // `part` (splits * M * N) and an ordered reduction (nt: columns of the whole
 // output, as in launch_gemm).  For products whose tile grid
-// alone leaves compute units idle (small M x N, long K).  Falls back to the plain
-// product when there is one range or the operands do not suit the direct kernel.
+// alone leaves compute units idle (small M x N, long K).  The tiles and, for rows
+// that are not 16-byte aligned, the register-direct kernel by pick_part_tiles.  On
+// 128 x 256 tiles alone, o=8 ran its 64 x 64 results there, and odd v unsplit: the
+// three occupied-index terms at o=8, P=400 913 -> 228 us (v = 100), 3541 -> 244 us
+// (v = 101).  The plain product when there is one range.
 template <class Tr>
 int launch_contract_split(const typename Tr::T* A, long long lda, const typename Tr::T* B,
                           long long ldb, double* C, long long ldc, int M, int N, int K, int splits,
                           double* part, int drain_steps, int nt, hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0) return CC_LADDER_OK;
-  if (splits <= 1 || !part || !vec_ok(A, lda) || !vec_ok(B, ldb))
+  if (splits <= 1 || !part)
     return launch_gemm<Tr, KC, KC, EPI_ACC>(A, lda, B, ldb, C, ldc, M, N, K, 0, drain_steps, stream,
                                             0, 0, nullptr, 1.0, 0, 0, 0, M, nt);
   GemmArgs<typename Tr::T> g;
@@ -334,19 +338,43 @@ int launch_contract_split(const typename Tr::T* A, long long lda, const typename
   g.C = part; g.ldc = N;
   g.M = M; g.N = N; g.K = K;
   g.v = 0; g.o = 0; g.a0 = 0; g.row_tiles = nullptr;
-  g.tiles_m = (M + kDBM - 1) / kDBM;
-  g.tiles_n = (N + kDBN - 1) / kDBN;
-  g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
   g.drain_steps = drain_steps > 0 ? drain_steps : 1;
   const int bk = kDRow / static_cast<int>(sizeof(typename Tr::T));
   const int nk = (K + bk - 1) / bk;
+  const bool aligned = vec_ok(A, lda) && vec_ok(B, ldb);
   g.split_steps = (nk + splits - 1) / splits;
+  // (unaligned float32 rows: ranges of whole drain chunks, so that the float32 partial
+  // sums are those of the plain product)
+  if (Tr::kDrain && !aligned)
+    g.split_steps = (g.split_steps + g.drain_steps - 1) / g.drain_steps * g.drain_steps;
   const int S = (nk + g.split_steps - 1) / g.split_steps;  // non-empty ranges
   g.part_stride = (long long)M * N;
+  // the whole output (M x nt) decides the waves along K, and with them the order of
+  // the sums
+  const TilePick pick = pick_part_tiles(
+      M, nt, S, Tr::kDrain ? (g.split_steps + g.drain_steps - 1) / g.drain_steps : g.split_steps,
+      aligned);
+  g.tiles_m = (M + pick.bm - 1) / pick.bm;
+  g.tiles_n = (N + pick.bn - 1) / pick.bn;
+  g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
   const long long grid = (long long)g.tiles_m * g.tiles_n * S;
   if (grid > 0x7fffffffLL) return CC_LADDER_EINVAL;
-  hipLaunchKernelGGL((gemm_kc_direct_kernel<Tr, EPI_PART>), dim3(static_cast<unsigned>(grid)),
-                     dim3(kDThreads), 0, stream, g);
+  const dim3 blocks_of(static_cast<unsigned>(grid));
+  if (pick.side == 1)
+    hipLaunchKernelGGL((gemm_wave_kernel<Tr, KC, KC, EPI_PART, 1, 1>), blocks_of,
+                       dim3(64 * pick.wk), wave_lds_bytes(1, pick.wk), stream, g);
+  else if (pick.side == 2)
+    hipLaunchKernelGGL((gemm_wave_kernel<Tr, KC, KC, EPI_PART, 2, 2>), blocks_of,
+                       dim3(256 * pick.wk), wave_lds_bytes(4, pick.wk), stream, g);
+  else if (pick.bn == 64)
+    hipLaunchKernelGGL((gemm_kc_direct_kernel<Tr, EPI_PART, 64, 64>), blocks_of, dim3(kDThreads), 0,
+                       stream, g);
+  else if (pick.bn == 128)
+    hipLaunchKernelGGL((gemm_kc_direct_kernel<Tr, EPI_PART, 64, 128>), blocks_of, dim3(kDThreads), 0,
+                       stream, g);
+  else
+    hipLaunchKernelGGL((gemm_kc_direct_kernel<Tr, EPI_PART>), blocks_of, dim3(kDThreads), 0, stream,
+                       g);
   const long long MN = (long long)M * N;
   const long long blocks = std::min<long long>((MN + 255) / 256, 4096);
   hipLaunchKernelGGL(part_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream,

@@ -131,7 +131,8 @@ struct GemmArgs {
   long long ldc;
   int M, N, K;
   int v;             // EPI_PERM/PACK/PAIR index split
-  long long ldv = 0; // EPI_PERM: row stride of the integral-shaped block
+  long long ldv = 0; // EPI_PERM: row stride of the integral-shaped block,
+  long long lda_v = 0;  // and N/v rows of it (the stride of a)
   int sym = 0;       // EPI_PERM, direct-to-LDS kernel: one operand with itself, only the
                      // elements n >= m formed and stored at (m, n) and (n, m)
   int o;             // EPI_PAIR: occupied count (rows are (i,j))
@@ -246,8 +247,7 @@ __device__ __forceinline__ void epi_store(const GemmArgs<T>& g, int m, int n, co
     static_cast<double*>(g.C)[(long long)m * g.ldc + n] = val;
   } else if (EPI == EPI_PERM) {
     const int a = m / g.v, x = m - a * g.v;
-    static_cast<T*>(g.C)[(long long)a * (g.N / g.v) * g.ldv + c.off + (long long)x * v] =
-        static_cast<T>(val);
+    static_cast<T*>(g.C)[a * g.lda_v + c.off + (long long)x * v] = static_cast<T>(val);
   } else if (EPI == EPI_SYM) {
     T* C = static_cast<T*>(g.C);
     C[(long long)m * g.ldc + n] = static_cast<T>(val);

@@ -512,7 +512,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
       return (long long)(a - g.a0) * v * v * v + (long long)y * v * v + (long long)b * v + d;
     }
     const int a = m / g.v, x = m - a * g.v;
-    if (EPI == EPI_PERM) return ((long long)a * (g.N / g.v) + y) * g.ldv + (long long)x * v + d;
+    if (EPI == EPI_PERM) return a * g.lda_v + y * g.ldv + (long long)x * v + d;
     if (y < a) return -1;
     const long long row = pair_prefix_d(g.a0 + a, v) - pair_prefix_d(g.a0, v) + (y - a);
     return row * v * v + (long long)x * v + d;
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
       // rows of 4 adjacent m per (r), columns of CH adjacent n: the group on or above
       // the diagonal, and its mirror with rows and columns exchanged
       T* C = static_cast<T*>(g.C);
-      const int nv = g.N / g.v, yb = nb / g.v, db = nb - yb * g.v;
+      const int yb = nb / g.v, db = nb - yb * g.v;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         T val[4][CH];
@@ -542,8 +542,8 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
           const int ab = mb / g.v, xb = mb - ab * g.v;
           if (vec && mb + CH - 1 <= nb) {
             // wholly on or above the diagonal (M and N are multiples of CH here)
-            T* up = C + ((long long)ab * nv + yb) * g.ldv + (long long)xb * v + db;
-            T* down = C + ((long long)yb * nv + ab) * g.ldv + (long long)db * v + xb;
+            T* up = C + ab * g.lda_v + yb * g.ldv + (long long)xb * v + db;
+            T* down = C + yb * g.lda_v + ab * g.ldv + (long long)db * v + xb;
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
               Chunk x, y;
@@ -565,8 +565,8 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
               for (int e = 0; e < CH; ++e) {
                 const int m = mb + i, n = nb + e;
                 if (m < g.M && n < g.N && m <= n) {
-                  C[((long long)a * nv + y) * g.ldv + (long long)x * v + d] = val[CH * q + i][e];
-                  C[((long long)y * nv + a) * g.ldv + (long long)d * v + x] = val[CH * q + i][e];
+                  C[a * g.lda_v + y * g.ldv + (long long)x * v + d] = val[CH * q + i][e];
+                  C[y * g.lda_v + a * g.ldv + (long long)d * v + x] = val[CH * q + i][e];
                 }
                 if (++d == g.v) { d = 0; ++y; }
               }

@@ -144,7 +144,20 @@ __global__ __launch_bounds__(64 * kWMaxWaves) void gemm_wave_kernel(GemmArgs<typ
   const int WK = static_cast<int>(blockDim.x >> 6) / (WM * WN);
   const int wk = wave / (WM * WN), wt = wave % (WM * WN);
   int tm, tn;
-  tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
+  const int nk_all = (g.K + STEP - 1) / STEP;
+  int ks0 = 0, nk = nk_all;  // K-steps of this workgroup
+  if (EPI == EPI_PART) {
+    // grid = tiles x splits, as in the K-contiguous direct kernel
+    const int ntiles = g.tiles_m * g.tiles_n;
+    const int id = xcd_linear(blockIdx.x, gridDim.x);
+    const int split = id / ntiles;
+    tile_from_linear(id - split * ntiles, ntiles, g.tiles_m, g.group_m, tm, tn);
+    ks0 = split * g.split_steps;
+    nk = ks0 + g.split_steps < nk_all ? ks0 + g.split_steps : nk_all;
+    g.C = static_cast<double*>(g.C) + split * g.part_stride;
+  } else {
+    tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
+  }
   const int m0 = tm * BM, n0 = tn * BN;
   if (EPI == EPI_PACK || EPI == EPI_SYM) {
     // every column's b below every row's a: nothing of this tile is kept
@@ -185,8 +198,8 @@ __global__ __launch_bounds__(64 * kWMaxWaves) void gemm_wave_kernel(GemmArgs<typ
   };
   typename OA::Vec a0[OA::NV], a1[OA::NV];
   typename OB::Vec b0[OB::NV], b1[OB::NV];
-  const int nfull = g.K / STEP;                // steps loaded without tests
-  const int nk = (g.K + STEP - 1) / STEP;
+  // steps loaded without tests: all but a ragged last one of the whole product
+  const int nfull = nk < g.K / STEP ? nk : g.K / STEP;
 
   // Steps s, s + stride, ... < s1 of this wave, all full: loads one step ahead.
   auto run = [&](int s, int s1, int stride) {
@@ -205,13 +218,14 @@ __global__ __launch_bounds__(64 * kWMaxWaves) void gemm_wave_kernel(GemmArgs<typ
     if (s < s1) compute(a0, b0);
   };
   auto tail = [&]() {
-    a.load_tail(a0, nfull * STEP, g.K);
-    b.load_tail(b0, nfull * STEP, g.K);
+    const int kt = g.K / STEP * STEP;
+    a.load_tail(a0, kt, g.K);
+    b.load_tail(b0, kt, g.K);
     compute(a0, b0);
   };
   if (!Tr::kDrain) {
-    run(wk, nfull, WK);
-    if (nk > nfull && nfull % WK == wk) tail();
+    run(ks0 + wk, nfull, WK);
+    if (nk > nfull && (nfull - ks0) % WK == wk) tail();
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -220,7 +234,7 @@ __global__ __launch_bounds__(64 * kWMaxWaves) void gemm_wave_kernel(GemmArgs<typ
         for (int r = 0; r < 4; ++r) sum[i][j][r] = static_cast<double>(acc[i][j][r]);
   } else {
     // chunks of drain_steps K-steps: float32 within a chunk, float64 across
-    for (int c = wk * g.drain_steps; c < nk; c += WK * g.drain_steps) {
+    for (int c = ks0 + wk * g.drain_steps; c < nk; c += WK * g.drain_steps) {
       const int e = c + g.drain_steps < nk ? c + g.drain_steps : nk;
       run(c, e < nfull ? e : nfull, 1);
       if (e > nfull) tail();

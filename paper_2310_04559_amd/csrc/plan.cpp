@@ -478,8 +478,8 @@ namespace {
 // the grid over the 256 compute units times the tile, over the share of the matrix
 // cores' rate that the tile reaches.  The shares are float64 measurements on
 // products that fill whole rounds: 128 x 256 (and 160) 0.88 (o=40 v=360 P=1200
-// contraction), 64 x 128 0.84 (225 x 16290 x 16290: 2.05 ms against 2.17 on 64 x 256),
-// 64 x 64 0.80 (400 x 16290 x 16290: 3.66 ms).  The smaller tiles win where the larger ones would leave part of a
+// contraction), 64 x 128 0.82 (225 x 16290 x 16290: 2.05 ms against 2.17 on 64 x 256),
+// 64 x 64 0.78 (400 x 16290 x 16290: 3.66 ms).  The smaller tiles win where the larger ones would leave part of a
 // round idle: 169 x 4753 x 4753 0.19 ms on 64 x 64 against 1.17 on 128 x 256,
 // 800 x 4950 x 4950 0.63 on 64 x 128 against 1.23.
 double tile_cost(long long M, long long N, int bm, int bn, double rate) {
@@ -528,13 +528,13 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
                                        tile_cost(M - main_rows, N, 64, 256, 0.88)
                                  : tile_cost(M, N, bm, 256, 0.88);
     take(bm == 64 ? 128 : bm, 256, main_rows, cost);
-    take(64, 128, M, tile_cost(M, N, 64, 128, 0.84));
-    take(64, 64, M, tile_cost(M, N, 64, 64, 0.80));
+    take(64, 128, M, tile_cost(M, N, 64, 128, 0.82));
+    take(64, 64, M, tile_cost(M, N, 64, 64, 0.78));
   } else if (cls == kTilesKR) {
     take(128, 256, M, tile_cost(M, N, 128, 256, 0.88));
     if (tall) {
-      take(64, 128, M, tile_cost(M, N, 64, 128, 0.84));
-      take(64, 64, M, tile_cost(M, N, 64, 64, 0.80));
+      take(64, 128, M, tile_cost(M, N, 64, 128, 0.82));
+      take(64, 64, M, tile_cost(M, N, 64, 64, 0.78));
     }
   } else {
     take(128, 128, M, tile_cost(M, N, 128, 128, 0.80));
@@ -562,6 +562,44 @@ TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long l
   // one wave along K or a big tile: the same order of the sums, so the launch's own
   // extents decide
   return pick_launch(cls, M, N, K, 1, es, tall, split);
+}
+
+TilePick pick_part_tiles(long long M, long long N, int splits, long long units, bool direct) {
+  TilePick p;
+  p.main_rows = M;
+  double best = 0.0;
+  auto rounds = [&](long long bm, long long bn) {
+    return static_cast<double>((((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits + 255) / 256);
+  };
+  auto take = [&](int bm, int bn, double rate) {
+    const double cost = rounds(bm, bn) * bm * bn / rate;
+    if (p.bm && cost >= best) return;
+    best = cost;
+    p.bm = bm;
+    p.bn = bn;
+  };
+  if (direct) {
+    take(128, 256, 0.88);
+    // (shares on short ranges of K; 1600 x 1600 over 14 ranges of 9257: 18.6 ms on
+    // 128 x 256, 19.8 on 64 x 128)
+    take(64, 128, 0.78);
+    take(64, 64, 0.76);
+  }
+  for (int side = 2; side >= 1; --side) {
+    const int t = 32 * side;
+    const double r = rounds(t, t);
+    int wk = 1;
+    while (2 * wk * side * side <= 16 && units >= 4LL * wk && r * wk * side * side < 8) wk *= 2;
+    const double busy = r * wk * side * side >= 8 ? 1.0 : r * wk * side * side / 8;
+    const double cost = r * t * t / (0.62 * busy);
+    if (p.bm && cost >= best) continue;
+    best = cost;
+    p.bm = p.bn = t;
+    p.side = side;
+    p.wk = wk;
+  }
+  p.cost = best;
+  return p;
 }
 
 PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, long long kp, int es,

@@ -192,6 +192,12 @@ struct FoldAdjoint {
 };
 bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a);
 
+// The cut of a split-K product of M x N partials over `splits` ranges of `units`
+// pieces of K each (as in pick_tiles): the tiles of the K-contiguous direct kernel when
+// `direct`, else (or where it is faster) the register-direct kernel, whose waves along
+// K divide a range.  Depends on the whole output only.
+TilePick pick_part_tiles(long long M, long long N, int splits, long long units, bool direct);
+
 // The two products of a +- contraction in one launch of float64 partials that a
 // pass combines into R: K cut into `splits` ranges of whole drain chunks (`chunk`
 // K-steps; 1 in float64), tiles of bm x bn.
