@@ -246,20 +246,20 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
   // The tiles, by the whole output's extents and the kernels that the operands
   // suit.  (Float32 row-contiguous products on the direct kernel, above, deal k to
   // the MFMA slots in another order: a switch of kernels would change their sums.)
-  // The register-direct kernel has no K bands, and loads row-contiguous operands
-  // by pairs of rows.
+  // The register-direct kernel loads row-contiguous operands by pairs of rows.
   constexpr bool kKC = LA == KC && LB == KC && Tr::kDirectKC;
   constexpr bool kKR =
-      LA == KC && LB == RC && (EPI == EPI_ACC || EPI == EPI_FOLD) && Tr::kDirectKR;
+      LA == KC && LB == RC && (EPI == EPI_ACC || EPI == EPI_FOLD || EPI == EPI_PM) && Tr::kDirectKR;
   const bool aligned = vec_ok(A, lda) && vec_ok(B, ldb);
   const bool direct = aligned && (kKC || (kKR && (n_load ? n_load : N) % Tr::CH == 0));
+  g.band_cols = direct ? kDBN : kBN;
   const int nk = (K + Tr::BK - 1) / Tr::BK;
   const TilePick pick =
       pick_tiles(!direct ? kTilesStaged : kKC ? kTilesKC : kTilesKR, M, N, K, mt ? mt : M,
                  nt ? nt : N, Tr::kDrain ? (nk + g.drain_steps - 1) / g.drain_steps : nk,
                  sizeof(typename Tr::T), !Tr::kDrain,
                  EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM || EPI == EPI_FOLD);
-  if (pick.side && !kband && (LA == KC || M >= 2) && (LB == KC || N >= 2))
+  if (pick.side && (LA == KC || M >= 2) && (LB == KC || N >= 2))
     return pick.side == 1 ? launch_wave_side<Tr, LA, LB, EPI, 1>(g, pick.wk, stream)
                           : launch_wave_side<Tr, LA, LB, EPI, 2>(g, pick.wk, stream);
   if constexpr (kKC) {
@@ -630,7 +630,7 @@ __global__ __launch_bounds__(256) void pm_rows_kernel(const In* __restrict__ X, 
                                                       int n, int a0, int v, int tiles,
                                                       Out* __restrict__ plus, long long ldp,
                                                       Out* __restrict__ minus, long long ldm,
-                                                      double wdiag, double sm) {
+                                                      double wdiag, double sm, double wrow) {
   __shared__ double xs[kSwapTile][kSwapTile + 1], ys[kSwapTile][kSwapTile + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const long long ntp = (long long)tiles * (tiles + 1) / 2;
@@ -642,11 +642,13 @@ __global__ __launch_bounds__(256) void pm_rows_kernel(const In* __restrict__ X, 
     const int D = C + static_cast<int>(tp - pair_prefix_d(C, tiles));
     const int c0 = C * kSwapTile, d0 = D * kSwapTile;
     long long src, rm;
+    double wr = 1.0;  // AMPS: wrow on rows i < j
     if (MODE == PM_AMPS) {
       const int i = pair_row(r, n);
       const int j = i + static_cast<int>(r - pair_prefix_d(i, n));
       src = (long long)i * n + j;
       rm = i < j ? pair_prefix_d(i, n - 1) + (j - i - 1) : -1;
+      if (i < j) wr = wrow;
     } else if (MODE == PM_ALL) {
       src = rm = r;
     } else {
@@ -671,10 +673,10 @@ __global__ __launch_bounds__(256) void pm_rows_kernel(const In* __restrict__ X, 
       if (c < v && d < v && c <= d) {
         const double xcd = xs[k][tx], xdc = ys[tx][k];
         const long long kp = pair_prefix_d(c, v) + (d - c);
-        plus[r * ldp + kp] = static_cast<Out>(c == d ? wdiag * xcd : xcd + xdc);
+        plus[r * ldp + kp] = static_cast<Out>(wr * (c == d ? wdiag * xcd : xcd + xdc));
         if (rm >= 0 && c < d) {
           const long long km = pair_prefix_d(c, v - 1) + (d - c - 1);
-          minus[rm * ldm + km] = static_cast<Out>(sm * (xcd - xdc));
+          minus[rm * ldm + km] = static_cast<Out>(wr * (sm * (xcd - xdc)));
         }
       }
     }
@@ -684,13 +686,13 @@ __global__ __launch_bounds__(256) void pm_rows_kernel(const In* __restrict__ X, 
 
 template <int MODE, typename In, typename Out>
 int pm_rows(const In* X, long long nrows, int n, int a0, int v, Out* plus, long long ldp,
-            Out* minus, long long ldm, double wdiag, double sm, hipStream_t s) {
+            Out* minus, long long ldm, double wdiag, double sm, hipStream_t s, double wrow = 1.0) {
   if (nrows <= 0) return CC_LADDER_OK;
   const int tiles = (v + kSwapTile - 1) / kSwapTile;
   const long long work = nrows * ((long long)tiles * (tiles + 1) / 2);
   const long long blocks = std::min<long long>(work, 65536);
   hipLaunchKernelGGL((pm_rows_kernel<MODE, In, Out>), dim3(static_cast<unsigned>(blocks)), dim3(256),
-                     0, s, X, nrows, n, a0, v, tiles, plus, ldp, minus, ldm, wdiag, sm);
+                     0, s, X, nrows, n, a0, v, tiles, plus, ldp, minus, ldm, wdiag, sm, wrow);
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
@@ -1609,7 +1611,7 @@ __global__ __launch_bounds__(256) void unfold_kernel(const double* __restrict__ 
     const int a = pair_row(r, v);
     const int b = a + static_cast<int>(r - pair_prefix_d(a, v));
     const double* wp = Wp + r * ldp;
-    const double* wm = a < b ? Wm + (pair_prefix_d(a, v - 1) + (b - a - 1)) * ldm : nullptr;
+    const double* wm = Wm && a < b ? Wm + (pair_prefix_d(a, v - 1) + (b - a - 1)) * ldm : nullptr;
     const double wab = a == b ? 1.0 : 0.5;
     // xs[k][l] = S[a,b][c0+k,d0+l], ys[k][l] = S[a,b][d0+l,c0+k] for c0+k <= d0+l
 #pragma unroll
@@ -1670,7 +1672,7 @@ int backward_fold(const Plan& pl, const FoldAdjoint& fa, const double* L, const 
                   const double* lam, double* dL, double* dt, char* base, const Tracer& tr,
                   hipStream_t s) {
   const FoldPlan& f = fa.f;
-  const int o = pl.o, v = pl.v, P = pl.P, o2 = o * o, iv2 = v * v;
+  const int o = pl.o, v = pl.v, P = pl.P, iv2 = v * v;
   const long long v2 = (long long)v * v;
   const int kp = static_cast<int>((long long)v * (v + 1) / 2);
   const int km = static_cast<int>((long long)v * (v - 1) / 2);
@@ -1681,10 +1683,22 @@ int backward_fold(const Plan& pl, const FoldAdjoint& fa, const double* L, const 
   int* row_tiles = reinterpret_cast<int*>(base + f.off_tiles);
   // exchange: the ladder of swapped amplitudes, t- and dt- with the other sign
   const double sm = pl.exchange ? -1.0 : 1.0;
+  const bool pairs = pl.pairsym_adj != 0;
+  const int mp = static_cast<int>(f.rows_p), mm = static_cast<int>(f.rows_m);
+  double *Lp = pl.gsym ? at(fa.off_Lp) : nullptr, *G = pl.gsym ? at(fa.off_G) : nullptr;
   tr(CC_LADDER_PHASE_PREP, 0, 0);
-  int rc = pm_rows<PM_ALL>(t, o2, o, 0, v, Tp, f.ldp, Tm, f.ldm, 1.0, sm, s);
-  if (!rc) rc = pm_rows<PM_ALL>(lam, o2, o, 0, v, Mp, f.ldp, Mm, f.ldm, 1.0, 1.0, s);
+  int rc;
+  if (pairs) {
+    rc = pm_rows<PM_AMPS>(t, mp, o, 0, v, Tp, f.ldp, Tm, f.ldm, 1.0, sm, s, 2.0);
+    if (!rc) rc = pm_rows<PM_AMPS>(lam, mp, o, 0, v, Mp, f.ldp, Mm, f.ldm, 1.0, 1.0, s);
+    if (!rc && pl.gsym) rc = pack_sym(L, Lp, P, v, f.ldp, s);
+  } else {
+    rc = pm_rows<PM_ALL>(t, mp, o, 0, v, Tp, f.ldp, Tm, f.ldm, 1.0, sm, s);
+    if (!rc) rc = pm_rows<PM_ALL>(lam, mp, o, 0, v, Mp, f.ldp, Mm, f.ldm, 1.0, 1.0, s);
+  }
   tr(CC_LADDER_PHASE_PREP, 0, 1);
+  if (rc) return rc;
+  if (pl.gsym) rc = build_pair_integral<TrF64>(pl, Lp, G, row_tiles, tr, s);
   if (rc) return rc;
   for (int blk = 0; blk < f.nb; ++blk) {
     const int a0 = pair_block_start(v, f.nb, blk);
@@ -1694,36 +1708,49 @@ int backward_fold(const Plan& pl, const FoldAdjoint& fa, const double* L, const 
     const long long p0 = pair_prefix(a0, v), m0 = pair_prefix(a0, v - 1);  // first pairs
     const long long np = pair_prefix(a0 + na, v) - p0, nm = np - na;
     tr(CC_LADDER_PHASE_BUILD, blk, 0);
-    rc = launch_gemm<TrF64, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
-                                              static_cast<int>((long long)(v - a0) * v), P, v, 0, s,
-                                              o, a0, row_tiles, 1.0, 0, 0, 0, iv2, iv2);
-    if (!rc) rc = pm_rows<PM_INTS>(V, np, v, a0, v, Vp, f.ldp, Vm, f.ldm, 2.0, 1.0, s);
+    if (pl.gsym) {
+      rc = pm_gather<GATHER_PM>(static_cast<const double*>(G), pl.ldg, np, a0, v, Vp, f.ldp, Vm,
+                                f.ldm, s);
+    } else {
+      rc = launch_gemm<TrF64, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
+                                                static_cast<int>((long long)(v - a0) * v), P, v, 0,
+                                                s, o, a0, row_tiles, 1.0, 0, 0, 0, iv2, iv2);
+      if (!rc) rc = pm_rows<PM_INTS>(V, np, v, a0, v, Vp, f.ldp, Vm, f.ldm, 2.0, 1.0, s);
+    }
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
     // dt over the pairs of c, d, from the block's pairs of a, b (the pads of V+- rows
     // may be read: their columns are not stored)
     tr(CC_LADDER_PHASE_DT, blk, 0);
-    rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mp + p0, f.ldp, Vp, f.ldp, dt, v2, o2, kp,
-                                              static_cast<int>(np), v, 0, s, o, 0, nullptr, 0.5, 1,
-                                              0, 0, 0, 0, static_cast<int>(f.ldp));
-    if (!rc)
-      rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mm + m0, f.ldm, Vm, f.ldm, dt, v2, o2, km,
-                                                static_cast<int>(nm), v, 0, s, o, 0, nullptr,
-                                                0.5 * sm, 2, 0, 0, 0, 0, static_cast<int>(f.ldm));
+    const int inp = static_cast<int>(np), inm = static_cast<int>(nm);
+    const int ldp = static_cast<int>(f.ldp), ldm = static_cast<int>(f.ldm);
+    if (pairs) {
+      rc = launch_gemm<TrF64, KC, RC, EPI_PM>(Mp + p0, f.ldp, Vp, f.ldp, dt, v2, mp, kp, inp, v, 0,
+                                              s, o, 0, nullptr, 0.5, 1, 0, 0, 0, 0, ldp);
+      if (!rc)
+        rc = launch_gemm<TrF64, KC, RC, EPI_PM>(Mm + m0, f.ldm, Vm, f.ldm, dt, v2, mm, km, inm, v,
+                                                0, s, o, 0, nullptr, 0.5 * sm, 2, 0, 0, 0, 0, ldm);
+    } else {
+      rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mp + p0, f.ldp, Vp, f.ldp, dt, v2, mp, kp, inp, v, 0,
+                                                s, o, 0, nullptr, 0.5, 1, 0, 0, 0, 0, ldp);
+      if (!rc)
+        rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mm + m0, f.ldm, Vm, f.ldm, dt, v2, mm, km, inm, v,
+                                                  0, s, o, 0, nullptr, 0.5 * sm, 2, 0, 0, 0, 0, ldm);
+    }
     tr(CC_LADDER_PHASE_DT, blk, 1);
     if (rc) return rc;
   }
   tr(CC_LADDER_PHASE_W, 0, 0);
-  rc = launch_gemm<TrF64, RC, RC, EPI_STORE>(Mp, f.ldp, Tp, f.ldp, Wp, f.ldp, kp, kp, o2, v, 0, s);
+  rc = launch_gemm<TrF64, RC, RC, EPI_STORE>(Mp, f.ldp, Tp, f.ldp, Wp, f.ldp, kp, kp, mp, v, 0, s);
   if (!rc)
-    rc = launch_gemm<TrF64, RC, RC, EPI_STORE>(Mm, f.ldm, Tm, f.ldm, Wm, f.ldm, km, km, o2, v, 0, s);
+    rc = launch_gemm<TrF64, RC, RC, EPI_STORE>(Mm, f.ldm, Tm, f.ldm, Wm, f.ldm, km, km, mm, v, 0, s);
   tr(CC_LADDER_PHASE_W, 0, 1);
   if (rc) return rc;
   tr(CC_LADDER_PHASE_DL, 0, 0);
   const int tiles = (v + kSwapTile - 1) / kSwapTile;
   const long long work = (long long)kp * ((long long)tiles * (tiles + 1) / 2);
   hipLaunchKernelGGL(unfold_kernel, dim3(static_cast<unsigned>(std::min<long long>(work, 65536))),
-                     dim3(256), 0, s, Wp, f.ldp, Wm, f.ldm, v, tiles, S, fa.lds);
+                     dim3(256), 0, s, Wp, f.ldp, mm > 0 ? Wm : nullptr, f.ldm, v, tiles, S, fa.lds);
   const double* Lr = L;
   if (fa.copy_L) {
     double* Lc = at(fa.off_L);

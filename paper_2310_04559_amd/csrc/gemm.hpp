@@ -146,17 +146,21 @@ struct GemmArgs {
   double alpha;          // EPI_ACC: C += alpha * acc (1, or 2 for a term counted twice)
   int m_off = 0;         // EPI_PAIR/PM: global row of this launch's row 0 (a remainder launch)
   int pm = 0;            // EPI_PM/FOLD: 1 = symmetric pairs (i <= j, a <= b), 2 = antisymmetric (<)
-  int kband = 0;         // K bands of a half-written B operand (0 = the whole K range)
+  int kband = 0;         // K bands of a half-written B operand (0 = the whole K range), by
+  int band_cols = 256;   // so many columns: the big tile of the operands' layout and alignment
   int m_load = 0, n_load = 0;  // direct-to-LDS kernels, row-contiguous operands: rows of A and
                          // columns of B that may be read (M, N and pads up to whole
                          // 16-byte chunks; 0 = M, N)
   int m_keep = 0;        // EPI_UNPACK: rows stored (M may be padded to whole 16-byte chunks)
 };
 
-// K-steps [ks0, ks1) of the tile whose columns start at n0 (bn wide), steps of bk.
+// K-steps [ks0, ks1) of a tile whose columns start at n0, steps of bk: the range of the
+// band_cols columns that the tile lies in, so that a sum starts at the same k (and a
+// float32 chunk ends at the same k) on the smaller tiles as on the big ones.
 template <class T>
-__device__ __forceinline__ void k_band(const GemmArgs<T>& g, int n0, int bn, int bk, int& ks0,
-                                       int& ks1) {
+__device__ __forceinline__ void k_band(const GemmArgs<T>& g, int n0, int bk, int& ks0, int& ks1) {
+  const int bn = g.band_cols;
+  n0 = n0 / bn * bn;
   ks0 = 0;
   ks1 = (g.K + bk - 1) / bk;
   if (g.kband == 1) {
@@ -604,7 +608,7 @@ __global__ __launch_bounds__(kThreads, Tr::kWaves) void gemm_kernel(GemmArgs<typ
     }
 
   int ks0, ks1;
-  k_band(g, n0, kBN, Tr::BK, ks0, ks1);
+  k_band(g, n0, Tr::BK, ks0, ks1);
   const bool interior = (m0 + kBM <= g.M) && (n0 + kBN <= g.N);
   if (interior)
     tile_mainloop<Tr, LA, LB, true>(g, m0, n0, ks0, ks1, sA[0], sA[1], sB[0], sB[1], acc, acc64);

@@ -104,7 +104,7 @@ __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const
     tile_of(bid, nwg, g.tiles_m, g.group_m, tm, tn);
   }
   const int m0 = tm * BM, n0 = tn * BN;
-  if (EPI != EPI_PART && g.kband) k_band(g, n0, BN, BK, ks0, ks1);
+  if (EPI != EPI_PART && g.kband) k_band(g, n0, BK, ks0, ks1);
 
   // Slabs: A rows 8*(wave + 8*j), j < JA; B rows 8*(wave + 8*j), j < NJ.  The
   // swizzle of a lane depends on the slab's parity only (slab origin 8*s rows).
@@ -626,7 +626,7 @@ namespace ccl {
 // Mixed-layout GEMM with direct global->LDS loads (gfx950): A K-contiguous, B
 // row-contiguous, float64 accumulation into C:
 //
-//   C[m*ldc + n] += sum_k A[m*lda + k] B[k*ldb + n]        (EPI_ACC, or EPI_FOLD)
+//   C[m*ldc + n] += sum_k A[m*lda + k] B[k*ldb + n]        (EPI_ACC, EPI_FOLD or EPI_PM)
 //
 // (the adjoint's dt and second dL term, the hole-hole ladder's contraction).
 // BM x BN tiles: 128 x 256 (2 x 4 waves of 64 x 64); float64 also 64 x 128 (2 x 4
@@ -644,7 +644,7 @@ namespace ccl {
 template <class Tr, int EPI = EPI_ACC, int BM = kDBM, int BN = kDBN>
 __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_direct_kernel(
     GemmArgs<typename Tr::T> g) {
-  static_assert(EPI == EPI_ACC || EPI == EPI_FOLD, "float64 accumulation");
+  static_assert(EPI == EPI_ACC || EPI == EPI_FOLD || EPI == EPI_PM, "float64 accumulation");
   static_assert((BM == kDBM && BN == kDBN) || (BM == 64 && BN <= 128 && Tr::CH == 2),
                 "tiles; the interleave of two column blocks is float64's");
   using T = typename Tr::T;
@@ -676,7 +676,7 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_
     tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   int ks0, ks1;  // this tile's K-steps
-  k_band(g, n0, BN, BK, ks0, ks1);
+  k_band(g, n0, BK, ks0, ks1);
 
   // A: slabs of 8 rows, lane -> row lane/8, physical chunk lane%8 holding
   // logical chunk (lane%8) ^ ((row/2)%8)

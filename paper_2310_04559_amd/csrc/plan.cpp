@@ -528,8 +528,10 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
                                        tile_cost(M - main_rows, N, 64, 256, 0.88)
                                  : tile_cost(M, N, bm, 256, 0.88);
     take(bm == 64 ? 128 : bm, 256, main_rows, cost);
-    take(64, 128, M, tile_cost(M, N, 64, 128, 0.82));
-    take(64, 64, M, tile_cost(M, N, 64, 64, 0.78));
+    // (float32 has twice the rate for the same bytes: 576 x 41209 x 41209 16.8 ms on 64
+    // x 128)
+    take(64, 128, M, tile_cost(M, N, 64, 128, es == 4 ? 0.77 : 0.82));
+    take(64, 64, M, tile_cost(M, N, 64, 64, es == 4 ? 0.70 : 0.78));
   } else if (cls == kTilesKR) {
     take(128, 256, M, tile_cost(M, N, 128, 256, 0.88));
     if (tall) {
@@ -658,8 +660,9 @@ FoldPlan layout_fold(const Plan& pl, int nb) {
   f.nb = nb;
   f.ldp = static_cast<long long>((static_cast<size_t>(v) * (v + 1) / 2 + 3) / 4 * 4);
   f.ldm = static_cast<long long>((static_cast<size_t>(v) * (v - 1) / 2 + 3) / 4 * 4);
-  f.rows_p = pl.pairsym ? (long long)pl.o * (pl.o + 1) / 2 : (long long)pl.o * pl.o;
-  f.rows_m = pl.pairsym ? (long long)pl.o * (pl.o - 1) / 2 : (long long)pl.o * pl.o;
+  const bool pairs = pl.pairsym || pl.pairsym_adj;
+  f.rows_p = pairs ? (long long)pl.o * (pl.o + 1) / 2 : (long long)pl.o * pl.o;
+  f.rows_m = pairs ? (long long)pl.o * (pl.o - 1) / 2 : (long long)pl.o * pl.o;
   size_t np = 0, nm = 0, na_max = 0;
   for (int k = 0; k < nb; ++k) {
     const int a0 = pair_block_start(v, nb, k), a1 = pair_block_start(v, nb, k + 1);
@@ -675,7 +678,9 @@ FoldPlan layout_fold(const Plan& pl, int nb) {
   f.off_V = take(&cur, np * v2 * sizeof(double));
   f.off_Vp = take(&cur, np * f.ldp * sizeof(double));
   f.off_Vm = take(&cur, nm * f.ldm * sizeof(double));
-  f.off_tiles = take(&cur, ((na_max * v + 127) / 128 + 1) * sizeof(int));
+  // tile rows of the packed build, or of the pair-pair integral's upper triangle
+  const size_t rows_m = pl.gsym ? static_cast<size_t>(f.ldp) : na_max * v;
+  f.off_tiles = take(&cur, ((rows_m + 127) / 128 + 1) * sizeof(int));
   f.bytes = cur;
   return f;
 }
@@ -775,41 +780,52 @@ bool plan_stacked_i8(const Plan& pl, StackedPlan* q) {
 
 bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a) {
   // From 64 virtuals on, as the forward: below, the extra launches take what the
-  // products save.  W is formed whole, so a plan of several blocks keeps the direct
-  // route.
-  if (pl.op != kOpLadder || pl.precision != CC_LADDER_FP64 || !pl.backward || pl.pairsym_adj ||
-      pl.n_a != pl.v || pl.v < 64)
+  // products save; from 16 for pair-symmetric t and lam, whose direct route has as many
+  // launches and K-banded products (o=6 v=33 P=120: 567 -> 93 us).  W is
+  // formed whole, so a plan of several blocks keeps the direct route.
+  if (pl.op != kOpLadder || pl.precision != CC_LADDER_FP64 || !pl.backward || pl.n_a != pl.v ||
+      pl.v < (pl.pairsym_adj ? 16 : 64))
     return false;
+  const size_t room = pl.bytes - (pl.check_sym ? kAlign : 0);
   const int v = pl.v;
   const size_t v2 = static_cast<size_t>(v) * v;
   const size_t kp = static_cast<size_t>(v) * (v + 1) / 2;
-  for (int nb = 1; nb <= 4; ++nb) {
-    FoldAdjoint p;
-    p.f = layout_fold(pl, nb);  // t+- first, then the blocks
-    if (!p.f.nb) return false;
-    p.lds = static_cast<long long>((v2 + 1) / 2 * 2);
-    p.copy_L = p.lds != static_cast<long long>(v2);
-    const size_t ldp = p.f.ldp, ldm = p.f.ldm;
-    // lam+- after t+-; the blocks of dt's stage and W+-, S share what follows
-    size_t cur = p.f.off_V;
-    p.off_Mp = take(&cur, p.f.rows_p * ldp * sizeof(double));
-    p.off_Mm = take(&cur, p.f.rows_m * ldm * sizeof(double));
-    const size_t shift = cur - p.f.off_V;
-    p.f.off_V += shift;
-    p.f.off_Vp += shift;
-    p.f.off_Vm += shift;
-    p.f.off_tiles += shift;
-    p.f.bytes += shift;
-    p.off_Wp = take(&cur, kp * ldp * sizeof(double));
-    p.off_Wm = take(&cur, (kp - v) * ldm * sizeof(double));
-    p.off_S = take(&cur, v2 * p.lds * sizeof(double));
-    if (p.copy_L) p.off_L = take(&cur, static_cast<size_t>(pl.P) * p.lds * sizeof(double));
-    p.bytes = cur > p.f.bytes ? cur : p.f.bytes;
-    if (p.bytes <= pl.bytes) {
-      *a = p;
-      return true;
+  // (odd v: with S and a copy of L on padded rows where they fit)
+  for (int pad = v % 2; pad >= 0; --pad) {
+    for (int nb = 1; nb <= 4; ++nb) {
+      FoldAdjoint p;
+      p.f = layout_fold(pl, nb);  // t+- first, then the blocks
+      if (!p.f.nb) break;
+      p.lds = static_cast<long long>(v2) + pad;
+      p.copy_L = pad != 0;
+      const size_t ldp = p.f.ldp, ldm = p.f.ldm;
+      // lam+- after t+-; the blocks of dt's stage and W+-, S share what follows
+      size_t cur = p.f.off_V;
+      p.off_Mp = take(&cur, p.f.rows_p * ldp * sizeof(double));
+      p.off_Mm = take(&cur, p.f.rows_m * ldm * sizeof(double));
+      if (pl.gsym) {
+        p.off_Lp = take(&cur, static_cast<size_t>(pl.P) * ldp * sizeof(double));
+        p.off_G = take(&cur, ldp * ldp * sizeof(double));
+      }
+      const size_t shift = cur - p.f.off_V;
+      p.f.off_V += shift;
+      p.f.off_Vp += shift;
+      p.f.off_Vm += shift;
+      p.f.off_tiles += shift;
+      p.f.bytes += shift;
+      // (W+- and S follow lam+-, in the place of the vectors and G as well)
+      cur = p.off_Mm + (p.f.rows_m * ldm * sizeof(double) + kAlign - 1) / kAlign * kAlign;
+      p.off_Wp = take(&cur, kp * ldp * sizeof(double));
+      p.off_Wm = take(&cur, (kp - v) * ldm * sizeof(double));
+      p.off_S = take(&cur, v2 * p.lds * sizeof(double));
+      if (p.copy_L) p.off_L = take(&cur, static_cast<size_t>(pl.P) * p.lds * sizeof(double));
+      p.bytes = cur > p.f.bytes ? cur : p.f.bytes;
+      if (p.bytes <= room) {
+        *a = p;
+        return true;
+      }
+      if (cur > room) break;  // more blocks shrink dt's stage only
     }
-    if (cur > pl.bytes) return false;  // more blocks shrink dt's stage only
   }
   return false;
 }

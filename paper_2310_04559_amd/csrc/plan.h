@@ -180,12 +180,16 @@ bool plan_stacked_i8(const Plan& pl, StackedPlan* q);
 // and the symmetric part of W that dL needs is
 //   S[a,b][c,d] = W[a,b][c,d] + W[b,a][d,c] = (W+ + W-) / 2,  W+- = sum_ij lam+- t+-,
 // so the build, dt and W take half their multiply-adds; dL = L S is as before.
+// Pair-symmetric t and lam (pl.pairsym_adj): the rows of lam+- and t+- are the pairs
+// i <= j (i < j), t's weighted by 2 for i < j where W sums over them; with symmetric
+// vectors (pl.gsym) V+- are gathered from the pair-pair integral.
 struct FoldAdjoint {
   FoldPlan f;                        // t+-, V, V+- (blocks of dt's stage)
   size_t off_Mp = 0, off_Mm = 0;     // lam+, lam- (strides f.ldp, f.ldm)
   size_t off_Wp = 0, off_Wm = 0;     // W+ [pairs a <= b][f.ldp], W- [pairs a < b][f.ldm]
   size_t off_S = 0;                  // S as rows (a,c), columns (b,d), row stride lds
   size_t off_L = 0;                  // copy of L with row stride lds (odd v only)
+  size_t off_Lp = 0, off_G = 0;      // symmetric vectors: packed vectors, pair-pair integral
   long long lds = 0;                 // v^2 rounded to 2: rows on 16-byte boundaries
   bool copy_L = false;
   size_t bytes = 0;

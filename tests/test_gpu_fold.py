@@ -99,3 +99,30 @@ def test_folded_backward_integer_exact(gpu_lib):
     torch.cuda.synchronize()
     dL_ref, dt_ref = oracle.ladder_backward(L, t, lam)
     assert np.array_equal(host(dL), dL_ref) and np.array_equal(host(dt), dt_ref)
+
+
+# pair-symmetric t and lam: rows i <= j (none i < j at o = 1), gathered from the
+# pair-pair integral with symmetric vectors; v from the smallest folded size on, odd and
+# even; a_block = 20 keeps the direct route
+@pytest.mark.parametrize("o,v,P,a_block", [(5, 16, 20, 0), (1, 21, 9, 0), (7, 33, 41, 0),
+                                           (12, 64, 30, 0), (5, 40, 20, 20)])
+@pytest.mark.parametrize("exchange", [False, True])
+@pytest.mark.parametrize("symv", [False, True])
+def test_folded_pair_symmetric_backward(gpu_lib, o, v, P, a_block, exchange, symv):
+    import torch
+
+    announce("fold-backward-pairsym", o, v, P, "a_block", a_block, exchange, "symv", symv)
+    L, t, lam = random_general(o, v, P, 4500 + o + v)
+    t, lam = (0.5 * (x + x.transpose(1, 0, 3, 2)) for x in (t, lam))
+    if symv:
+        L = 0.5 * (L + L.transpose(0, 2, 1))
+    dL0 = np.random.default_rng(26).standard_normal(L.shape)
+    dt0 = np.random.default_rng(27).standard_normal(t.shape)
+    dL, dt = dev(dL0), dev(dt0)
+    gpu_lib.cc_ladder_backward(dev(L), dev(t), dev(lam), dL, dt, 0,
+                               opts=gpu_lib.make_opts(a_block=a_block, exchange=exchange,
+                                                      pair_symmetric=True, symmetric_vectors=symv))
+    torch.cuda.synchronize()
+    ref = oracle.exchange_backward(L, t, lam) if exchange else oracle.ladder_backward(L, t, lam)
+    assert rel_fro(host(dL) - dL0, ref[0]) < TOL[0]
+    assert rel_fro(host(dt) - dt0, ref[1]) < TOL[0]
