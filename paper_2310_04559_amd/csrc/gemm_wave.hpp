@@ -155,6 +155,10 @@ __global__ __launch_bounds__(64 * kWMaxWaves) void gemm_wave_kernel(GemmArgs<typ
     ks0 = split * g.split_steps;
     nk = ks0 + g.split_steps < nk_all ? ks0 + g.split_steps : nk_all;
     g.C = static_cast<double*>(g.C) + split * g.part_stride;
+  } else if (EPI == EPI_PACK || EPI == EPI_SYM) {
+    // tiles below the diagonal end at once: dealt to the XCDs in turn, so that each has
+    // as many of the others
+    tile_from_linear(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
   } else if (g.kband) {
     tile_of_banded(g.kband, blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
     k_band(g, tn * BN, STEP, ks0, nk);
