@@ -74,32 +74,39 @@ bool vec_ok(const T* p, long long ld) {
   return (reinterpret_cast<uintptr_t>(p) % 16) == 0 && (ld % per16) == 0;
 }
 
+// Rows that the dword loads of the direct-to-LDS kernels reach from a tile's first one
+// with 32-bit byte offsets (at most 256 of them).
+template <class T>
+bool dword_ok(long long ld) {
+  return ld * static_cast<long long>(sizeof(T)) * 256 < (1LL << 31);
+}
+
 // One launch of the K-contiguous direct-to-LDS kernel on BM x BN tiles.
-template <class Tr, int EPI, int BM, int BN>
+template <class Tr, int EPI, int BM, int BN, bool DW = false>
 void launch_kc_tiles(const GemmArgs<typename Tr::T>& g0, hipStream_t stream) {
   GemmArgs<typename Tr::T> g = g0;
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (g.N + BN - 1) / BN;
   g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
-  hipLaunchKernelGGL((gemm_kc_direct_kernel<Tr, EPI, BM, BN>),
+  hipLaunchKernelGGL((gemm_kc_direct_kernel<Tr, EPI, BM, BN, DW>),
                      dim3(static_cast<unsigned>((long long)g.tiles_m * g.tiles_n)), dim3(kDThreads),
                      0, stream, g);
 }
 
-// Products with both operands K-contiguous and 16-byte aligned rows, on the tiles
-// that pick_tiles chose.
-template <class Tr, int EPI>
+// Products with both operands K-contiguous, on the tiles that pick_tiles chose (DW: rows
+// not on 16-byte boundaries, 128 x 256 and smaller tiles).
+template <class Tr, int EPI, bool DW = false>
 int launch_kc_direct(const GemmArgs<typename Tr::T>& g0, const TilePick& pick, hipStream_t stream) {
   GemmArgs<typename Tr::T> g = g0;
   if ((long long)((g.M + 63) / 64) * ((g.N + 63) / 64) > 0x7fffffffLL) return CC_LADDER_EINVAL;
   if (pick.bm == 160) {
-    if constexpr (!Tr::kDrain) launch_kc_tiles<Tr, EPI, 160, 256>(g, stream);
+    if constexpr (!Tr::kDrain && !DW) launch_kc_tiles<Tr, EPI, 160, 256>(g, stream);
   } else if (pick.bn == 64) {
-    launch_kc_tiles<Tr, EPI, 64, 64>(g, stream);
+    if constexpr (!DW || Tr::kDrain) launch_kc_tiles<Tr, EPI, 64, 64, DW>(g, stream);
   } else if (pick.bn == 128) {
-    launch_kc_tiles<Tr, EPI, 64, 128>(g, stream);
+    launch_kc_tiles<Tr, EPI, 64, 128, DW>(g, stream);
   } else {
-    if (pick.main_rows < g.M) {  // 64-row tiles over the remainder rows
+    if (pick.main_rows < g.M && !DW) {  // 64-row tiles over the remainder rows
       GemmArgs<typename Tr::T> rest = g;
       g.M = static_cast<int>(pick.main_rows);
       rest.M -= g.M;
@@ -110,7 +117,7 @@ int launch_kc_direct(const GemmArgs<typename Tr::T>& g0, const TilePick& pick, h
         rest.C = static_cast<double*>(g.C) + pick.main_rows * g.ldc;
       launch_kc_tiles<Tr, EPI, 64, 256>(rest, stream);
     }
-    launch_kc_tiles<Tr, EPI, 128, 256>(g, stream);
+    launch_kc_tiles<Tr, EPI, 128, 256, DW>(g, stream);
   }
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
@@ -129,14 +136,15 @@ __global__ void pack_rows_kernel(int* row_tiles, int tiles_m, int tiles_n, int v
 }
 
 // Integral builds (both operands row-contiguous, permuted or packed store) take
-// the direct-to-LDS RC kernel when rows are whole 16-byte chunks and aligned.
-template <class Tr, int EPI>
+// the direct-to-LDS RC kernel when rows are whole 16-byte chunks and aligned; DW: other
+// rows, by dword loads, with the sums of the register-staged kernel (KMAP 1).
+template <class Tr, int EPI, bool DW = false>
 bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, int* rc) {
-  if (!vec_ok(g0.A, g0.lda) || !vec_ok(g0.B, g0.ldb) || g0.K <= 0) return false;
+  if (g0.K <= 0 || (!DW && (!vec_ok(g0.A, g0.lda) || !vec_ok(g0.B, g0.ldb)))) return false;
   // rows that end in a part of a 16-byte chunk: readable pads, and the order of k that
   // these products have on the register-staged kernel
   const bool whole = g0.M % Tr::CH == 0 && g0.N % Tr::CH == 0;
-  if (!whole && (EPI != EPI_PERM || !g0.m_load || g0.m_load % Tr::CH || !g0.n_load ||
+  if (!DW && !whole && (EPI != EPI_PERM || !g0.m_load || g0.m_load % Tr::CH || !g0.n_load ||
                  g0.n_load % Tr::CH))
     return false;
   GemmArgs<typename Tr::T> g = g0;
@@ -160,8 +168,14 @@ bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, in
                        const_cast<int*>(g.row_tiles), g.tiles_m, g.tiles_n, g.v, kDBM, kDBN);
     grid = needed;
   }
+  if (EPI == EPI_PERM && g.sym) grid = sym_tiles_before(g.tiles_m, g.tiles_n);
+  if constexpr (DW) {
+    hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI, 1, true>), dim3(static_cast<unsigned>(grid)),
+                       dim3(kDThreads), 0, stream, g);
+    *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
+    return true;
+  }
   if constexpr (EPI == EPI_PERM) {
-    if (g.sym) grid = sym_tiles_before(g.tiles_m, g.tiles_n);
     if (!whole) {
       hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI, 1>), dim3(static_cast<unsigned>(grid)),
                          dim3(kDThreads), 0, stream, g);
@@ -178,7 +192,7 @@ bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, in
 // K-contiguous A times row-contiguous B, float64 accumulation: the mixed
 // direct-to-LDS kernel (rows aligned, whole 16-byte chunks of columns) on BM x BN
 // tiles.
-template <class Tr, int EPI, int BM, int BN>
+template <class Tr, int EPI, int BM, int BN, bool DW = false>
 int launch_kr_tiles(const GemmArgs<typename Tr::T>& g0, hipStream_t stream) {
   GemmArgs<typename Tr::T> g = g0;
   g.tiles_m = (g.M + BM - 1) / BM;
@@ -186,7 +200,7 @@ int launch_kr_tiles(const GemmArgs<typename Tr::T>& g0, hipStream_t stream) {
   const long long tiles = (long long)g.tiles_m * g.tiles_n;
   if (tiles > 0x7fffffffLL) return CC_LADDER_EINVAL;
   g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
-  hipLaunchKernelGGL((gemm_kr_direct_kernel<Tr, EPI, BM, BN>), dim3(static_cast<unsigned>(tiles)),
+  hipLaunchKernelGGL((gemm_kr_direct_kernel<Tr, EPI, BM, BN, DW>), dim3(static_cast<unsigned>(tiles)),
                      dim3(kDThreads), 0, stream, g);
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
@@ -252,11 +266,20 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
       LA == KC && LB == RC && (EPI == EPI_ACC || EPI == EPI_FOLD || EPI == EPI_PM) && Tr::kDirectKR;
   const bool aligned = vec_ok(A, lda) && vec_ok(B, ldb);
   const bool direct = aligned && (kKC || (kKR && (n_load ? n_load : N) % Tr::CH == 0));
+  // rows off 16-byte boundaries: dword loads, in the float64 and float32 accumulations
+  // that meet them (odd v); K bands stay with the 128 columns that they are cut by there
+  constexpr bool kDW = (kKC && (EPI == EPI_ACC || EPI == EPI_PAIR)) || (kKR && EPI == EPI_ACC);
+  const bool dwords = kDW && !direct && !kband && dword_ok<typename Tr::T>(lda) &&
+                      dword_ok<typename Tr::T>(ldb);
   g.band_cols = direct ? kDBN : kBN;
   const int nk = (K + Tr::BK - 1) / Tr::BK;
   const TilePick pick =
-      pick_tiles(!direct ? kTilesStaged : kKC ? kTilesKC : kTilesKR, M, N, K, mt ? mt : M,
-                 nt ? nt : N, Tr::kDrain ? (nk + g.drain_steps - 1) / g.drain_steps : nk,
+      pick_tiles(dwords    ? (kKC ? kTilesKCDword : kTilesKRDword)
+                 : !direct ? kTilesStaged
+                 : kKC     ? kTilesKC
+                           : kTilesKR,
+                 M, N, K, mt ? mt : M, nt ? nt : N,
+                 Tr::kDrain ? (nk + g.drain_steps - 1) / g.drain_steps : nk,
                  sizeof(typename Tr::T), !Tr::kDrain,
                  EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM || EPI == EPI_FOLD);
   if (pick.side && (LA == KC || M >= 2) && (LB == KC || N >= 2))
@@ -264,6 +287,17 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
                           : launch_wave_side<Tr, LA, LB, EPI, 2>(g, pick.wk, stream);
   if constexpr (kKC) {
     if (direct) return launch_kc_direct<Tr, EPI>(g, pick, stream);
+    if constexpr (kDW) {
+      if (dwords) return launch_kc_direct<Tr, EPI, true>(g, pick, stream);
+    }
+  }
+  if constexpr (LA == RC && LB == RC && (EPI == EPI_PERM || EPI == EPI_PACK) && Tr::kDirectRC) {
+    // builds from rows off 16-byte boundaries: dword loads, the order of k of the
+    // register-staged kernel
+    if (dword_ok<typename Tr::T>(lda) && dword_ok<typename Tr::T>(ldb)) {
+      int rc = CC_LADDER_OK;
+      if (launch_rc_direct<Tr, EPI, true>(g, stream, &rc)) return rc;
+    }
   }
   if constexpr (kKR) {
     if (direct) {
@@ -272,6 +306,14 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
         if (pick.bn == 128) return launch_kr_tiles<Tr, EPI, 64, 128>(g, stream);
       }
       return launch_kr_tiles<Tr, EPI, kDBM, kDBN>(g, stream);
+    }
+    if constexpr (kDW) {
+      if (dwords) {
+        if constexpr (!Tr::kDrain) {
+          if (pick.bn == 128) return launch_kr_tiles<Tr, EPI, 64, 128, true>(g, stream);
+        }
+        return launch_kr_tiles<Tr, EPI, kDBM, kDBN, true>(g, stream);
+      }
     }
   }
   g.tiles_m = (M + kBM - 1) / kBM;

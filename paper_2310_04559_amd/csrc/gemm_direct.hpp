@@ -35,7 +35,8 @@ __device__ __forceinline__ void d_wait_vm(int n) {
   case N:          \
     __builtin_amdgcn_s_waitcnt(((N)&15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14)); \
     break;
-    CCL_DVM(0) CCL_DVM(2) CCL_DVM(3) CCL_DVM(5) CCL_DVM(6) CCL_DVM(7)
+    CCL_DVM(0) CCL_DVM(2) CCL_DVM(3) CCL_DVM(5) CCL_DVM(6) CCL_DVM(7) CCL_DVM(8) CCL_DVM(12)
+    CCL_DVM(24)
 #undef CCL_DVM
     default:
       __builtin_amdgcn_s_waitcnt(7 << 4 | 15 << 8);
@@ -55,8 +56,57 @@ __device__ __forceinline__ void d_wait_vm(int n) {
 template <int BM, int BN>
 constexpr int kc_groups() { return BM == 64 && BN < 256 ? 2 : 1; }  // per compute unit
 
+// Dword load q (of four) of a 1 KB slab (8 rows of 128 bytes) of a K-contiguous operand,
+// to the image that one 16-byte load per lane leaves: it brings rows 2q and 2q + 1.
+// `tile` is the tile's first row at this step, `row` the slab's first row in the tile and
+// `last` the last one that exists (rows past it repeat it; never stored).  Row addresses
+// are uniform; a lane keeps the swizzled offset `at` and its second row's `hi`.
+__device__ __forceinline__ void d_slab_dword(const char* tile, int row, int last, int ld_bytes,
+                                             int q, unsigned at, unsigned hi,
+                                             unsigned char* slab) {
+  const int r = row + 2 * q;
+  const char* base = tile + static_cast<unsigned>((r < last ? r : last) * ld_bytes);
+  __builtin_amdgcn_global_load_lds((const void*)(base + (at + (r < last ? hi : 0u))),
+                                   (lds_void*)(slab + 256 * q), 4, 0, 0);
+}
+
+// float64 steps issue the dword loads between their products: 24 in a row hold a wave's
+// MFMAs up behind the address unit (o=75 v=225 X 57.3 -> 52.2 ms, Y 171 -> 155).  float32
+// ones, whose drained sums fill the registers, keep them together (o=40 v=211 packed
+// forward 54.2 ms, 67.2 with the spread loop's spills).
+template <class T, bool DW>
+constexpr bool d_spread() { return DW && sizeof(T) == 8; }
+
+// The swizzled byte offset of a lane in load q of a slab of the wave's parity.
+__device__ __forceinline__ unsigned d_dword_at(int lane, int wave, int q) {
+  return ((((lane & 31) >> 2) ^ ((4 * (wave & 1) + q) & 7)) << 4) + ((lane & 3) << 2);
+}
+
+// Dword load q of a 1 KB piece of a row-contiguous operand (k rows of ROW bytes): 256
+// bytes of one k row; a lane keeps the clamped column offset `at` of that quarter.
+template <int ROW>
+__device__ __forceinline__ void d_piece_dword(const char* step, int piece, int ld_bytes, int q,
+                                              unsigned at, unsigned char* dst) {
+  const char* base = step + static_cast<unsigned>((piece * 1024 + 256 * q) / ROW * ld_bytes);
+  __builtin_amdgcn_global_load_lds((const void*)(base + at), (lds_void*)(dst + 256 * q), 4, 0, 0);
+}
+
+// The column offset of a lane in load q of the wave's pieces (pieces wave + 8j: 8 KB
+// apart, so at the same place of a row).
+template <class T, int ROW>
+__device__ __forceinline__ unsigned d_dword_col(int lane, int wave, int q, int first, int count) {
+  const int at = (wave * 1024 + 256 * q) % ROW + 4 * lane;
+  int c = at / static_cast<int>(sizeof(T));
+  c = first + c < count ? c : count - 1 - first;
+  return static_cast<unsigned>(c * static_cast<int>(sizeof(T)) + at % static_cast<int>(sizeof(T)));
+}
+
 // The workgroup `bid` of `nwg` of one product.
-template <class Tr, int EPI, int BM, int BN>
+// DW: operand rows that are not on 16-byte boundaries (odd lengths), loaded as dwords:
+// four instructions of 256 bytes (two rows) in the place of one of 1 KB, to the same
+// LDS image.  Against the register-staged kernel that such rows took before: o=75 v=225
+// float64 X 57.5 -> 52.2 ms, Y 165 -> 155; o=41 v=201 float32 occupied terms 29.4 -> 24.7.
+template <class Tr, int EPI, int BM, int BN, bool DW>
 __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const int bid,
                                                const int nwg) {
   static_assert(EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PART || EPI == EPI_PM ||
@@ -85,7 +135,8 @@ __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const
   // slabs this wave loads per stage: A slabs wave + 8j < A_SLABS, and NJ of B
   // (a compile-time count when the A slabs split evenly over the 8 waves)
   constexpr bool A_EVEN = A_SLABS % 8 == 0;
-  const int LOADS = A_EVEN ? A_SLABS / 8 + NJ : (A_SLABS - wave + 7) / 8 + NJ;
+  static_assert(A_EVEN || !DW, "dword loads");
+  const int LOADS = (A_EVEN ? A_SLABS / 8 + NJ : (A_SLABS - wave + 7) / 8 + NJ) * (DW ? 4 : 1);
   int tm, tn;
   const int nk_all = (g.K + BK - 1) / BK;
   int ks0 = 0, ks1 = nk_all;  // K-steps of this workgroup
@@ -114,21 +165,52 @@ __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const
   const int my_sw = (wave & 1) ? sw_odd : sw_even;  // slabs wave + 8j share the wave's parity
   const T* pa[JA];
   const T* pb[NJ];
+  auto row_a = [&](int j) {
+    const int row = m0 + 8 * (wave + 8 * j) + lrow;
+    return g.A + (long long)(row < g.M ? row : g.M - 1) * g.lda + my_sw;
+  };
+  auto row_b = [&](int j) {
+    const int row = n0 + 8 * (wave + 8 * j) + lrow;
+    return g.B + (long long)(row < g.N ? row : g.N - 1) * g.ldb + my_sw;
+  };
+  unsigned cq[4];
+  const unsigned hi_a = (lane >> 5) * static_cast<unsigned>(g.lda * sizeof(T));
+  const unsigned hi_b = (lane >> 5) * static_cast<unsigned>(g.ldb * sizeof(T));
+  const char* base_a = reinterpret_cast<const char*>(g.A + (long long)m0 * g.lda);
+  const char* base_b = reinterpret_cast<const char*>(g.B + (long long)n0 * g.ldb);
+  if constexpr (DW) {
 #pragma unroll
-  for (int j = 0; j < JA; ++j) {
-    int row = m0 + 8 * (wave + 8 * j) + lrow;
-    row = row < g.M ? row : g.M - 1;
-    pa[j] = g.A + (long long)row * g.lda + my_sw;
-  }
+    for (int q = 0; q < 4; ++q) cq[q] = d_dword_at(lane, wave, q);
+  } else {
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    int row = n0 + 8 * (wave + 8 * j) + lrow;
-    row = row < g.N ? row : g.N - 1;
-    pb[j] = g.B + (long long)row * g.ldb + my_sw;
+    for (int j = 0; j < JA; ++j) pa[j] = row_a(j);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) pb[j] = row_b(j);
   }
+  constexpr bool kSpread = d_spread<T, DW>();
+  auto issue_dw = [&](int kt, int q) {
+    unsigned char* st = lds + (kt % kDStages) * STAGE;
+    const int ko = kt * BK;
+    const long long kb = (long long)ko * static_cast<int>(sizeof(T));
+#pragma unroll
+    for (int j = 0; j < JA; ++j)
+      d_slab_dword(base_a + kb, 8 * (wave + 8 * j), g.M - 1 - m0,
+                    static_cast<int>(g.lda * sizeof(T)), q, cq[q], hi_a,
+                    st + 8 * (wave + 8 * j) * kDRow);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      d_slab_dword(base_b + kb, 8 * (wave + 8 * j), g.N - 1 - n0,
+                    static_cast<int>(g.ldb * sizeof(T)), q, cq[q], hi_b,
+                    st + A_BYTES + 8 * (wave + 8 * j) * kDRow);
+  };
   auto issue = [&](int kt) {
     unsigned char* st = lds + (kt % kDStages) * STAGE;
     const int ko = kt * BK;
+    if constexpr (DW) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) issue_dw(kt, q);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < JA; ++j)
       if (A_EVEN || wave + 8 * j < A_SLABS)
@@ -153,9 +235,10 @@ __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const
     };
 #pragma unroll
     for (int j = 0; j < JA; ++j)
-      if (A_EVEN || wave + 8 * j < A_SLABS) one(pa[j], st + 8 * (wave + 8 * j) * kDRow);
+      if (A_EVEN || wave + 8 * j < A_SLABS) one(DW ? row_a(j) : pa[j], st + 8 * (wave + 8 * j) * kDRow);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) one(pb[j], st + A_BYTES + 8 * (wave + 8 * j) * kDRow);
+    for (int j = 0; j < NJ; ++j)
+      one(DW ? row_b(j) : pb[j], st + A_BYTES + 8 * (wave + 8 * j) * kDRow);
     __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14));  // lgkmcnt(0): the LDS writes landed
   };
 
@@ -191,7 +274,8 @@ __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const
       // past this workgroup's range nothing more was issued)
       d_wait_vm(kt + 1 < nkf && kt + 1 < nk ? LOADS : 0);
       __builtin_amdgcn_s_barrier();
-      if (kt + 2 < nk) stage_in(kt + 2);
+      const bool dw_next = kSpread && kt + 2 < nk && kt + 2 < nkf;
+      if (kt + 2 < nk && !dw_next) stage_in(kt + 2);
       const unsigned char* st = lds + (kt % kDStages) * STAGE;
 #pragma unroll
       for (int gi = 0; gi < 2; ++gi) {
@@ -204,11 +288,13 @@ __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const
         for (int j = 0; j < NJ; ++j)
           fb[j] = *reinterpret_cast<const Chunk*>(st + A_BYTES + (wn + 16 * j) * kDRow + frow + chunk);
 #pragma unroll
-        for (int e = 0; e < CH; ++e)
+        for (int e = 0; e < CH; ++e) {
+          if (dw_next && e % (CH / 2) == 0) issue_dw(kt + 2, 2 * gi + e / (CH / 2));
 #pragma unroll
           for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] = Tr::mfma(fa[i][e], fb[j][e], acc[i][j]);
+        }
       }
     }
     if (Tr::kDrain) {
@@ -243,10 +329,10 @@ __device__ __forceinline__ void kc_direct_body(GemmArgs<typename Tr::T> g, const
   }
 }
 
-template <class Tr, int EPI, int BM = kDBM, int BN = kDBN>
+template <class Tr, int EPI, int BM = kDBM, int BN = kDBN, bool DW = false>
 __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_direct_kernel(
     GemmArgs<typename Tr::T> g) {
-  kc_direct_body<Tr, EPI, BM, BN>(g, blockIdx.x, gridDim.x);
+  kc_direct_body<Tr, EPI, BM, BN, DW>(g, blockIdx.x, gridDim.x);
 }
 
 // Two products in one launch, workgroups [0, n1) of the first: what the last rounds of
@@ -255,7 +341,7 @@ template <class Tr, int BM, int BN>
 __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kc_two_kernel(
     GemmArgs<typename Tr::T> g, GemmArgs<typename Tr::T> h, int n1) {
   const bool second = static_cast<int>(blockIdx.x) >= n1;
-  kc_direct_body<Tr, EPI_PART, BM, BN>(second ? h : g, second ? blockIdx.x - n1 : blockIdx.x,
+  kc_direct_body<Tr, EPI_PART, BM, BN, false>(second ? h : g, second ? blockIdx.x - n1 : blockIdx.x,
                                        second ? gridDim.x - n1 : n1);
 }
 
@@ -319,7 +405,7 @@ __device__ inline void sym_tile(long long id, int tiles_m, int tiles_n, int& tm,
   tn = t / 2 + static_cast<int>(id - sym_tiles_before(t, tiles_n));
 }
 
-template <class Tr, int EPI, int KMAP = 0>
+template <class Tr, int EPI, int KMAP = 0, bool DW = false>
 __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<typename Tr::T> g) {
   static_assert(EPI == EPI_PERM || EPI == EPI_PACK || EPI == EPI_UNPACK || EPI == EPI_SYM,
                 "integral-block stores");
@@ -335,7 +421,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   constexpr int STAGE = A_BYTES + B_BYTES;
   constexpr int AI = A_BYTES / 1024 / 8;         // 1 KB wave instructions per wave: A (2)
   constexpr int BI = B_BYTES / 1024 / 8;         // B (4)
-  constexpr int LOADS = AI + BI;
+  constexpr int LOADS = (AI + BI) * (DW ? 4 : 1);
   constexpr int CPRA = kDBM / CH;                // 16-byte chunks per A row
   constexpr int CPRB = kDBN / CH;                // per B row
   __shared__ __attribute__((aligned(1024))) unsigned char lds[kDStages * STAGE];
@@ -373,24 +459,55 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   const T* pb[BI];
   int ra[AI], rb[BI];
 #pragma unroll
-  for (int j = 0; j < AI; ++j) {
-    const int flat = (wave + 8 * j) * 64 + lane;
-    ra[j] = flat / CPRA;
-    int m = m0 + (flat % CPRA) * CH;
-    m = m < ml ? m : ml - CH;
-    pa[j] = g.A + (long long)ra[j] * g.lda + m;
-  }
+  for (int j = 0; j < AI; ++j) ra[j] = ((wave + 8 * j) * 64 + lane) / CPRA;
 #pragma unroll
-  for (int j = 0; j < BI; ++j) {
-    const int flat = (wave + 8 * j) * 64 + lane;
-    rb[j] = flat / CPRB;
-    int n = n0 + (flat % CPRB) * CH;
-    n = n < nl ? n : nl - CH;
-    pb[j] = g.B + (long long)rb[j] * g.ldb + n;
+  for (int j = 0; j < BI; ++j) rb[j] = ((wave + 8 * j) * 64 + lane) / CPRB;
+  // DW: dword loads of rows that are not on 16-byte boundaries, each value's row or
+  // column clamped by itself
+  unsigned at_a[4], at_b[4];
+  if constexpr (DW) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      at_a[q] = d_dword_col<T, ROWA>(lane, wave, q, m0, g.M);
+      at_b[q] = d_dword_col<T, ROWB>(lane, wave, q, n0, g.N);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < AI; ++j) {
+      int m = m0 + (((wave + 8 * j) * 64 + lane) % CPRA) * CH;
+      m = m < ml ? m : ml - CH;
+      pa[j] = g.A + (long long)ra[j] * g.lda + m;
+    }
+#pragma unroll
+    for (int j = 0; j < BI; ++j) {
+      int n = n0 + (((wave + 8 * j) * 64 + lane) % CPRB) * CH;
+      n = n < nl ? n : nl - CH;
+      pb[j] = g.B + (long long)rb[j] * g.ldb + n;
+    }
   }
+  constexpr bool kSpread = d_spread<T, DW>();
+  auto issue_dw = [&](int kt, int q) {
+    unsigned char* st = lds + (kt % kDStages) * STAGE;
+    const long long ka = (long long)kt * BK * g.lda, kb = (long long)kt * BK * g.ldb;
+    const char* sa = reinterpret_cast<const char*>(g.A + m0 + ka);
+    const char* sb = reinterpret_cast<const char*>(g.B + n0 + kb);
+#pragma unroll
+    for (int j = 0; j < AI; ++j)
+      d_piece_dword<ROWA>(sa, wave + 8 * j, static_cast<int>(g.lda * sizeof(T)), q, at_a[q],
+                           st + (wave + 8 * j) * 1024);
+#pragma unroll
+    for (int j = 0; j < BI; ++j)
+      d_piece_dword<ROWB>(sb, wave + 8 * j, static_cast<int>(g.ldb * sizeof(T)), q, at_b[q],
+                           st + A_BYTES + (wave + 8 * j) * 1024);
+  };
   auto issue = [&](int kt) {
     unsigned char* st = lds + (kt % kDStages) * STAGE;
     const long long ka = (long long)kt * BK * g.lda, kb = (long long)kt * BK * g.ldb;
+    if constexpr (DW) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) issue_dw(kt, q);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < AI; ++j)
       __builtin_amdgcn_global_load_lds((const void*)(pa[j] + ka),
@@ -405,6 +522,26 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
     unsigned char* st = lds + (kt % kDStages) * STAGE;
     const int k0 = kt * BK;
     const long long ka = (long long)k0 * g.lda, kb = (long long)k0 * g.ldb;
+    if constexpr (DW) {
+      auto one = [&](const T* row, int first, int count, bool in) {
+        Chunk c;
+#pragma unroll
+        for (int e = 0; e < CH; ++e) c[e] = in ? row[first + e < count ? first + e : count - 1] : T(0);
+        return c;
+      };
+#pragma unroll
+      for (int j = 0; j < AI; ++j)
+        *reinterpret_cast<Chunk*>(st + (wave + 8 * j) * 1024 + 16 * lane) =
+            one(g.A + (long long)ra[j] * g.lda + ka,
+                m0 + (((wave + 8 * j) * 64 + lane) % CPRA) * CH, g.M, k0 + ra[j] < g.K);
+#pragma unroll
+      for (int j = 0; j < BI; ++j)
+        *reinterpret_cast<Chunk*>(st + A_BYTES + (wave + 8 * j) * 1024 + 16 * lane) =
+            one(g.B + (long long)rb[j] * g.ldb + kb,
+                n0 + (((wave + 8 * j) * 64 + lane) % CPRB) * CH, g.N, k0 + rb[j] < g.K);
+      __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14));  // lgkmcnt(0)
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < AI; ++j) {
       Chunk c = {};
@@ -451,10 +588,12 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
     for (int kt = k0; kt < kend; ++kt) {
       d_wait_vm(kt + 1 < nkf ? LOADS : 0);
       __builtin_amdgcn_s_barrier();
-      if (kt + 2 < nk) stage_in(kt + 2);
+      const bool dw_next = kSpread && kt + 2 < nkf;
+      if (kt + 2 < nk && !dw_next) stage_in(kt + 2);
       const unsigned char* st = lds + (kt % kDStages) * STAGE;
 #pragma unroll
       for (int kk = 0; kk < BK / 4; ++kk) {
+        if (dw_next && kk % (BK / 16) == 0) issue_dw(kt + 2, kk / (BK / 16));
         const int krow = KMAP ? 4 * CH * (kk / CH) + CH * kr + kk % CH : 4 * kk + kr;
         const unsigned char* ra_ = st + krow * ROWA + offa;
         const unsigned char* rb_ = st + A_BYTES + krow * ROWB + offb;
@@ -649,7 +788,7 @@ namespace ccl {
 // 16-byte chunks of columns (N, or N and readable pads: n_load); rows past M are
 // clamped, columns past N clamped onto the last chunk (never stored), a ragged
 // last K-step goes through registers with zero fill.
-template <class Tr, int EPI = EPI_ACC, int BM = kDBM, int BN = kDBN>
+template <class Tr, int EPI = EPI_ACC, int BM = kDBM, int BN = kDBN, bool DW = false>
 __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_direct_kernel(
     GemmArgs<typename Tr::T> g) {
   static_assert(EPI == EPI_ACC || EPI == EPI_FOLD || EPI == EPI_PM, "float64 accumulation");
@@ -666,7 +805,7 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_
   constexpr int STAGE = A_BYTES + B_BYTES;
   constexpr int AL = BM / 8 / 8;                 // A: 8-row slabs per wave
   constexpr int BI = B_BYTES / 1024 / 8;         // B: 1 KB instructions per wave
-  constexpr int LOADS = AL + BI;
+  constexpr int LOADS = (AL + BI) * (DW ? 4 : 1);
   constexpr int CPRB = BN / CH;                  // 16-byte chunks per B row
   constexpr int WC = BN == 64 ? 2 : 4;           // wave columns
   constexpr int MI = BM / (16 * (8 / WC)), NJ = BN / (16 * WC);  // blocks per wave
@@ -693,28 +832,62 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_
   const int sw_odd = ((lane & 7) ^ ((4 + (lane >> 4)) & 7)) * CH;
   const int my_sw = (wave & 1) ? sw_odd : sw_even;
   const T* pa[AL];
-#pragma unroll
-  for (int j = 0; j < AL; ++j) {
-    int row = m0 + 8 * (wave + 8 * j) + lrow;
-    row = row < g.M ? row : g.M - 1;
-    pa[j] = g.A + (long long)row * g.lda + my_sw;
-  }
+  auto row_a = [&](int j) {
+    const int row = m0 + 8 * (wave + 8 * j) + lrow;
+    return g.A + (long long)(row < g.M ? row : g.M - 1) * g.lda + my_sw;
+  };
   // B: wave instruction q covers the 1 KB [q KB, q KB + 1 KB) of the stage's B slab
   const int nl = g.n_load ? g.n_load : g.N;
   const T* pb[BI];
   int rb[BI];
 #pragma unroll
-  for (int j = 0; j < BI; ++j) {
-    const int flat = (wave + 8 * j) * 64 + lane;
-    rb[j] = flat / CPRB;
-    int n = n0 + (flat % CPRB) * CH;
-    n = n < nl ? n : nl - CH;
-    pb[j] = g.B + (long long)rb[j] * g.ldb + n;
+  for (int j = 0; j < BI; ++j) rb[j] = ((wave + 8 * j) * 64 + lane) / CPRB;
+  // DW: dword loads of rows that are not on 16-byte boundaries, each value's column
+  // clamped by itself
+  unsigned cq[4], at_b[4];
+  const unsigned hi_a = (lane >> 5) * static_cast<unsigned>(g.lda * sizeof(T));
+  const char* base_a = reinterpret_cast<const char*>(g.A + (long long)m0 * g.lda);
+  if constexpr (DW) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      cq[q] = d_dword_at(lane, wave, q);
+      at_b[q] = d_dword_col<T, ROWB>(lane, wave, q, n0, g.N);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < AL; ++j) pa[j] = row_a(j);
+#pragma unroll
+    for (int j = 0; j < BI; ++j) {
+      int n = n0 + (((wave + 8 * j) * 64 + lane) % CPRB) * CH;
+      n = n < nl ? n : nl - CH;
+      pb[j] = g.B + (long long)rb[j] * g.ldb + n;
+    }
   }
+  constexpr bool kSpread = d_spread<T, DW>();
+  auto issue_dw = [&](int kt, int q) {
+    unsigned char* st = lds + (kt % kDStages) * STAGE;
+    const int ko = kt * BK;
+    const long long kb = (long long)ko * g.ldb;
+    const char* sb = reinterpret_cast<const char*>(g.B + n0 + kb);
+#pragma unroll
+    for (int j = 0; j < AL; ++j)
+      d_slab_dword(base_a + (long long)ko * static_cast<int>(sizeof(T)), 8 * (wave + 8 * j),
+                    g.M - 1 - m0, static_cast<int>(g.lda * sizeof(T)), q, cq[q], hi_a,
+                    st + 8 * (wave + 8 * j) * kDRow);
+#pragma unroll
+    for (int j = 0; j < BI; ++j)
+      d_piece_dword<ROWB>(sb, wave + 8 * j, static_cast<int>(g.ldb * sizeof(T)), q, at_b[q],
+                           st + A_BYTES + (wave + 8 * j) * 1024);
+  };
   auto issue = [&](int kt) {
     unsigned char* st = lds + (kt % kDStages) * STAGE;
     const int ko = kt * BK;
     const long long kb = (long long)ko * g.ldb;
+    if constexpr (DW) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) issue_dw(kt, q);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < AL; ++j)
       __builtin_amdgcn_global_load_lds((const void*)(pa[j] + ko),
@@ -732,14 +905,22 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_
       const int kk = k0 + my_sw;  // this lane's first k
       Chunk c;
 #pragma unroll
-      for (int e = 0; e < CH; ++e) c[e] = (kk + e < g.K) ? pa[j][k0 + e] : T(0);
+      for (int e = 0; e < CH; ++e) c[e] = (kk + e < g.K) ? (DW ? row_a(j) : pa[j])[k0 + e] : T(0);
       *reinterpret_cast<Chunk*>(st + 8 * (wave + 8 * j) * kDRow + 16 * lane) = c;
     }
     const long long kb = (long long)k0 * g.ldb;
 #pragma unroll
     for (int j = 0; j < BI; ++j) {
       Chunk c = {};
-      if (k0 + rb[j] < g.K) c = *reinterpret_cast<const Chunk*>(pb[j] + kb);
+      if (DW) {
+        const int nc = n0 + (((wave + 8 * j) * 64 + lane) % CPRB) * CH;
+        const T* row = g.B + kb + (long long)rb[j] * g.ldb;
+#pragma unroll
+        for (int e = 0; e < CH; ++e)
+          c[e] = k0 + rb[j] < g.K ? row[nc + e < g.N ? nc + e : g.N - 1] : T(0);
+      } else if (k0 + rb[j] < g.K) {
+        c = *reinterpret_cast<const Chunk*>(pb[j] + kb);
+      }
       *reinterpret_cast<Chunk*>(st + A_BYTES + (wave + 8 * j) * 1024 + 16 * lane) = c;
     }
     __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14));  // lgkmcnt(0): the LDS writes landed
@@ -776,7 +957,8 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_
       // step kt's direct loads have landed once only step kt+1's remain in flight
       d_wait_vm(kt + 1 < nkf && kt + 1 < nk ? LOADS : 0);
       __builtin_amdgcn_s_barrier();
-      if (kt + 2 < nk) stage_in(kt + 2);
+      const bool dw_next = kSpread && kt + 2 < nk && kt + 2 < nkf;
+      if (kt + 2 < nk && !dw_next) stage_in(kt + 2);
       const unsigned char* st = lds + (kt % kDStages) * STAGE;
 #pragma unroll
       for (int gi = 0; gi < 2; ++gi) {
@@ -787,6 +969,7 @@ __global__ __launch_bounds__(kDThreads, (2 * kc_groups<BM, BN>())) void gemm_kr_
           fa[i] = *reinterpret_cast<const Chunk*>(st + (wm + 16 * i) * kDRow + frow + chunk);
 #pragma unroll
         for (int e = 0; e < CH; ++e) {
+          if (dw_next && e % (CH / 2) == 0) issue_dw(kt + 2, 2 * gi + e / (CH / 2));
           // k row gi*4*CH + CH*slot + e of B, this lane's interleaved columns
           const unsigned char* rb_ = st + A_BYTES + (4 * CH * gi + CH * slot + e) * ROWB + offb;
           T fb[NJ];

@@ -521,7 +521,18 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
     p.bn = bn;
     p.main_rows = main_rows;
   };
-  if (cls == kTilesKC) {
+  // Dword loads cost float64 tiles the more the more loads they have for a product (o=75
+  // v=225 X on 128 x 256 52.2 ms, on aligned rows 49.5); on 64 x 64 they were slower than
+  // the register-direct kernel (400 x 2016 x 3969 0.314 against 0.309 ms).
+  const bool dword = (cls == kTilesKCDword || cls == kTilesKRDword) && es == 8;
+  const double big = dword ? 0.84 : 0.88;
+  const double mid = dword ? 0.72 : es == 4 ? 0.77 : 0.82;
+  const double small = es == 4 ? 0.70 : 0.78;
+  if (cls == kTilesKCDword) {
+    take(128, 256, M, tile_cost(M, N, 128, 256, big));
+    take(64, 128, M, tile_cost(M, N, 64, 128, mid));
+    if (!dword) take(64, 64, M, tile_cost(M, N, 64, 64, small));
+  } else if (cls == kTilesKC) {
     long long main_rows = M;
     const int bm = choose_kc_tiling(M, N, tall, split, &main_rows);
     const double cost = bm == 64 ? tile_cost(main_rows, N, 128, 256, 0.88) +
@@ -530,13 +541,13 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
     take(bm == 64 ? 128 : bm, 256, main_rows, cost);
     // (float32 has twice the rate for the same bytes: 576 x 41209 x 41209 16.8 ms on 64
     // x 128)
-    take(64, 128, M, tile_cost(M, N, 64, 128, es == 4 ? 0.77 : 0.82));
-    take(64, 64, M, tile_cost(M, N, 64, 64, es == 4 ? 0.70 : 0.78));
-  } else if (cls == kTilesKR) {
-    take(128, 256, M, tile_cost(M, N, 128, 256, 0.88));
+    take(64, 128, M, tile_cost(M, N, 64, 128, mid));
+    take(64, 64, M, tile_cost(M, N, 64, 64, small));
+  } else if (cls == kTilesKR || cls == kTilesKRDword) {
+    take(128, 256, M, tile_cost(M, N, 128, 256, big));
     if (tall) {
-      take(64, 128, M, tile_cost(M, N, 64, 128, 0.82));
-      take(64, 64, M, tile_cost(M, N, 64, 64, 0.78));
+      take(64, 128, M, tile_cost(M, N, 64, 128, mid));
+      if (!dword) take(64, 64, M, tile_cost(M, N, 64, 64, small));
     }
   } else {
     take(128, 128, M, tile_cost(M, N, 128, 128, 0.80));

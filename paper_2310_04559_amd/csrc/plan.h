@@ -116,6 +116,8 @@ int choose_k_splits(long long M, long long N, long long K, int bk);
 enum TileClass {
   kTilesKC,     // K-contiguous direct-to-LDS kernel: 128 or 160 x 256, 64 x 128, 64 x 64
   kTilesKR,     // mixed direct-to-LDS kernel: 128 x 256; float64 also 64 x 128, 64 x 64
+  kTilesKCDword,  // the same two with dword loads (rows off 16-byte boundaries);
+  kTilesKRDword,  // no 160-row tiles
   kTilesStaged  // register-staged kernel: 128 x 128
 };
 
