@@ -281,7 +281,8 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
                  M, N, K, mt ? mt : M, nt ? nt : N,
                  Tr::kDrain ? (nk + g.drain_steps - 1) / g.drain_steps : nk,
                  sizeof(typename Tr::T), !Tr::kDrain,
-                 EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM || EPI == EPI_FOLD);
+                 EPI == EPI_ACC || EPI == EPI_PAIR || EPI == EPI_PM || EPI == EPI_FOLD,
+                 EPI == EPI_PACK || EPI == EPI_SYM);
   if (pick.side && (LA == KC || M >= 2) && (LB == KC || N >= 2))
     return pick.side == 1 ? launch_wave_side<Tr, LA, LB, EPI, 1>(g, pick.wk, stream)
                           : launch_wave_side<Tr, LA, LB, EPI, 2>(g, pick.wk, stream);

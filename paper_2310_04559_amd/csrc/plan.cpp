@@ -487,13 +487,28 @@ double tile_cost(long long M, long long N, int bm, int bn, double rate) {
   return static_cast<double>((tiles + 255) / 256) * bm * bn / rate;
 }
 
+// Tiles of a launch; of an upper one those with columns n >= their first row m.
+long long tiles_run(long long M, long long N, long long bm, long long bn, bool upper) {
+  const long long tm = (M + bm - 1) / bm, tn = (N + bn - 1) / bn;
+  return upper ? tm * tn - tm * (tm - 1) * bm / (2 * bn) : tm * tn;
+}
+
+// The register-staged kernel: float64 workgroups run two to a compute unit and reach
+// 0.80 so, 0.50 alone (2556 x 2556 x 263 above the diagonal, 210 tiles: 61 us, on the
+// register-direct kernel 54; o=10 v=64 P=230 +- forward 224 -> 206 us, adjoint 524 -> 497).
+double staged_cost(long long M, long long N, int es, bool upper) {
+  const long long rounds = (tiles_run(M, N, 128, 128, upper) + 255) / 256;
+  const long long alone = es == 8 ? rounds % 2 : 0;
+  return 128.0 * 128.0 * (static_cast<double>(rounds - alone) / 0.80 + static_cast<double>(alone) / 0.50);
+}
+
 // The register-direct kernel reaches 0.62 of the rate while its operands stay in
 // the 256 MB last-level cache (400 x 4950 x 4950: 0.40 ms on 32 x 32, 0.49 on 64 x
 // 64 direct-to-LDS tiles) and 0.42 beyond (400 x 16290 x 16290: 6.7 ms against 3.7);
 // a compute unit needs eight waves to cover the latency of their loads.
-double wave_cost(long long M, long long N, double bytes, int side, int wk) {
+double wave_cost(long long M, long long N, double bytes, int side, int wk, bool upper) {
   const long long t = 32 * side;
-  const long long tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
+  const long long tiles = tiles_run(M, N, t, t, upper);
   const long long rounds = (tiles + 255) / 256;
   const long long waves = rounds * side * side * wk;
   const double busy = waves >= 8 ? 1.0 : static_cast<double>(waves) / 8;
@@ -511,7 +526,7 @@ int waves_along_k(long long M, long long N, long long units, int side) {
 }
 
 TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long long units, int es,
-                     bool tall, bool split) {
+                     bool tall, bool split, bool upper = false) {
   TilePick p;
   double best = 0.0;
   auto take = [&](int bm, int bn, long long main_rows, double cost) {
@@ -550,12 +565,12 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
       if (!dword) take(64, 64, M, tile_cost(M, N, 64, 64, small));
     }
   } else {
-    take(128, 128, M, tile_cost(M, N, 128, 128, 0.80));
+    take(128, 128, M, staged_cost(M, N, es, upper));
   }
   const double bytes = (static_cast<double>(M) + static_cast<double>(N)) * K * es;
   for (int side = 2; side >= 1; --side) {
     const int wk = waves_along_k(M, N, units, side);
-    const double cost = wave_cost(M, N, bytes, side, wk);
+    const double cost = wave_cost(M, N, bytes, side, wk, upper);
     if (cost < best) {
       best = cost;
       p.side = side;
@@ -569,12 +584,13 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
 }  // namespace
 
 TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long long mt,
-                    long long nt, long long units, int es, bool tall, bool split) {
-  const TilePick whole = pick_launch(cls, mt, nt, K, units, es, tall, split);
+                    long long nt, long long units, int es, bool tall, bool split,
+                    bool upper) {
+  const TilePick whole = pick_launch(cls, mt, nt, K, units, es, tall, split, upper);
   if (whole.side && whole.wk > 1) return whole;
   // one wave along K or a big tile: the same order of the sums, so the launch's own
   // extents decide
-  return pick_launch(cls, M, N, K, 1, es, tall, split);
+  return pick_launch(cls, M, N, K, 1, es, tall, split, upper);
 }
 
 TilePick pick_part_tiles(long long M, long long N, int splits, long long units, bool direct) {

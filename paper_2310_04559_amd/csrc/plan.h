@@ -134,11 +134,13 @@ struct TilePick {
 // `units` is the number of pieces of K that the waves of the register-direct
 // kernel can share (K-steps; float32: drain chunks), `es` the element size.
 // `tall` (kTilesKC: 160-row tiles; kTilesKR: the 64-row ones) and `split` as in
-// choose_kc_tiling.  wk alone decides the order
+// choose_kc_tiling; `upper`: a packed or symmetric build, tiles on or above the diagonal
+// only.  wk alone decides the order
 // in which an element's sum is formed and depends on the whole output only, so
 // results do not depend on the blocks.
 TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long long mt,
-                    long long nt, long long units, int es, bool tall, bool split);
+                    long long nt, long long units, int es, bool tall, bool split,
+                    bool upper = false);
 
 // The float64 forward folded over the exchange of both virtual pairs, inside the
 // scratch of a plan for the direct forward.  (ac|bd) = (bd|ac) for any vectors, so
