@@ -88,32 +88,43 @@ def mfma_products(form):
 
 
 def executed_flops(form, o, v, P):
-    """(build, contraction) flops a form executes per forward: 2 P v^4 and
-    2 o^2 v^4 in general; packed rows a <= b halve both (the build's (v+1)/(2v));
-    the +- combinations contract o(o+1)/2 rows with the v(v+1)/2 pairs c <= d
-    and o(o-1)/2 rows with the v(v-1)/2 pairs c < d; with symmetric vectors the
-    build is the upper triangle of the pair-pair integral, P n(n+1) for
-    n = v(v+1)/2 pairs."""
+    """(build, contraction) flops a form executes per forward at this workload.
+
+    Nominal: 2 P v^4 and 2 o^2 v^4.  (ac|bd) = (bd|ac) holds for any vectors, so
+    the float64 and split-int8 builds form packed rows a <= b ((v+1)/(2v) of the
+    build) and the float32 one its elements on or above the diagonal.  The float64
+    contraction runs over the +- combinations: o^2 rows (o(o+1)/2 and o(o-1)/2 with
+    pair-symmetric amplitudes) with the v(v+1)/2 pairs c <= d and the v(v-1)/2
+    pairs c < d; the other pair-symmetric forms contract packed rows, split-int8
+    packed rows with t and its swapped copy.  With symmetric vectors the build is
+    the upper triangle of the pair-pair integral, P n(n+1) for n = v(v+1)/2 pairs."""
     v4 = float(v) ** 4
-    sym = FORMS[form][2]
-    if not sym:
-        return 2.0 * P * v4, 2.0 * o * o * v4
-    npk = v * (v + 1) / 2.0
+    prec, _, sym, _ = FORMS[form]
+    npk, nm = v * (v + 1) / 2.0, v * (v - 1) / 2.0
     build = 2.0 * P * v * v * npk
     if sym in ("pmv", "sv"):
         build = P * npk * (npk + 1)  # the pair-pair integral's upper triangle
-    if sym in ("pm", "pmv"):
-        nm = v * (v - 1) / 2.0
+    if sym in ("pm", "pmv") or (sym is True and prec == "fp64"):
         return build, 2.0 * (o * (o + 1) / 2.0 * npk * npk + o * (o - 1) / 2.0 * nm * nm)
-    return build, 2.0 * o * o * v * v * npk
+    if sym:
+        return build, 2.0 * o * o * v * v * npk
+    if prec == "fp64":
+        return build, 2.0 * o * o * (npk * npk + nm * nm)
+    if prec == "split_int8":
+        return build, 4.0 * o * o * v * v * npk
+    if prec == "fp32":
+        return P * v * v * (v * v + 1.0), 2.0 * o * o * v4
+    return 2.0 * P * v4, 2.0 * o * o * v4
 
 
 def executed_fraction(form, v, o=1, P=1):
     """Share of the nominal flops a form executes per forward."""
     b, c = executed_flops(form, o, v, P)
     return (b + c) / (2.0 * (P + o * o) * float(v) ** 4)
+
+
 KERNEL_SRC = [os.path.join(ROOT, "paper_2310_04559_amd", "csrc", f)
-              for f in ("gemm.hpp", "gemm_direct.hpp", "ccladder.hip", "split.hip", "split.hpp",
+              for f in ("gemm.hpp", "gemm_direct.hpp", "gemm_wave.hpp", "ccladder.hip", "split.hip", "split.hpp",
                         "split_i8.hip", "plan.cpp", "plan.h")]
 
 
@@ -308,19 +319,23 @@ def cpu_baseline(inp, target_s=15.0):
                       f"({k}/{v} of its flops, {dt:.1f} s)"}
 
 
-def adjoint_executed_flops(o, v, P, sym, symv, n_a):
-    """Flops the adjoint executes: build 2 P v^4, dt and W 2 o^2 v^4 each, and the
-    two dL terms 2 P v^4 each, or one product of 2 P v^4 when one block holds
-    all of W (its symmetric part gives both terms).  Pair-symmetric: every
-    product over the packed pairs, n = v(v+1)/2 rows instead of v^2 (the dL
-    terms over the half-written W, K ranges b >= a); with symmetric vectors the
-    build is the pair-pair integral's upper triangle, P n(n+1)."""
+def adjoint_executed_flops(o, v, P, prec, sym, symv, n_a):
+    """Flops the adjoint executes with all virtuals in one block (n_a = v).
+    Float64: the build over packed pairs, dt and W over the +- combinations
+    (o^2 rows, or the pairs i <= j and i < j of pair-symmetric t and lam), and one dL
+    product of 2 P v^4.  Float32: half the build and 2 o^2 v^4 for dt and W each,
+    one dL product; pair-symmetric, every product over the packed pairs,
+    n = v(v+1)/2 rows instead of v^2 (the dL terms over the half-written W, K ranges
+    b >= a).  With symmetric vectors the build is the pair-pair integral's upper
+    triangle, P n(n+1).  Several blocks (n_a < v): full build, dt, W and two dL terms."""
     v4 = float(v) ** 4
-    if not sym:
-        dl = 2.0 if n_a == v else 4.0
-        return (2.0 * P + 4.0 * o * o + dl * P) * v4
-    n = v * (v + 1) / 2.0
+    n, m = v * (v + 1) / 2.0, v * (v - 1) / 2.0
     build = P * n * (n + 1) if symv else 2.0 * P * v * v * n
+    if prec == "fp64" and n_a == v:
+        rp, rm = (o * (o + 1) / 2.0, o * (o - 1) / 2.0) if sym else (o * o, o * o)
+        return build + 4.0 * (rp * n * n + rm * m * m) + 2.0 * P * v4
+    if not sym:
+        return ((1.0 if n_a == v else 2.0) * P + 4.0 * o * o + (2.0 if n_a == v else 4.0) * P) * v4
     return build + (4.0 * o * o + 4.0 * P) * v * v * n
 
 
@@ -378,7 +393,7 @@ def bench_adjoint(native, steps, forms=("fp64", "fp32", "fp64_pairsym", "fp32_pa
         e1.record(stream)
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / steps
-        executed = adjoint_executed_flops(o, v, P, sym, symv, n_a)
+        executed = adjoint_executed_flops(o, v, P, form.split("_")[0], sym, symv, n_a)
         res[form] = {"ms_per_step": ms, "tflops": flops / (ms * 1e-3) / 1e12,
                      "tflops_executed": executed / (ms * 1e-3) / 1e12, "a_block": n_a,
                      "rel_err_vs_fp64_gpu": err,
