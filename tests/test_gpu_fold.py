@@ -23,13 +23,16 @@ def _run(native, L, t, R0, **kw):
 
 
 # v from the smallest folded size on, odd and even; the scratch of 30 virtuals
-# (a_block) holds three folded blocks, that of one or seven virtuals none worth it
-@pytest.mark.parametrize("o,v,P,a_block,folded", [(20, 64, 100, 0, True), (9, 71, 263, 0, True),
-                                                  (16, 72, 20, 30, True), (12, 81, 50, 30, True),
-                                                  (9, 71, 60, 1, False), (16, 64, 200, 7, False),
-                                                  (20, 63, 100, 0, False)])
-@pytest.mark.parametrize("exchange", [False, True])
-@pytest.mark.parametrize("pairsym", [False, True])
+# (a_block) holds three folded blocks, that of one or seven virtuals none worth it (the
+# direct route, whose flags are tested with it)
+FOLDED = [(20, 64, 100, 0), (9, 71, 263, 0), (16, 72, 20, 30), (12, 81, 50, 30)]
+DIRECT = [(9, 71, 60, 1), (16, 64, 200, 7), (20, 63, 100, 0)]
+
+
+@pytest.mark.parametrize("o,v,P,a_block,folded,exchange,pairsym",
+                         [(*c, True, x, p) for c in FOLDED for x in (False, True)
+                          for p in (False, True)] +
+                         [(*c, False, False, False) for c in DIRECT])
 def test_folded_forward(gpu_lib, o, v, P, a_block, folded, exchange, pairsym):
     announce("fold", o, v, P, "a_block", a_block, "exchange", exchange, "pairsym", pairsym)
     L, t, _ = random_general(o, v, P, 4000 + o + v)

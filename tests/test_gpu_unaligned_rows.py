@@ -9,11 +9,11 @@ from tests.gpu_common import TOL, announce, dev, host, rel_fro
 
 pytestmark = pytest.mark.gpu
 
-# v^2 = 3969 or 3721 columns and K (one past whole K-steps; o^2 = 441 and 2025 as K of the
-# hole-hole ladder leave 9 of 16): 64 x 128 tiles (o^2 = 400, 441; float32 pairs 64 x 64)
-# and 128 x 256 (1600, 2025, 2116), which do not divide the output
-FORWARD = [(20, 63, 30), (40, 63, 30), (46, 61, 17)]
-HOLE = [(21, 63, 17), (45, 63, 17), (46, 61, 17)]
+# v^2 = 3969 or 3721 columns and K (1 and 9 past whole K-steps; o^2 = 441 and 2025 as K of
+# the hole-hole ladder leave 9 of 16): 64 x 128 tiles (o^2 = 400, 441; float32 pairs 64 x 64)
+# and 128 x 256 (2025, 2116), which do not divide the output
+FORWARD = [(20, 63, 30), (46, 61, 17)]
+HOLE = [(21, 63, 17), (45, 61, 17)]
 
 
 @pytest.mark.parametrize("precision", [0, 1])
