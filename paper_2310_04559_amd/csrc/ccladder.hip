@@ -743,14 +743,15 @@ int pm_rows(const In* X, long long nrows, int n, int a0, int v, Out* plus, long 
 // R: with p = half the sum of the first product's `splits` partials and m = half the
 // second's (0 on a = b, and on i = j where rows are pairs i <= j),
 //   R[i,j,a,b] += p + m, R[i,j,b,a] += p - m   (a < b; R[i,j,a,a] += p)
-// and, for rows i < j of pairs (o > 0), R[j,i,b,a] += p + m, R[j,i,a,b] += p - m.
+// and, for rows i < j of pairs (o > 0), R[j,i,b,a] += p + m, R[j,i,a,b] += p - m.  The
+// partials hold `rows` rows of the first product from r0 on, and of the second from m0.
 // One workgroup per (row, 32 x 32 tile of (a,b) with some a <= b): the partials and
 // R[..][a][b] run along b, the transposed elements along a through LDS, so that all
 // of it is coalesced; R's elements are each touched once.
 __global__ __launch_bounds__(256) void pm_combine_kernel(const double* __restrict__ Pp, long long sp,
                                                          int np, const double* __restrict__ Pm,
                                                          long long sm, int nm, int splits, int rows,
-                                                         int o, int v, int a0, int na,
+                                                         int o, int v, int a0, int na, int r0, int m0,
                                                          double* __restrict__ R) {
   __shared__ double xs[kSwapTile][kSwapTile + 1], ys[kSwapTile][kSwapTile + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -764,12 +765,12 @@ __global__ __launch_bounds__(256) void pm_combine_kernel(const double* __restric
     if (B < A) continue;
     const int as = a0 + A * kSwapTile, bs = a0 + B * kSwapTile;
     int rm = r;
-    long long rij = r, rji = -1;
+    long long rij = r0 + r, rji = -1;
     if (o > 0) {
-      const int i = pair_row(r, o), j = i + static_cast<int>(r - pair_prefix_d(i, o));
+      const int i = pair_row(r0 + r, o), j = i + static_cast<int>(r0 + r - pair_prefix_d(i, o));
       rij = (long long)i * o + j;
       rji = i < j ? (long long)j * o + i : -1;
-      rm = i < j ? static_cast<int>(pair_prefix_d(i, o - 1)) + (j - i - 1) : -1;
+      rm = i < j ? static_cast<int>(pair_prefix_d(i, o - 1)) + (j - i - 1) - m0 : -1;
     }
     double* Rij = R + rij * v2;
     double* Rji = R + rji * v2;
@@ -802,27 +803,36 @@ __global__ __launch_bounds__(256) void pm_combine_kernel(const double* __restric
   }
 }
 
+// Pairs i < j among the first r pairs i <= j of o.
+int strict_pairs_before(int r, int o) {
+  int i = 0;
+  while (i < o && pair_prefix(i + 1, o) <= r) ++i;
+  return r - i - (r > pair_prefix(i, o) ? 1 : 0);
+}
+
 // Both +- contractions of a block, R from T+ V+ and T- V- (rows of all (i,j), or pairs
-// i <= j and i < j when pairs is set).  `part`: scratch that holds nothing any more and
-// takes `max_splits` partials of both products (null: none, whatever the blocks).  With
-// it the two products run in one launch, K split where their grids leave compute units
-// idle, and one coalesced pass adds both to R; without, one after the other into R,
+// i <= j and i < j when pairs is set).  `part`: scratch of `room` doubles that holds
+// nothing any more, for up to `max_splits` partials of both products: a number that
+// depends on the sizes alone, like the ranges of K, so that R does not depend on the
+// blocks; the rows are taken in runs whose partials fit the room.  The two products of a
+// run share a launch, K split where their grids leave compute units idle, and one
+// coalesced pass adds both to R.  max_splits 0: one product after the other into R,
 // whose transposed elements are then scattered read-modify-writes of 8 bytes.
 // o=13 v=97, two blocks: 860 -> 395 us; o=9 v=71: 114 -> 57 us; o=40 v=360 forward: 778 ->
 // 768 ms.
 template <class Tr>
 int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ldp,
                 const typename Tr::T* Tm, const typename Tr::T* Vm, long long ldm, double* R, int o,
-                int v, int a0, int na, bool pairs, double* part, long long max_splits, int drain,
-                hipStream_t s) {
+                int v, int a0, int na, bool pairs, double* part, long long room,
+                long long max_splits, int drain, hipStream_t s) {
   using T = typename Tr::T;
   const long long v2 = (long long)v * v;
   const int kp = static_cast<int>((long long)v * (v + 1) / 2), km = kp - v;
   const int mp = pairs ? o * (o + 1) / 2 : o * o, mm = pairs ? o * (o - 1) / 2 : o * o;
   const int np = static_cast<int>(pair_prefix(a0 + na, v) - pair_prefix(a0, v)), nm = np - na;
-  const PairPick pick =
-      pick_pair_products(PairExtents{mp, kp, mm, km}, PairExtents{mp, np, mm, nm}, kp, sizeof(T),
-                         Tr::kDrain ? drain : 1, part ? max_splits : 0);
+  const PairExtents whole{mp, kp, mm, km};
+  PairPick pick = pick_pair_products(whole, PairExtents{mp, np, mm, nm}, kp, sizeof(T),
+                                     Tr::kDrain ? drain : 1, max_splits);
   if (pick.splits == 0) {
     int rc;
     if (pairs) {
@@ -859,28 +869,41 @@ int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ld
     g.part_stride = (long long)M * N;
     return g;
   };
-  double* Pm = part + (long long)pick.splits * mp * np;
-  const GemmArgs<T> g = args(Tp, Vp, ldp, mp, np, kp, part);
-  const GemmArgs<T> h = args(Tm, Vm, ldm, mm, nm, km, Pm);
-  const long long n1 = (long long)g.tiles_m * g.tiles_n * pick.splits;
-  const long long n2 = mm > 0 && nm > 0 ? (long long)h.tiles_m * h.tiles_n * pick.splits : 0;
-  if (n1 + n2 > 0x7fffffffLL) return CC_LADDER_EINVAL;
-  const dim3 grid(static_cast<unsigned>(n1 + n2)), block(kDThreads);
-  const int in1 = static_cast<int>(n1);
-  if (pick.bn == 64)
-    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 64>), grid, block, 0, s, g, h, in1);
-  else if (pick.bn == 128)
-    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 128>), grid, block, 0, s, g, h, in1);
-  else if (pick.bm == 128)
-    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 128, 256>), grid, block, 0, s, g, h, in1);
-  else if constexpr (!Tr::kDrain)
-    hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 160, 256>), grid, block, 0, s, g, h, in1);
-  const long long ta = (na + kSwapTile - 1) / kSwapTile, tb = (v - a0 + kSwapTile - 1) / kSwapTile;
-  const long long blocks = std::min<long long>(mp * ta * tb, 65536);
-  hipLaunchKernelGGL(pm_combine_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s,
-                     static_cast<const double*>(part), g.part_stride, np,
-                     static_cast<const double*>(Pm), h.part_stride, nm, pick.splits, mp,
-                     pairs ? o : 0, v, a0, na, R);
+  // rows of a run: all, or as many as fit the room
+  const long long splits = pick.splits;
+  long long run = mp;
+  if (splits * ((long long)mp * np + (long long)mm * nm) > room) run = room / (splits * (np + nm));
+  if (run < 1) return CC_LADDER_EINVAL;
+  for (int r0 = 0; r0 < mp; r0 += static_cast<int>(run)) {
+    const int rows = static_cast<int>(mp - r0 < run ? mp - r0 : run);
+    const int m0 = pairs ? strict_pairs_before(r0, o) : r0;
+    const int rows_m = (pairs ? strict_pairs_before(r0 + rows, o) : r0 + rows) - m0;
+    if (rows < mp)
+      pick = pick_pair_products(whole, PairExtents{rows, np, rows_m, nm}, kp, sizeof(T), chunk,
+                                max_splits);
+    double* Pm = part + splits * rows * np;
+    const GemmArgs<T> g = args(Tp + r0 * ldp, Vp, ldp, rows, np, kp, part);
+    const GemmArgs<T> h = args(Tm + m0 * ldm, Vm, ldm, rows_m, nm, km, Pm);
+    const long long n1 = (long long)g.tiles_m * g.tiles_n * splits;
+    const long long n2 = rows_m > 0 && nm > 0 ? (long long)h.tiles_m * h.tiles_n * splits : 0;
+    if (n1 + n2 > 0x7fffffffLL) return CC_LADDER_EINVAL;
+    const dim3 grid(static_cast<unsigned>(n1 + n2)), block(kDThreads);
+    const int in1 = static_cast<int>(n1);
+    if (pick.bn == 64)
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 64>), grid, block, 0, s, g, h, in1);
+    else if (pick.bn == 128)
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 128>), grid, block, 0, s, g, h, in1);
+    else if (pick.bm == 128)
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 128, 256>), grid, block, 0, s, g, h, in1);
+    else if constexpr (!Tr::kDrain)
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 160, 256>), grid, block, 0, s, g, h, in1);
+    const long long ta = (na + kSwapTile - 1) / kSwapTile, tb = (v - a0 + kSwapTile - 1) / kSwapTile;
+    const long long blocks = std::min<long long>(rows * ta * tb, 65536);
+    hipLaunchKernelGGL(pm_combine_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s,
+                       static_cast<const double*>(part), g.part_stride, np,
+                       static_cast<const double*>(Pm), h.part_stride, nm, pick.splits, rows,
+                       pairs ? o : 0, v, a0, na, r0, m0, R);
+  }
   return hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
 }
 
@@ -1423,19 +1446,23 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     tr(CC_LADDER_PHASE_BUILD, blk, 1);
     if (rc) return rc;
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
-    // partial sums in the packed block's room (np rows of v^2, np columns of o^2 rows),
-    // or, after the only block's gather, G's
-    double* part = nullptr;
-    long long bytes = 0;  // per column
-    if (!pl.gsym) {
-      part = reinterpret_cast<double*>(V);
-      bytes = v2 * static_cast<long long>(sizeof(typename Tr::T));
-    } else if (pl.nblocks == 1) {
-      part = reinterpret_cast<double*>(G);
-      bytes = pl.ldg * static_cast<long long>(sizeof(typename Tr::T));
+    // partial sums in the packed block's room (np rows of v^2 values for np columns of
+    // o^2), or, with symmetric vectors, in that of the packed vectors, which G was the last
+    // to need, and after the only block's gather of G too.  As many as the packed block
+    // holds either way; a row of both products has to fit the packed vectors.
+    const long long es = sizeof(typename Tr::T);
+    double* part = reinterpret_cast<double*>(V);
+    long long room = np * v2 * es / 8;
+    long long splits = v2 * es / ((long long)o * o * 8);
+    if (pl.gsym) {
+      part = reinterpret_cast<double*>(const_cast<typename Tr::T*>(Lp));
+      room = P * pl.ldg * es / 8;
+      splits = std::min<long long>(splits, P * es / 16);
+      if (pl.nblocks == 1)
+        room = static_cast<long long>(pl.off_G - pl.off_Lp) / 8 + pl.ldg * pl.ldg * es / 8;
     }
-    rc = pm_products<Tr>(Tp, Vp, pl.ldp, Tm, Vm, pl.ldm, R, o, v, a0, na, true, part,
-                         bytes / ((long long)o * o * 8), drain, s);
+    rc = pm_products<Tr>(Tp, Vp, pl.ldp, Tm, Vm, pl.ldm, R, o, v, a0, na, true, part, room, splits,
+                         drain, s);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }
@@ -1483,7 +1510,7 @@ int forward_fold(const Plan& pl, const FoldPlan& f, const double* L, const doubl
     if (rc) return rc;
     // (the packed block's room takes the partial sums)
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
-    rc = pm_products<TrF64>(Tp, Vp, f.ldp, Tm, Vm, f.ldm, R, o, v, a0, na, pl.pairsym, V,
+    rc = pm_products<TrF64>(Tp, Vp, f.ldp, Tm, Vm, f.ldm, R, o, v, a0, na, pl.pairsym, V, np * v2,
                             v2 / (f.rows_p + f.rows_m), 0, s);
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;

@@ -216,9 +216,9 @@ struct PairPick {
   int bm = 0, bn = 0;
   int splits = 0;  // 0: no room for one partial of each
 };
-// `whole` are the extents over all pairs (a,b), which alone decide the order of the
-// sums (splits), so that results do not depend on the blocks; `block` those of this
-// launch.  kp: contracted pairs c <= d; max_splits: what the scratch holds.
+// `whole` are the extents over all pairs (a,b), which with max_splits, a number of the
+// sizes alone, decide the order of the sums (splits), so that results do not depend on
+// the blocks; `block` those of this launch.  kp: contracted pairs c <= d.
 PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, long long kp, int es,
                             int chunk, long long max_splits);
 
