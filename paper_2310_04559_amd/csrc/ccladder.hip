@@ -1448,8 +1448,8 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
     // partial sums in the packed block's room (np rows of v^2 values for np columns of
     // o^2), or, with symmetric vectors, in that of the packed vectors, which G was the last
-    // to need, and after the only block's gather of G too.  As many as the packed block
-    // holds either way; a row of both products has to fit the packed vectors.
+    // to need, and after the only block's gather of G too: as many as G holds, of which a
+    // row of both products has to fit the packed vectors.
     const long long es = sizeof(typename Tr::T);
     double* part = reinterpret_cast<double*>(V);
     long long room = np * v2 * es / 8;
@@ -1457,7 +1457,7 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     if (pl.gsym) {
       part = reinterpret_cast<double*>(const_cast<typename Tr::T*>(Lp));
       room = P * pl.ldg * es / 8;
-      splits = std::min<long long>(splits, P * es / 16);
+      splits = std::min<long long>(pl.ldg * es / ((long long)o * o * 8), P * es / 16);
       if (pl.nblocks == 1)
         room = static_cast<long long>(pl.off_G - pl.off_Lp) / 8 + pl.ldg * pl.ldg * es / 8;
     }

@@ -3,6 +3,7 @@
 
 #include "split.hpp"
 
+#include <cmath>
 #include <cstdint>
 
 namespace ccl {
@@ -118,12 +119,13 @@ int pair_block_start(int v, int nb, int k) {
   if (k <= 0) return 0;
   if (k >= nb) return v;
   const long long target = (long long)k * ((long long)v * (v + 1) / 2);
-  int lo = 0, hi = v;  // smallest a with pair_prefix(a) * nb >= target
-  while (lo < hi) {
-    const int mid = lo + (hi - lo) / 2;
-    if (pair_prefix(mid, v) * nb >= target) hi = mid; else lo = mid + 1;
-  }
-  return lo;
+  // smallest a with pair_prefix(a) * nb >= target: the root of the quadratic, then exactly
+  const double b = 2.0 * v + 1.0, d = b * b - 8.0 * static_cast<double>(target) / nb;
+  int a = static_cast<int>((b - std::sqrt(d > 0.0 ? d : 0.0)) * 0.5);
+  a = a < 0 ? 0 : (a > v ? v : a);
+  while (a < v && pair_prefix(a, v) * nb < target) ++a;
+  while (a > 0 && pair_prefix(a - 1, v) * nb >= target) --a;
+  return a;
 }
 
 void block_range(const Plan& pl, int blk, int* a0, int* na) {
@@ -136,9 +138,13 @@ void block_range(const Plan& pl, int blk, int* a0, int* na) {
   *na = (pl.v - *a0) < pl.n_a ? (pl.v - *a0) : pl.n_a;
 }
 
+namespace {
+RouteRule route_rule(int o, int v, int P, int precision, int backward, unsigned flags, bool least);
+}  // namespace
+
 int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
                 int slices, int depth, int k_chunk, unsigned flags, Plan* plan, int nb,
-                bool padded) {
+                bool padded, const RouteRule* rule) {
   const int pairsym = (flags & CC_LADDER_PAIR_SYMMETRIC) ? 1 : 0;
   Plan p;
   // packed forward in pair-balanced blocks: the widest block sizes the tile
@@ -307,6 +313,15 @@ int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
     const size_t tiles_m = (rows_m + bm - 1) / bm;
     p.off_tiles = take(&cur, (tiles_m + 1) * sizeof(int));
   }
+  if (!p.gsym) {
+    const RouteRule by_size =
+        rule ? *rule : route_rule(o, v, P, precision, backward, flags, true);
+    if (by_size.pays) {
+      p.fold = 1;
+      const size_t need = by_size.bytes + (p.check_sym ? kAlign : 0);
+      cur = need > cur ? need : cur;
+    }
+  }
   p.bytes = cur;
   *plan = p;
   return CC_LADDER_OK;
@@ -327,6 +342,8 @@ int search_block(int n_max, size_t budget, int fixed, Layout layout, Plan* plan)
   }
   // the footprint grows monotonically with the block size
   Plan best;
+  rc = layout(n_max, plan);
+  if (rc || !budget || plan->bytes <= budget) return rc;
   rc = layout(1, &best);
   if (rc) return rc;
   if (budget && best.bytes > budget) return CC_LADDER_ENOMEM;
@@ -358,7 +375,7 @@ int search_block(int n_max, size_t budget, int fixed, Layout layout, Plan* plan)
 namespace {
 
 int make_plan_flags(int o, int v, int P, int precision, int backward, size_t budget,
-                    const cc_ladder_opts* opts, unsigned flags, Plan* plan) {
+                    const cc_ladder_opts* opts, unsigned flags, const RouteRule& rule, Plan* plan) {
   const int slices = opts ? opts->split_slices : 0;
   const int depth = opts ? opts->split_depth : 0;
   const int k_chunk = opts ? opts->k_chunk : 0;
@@ -369,12 +386,14 @@ int make_plan_flags(int o, int v, int P, int precision, int backward, size_t bud
     // small fraction of the first one's work); the fewest blocks that fit
     auto fits = [&](int nb, Plan* p) {
       const int rc = layout_plan(o, v, P, precision, backward, 0, slices, depth, k_chunk, flags, p,
-                                 nb);
+                                 nb, false, &rule);
       if (rc) return rc;
       return (budget && p->bytes > budget) ? CC_LADDER_ENOMEM : CC_LADDER_OK;
     };
+    int rc = fits(1, plan);
+    if (rc != CC_LADDER_ENOMEM) return rc;
     Plan best;
-    int rc = fits(v, &best);
+    rc = fits(v, &best);
     if (rc) return rc;
     int lo = 1, hi = v;
     while (lo < hi) {
@@ -398,7 +417,8 @@ int make_plan_flags(int o, int v, int P, int precision, int backward, size_t bud
     return CC_LADDER_OK;
   }
   const int rc = search_block(v, budget, fixed, [&](int n_a, Plan* p) {
-    return layout_plan(o, v, P, precision, backward, n_a, slices, depth, k_chunk, flags, p);
+    return layout_plan(o, v, P, precision, backward, n_a, slices, depth, k_chunk, flags, p, 0,
+                       false, &rule);
   }, plan);
   if (rc || precision != CC_LADDER_FP32 || v % 2 == 0) return rc;
   // odd v: padded rows where the same blocks still fit (a plan sized without the
@@ -420,11 +440,22 @@ int make_plan(int o, int v, int P, int precision, int backward, size_t budget,
   rc = check_precision_opts(precision, opts);
   if (rc) return rc;
   const unsigned flags = opts ? opts->flags : 0u;
-  rc = make_plan_flags(o, v, P, precision, backward, budget, opts, flags, plan);
+  RouteRule rule = route_rule(o, v, P, precision, backward, flags, false);
+  if (rule.pays) {
+    // the least scratch of the route counts only where the whole does not fit
+    rc = make_plan_flags(o, v, P, precision, backward, 0, opts, flags, rule, plan);
+    const bool whole = plan->nblocks == 1 && (!budget || plan->bytes <= budget);
+    if (rc || whole) return rc;
+    rule = route_rule(o, v, P, precision, backward, flags, true);
+  }
+  rc = make_plan_flags(o, v, P, precision, backward, budget, opts, flags, rule, plan);
   // the whole pair-pair integral does not fit: the packed blocks instead
-  if (rc == CC_LADDER_ENOMEM && (flags & CC_LADDER_SYMMETRIC_VECTORS))
-    rc = make_plan_flags(o, v, P, precision, backward, budget, opts,
-                         flags & ~CC_LADDER_SYMMETRIC_VECTORS, plan);
+  const unsigned packed = flags & ~CC_LADDER_SYMMETRIC_VECTORS;
+  if (rc == CC_LADDER_ENOMEM && packed != flags)
+    rc = make_plan_flags(o, v, P, precision, backward, budget, opts, packed, rule, plan);
+  // nor do the folded route's fewest buffers: the direct one
+  if (rc == CC_LADDER_ENOMEM && rule.pays)
+    rc = make_plan_flags(o, v, P, precision, backward, budget, opts, packed, RouteRule{}, plan);
   return rc;
 }
 
@@ -646,33 +677,40 @@ PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, 
   const double kPartial = 16.0 * 0.14e12 / 4e12 * (es == 4 ? 2.0 : 1.0);
   const struct { int bm, bn; double rate; } tiles[] = {
       {160, 256, 0.86}, {128, 256, 0.86}, {64, 128, 0.82}, {64, 64, 0.78}};
-  auto best_tile = [&](const PairExtents& e, int s, PairPick* p) {
+  struct Counts { long long n[4]; double values; };
+  auto count = [&](const PairExtents& e) {
+    Counts c{{}, static_cast<double>(e.mp) * e.np + static_cast<double>(e.mm) * e.nm};
+    for (int i = 0; i < 4; ++i)
+      c.n[i] = ((e.mp + tiles[i].bm - 1) / tiles[i].bm) * ((e.np + tiles[i].bn - 1) / tiles[i].bn) +
+               ((e.mm + tiles[i].bm - 1) / tiles[i].bm) * ((e.nm + tiles[i].bn - 1) / tiles[i].bn);
+    return c;
+  };
+  auto best_tile = [&](const Counts& c, int s, PairPick* p) {
     double best = 0.0;
-    for (const auto& t : tiles) {
-      if (t.bm == 160 && es == 4) continue;
-      const long long n = ((e.mp + t.bm - 1) / t.bm) * ((e.np + t.bn - 1) / t.bn) +
-                          ((e.mm + t.bm - 1) / t.bm) * ((e.nm + t.bn - 1) / t.bn);
-      const double cost =
-          static_cast<double>((n * s + 255) / 256) * t.bm * t.bn * steps_of(s) * bk / t.rate;
+    const double steps = static_cast<double>(steps_of(s)) * bk;
+    for (int i = es == 4 ? 1 : 0; i < 4; ++i) {
+      const auto& t = tiles[i];
+      const double cost = static_cast<double>((c.n[i] * s + 255) / 256) * t.bm * t.bn * steps / t.rate;
       if (best == 0.0 || cost < best) {
         best = cost;
         p->bm = t.bm;
         p->bn = t.bn;
       }
     }
-    return best + (static_cast<double>(e.mp) * e.np + static_cast<double>(e.mm) * e.nm) * s * kPartial;
+    return best + c.values * s * kPartial;
   };
+  const Counts all = count(whole);
   double best = 0.0;
   for (int s = 1; s <= 16 && s <= max_splits; ++s) {
     if (s > 1 && (steps_of(s) < 8 || (nk + steps_of(s) - 1) / steps_of(s) != s)) continue;
     PairPick p;
-    const double cost = best_tile(whole, s, &p);
+    const double cost = best_tile(all, s, &p);
     if (pick.splits == 0 || cost < 0.99 * best) {
       best = cost;
       pick.splits = s;
     }
   }
-  best_tile(block, pick.splits, &pick);
+  pick.cost = best_tile(count(block), pick.splits, &pick);
   return pick;
 }
 
@@ -715,46 +753,107 @@ FoldPlan layout_fold(const Plan& pl, int nb) {
 }  // namespace
 
 bool plan_fold(const Plan& pl, FoldPlan* f) {
-  // Below 64 virtuals the extra launches (the combinations and a second product
-  // per block) take what the products save.
-  if (pl.op != kOpLadder || pl.precision != CC_LADDER_FP64 || pl.backward || pl.pm || pl.gsym ||
-      pl.v < 64)
-    return false;
-  const int v = pl.v;
+  if (!pl.fold) return false;
   const size_t room = pl.bytes - (pl.check_sym ? kAlign : 0);  // the same choice with the check
-  if (layout_fold(pl, v).bytes > room) return false;
-  int lo = 1, hi = v;  // the footprint shrinks as the block count grows
+  // the footprint shrinks as the block count grows; most plans hold few blocks
+  int lo = 1, hi = 1;
+  while (hi < pl.v && layout_fold(pl, hi).bytes > room) {
+    lo = hi + 1;
+    hi = 2 * hi < pl.v ? 2 * hi : pl.v;
+  }
   while (lo < hi) {
     const int mid = lo + (hi - lo) / 2;
     if (layout_fold(pl, mid).bytes <= room) hi = mid; else lo = mid + 1;
   }
   *f = layout_fold(pl, lo);
-  // Both routes in multiply-adds of one compute unit at the matrix rate (0.14e12 per
-  // second): builds at the register-staged kernel's share, contractions as tiled,
-  // memory passes at 4 TB/s, launches at 6 us.
-  constexpr double kLaunch = 6e-6 * 0.14e12, kByte = 0.14e12 / 4e12, kBuildRate = 256 * 0.80;
-  const double v2 = static_cast<double>(v) * v;
-  const double pairs = 0.5 * v * (v + 1.0);
-  const long long o2 = (long long)pl.o * pl.o;
-  auto contract = [](long long M, double N, long long K) {
-    const long long n = static_cast<long long>(N + 0.5);
-    if (M <= 0 || n <= 0 || K <= 0) return 0.0;
-    return pick_launch(kTilesKC, M, n, K, (K + 15) / 16, sizeof(double), true, true).cost * K;
-  };
-  double direct, fold;
-  if (pl.pairsym)
-    direct = pairs * v2 * pl.P / kBuildRate +
-             pl.nblocks * (contract(o2, pairs / pl.nblocks, (long long)v * v) + 2 * kLaunch);
-  else
-    direct = v2 * v2 * pl.P / kBuildRate +
-             pl.nblocks * (contract(o2, v2 / pl.nblocks, (long long)v * v) + 2 * kLaunch);
-  // the folded contraction keeps to whole rounds by splitting K: its multiply-adds at
-  // the tiles' share of the rate
-  fold = pairs * v2 * pl.P / kBuildRate +
-         (static_cast<double>(f->rows_p) + 63) * pairs * v2 / (256 * 0.72) +
-         f->nb * 4 * kLaunch + 16.0 * (pairs + f->rows_p) * v2 * kByte + kLaunch;
-  return fold < direct;
+  return f->bytes <= room;
 }
+
+namespace {
+
+// Times of the two float64 forwards in so many equal blocks, in multiply-adds of one
+// compute unit (0.14e12 a second): builds and contractions as they are tiled, or the bytes
+// of the integral where these take longer (memory passes at 4 TB/s), launches at 5 us.  On
+// 440 sizes (o = 1 to 75, v = 48 to 180, P = v / 4 and 3 (o + v), either flag, whole scratch
+// and a fifth) the ratio of the two is within 17% rms of the measured one, which runs from
+// 0.3 (o=2 v=65 pair-symmetric: combining costs more than the small contraction saves) to
+// 1.9 (o=20 v=72); the wrong choice costs 0.8% on average.  Where 2 o^2 > v^2 the scratch
+// holds no partial sums and the folded contraction scatters its results, in more blocks
+// for the larger t+-: o=60 v=64 direct 2.28 ms, folded 2.83; o=46 v=64 1.71 and 1.48.
+constexpr double kLaunch = 5e-6 * 0.14e12, kByte = 0.14e12 / 4e12;
+
+double build_cost(long long rows, long long cols, int P, long long values) {
+  const double build = pick_launch(kTilesStaged, rows, cols, P, (P + 15) / 16, sizeof(double), true,
+                                   false).cost * P;
+  const double write = 8.0 * values * kByte;
+  return build > write ? build : write;
+}
+
+double direct_forward_cost(int o, int v, int P, bool pairs, bool exchange, int blocks) {
+  const long long v2 = (long long)v * v, o2 = (long long)o * o, n = pairs ? (v2 + v) / 2 : v2;
+  const long long nb = (n + blocks - 1) / blocks;
+  const double contract = pick_launch(v % 2 ? kTilesKCDword : kTilesKC, o2, nb, v2, (v2 + 15) / 16,
+                                      sizeof(double), true, true).cost * v2;
+  // (the exchange partner's swapped copy of t; t+- need none)
+  return blocks * (build_cost((v2 + blocks - 1) / blocks, pairs ? v2 / 2 : v2, P, nb * v2) +
+                   contract + (pairs ? 3 : 2) * kLaunch) +
+         (exchange ? kLaunch + 16.0 * o2 * v2 * kByte : 0.0);
+}
+
+double folded_forward_cost(int o, int v, int P, bool pairs, int blocks) {
+  const long long v2 = (long long)v * v, o2 = (long long)o * o, kp = (v2 + v) / 2, km = kp - v;
+  const long long rp = pairs ? (o2 + o) / 2 : o2, rm = pairs ? rp - o : o2;
+  const long long np = (kp + blocks - 1) / blocks, nm = (km + blocks - 1) / blocks;
+  double cost = build_cost((v2 + blocks - 1) / blocks, v2 / 2, P, np * v2) +
+                16.0 * np * v2 * kByte + 3 * kLaunch;
+  const PairPick pick = pick_pair_products(PairExtents{rp, kp, rm, km}, PairExtents{rp, np, rm, nm},
+                                           kp, sizeof(double), 1, v2 / (rp + rm));
+  if (pick.splits)
+    cost += pick.cost + 32.0 * rp * np * kByte + 2 * kLaunch;
+  else
+    cost += pick_launch(kTilesKC, rp, np, kp, (kp + 15) / 16, sizeof(double), true, true).cost * kp +
+            pick_launch(kTilesKC, rm, nm, km, (km + 15) / 16, sizeof(double), true, true).cost * km +
+            128.0 * rp * np * kByte + 2 * kLaunch;
+  return blocks * cost + 16.0 * rp * v2 * kByte + kLaunch;
+}
+
+// `least` false: bytes is what the direct route's whole scratch holds, not the least.
+RouteRule route_rule(int o, int v, int P, int precision, int backward, unsigned flags, bool least) {
+  RouteRule r;
+  // Below 64 virtuals the extra launches take what the products save.
+  if (precision != CC_LADDER_FP64 || backward || (flags & CC_LADDER_PLUS_MINUS) || v < 64) return r;
+  const bool pairs = (flags & CC_LADDER_PAIR_SYMMETRIC) != 0, swap = (flags & CC_LADDER_EXCHANGE) != 0;
+  Plan pl;
+  pl.o = o;
+  pl.v = v;
+  pl.P = P;
+  pl.pairsym = pairs ? 1 : 0;
+  const size_t v2 = static_cast<size_t>(v) * v;
+  const size_t row = v2 * sizeof(double), rows = pairs ? (v2 + v) / 2 : v2;
+  int nb = 1;
+  while (nb <= 32 && nb < v && layout_fold(pl, nb).bytes > rows * row) ++nb;
+  // The faster route in the direct one's whole scratch, and down to the scratch where the
+  // direct one's blocks would be the faster ones (it needs no t+-).
+  for (int blocks = 1; nb <= v; nb = nb == v ? v + 1 : nb + nb / 2 + 1 < v ? nb + nb / 2 + 1 : v) {
+    const size_t bytes = layout_fold(pl, nb).bytes;
+    if (bytes > rows * row) break;
+    if (r.pays) {  // rows of a direct block in the scratch of one folded block less
+      size_t held = (nb > 1 ? layout_fold(pl, nb - 1).bytes : bytes) / row;
+      if (!pairs) held = held / v * v;
+      blocks = held ? static_cast<int>((rows + held - 1) / held) : v;
+      if (blocks < 1) blocks = 1;
+    }
+    // (a tenth more on the way down: the rounds of either grid jump by as much)
+    const double folded = folded_forward_cost(o, v, P, pairs, nb);
+    if (folded >= (r.pays ? 1.1 : 1.0) * direct_forward_cost(o, v, P, pairs, swap, blocks)) break;
+    r.pays = true;
+    r.bytes = bytes;
+    if (!least) break;
+  }
+  return r;
+}
+
+}  // namespace
 
 namespace {
 

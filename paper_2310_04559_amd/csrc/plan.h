@@ -63,16 +63,26 @@ struct Plan {
   int balanced = 0;     // packed forward: nblocks blocks of about equal pair counts (n_a is
                         // then the widest block's virtual count)
   long long npk = 0;    // packed forward: packed rows (a,b) of the block that has the most
+  int fold = 0;         // float64 forward: folded over the exchange of the virtual pairs
   size_t bytes = 0;     // total scratch
 };
 
-// `padded`: row strides of a general float32 plan rounded to 4 elements.
+// Which route the sizes and flags give a forward, and the least scratch with which it is
+// taken: every plan of at least that budget holds it, so that the order of R's sums does
+// not depend on the blocks.
+struct RouteRule {
+  bool pays = false;  // folded rather than direct
+  size_t bytes = 0;
+};
+
+// `padded`: row strides of a general float32 plan rounded to 4 elements.  `rule`: the
+// route (null: by sizes and flags); a plan of a route that pays holds at least its bytes.
 // Fills `plan` for a block size of n_a (1 <= n_a <= v), or, when nb > 0 and the
 // plan is a packed (pair-symmetric) forward, for nb pair-balanced blocks (n_a
 // ignored).  Returns 0, CC_LADDER_EINVAL or CC_LADDER_EUNSUPPORTED.
 int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
                 int slices, int depth, int k_chunk, unsigned flags, Plan* plan, int nb = 0,
-                bool padded = false);
+                bool padded = false, const RouteRule* rule = nullptr);
 
 // Packed integral rows (a,b), a <= b, ordered by a then b: rows of virtuals
 // [0, a) come first.  pair_prefix(a, v) = sum_{a' < a} (v - a').
@@ -143,7 +153,7 @@ TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long l
                     bool upper = false);
 
 // The float64 forward folded over the exchange of both virtual pairs, inside the
-// scratch of a plan for the direct forward.  (ac|bd) = (bd|ac) for any vectors, so
+// scratch of its plan.  (ac|bd) = (bd|ac) for any vectors, so
 // the map t -> R commutes with swapping (c,d) and (a,b) together and splits into its
 // symmetric and antisymmetric parts: with t+- = t[i][j][c][d] +- t[i][j][d][c] and
 // V+-[ab][cd] = (ac|bd) +- (ad|bc),
@@ -158,7 +168,8 @@ struct FoldPlan {
   size_t bytes = 0;
 };
 
-// True when the folded forward fits the plan's scratch and is the faster route.
+// The folded forward's layout in the fewest blocks that the plan's scratch holds; false
+// for a plan of the direct route.
 bool plan_fold(const Plan& pl, FoldPlan* f);
 
 // The split-int8 general forward over the pairs a <= b, inside the scratch of its
@@ -215,6 +226,7 @@ struct PairExtents {
 struct PairPick {
   int bm = 0, bn = 0;
   int splits = 0;  // 0: no room for one partial of each
+  double cost = 0.0;  // time of the block's launch, as TilePick's times K
 };
 // `whole` are the extents over all pairs (a,b), which with max_splits, a number of the
 // sizes alone, decide the order of the sums (splits), so that results do not depend on

@@ -1,0 +1,81 @@
+// Host-only checker of the routes that the planner gives the forwards, built by the CPU
+// test suite with g++ under AddressSanitizer and UndefinedBehaviorSanitizer: the route
+// follows from sizes and flags, never from the blocks or (down to the least scratch that
+// a route needs) from the budget.  Prints "route_check OK" and returns 0 when every check
+// holds.
+#include <cstdio>
+#include <random>
+
+#include "plan.h"
+
+using namespace ccl;
+
+static int g_fail = 0;
+#define CHECK(cond)                                                                     \
+  do {                                                                                  \
+    if (!(cond)) {                                                                      \
+      std::fprintf(stderr, "FAILED %s:%d: %s (o=%d v=%d P=%d flags=%u)\n", __FILE__,    \
+                   __LINE__, #cond, o, v, P, opts.flags);                               \
+      ++g_fail;                                                                         \
+    }                                                                                   \
+  } while (0)
+
+static int route(const Plan& p) {
+  FoldPlan f;
+  return plan_fold(p, &f) ? 1 : 0;
+}
+
+static void float64_forward(std::mt19937_64& rng) {
+  int folded = 0, direct = 0, less = 0;
+  for (int it = 0; it < 1500; ++it) {
+    cc_ladder_opts opts{};
+    const int o = 1 + static_cast<int>(rng() % 76), v = 40 + static_cast<int>(rng() % 260);
+    const int P = 1 + static_cast<int>(rng() % (4 * (o + v)));
+    const unsigned sets[] = {0, CC_LADDER_PAIR_SYMMETRIC, CC_LADDER_EXCHANGE,
+                             CC_LADDER_PAIR_SYMMETRIC | CC_LADDER_EXCHANGE,
+                             CC_LADDER_PAIR_SYMMETRIC | CC_LADDER_CHECK_SYMMETRY};
+    opts.flags = sets[rng() % 5];
+    Plan whole, p;
+    CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, 0, &opts, &whole) == CC_LADDER_OK);
+    const int r = route(whole);
+    r ? ++folded : ++direct;
+    // any block, without a limit
+    for (int k = 0; k < 4; ++k) {
+      opts.a_block = k == 0 ? 1 : 1 + static_cast<int>(rng() % v);
+      CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, 0, &opts, &p) == CC_LADDER_OK);
+      CHECK(route(p) == r);
+    }
+    opts.a_block = 1;
+    CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, 0, &opts, &p) == CC_LADDER_OK);
+    const size_t least = p.bytes;
+    opts.a_block = 0;
+    // any budget from the least on; below it every plan is the direct route's
+    for (int k = 0; k < 6; ++k) {
+      const size_t span = whole.bytes > least ? whole.bytes - least : 0;
+      const size_t budget = k == 0 ? least : least + (span ? rng() % span : 0);
+      CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, budget, &opts, &p) == CC_LADDER_OK);
+      CHECK(p.bytes <= budget && route(p) == r);
+      const size_t under = k == 0 ? least - 1 : 1 + rng() % (least - 1);
+      const int rc = make_plan(o, v, P, CC_LADDER_FP64, 0, under, &opts, &p);
+      CHECK(rc == CC_LADDER_OK || rc == CC_LADDER_ENOMEM);
+      if (!rc) {
+        CHECK(p.bytes <= under && route(p) == 0);
+        ++less;
+      }
+    }
+  }
+  cc_ladder_opts opts{};
+  const int o = 0, v = 0, P = 0;
+  CHECK(folded > 300 && direct > 300 && less > 300);
+}
+
+int main() {
+  std::mt19937_64 rng(4321);
+  float64_forward(rng);
+  if (g_fail) {
+    std::fprintf(stderr, "route_check: %d failures\n", g_fail);
+    return 1;
+  }
+  std::printf("route_check OK\n");
+  return 0;
+}

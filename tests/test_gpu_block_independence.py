@@ -40,3 +40,44 @@ def test_plus_minus_symmetric_vectors(gpu_lib, o, v, P, precision, exchange):
     assert rel_fro(host(one), ref) < TOL[precision]
     for a_block in (v - 1, v // 2, v // 5):
         assert torch.equal(_residual(gpu_lib, Ld, td, precision, a_block=a_block, **kw), one), a_block
+
+
+def _prepares(native, Ld, td, **kw):
+    """Whether the float64 forward prepares amplitudes: the folded route's own phase."""
+    seen = []
+    fn = native.TRACE_FN(lambda user, phase, block, end, stream: seen.append(phase))
+    _residual(native, Ld, td, 0, trace=fn, **kw)
+    return 0 in seen
+
+
+# the float64 forward: folded sizes (46 occupied with 64 virtuals: 2 o^2 > v^2, no room for
+# partial sums) and sizes of the direct route; explicit blocks, and scratch down to the
+# folded route's least, which is what one virtual per block asks for
+@pytest.mark.parametrize("o,v,P,pairsym,folded", [
+    (9, 71, 263, False, True), (20, 64, 100, False, True), (12, 81, 50, False, True),
+    (46, 64, 20, False, True), (46, 72, 30, True, True), (30, 72, 50, True, True),
+    (16, 64, 200, False, False), (12, 100, 300, True, False), (9, 71, 60, False, False)])
+@pytest.mark.parametrize("exchange", [False, True])
+def test_float64_forward(gpu_lib, o, v, P, pairsym, folded, exchange):
+    import torch
+
+    announce("blocks-float64", o, v, P, "pairsym", pairsym, "exchange", exchange)
+    L, t, _ = random_general(o, v, P, 6100 + o + v)
+    if pairsym:
+        t = 0.5 * (t + t.transpose(1, 0, 3, 2))
+    Ld, td = dev(L), dev(t)
+    kw = dict(pair_symmetric=pairsym, exchange=exchange)
+    one = _residual(gpu_lib, Ld, td, 0, **kw)
+    ref = oracle.exchange_forward(L, t) if exchange else oracle.ladder_forward(L, t)
+    assert rel_fro(host(one), ref) < TOL[0]
+    assert exchange or _prepares(gpu_lib, Ld, td, **kw) == folded
+    for a_block in (1, 7, v // 3, v - 1):
+        assert torch.equal(_residual(gpu_lib, Ld, td, 0, a_block=a_block, **kw), one), a_block
+    full, _ = gpu_lib.cc_ladder_workspace_query(o, v, P, 0, opts=gpu_lib.make_opts(**kw))
+    least, _ = gpu_lib.cc_ladder_workspace_query(o, v, P, 0, opts=gpu_lib.make_opts(a_block=1, **kw))
+    for budget in (full - 1, (full + least) // 2, least):
+        assert torch.equal(_residual(gpu_lib, Ld, td, 0, hbm_budget=budget, **kw), one), budget
+    if folded and not exchange:  # less scratch than the folded route needs: the direct one
+        small = _residual(gpu_lib, Ld, td, 0, hbm_budget=least - 1, **kw)
+        assert rel_fro(host(small), ref) < TOL[0]
+        assert not _prepares(gpu_lib, Ld, td, hbm_budget=least - 1, **kw)
