@@ -316,8 +316,8 @@ int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
   if (!p.gsym) {
     const RouteRule by_size =
         rule ? *rule : route_rule(o, v, P, precision, backward, flags, true);
-    if (by_size.pays) {
-      p.fold = 1;
+    if (by_size.blocks) {
+      p.fold = by_size.blocks;
       const size_t need = by_size.bytes + (p.check_sym ? kAlign : 0);
       cur = need > cur ? need : cur;
     }
@@ -441,7 +441,7 @@ int make_plan(int o, int v, int P, int precision, int backward, size_t budget,
   if (rc) return rc;
   const unsigned flags = opts ? opts->flags : 0u;
   RouteRule rule = route_rule(o, v, P, precision, backward, flags, false);
-  if (rule.pays) {
+  if (rule.blocks) {
     // the least scratch of the route counts only where the whole does not fit
     rc = make_plan_flags(o, v, P, precision, backward, 0, opts, flags, rule, plan);
     const bool whole = plan->nblocks == 1 && (!budget || plan->bytes <= budget);
@@ -454,7 +454,7 @@ int make_plan(int o, int v, int P, int precision, int backward, size_t budget,
   if (rc == CC_LADDER_ENOMEM && packed != flags)
     rc = make_plan_flags(o, v, P, precision, backward, budget, opts, packed, rule, plan);
   // nor do the folded route's fewest buffers: the direct one
-  if (rc == CC_LADDER_ENOMEM && rule.pays)
+  if (rc == CC_LADDER_ENOMEM && rule.blocks)
     rc = make_plan_flags(o, v, P, precision, backward, budget, opts, packed, RouteRule{}, plan);
   return rc;
 }
@@ -755,18 +755,19 @@ FoldPlan layout_fold(const Plan& pl, int nb) {
 bool plan_fold(const Plan& pl, FoldPlan* f) {
   if (!pl.fold) return false;
   const size_t room = pl.bytes - (pl.check_sym ? kAlign : 0);  // the same choice with the check
-  // the footprint shrinks as the block count grows; most plans hold few blocks
+  // The fewest blocks that fit (the footprint shrinks, but for the odd pair, as their count
+  // grows; most plans hold few), at most the least scratch's, which do.
   int lo = 1, hi = 1;
-  while (hi < pl.v && layout_fold(pl, hi).bytes > room) {
+  while (hi < pl.fold && layout_fold(pl, hi).bytes > room) {
     lo = hi + 1;
-    hi = 2 * hi < pl.v ? 2 * hi : pl.v;
+    hi = 2 * hi < pl.fold ? 2 * hi : pl.fold;
   }
   while (lo < hi) {
     const int mid = lo + (hi - lo) / 2;
     if (layout_fold(pl, mid).bytes <= room) hi = mid; else lo = mid + 1;
   }
-  *f = layout_fold(pl, lo);
-  return f->bytes <= room;
+  *f = layout_fold(pl, hi);
+  return true;
 }
 
 namespace {
@@ -837,7 +838,7 @@ RouteRule route_rule(int o, int v, int P, int precision, int backward, unsigned 
   for (int blocks = 1; nb <= v; nb = nb == v ? v + 1 : nb + nb / 2 + 1 < v ? nb + nb / 2 + 1 : v) {
     const size_t bytes = layout_fold(pl, nb).bytes;
     if (bytes > rows * row) break;
-    if (r.pays) {  // rows of a direct block in the scratch of one folded block less
+    if (r.blocks) {  // rows of a direct block in the scratch of one folded block less
       size_t held = (nb > 1 ? layout_fold(pl, nb - 1).bytes : bytes) / row;
       if (!pairs) held = held / v * v;
       blocks = held ? static_cast<int>((rows + held - 1) / held) : v;
@@ -845,8 +846,8 @@ RouteRule route_rule(int o, int v, int P, int precision, int backward, unsigned 
     }
     // (a tenth more on the way down: the rounds of either grid jump by as much)
     const double folded = folded_forward_cost(o, v, P, pairs, nb);
-    if (folded >= (r.pays ? 1.1 : 1.0) * direct_forward_cost(o, v, P, pairs, swap, blocks)) break;
-    r.pays = true;
+    if (folded >= (r.blocks ? 1.1 : 1.0) * direct_forward_cost(o, v, P, pairs, swap, blocks)) break;
+    r.blocks = nb;
     r.bytes = bytes;
     if (!least) break;
   }

@@ -63,7 +63,8 @@ struct Plan {
   int balanced = 0;     // packed forward: nblocks blocks of about equal pair counts (n_a is
                         // then the widest block's virtual count)
   long long npk = 0;    // packed forward: packed rows (a,b) of the block that has the most
-  int fold = 0;         // float64 forward: folded over the exchange of the virtual pairs
+  int fold = 0;         // float64 forward folded over the exchange of the virtual pairs: in at
+                        // most so many blocks (0: the direct route)
   size_t bytes = 0;     // total scratch
 };
 
@@ -71,12 +72,12 @@ struct Plan {
 // taken: every plan of at least that budget holds it, so that the order of R's sums does
 // not depend on the blocks.
 struct RouteRule {
-  bool pays = false;  // folded rather than direct
+  int blocks = 0;  // of that least scratch; 0: the direct route
   size_t bytes = 0;
 };
 
 // `padded`: row strides of a general float32 plan rounded to 4 elements.  `rule`: the
-// route (null: by sizes and flags); a plan of a route that pays holds at least its bytes.
+// route (null: by sizes and flags); a plan of the other route holds at least its bytes.
 // Fills `plan` for a block size of n_a (1 <= n_a <= v), or, when nb > 0 and the
 // plan is a packed (pair-symmetric) forward, for nb pair-balanced blocks (n_a
 // ignored).  Returns 0, CC_LADDER_EINVAL or CC_LADDER_EUNSUPPORTED.
