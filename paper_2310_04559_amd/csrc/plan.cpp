@@ -139,7 +139,8 @@ void block_range(const Plan& pl, int blk, int* a0, int* na) {
 }
 
 namespace {
-RouteRule route_rule(int o, int v, int P, int precision, int backward, unsigned flags, bool least);
+RouteRule route_rule(int o, int v, int P, int precision, int backward, int slices, unsigned flags,
+                     bool least);
 }  // namespace
 
 int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
@@ -315,9 +316,9 @@ int layout_plan(int o, int v, int P, int precision, int backward, int n_a,
   }
   if (!p.gsym) {
     const RouteRule by_size =
-        rule ? *rule : route_rule(o, v, P, precision, backward, flags, true);
+        rule ? *rule : route_rule(o, v, P, precision, backward, p.slices, flags, true);
     if (by_size.blocks) {
-      p.fold = by_size.blocks;
+      (precision == CC_LADDER_FP64 ? p.fold : p.stacked) = by_size.blocks;
       const size_t need = by_size.bytes + (p.check_sym ? kAlign : 0);
       cur = need > cur ? need : cur;
     }
@@ -440,13 +441,14 @@ int make_plan(int o, int v, int P, int precision, int backward, size_t budget,
   rc = check_precision_opts(precision, opts);
   if (rc) return rc;
   const unsigned flags = opts ? opts->flags : 0u;
-  RouteRule rule = route_rule(o, v, P, precision, backward, flags, false);
+  const int slices = opts && opts->split_slices ? opts->split_slices : 5;  // (of split-int8)
+  RouteRule rule = route_rule(o, v, P, precision, backward, slices, flags, false);
   if (rule.blocks) {
     // the least scratch of the route counts only where the whole does not fit
     rc = make_plan_flags(o, v, P, precision, backward, 0, opts, flags, rule, plan);
     const bool whole = plan->nblocks == 1 && (!budget || plan->bytes <= budget);
     if (rc || whole) return rc;
-    rule = route_rule(o, v, P, precision, backward, flags, true);
+    rule = route_rule(o, v, P, precision, backward, slices, flags, true);
   }
   rc = make_plan_flags(o, v, P, precision, backward, budget, opts, flags, rule, plan);
   // the whole pair-pair integral does not fit: the packed blocks instead
@@ -818,9 +820,18 @@ double folded_forward_cost(int o, int v, int P, bool pairs, int blocks) {
   return blocks * cost + 16.0 * rp * v2 * kByte + kLaunch;
 }
 
+// The same of the split-int8 forward.  Against the direct route the stacked one has half the
+// build and half the re-cut integral rows, and twice the re-cut t: over o = 2 to 75, v =
+// 64 to 150 it took 0.61 to 0.99 of the direct route's time for v >= 3 o (o=20 v=64 P=16
+// 1.05) and up to 1.47 below (o=60 v=64 1.13 -> 1.52 ms, o=40 v=96 P=24 2.11 -> 2.21), but where
+// its contraction takes fewer rounds of the compute units (o=30 v=65: one for two, 685 -> 488 us).
+RouteRule stacked_rule(int o, int v, int P, int slices, unsigned flags, bool least);
+
 // `least` false: bytes is what the direct route's whole scratch holds, not the least.
-RouteRule route_rule(int o, int v, int P, int precision, int backward, unsigned flags, bool least) {
+RouteRule route_rule(int o, int v, int P, int precision, int backward, int slices, unsigned flags,
+                     bool least) {
   RouteRule r;
+  if (precision == CC_LADDER_SPLIT_INT8 && !backward) return stacked_rule(o, v, P, slices, flags, least);
   // Below 64 virtuals the extra launches take what the products save.
   if (precision != CC_LADDER_FP64 || backward || (flags & CC_LADDER_PLUS_MINUS) || v < 64) return r;
   const bool pairs = (flags & CC_LADDER_PAIR_SYMMETRIC) != 0, swap = (flags & CC_LADDER_EXCHANGE) != 0;
@@ -889,20 +900,62 @@ StackedPlan layout_stacked_i8(const Plan& pl, int nb) {
   return q;
 }
 
+RouteRule stacked_rule(int o, int v, int P, int slices, unsigned flags, bool least) {
+  RouteRule r;
+  if ((flags & CC_LADDER_PAIR_SYMMETRIC) || v < 64) return r;
+  const long long o2 = (long long)o * o, v2 = (long long)v * v;
+  auto rounds = [](long long M, long long N) { return ((M + 127) / 128 * ((N + 127) / 128) + 255) / 256; };
+  if (v < 3 * o && 4 * rounds(2 * o2, (v2 + v) / 2) > 3 * rounds(o2, v2)) return r;
+  Plan pl, one;  // the direct route's whole range and one virtual
+  const RouteRule none;
+  if (layout_plan(o, v, P, CC_LADDER_SPLIT_INT8, 0, v, slices, 0, 0, flags, &pl, 0, false, &none) ||
+      layout_plan(o, v, P, CC_LADDER_SPLIT_INT8, 0, 1, slices, 0, 0, flags, &one, 0, false, &none))
+    return r;
+  const double per = static_cast<double>(pl.bytes - one.bytes) / (v - 1);
+  // as long as it needs at most twice the blocks that the direct route would have in the
+  // same scratch
+  for (int nb = 1; nb <= v; nb = nb == v ? v + 1 : nb + nb / 2 + 1 < v ? nb + nb / 2 + 1 : v) {
+    const size_t bytes = layout_stacked_i8(pl, nb).bytes;
+    if (bytes > pl.bytes) continue;
+    if (r.blocks) {
+      const double held = 1.0 + (static_cast<double>(bytes) - static_cast<double>(one.bytes)) / per;
+      if (held >= 1.0 && nb > 2 * ((v + static_cast<int>(held) - 1) / static_cast<int>(held))) break;
+    }
+    r.blocks = nb;
+    r.bytes = bytes;
+    if (!least) break;
+  }
+  return r;
+}
+
 }  // namespace
 
 bool plan_stacked_i8(const Plan& pl, StackedPlan* q) {
-  // From 64 virtuals on; below, a call is launches rather than digit products.  At
-  // most twice the direct plan's blocks: smaller ones would leave the contraction's
-  // grid short.
-  if (pl.op != kOpLadder || pl.precision != CC_LADDER_SPLIT_INT8 || pl.backward || pl.pairsym ||
-      pl.v < 64)
-    return false;
-  for (int nb = 1; nb <= 2 * pl.nblocks && nb <= pl.v; ++nb) {
-    *q = layout_stacked_i8(pl, nb);
-    if (q->bytes <= pl.bytes) return true;
+  if (!pl.stacked) return false;
+  int nb = 1;
+  while (nb < pl.stacked && layout_stacked_i8(pl, nb).bytes > pl.bytes) ++nb;
+  // One persistent workgroup per compute unit walks a contraction's 128 x 128 tiles: a
+  // block or two more may leave fewer rounds (o=30 v=128 in a third of the whole scratch: 3
+  // blocks of 2 rounds, or 4 of one)
+  auto rounds = [&](int n) {
+    const long long tm = (2LL * pl.o * pl.o + 127) / 128;
+    double sum = 0.05 * n;
+    for (int k = 0; k < n; ++k) {
+      const int a0 = pair_block_start(pl.v, n, k), a1 = pair_block_start(pl.v, n, k + 1);
+      const long long np = pair_prefix(a1, pl.v) - pair_prefix(a0, pl.v);
+      sum += static_cast<double>((tm * ((np + 127) / 128) + 255) / 256);
+    }
+    return sum;
+  };
+  *q = layout_stacked_i8(pl, nb);
+  double best = rounds(nb);
+  for (int n = nb + 1; n <= nb + 3 && n <= pl.stacked; ++n) {
+    const StackedPlan more = layout_stacked_i8(pl, n);
+    if (more.bytes > pl.bytes || rounds(n) >= best) continue;
+    best = rounds(n);
+    *q = more;
   }
-  return false;
+  return true;
 }
 
 bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a) {

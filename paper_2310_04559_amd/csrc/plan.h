@@ -65,6 +65,7 @@ struct Plan {
   long long npk = 0;    // packed forward: packed rows (a,b) of the block that has the most
   int fold = 0;         // float64 forward folded over the exchange of the virtual pairs: in at
                         // most so many blocks (0: the direct route)
+  int stacked = 0;      // split-int8 forward over pairs a <= b, t stacked on its swapped copy: the same
   size_t bytes = 0;     // total scratch
 };
 
@@ -187,7 +188,8 @@ struct StackedPlan {
   size_t off_tiles = 0;
   size_t bytes = 0;
 };
-// True when it fits the plan's scratch (V must also hold the swapped copy of t).
+// Its layout in the blocks that take the fewest rounds of the compute units, from the
+// fewest that the plan's scratch holds on; false for a plan of the direct route.
 bool plan_stacked_i8(const Plan& pl, StackedPlan* q);
 
 // The float64 adjoint folded the same way, inside the scratch of a plan that holds

@@ -20,16 +20,19 @@ static int g_fail = 0;
     }                                                                                   \
   } while (0)
 
-static int route(const Plan& p) {
+static int route(const Plan& p) {  // -1: laid out past the plan's scratch
   FoldPlan f;
-  if (!plan_fold(p, &f)) return 0;
-  return f.bytes <= p.bytes ? 1 : -1;  // -1: laid out past the plan's scratch
+  StackedPlan q;
+  if (plan_fold(p, &f)) return f.bytes <= p.bytes ? 1 : -1;
+  if (plan_stacked_i8(p, &q)) return q.bytes <= p.bytes ? 1 : -1;
+  return 0;
 }
 
-static void float64_forward(std::mt19937_64& rng) {
+static void forward_routes(std::mt19937_64& rng, int precision, int plans) {
   int folded = 0, direct = 0, less = 0;
-  for (int it = 0; it < 1500; ++it) {
+  for (int it = 0; it < plans; ++it) {
     cc_ladder_opts opts{};
+    if (precision == CC_LADDER_SPLIT_INT8) opts.split_slices = it % 3 ? 0 : 4;
     const int o = 1 + static_cast<int>(rng() % 76), v = 40 + static_cast<int>(rng() % 260);
     const int P = 1 + static_cast<int>(rng() % (4 * (o + v)));
     const unsigned sets[] = {0, CC_LADDER_PAIR_SYMMETRIC, CC_LADDER_EXCHANGE,
@@ -37,27 +40,27 @@ static void float64_forward(std::mt19937_64& rng) {
                              CC_LADDER_PAIR_SYMMETRIC | CC_LADDER_CHECK_SYMMETRY};
     opts.flags = sets[rng() % 5];
     Plan whole, p;
-    CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, 0, &opts, &whole) == CC_LADDER_OK);
+    CHECK(make_plan(o, v, P, precision, 0, 0, &opts, &whole) == CC_LADDER_OK);
     const int r = route(whole);
     r ? ++folded : ++direct;
     // any block, without a limit
     for (int k = 0; k < 4; ++k) {
       opts.a_block = k == 0 ? 1 : 1 + static_cast<int>(rng() % v);
-      CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, 0, &opts, &p) == CC_LADDER_OK);
+      CHECK(make_plan(o, v, P, precision, 0, 0, &opts, &p) == CC_LADDER_OK);
       CHECK(route(p) == r);
     }
     opts.a_block = 1;
-    CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, 0, &opts, &p) == CC_LADDER_OK);
+    CHECK(make_plan(o, v, P, precision, 0, 0, &opts, &p) == CC_LADDER_OK);
     const size_t least = p.bytes;
     opts.a_block = 0;
     // any budget from the least on; below it every plan is the direct route's
     for (int k = 0; k < 6; ++k) {
       const size_t span = whole.bytes > least ? whole.bytes - least : 0;
       const size_t budget = k == 0 ? least : least + (span ? rng() % span : 0);
-      CHECK(make_plan(o, v, P, CC_LADDER_FP64, 0, budget, &opts, &p) == CC_LADDER_OK);
+      CHECK(make_plan(o, v, P, precision, 0, budget, &opts, &p) == CC_LADDER_OK);
       CHECK(p.bytes <= budget && route(p) == r);
       const size_t under = k == 0 ? least - 1 : 1 + rng() % (least - 1);
-      const int rc = make_plan(o, v, P, CC_LADDER_FP64, 0, under, &opts, &p);
+      const int rc = make_plan(o, v, P, precision, 0, under, &opts, &p);
       CHECK(rc == CC_LADDER_OK || rc == CC_LADDER_ENOMEM);
       if (!rc) {
         CHECK(p.bytes <= under && route(p) == 0);
@@ -67,12 +70,13 @@ static void float64_forward(std::mt19937_64& rng) {
   }
   cc_ladder_opts opts{};
   const int o = 0, v = 0, P = 0;
-  CHECK(folded > 300 && direct > 300 && less > 300);
+  CHECK(folded > plans / 5 && direct > plans / 5 && less > plans / 5);
 }
 
 int main() {
   std::mt19937_64 rng(4321);
-  float64_forward(rng);
+  forward_routes(rng, CC_LADDER_FP64, 1500);
+  forward_routes(rng, CC_LADDER_SPLIT_INT8, 1000);
   if (g_fail) {
     std::fprintf(stderr, "route_check: %d failures\n", g_fail);
     return 1;

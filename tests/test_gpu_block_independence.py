@@ -81,3 +81,27 @@ def test_float64_forward(gpu_lib, o, v, P, pairsym, folded, exchange):
         small = _residual(gpu_lib, Ld, td, 0, hbm_budget=least - 1, **kw)
         assert rel_fro(host(small), ref) < TOL[0]
         assert not _prepares(gpu_lib, Ld, td, hbm_budget=least - 1, **kw)
+
+
+# split-int8 past one chunk of 16384 contracted indices, which the stacked route's swapped
+# copy of t regroups: the stacked route's sizes (v >= 3 o) and the direct one's
+@pytest.mark.parametrize("o,v,P", [(4, 130, 9), (12, 133, 40), (44, 129, 6)])
+@pytest.mark.parametrize("exchange", [False, True])
+@pytest.mark.parametrize("slices", [4, 5])
+def test_split_int8_forward(gpu_lib, o, v, P, exchange, slices):
+    import torch
+
+    announce("blocks-int8", o, v, P, "exchange", exchange, "slices", slices)
+    L, t, _ = random_general(o, v, P, 6200 + o + v)
+    Ld, td = dev(L), dev(t)
+    kw = dict(exchange=exchange, split_slices=slices)
+    one = _residual(gpu_lib, Ld, td, 3, **kw)
+    for a_block in (1, v // 3, v - 1):
+        assert torch.equal(_residual(gpu_lib, Ld, td, 3, a_block=a_block, **kw), one), a_block
+    full, _ = gpu_lib.cc_ladder_workspace_query(o, v, P, 3, opts=gpu_lib.make_opts(**kw))
+    least, _ = gpu_lib.cc_ladder_workspace_query(o, v, P, 3, opts=gpu_lib.make_opts(a_block=1, **kw))
+    for budget in (full - 1, (full + least) // 2, least):
+        assert torch.equal(_residual(gpu_lib, Ld, td, 3, hbm_budget=budget, **kw), one), budget
+    if o < 20:
+        ref = oracle.exchange_forward(L, t) if exchange else oracle.ladder_forward(L, t)
+        assert rel_fro(host(one), ref) < (4e-8 if slices == 4 else 1e-9)
