@@ -1448,8 +1448,8 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     tr(CC_LADDER_PHASE_CONTRACT, blk, 0);
     // partial sums in the packed block's room (np rows of v^2 values for np columns of
     // o^2), or, with symmetric vectors, in that of the packed vectors, which G was the last
-    // to need, and after the only block's gather of G too: as many as G holds, of which a
-    // row of both products has to fit the packed vectors.
+    // to need, and after the only block's gather of G too: as many as G holds, and as a row
+    // of both products over one virtual's pairs, or a 256th of them all, of the packed vectors.
     const long long es = sizeof(typename Tr::T);
     double* part = reinterpret_cast<double*>(V);
     long long room = np * v2 * es / 8;
@@ -1457,12 +1457,20 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
     if (pl.gsym) {
       part = reinterpret_cast<double*>(const_cast<typename Tr::T*>(Lp));
       room = P * pl.ldg * es / 8;
-      splits = std::min<long long>(pl.ldg * es / ((long long)o * o * 8), P * es / 16);
+      splits = std::min({pl.ldg * es / ((long long)o * o * 8), room / (2 * v), 32 * P * es / ((long long)o * o)});
       if (pl.nblocks == 1)
         room = static_cast<long long>(pl.off_G - pl.off_Lp) / 8 + pl.ldg * pl.ldg * es / 8;
     }
-    rc = pm_products<Tr>(Tp, Vp, pl.ldp, Tm, Vm, pl.ldm, R, o, v, a0, na, true, part, room, splits,
-                         drain, s);
+    for (int c0 = a0; !rc && c0 < a0 + na;) {
+      // the block's virtuals, or (few vectors) as many as leave a row room
+      int nc = a0 + na - c0;
+      auto pairs = [&](int n) { return pair_prefix(c0 + n, v) - pair_prefix(c0, v); };
+      while (nc > 1 && std::min<long long>(splits, kPairSplits) * 2 * pairs(nc) > room) nc = (nc + 1) / 2;
+      const long long before = pair_prefix(c0, v) - pair_prefix(a0, v);
+      rc = pm_products<Tr>(Tp, Vp + before * pl.ldp, pl.ldp, Tm, Vm + (before - (c0 - a0)) * pl.ldm,
+                           pl.ldm, R, o, v, c0, nc, true, part, room, splits, drain, s);
+      c0 += nc;
+    }
     tr(CC_LADDER_PHASE_CONTRACT, blk, 1);
     if (rc) return rc;
   }

@@ -703,7 +703,7 @@ PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, 
   };
   const Counts all = count(whole);
   double best = 0.0;
-  for (int s = 1; s <= 16 && s <= max_splits; ++s) {
+  for (int s = 1; s <= kPairSplits && s <= max_splits; ++s) {
     if (s > 1 && (steps_of(s) < 8 || (nk + steps_of(s) - 1) / steps_of(s) != s)) continue;
     PairPick p;
     const double cost = best_tile(all, s, &p);

@@ -223,6 +223,7 @@ TilePick pick_part_tiles(long long M, long long N, int splits, long long units, 
 // The two products of a +- contraction in one launch of float64 partials that a
 // pass combines into R: K cut into `splits` ranges of whole drain chunks (`chunk`
 // K-steps; 1 in float64), tiles of bm x bn.
+constexpr int kPairSplits = 16;  // at most
 struct PairExtents {
   long long mp = 0, np = 0, mm = 0, nm = 0;  // rows and columns of the + and - products
 };
