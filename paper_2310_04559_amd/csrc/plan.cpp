@@ -537,15 +537,17 @@ double staged_cost(long long M, long long N, int es, bool upper) {
 
 // The register-direct kernel reaches 0.62 of the rate while its operands stay in
 // the 256 MB last-level cache (400 x 4950 x 4950: 0.40 ms on 32 x 32, 0.49 on 64 x
-// 64 direct-to-LDS tiles) and 0.42 beyond (400 x 16290 x 16290: 6.7 ms against 3.7);
+// 64 direct-to-LDS tiles) and 0.42 beyond (400 x 16290 x 16290: 6.7 ms against 3.7), or
+// where float32 rows lie whole multiples of 16 KB apart (`far`), on the same memory channels
+// (1681 x 2624 x 4096: 0.62 ms against 0.40 on 64 x 64 tiles);
 // a compute unit needs eight waves to cover the latency of their loads.
-double wave_cost(long long M, long long N, double bytes, int side, int wk, bool upper) {
+double wave_cost(long long M, long long N, bool far, int side, int wk, bool upper) {
   const long long t = 32 * side;
   const long long tiles = tiles_run(M, N, t, t, upper);
   const long long rounds = (tiles + 255) / 256;
   const long long waves = rounds * side * side * wk;
   const double busy = waves >= 8 ? 1.0 : static_cast<double>(waves) / 8;
-  const double rate = bytes > 256e6 ? 0.42 : 0.62;
+  const double rate = far ? 0.42 : 0.62;
   return static_cast<double>(rounds) * t * t / (rate * busy);
 }
 
@@ -600,10 +602,11 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
   } else {
     take(128, 128, M, staged_cost(M, N, es, upper));
   }
-  const double bytes = (static_cast<double>(M) + static_cast<double>(N)) * K * es;
+  const bool far = (static_cast<double>(M) + static_cast<double>(N)) * K * es > 256e6 ||
+                   (cls == kTilesKC && es == 4 && K % 4096 == 0);
   for (int side = 2; side >= 1; --side) {
     const int wk = waves_along_k(M, N, units, side);
-    const double cost = wave_cost(M, N, bytes, side, wk, upper);
+    const double cost = wave_cost(M, N, far, side, wk, upper);
     if (cost < best) {
       best = cost;
       p.side = side;
