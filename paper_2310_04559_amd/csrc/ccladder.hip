@@ -269,8 +269,8 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
   // rows off 16-byte boundaries: dword loads, in the float64 and float32 accumulations
   // that meet them (odd v); K bands stay with the 128 columns that they are cut by there
   constexpr bool kDW = (kKC && (EPI == EPI_ACC || EPI == EPI_PAIR)) || (kKR && EPI == EPI_ACC);
-  const bool dwords = kDW && !direct && !kband && dword_ok<typename Tr::T>(lda) &&
-                      dword_ok<typename Tr::T>(ldb);
+  bool dwords = kDW && !direct && !kband && dword_ok<typename Tr::T>(lda) &&
+                dword_ok<typename Tr::T>(ldb);
   g.band_cols = direct ? kDBN : kBN;
   const int nk = (K + Tr::BK - 1) / Tr::BK;
   const TilePick pick =
@@ -286,6 +286,7 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
   if (pick.side && (LA == KC || M >= 2) && (LB == KC || N >= 2))
     return pick.side == 1 ? launch_wave_side<Tr, LA, LB, EPI, 1>(g, pick.wk, stream)
                           : launch_wave_side<Tr, LA, LB, EPI, 2>(g, pick.wk, stream);
+  dwords = dwords && !(pick.bm == kBM && pick.bn == kBN);  // the register-staged kernel's tiles
   if constexpr (kKC) {
     if (direct) return launch_kc_direct<Tr, EPI>(g, pick, stream);
     if constexpr (kDW) {
@@ -394,9 +395,12 @@ int launch_contract_split(const typename Tr::T* A, long long lda, const typename
   g.part_stride = (long long)M * N;
   // the whole output (M x nt) decides the waves along K, and with them the order of
   // the sums
-  const TilePick pick = pick_part_tiles(
-      M, nt, S, Tr::kDrain ? (g.split_steps + g.drain_steps - 1) / g.drain_steps : g.split_steps,
-      aligned);
+  const int es = sizeof(typename Tr::T);
+  const auto units = [&](int steps) { return Tr::kDrain ? (steps + g.drain_steps - 1) / g.drain_steps : steps; };
+  const TilePick pick = pick_part_tiles(M, nt, K, S, units(g.split_steps), es, aligned);
+  if (!aligned && !split_pays(pick, M, nt, K, S, units(nk), es))
+    return launch_gemm<Tr, KC, KC, EPI_ACC>(A, lda, B, ldb, C, ldc, M, N, K, 0, drain_steps, stream,
+                                            0, 0, nullptr, 1.0, 0, 0, 0, M, nt);
   g.tiles_m = (M + pick.bm - 1) / pick.bm;
   g.tiles_n = (N + pick.bn - 1) / pick.bn;
   g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;

@@ -350,7 +350,8 @@ struct TileIO {
   __device__ static inline void advance(Cursor& cu) { cu.p += cu.kstep; }
 
   // Whole tile in bounds: one 16-byte load per chunk at the element's alignment
-  // (global vector loads need whole dwords only), so rows of any length take it.
+  // (global vector loads need whole dwords only), so row-contiguous operands of any
+  // row length take it.
   typedef T ChunkU __attribute__((ext_vector_type(CH), aligned(sizeof(T))));
   __device__ static inline void load_full(Chunk (&r)[NCH], const Cursor& cu) {
 #pragma unroll
@@ -442,7 +443,8 @@ __device__ inline void tile_of_banded(int kband, int bid, int nwg, int tiles_m, 
 
 // K loop of one tile.  FAST: the tile lies inside M x N, so every full K-step is
 // one vector load per chunk with no test; only a ragged last K-step is masked.
-// Otherwise every load is masked.
+// Otherwise every load is masked: also for K-contiguous rows off 16-byte boundaries, whose
+// 16-byte loads straddle lines (o=73 v=101 float64 X 10.6 ms so, 10.1 by elements).
 template <class Tr, int LA, int LB, bool FAST>
 __device__ __forceinline__ void tile_mainloop(const GemmArgs<typename Tr::T>& g, int m0, int n0,
                                               int ks0, int ks1,
@@ -610,7 +612,10 @@ __global__ __launch_bounds__(kThreads, Tr::kWaves) void gemm_kernel(GemmArgs<typ
   int ks0, ks1;
   k_band(g, n0, Tr::BK, ks0, ks1);
   const bool interior = (m0 + kBM <= g.M) && (n0 + kBN <= g.N);
-  if (interior)
+  auto aligned = [](const T* p, long long ld) {
+    return (reinterpret_cast<uintptr_t>(p) | static_cast<uintptr_t>(ld * sizeof(T))) % 16 == 0;
+  };
+  if (interior && (LA == RC || aligned(g.A, g.lda)) && (LB == RC || aligned(g.B, g.ldb)))
     tile_mainloop<Tr, LA, LB, true>(g, m0, n0, ks0, ks1, sA[0], sA[1], sB[0], sB[1], acc, acc64);
   else
     tile_mainloop<Tr, LA, LB, false>(g, m0, n0, ks0, ks1, sA[0], sA[1], sB[0], sB[1], acc, acc64);

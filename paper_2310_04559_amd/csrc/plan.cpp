@@ -527,27 +527,40 @@ long long tiles_run(long long M, long long N, long long bm, long long bn, bool u
 }
 
 // The register-staged kernel: float64 workgroups run two to a compute unit and reach
-// 0.80 so, 0.50 alone (2556 x 2556 x 263 above the diagonal, 210 tiles: 61 us, on the
-// register-direct kernel 54; o=10 v=64 P=230 +- forward 224 -> 206 us, adjoint 524 -> 497).
-double staged_cost(long long M, long long N, int es, bool upper) {
+// 0.80 (0.84 over a long K), an odd one alone 0.70 over a long K (1936 x 1936 x 22201, one
+// round: 3.6 ms) but 0.50 over a short one, which is filling and stores (2556 x 2556 x 263
+// above the diagonal, 210 tiles: 61 us, on the register-direct kernel 54; o=10 v=64 P=230 +-
+// forward 224 -> 206 us, adjoint 524 -> 497).
+double staged_cost(long long M, long long N, long long K, int es, bool upper) {
   const long long rounds = (tiles_run(M, N, 128, 128, upper) + 255) / 256;
   const long long alone = es == 8 ? rounds % 2 : 0;
-  return 128.0 * 128.0 * (static_cast<double>(rounds - alone) / 0.80 + static_cast<double>(alone) / 0.50);
+  const bool deep = es == 8 && K >= 1024;
+  return 128.0 * 128.0 * (static_cast<double>(rounds - alone) / (deep ? 0.84 : 0.80) +
+                          static_cast<double>(alone) / (deep ? 0.70 : 0.50));
 }
 
 // The register-direct kernel reaches 0.62 of the rate while its operands stay in
 // the 256 MB last-level cache (400 x 4950 x 4950: 0.40 ms on 32 x 32, 0.49 on 64 x
 // 64 direct-to-LDS tiles) and 0.42 beyond (400 x 16290 x 16290: 6.7 ms against 3.7), or
-// where float32 rows lie whole multiples of 16 KB apart (`far`), on the same memory channels
-// (1681 x 2624 x 4096: 0.62 ms against 0.40 on 64 x 64 tiles);
-// a compute unit needs eight waves to cover the latency of their loads.
-double wave_cost(long long M, long long N, bool far, int side, int wk, bool upper) {
+// where float32 rows lie whole multiples of 16 KB apart, on the same memory channels
+// (1681 x 2624 x 4096: 0.62 ms against 0.40 on 64 x 64 tiles).  Float64 rows off 16-byte
+// boundaries: K-contiguous and both sides over 1024 0.55, from 128 MB on 0.50 (3249 x 3249 x
+// 4489: 2.61 ms, 1.84 on 64 x 128 tiles), with row-contiguous columns 0.70.
+enum { kRowsAligned, kRowsOddKC, kRowsOddKR };
+double wave_rate(long long M, long long N, long long K, int es, int rows, bool channels) {
+  const double bytes = (static_cast<double>(M) + static_cast<double>(N)) * K * es;
+  if (bytes > 256e6 || channels) return 0.42;
+  if (rows == kRowsOddKC && M > 1024 && N > 1024) return bytes > 128e6 ? 0.50 : 0.55;
+  return rows == kRowsOddKR ? 0.70 : 0.62;
+}
+
+// A compute unit needs eight waves to cover the latency of their loads.
+double wave_cost(long long M, long long N, double rate, int side, int wk, bool upper) {
   const long long t = 32 * side;
   const long long tiles = tiles_run(M, N, t, t, upper);
   const long long rounds = (tiles + 255) / 256;
   const long long waves = rounds * side * side * wk;
   const double busy = waves >= 8 ? 1.0 : static_cast<double>(waves) / 8;
-  const double rate = far ? 0.42 : 0.62;
   return static_cast<double>(rounds) * t * t / (rate * busy);
 }
 
@@ -571,17 +584,24 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
     p.bn = bn;
     p.main_rows = main_rows;
   };
-  // Dword loads cost float64 tiles the more the more loads they have for a product (o=75
-  // v=225 X on 128 x 256 52.2 ms, on aligned rows 49.5); on 64 x 64 they were slower than
-  // the register-direct kernel (400 x 2016 x 3969 0.314 against 0.309 ms).
+  // Dword loads, float64 (o = 38 to 76, v = 51 to 229, K from 2600 on): X on 128 x 256 tiles
+  // 0.88 to 0.92, on 64 x 128 0.84 to 0.87 (4900 x 4900 x 12321: 12.6 ms in 3.05 rounds, 10.0 in
+  // 11.7, the register-staged kernel 10.1), the hole-hole ladder 0.86 to 0.89, 0.82 to 0.84 and
+  // there 0.81 to 0.94 (3600 x 7569 x 3600: 3.86, 3.54 and 3.30 ms), less over a shorter K
+  // (900: 0.71, 0.73; the register-direct kernel 0.70 to 0.78); 64 x 64 tiles were slower
+  // than the register-direct kernel (400 x 2016 x 3969 0.314 against 0.309 ms).
   const bool dword = (cls == kTilesKCDword || cls == kTilesKRDword) && es == 8;
-  const double big = dword ? 0.84 : 0.88;
-  const double mid = dword ? 0.72 : es == 4 ? 0.77 : 0.82;
+  const bool kr = cls == kTilesKRDword, shallow = dword && kr && K < 2048;
+  const double big = shallow ? 0.76 : dword && !kr ? 0.90 : 0.88;
+  const double mid = shallow ? 0.74 : dword ? (kr ? 0.82 : 0.85) : es == 4 ? 0.77 : 0.82;
   const double small = es == 4 ? 0.70 : 0.78;
   if (cls == kTilesKCDword) {
     take(128, 256, M, tile_cost(M, N, 128, 256, big));
-    take(64, 128, M, tile_cost(M, N, 64, 128, mid));
+    // (a single round of them 0.66 to 0.78)
+    const bool one = dword && ((M + 63) / 64) * ((N + 127) / 128) <= 256;
+    take(64, 128, M, tile_cost(M, N, 64, 128, one ? 0.75 : mid));
     if (!dword) take(64, 64, M, tile_cost(M, N, 64, 64, small));
+    if (dword) take(128, 128, M, staged_cost(M, N, K, es, false));
   } else if (cls == kTilesKC) {
     long long main_rows = M;
     const int bm = choose_kc_tiling(M, N, tall, split, &main_rows);
@@ -598,15 +618,16 @@ TilePick pick_launch(TileClass cls, long long M, long long N, long long K, long 
     if (tall) {
       take(64, 128, M, tile_cost(M, N, 64, 128, mid));
       if (!dword) take(64, 64, M, tile_cost(M, N, 64, 64, small));
+      if (dword) take(128, 128, M, staged_cost(M, N, K, es, false));
     }
   } else {
-    take(128, 128, M, staged_cost(M, N, es, upper));
+    take(128, 128, M, staged_cost(M, N, K, es, upper));
   }
-  const bool far = (static_cast<double>(M) + static_cast<double>(N)) * K * es > 256e6 ||
-                   (cls == kTilesKC && es == 4 && K % 4096 == 0);
+  const double rate = wave_rate(M, N, K, es, !dword ? kRowsAligned : kr ? kRowsOddKR : kRowsOddKC,
+                                cls == kTilesKC && es == 4 && K % 4096 == 0);
   for (int side = 2; side >= 1; --side) {
     const int wk = waves_along_k(M, N, units, side);
-    const double cost = wave_cost(M, N, far, side, wk, upper);
+    const double cost = wave_cost(M, N, rate, side, wk, upper);
     if (cost < best) {
       best = cost;
       p.side = side;
@@ -629,7 +650,8 @@ TilePick pick_tiles(TileClass cls, long long M, long long N, long long K, long l
   return pick_launch(cls, M, N, K, 1, es, tall, split, upper);
 }
 
-TilePick pick_part_tiles(long long M, long long N, int splits, long long units, bool direct) {
+TilePick pick_part_tiles(long long M, long long N, long long K, int splits, long long units, int es,
+                         bool direct) {
   TilePick p;
   p.main_rows = M;
   double best = 0.0;
@@ -650,13 +672,14 @@ TilePick pick_part_tiles(long long M, long long N, int splits, long long units, 
     take(64, 128, 0.78);
     take(64, 64, 0.76);
   }
+  const double rate = wave_rate(M, N, K, es, !direct && es == 8 ? kRowsOddKC : kRowsAligned, false);
   for (int side = 2; side >= 1; --side) {
     const int t = 32 * side;
     const double r = rounds(t, t);
     int wk = 1;
     while (2 * wk * side * side <= 16 && units >= 4LL * wk && r * wk * side * side < 8) wk *= 2;
     const double busy = r * wk * side * side >= 8 ? 1.0 : r * wk * side * side / 8;
-    const double cost = r * t * t / (0.62 * busy);
+    const double cost = r * t * t / (rate * busy);
     if (p.bm && cost >= best) continue;
     best = cost;
     p.bm = p.bn = t;
@@ -665,6 +688,16 @@ TilePick pick_part_tiles(long long M, long long N, int splits, long long units, 
   }
   p.cost = best;
   return p;
+}
+
+bool split_pays(const TilePick& part, long long M, long long N, long long K, int splits,
+                long long units, int es) {
+  const TilePick whole = pick_launch(kTilesKCDword, M, N, K, units, es, es == 8, true);
+  // a partial is written and read (16 bytes at 4 TB/s)
+  const double sums = 16.0 * splits * M * N * 0.14e12 / 4e12 * (es == 4 ? 2.0 : 1.0);
+  // (about equal: the ranges, whose workgroups are spread over more compute units, o=6 v=99
+  // float32 X 81 against 97 us)
+  return part.cost * K / splits + sums < 1.1 * whole.cost * K;
 }
 
 PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, long long kp, int es,

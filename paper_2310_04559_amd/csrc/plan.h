@@ -128,8 +128,8 @@ int choose_k_splits(long long M, long long N, long long K, int bk);
 enum TileClass {
   kTilesKC,     // K-contiguous direct-to-LDS kernel: 128 or 160 x 256, 64 x 128, 64 x 64
   kTilesKR,     // mixed direct-to-LDS kernel: 128 x 256; float64 also 64 x 128, 64 x 64
-  kTilesKCDword,  // the same two with dword loads (rows off 16-byte boundaries);
-  kTilesKRDword,  // no 160-row tiles
+  kTilesKCDword,  // the same two with dword loads (rows off 16-byte boundaries); no 160-row
+  kTilesKRDword,  // tiles, float64 also the register-staged kernel's (128 x 128)
   kTilesStaged  // register-staged kernel: 128 x 128
 };
 
@@ -217,8 +217,14 @@ bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a);
 // The cut of a split-K product of M x N partials over `splits` ranges of `units`
 // pieces of K each (as in pick_tiles): the tiles of the K-contiguous direct kernel when
 // `direct`, else (or where it is faster) the register-direct kernel, whose waves along
-// K divide a range.  Depends on the whole output only.
-TilePick pick_part_tiles(long long M, long long N, int splits, long long units, bool direct);
+// K divide a range (K: the whole contracted length).  Depends on the whole output only.
+TilePick pick_part_tiles(long long M, long long N, long long K, int splits, long long units, int es,
+                         bool direct);
+
+// Whether those partials, and their sum, take less time than the product in one piece on
+// rows off 16-byte boundaries, whose partials run on the register-direct kernel only.
+bool split_pays(const TilePick& part, long long M, long long N, long long K, int splits,
+                long long units, int es);
 
 // The two products of a +- contraction in one launch of float64 partials that a
 // pass combines into R: K cut into `splits` ranges of whole drain chunks (`chunk`
