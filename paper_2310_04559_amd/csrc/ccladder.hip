@@ -470,7 +470,10 @@ int to_f32_rows(const double* x, float* y, long long rows, long long n, long lon
 }
 
 // y[m][d][c] = x[m][c][d] for o^2 matrices m of v x v, through a 32 x 32 LDS
-// tile so that both the read and the write of a tile row are coalesced.  One
+// tile so that both the read and the write of a tile row are coalesced.  Tiles go to the
+// XCDs in turn: in contiguous runs (as the +- passes) the swap of o=30 v=160 took 76 us
+// instead of 57, the mirrored sum 142 for 107 and the symmetric one of v=130 0.79 ms for
+// 0.65; odd v, whose tiles share lines, gained 5 to 14%.  One
 // workgroup per (matrix, tile) pair, grid-stride.  Out is double or float
 // (the float32 form swaps while converting, round to nearest even).
 constexpr int kSwapTile = 32;
@@ -483,7 +486,7 @@ __global__ __launch_bounds__(256) void swap_cd_kernel(const double* __restrict__
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 8 rows of 32 lanes
   const long long per_mat = (long long)tiles * tiles;
   const long long v2 = (long long)v * v;
-  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < nmat * per_mat; w += gridDim.x) {
+  for (long long w = blockIdx.x; w < nmat * per_mat; w += gridDim.x) {
     const long long m = w / per_mat;
     const int r = static_cast<int>(w - m * per_mat);
     const int c0 = (r / tiles) * kSwapTile, d0 = (r % tiles) * kSwapTile;
@@ -578,7 +581,7 @@ __global__ __launch_bounds__(256) void mirror_add_kernel(const double* __restric
   const long long per_mat = (long long)tiles * tiles;
   const long long nmat = (long long)o * o;
   const long long v2 = (long long)v * v;
-  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < nmat * per_mat; w += gridDim.x) {
+  for (long long w = blockIdx.x; w < nmat * per_mat; w += gridDim.x) {
     const long long m = w / per_mat;
     const int i = static_cast<int>(m / o), j = static_cast<int>(m - (long long)i * o);
     const long long mp = (long long)j * o + i;
@@ -612,7 +615,7 @@ __global__ __launch_bounds__(256) void sym_add_kernel(T* __restrict__ W, long lo
   __shared__ double a[kSwapTile][kSwapTile + 1], b[kSwapTile][kSwapTile + 1];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const long long npairs = (long long)tiles * (tiles + 1) / 2;
-  for (long long w = xcd_linear(blockIdx.x, gridDim.x); w < npairs; w += gridDim.x) {
+  for (long long w = blockIdx.x; w < npairs; w += gridDim.x) {
     const int P = pair_row(w, tiles);
     const int Q = P + static_cast<int>(w - pair_prefix_d(P, tiles));
     const long long p0 = (long long)P * kSwapTile, q0 = (long long)Q * kSwapTile;
