@@ -137,16 +137,13 @@ __global__ void pack_rows_kernel(int* row_tiles, int tiles_m, int tiles_n, int v
 
 // Integral builds (both operands row-contiguous, permuted or packed store) take
 // the direct-to-LDS RC kernel when rows are whole 16-byte chunks and aligned; DW: other
-// rows, by dword loads, with the sums of the register-staged kernel (KMAP 1).
-template <class Tr, int EPI, bool DW = false>
+// rows, by dword loads, with the sums of the register-staged kernel (KMAP 1).  PADS: rows
+// that end in a part of a 16-byte chunk, with readable pads, and the same sums.
+template <class Tr, int EPI, bool DW = false, bool PADS = false>
 bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, int* rc) {
   if (g0.K <= 0 || (!DW && (!vec_ok(g0.A, g0.lda) || !vec_ok(g0.B, g0.ldb)))) return false;
-  // rows that end in a part of a 16-byte chunk: readable pads, and the order of k that
-  // these products have on the register-staged kernel
-  const bool whole = g0.M % Tr::CH == 0 && g0.N % Tr::CH == 0;
-  if (!DW && !whole && (EPI != EPI_PERM || !g0.m_load || g0.m_load % Tr::CH || !g0.n_load ||
-                 g0.n_load % Tr::CH))
-    return false;
+  if (!DW && !PADS && (g0.M % Tr::CH || g0.N % Tr::CH)) return false;
+  if (PADS && (!g0.m_load || g0.m_load % Tr::CH || !g0.n_load || g0.n_load % Tr::CH)) return false;
   GemmArgs<typename Tr::T> g = g0;
   g.tiles_m = (g.M + kDBM - 1) / kDBM;
   g.tiles_n = (g.N + kDBN - 1) / kDBN;
@@ -169,19 +166,11 @@ bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, in
     grid = needed;
   }
   if (EPI == EPI_PERM && g.sym) grid = sym_tiles_before(g.tiles_m, g.tiles_n);
-  if constexpr (DW) {
-    hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI, 1, true>), dim3(static_cast<unsigned>(grid)),
+  if constexpr (DW || PADS) {
+    hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI, 1, DW>), dim3(static_cast<unsigned>(grid)),
                        dim3(kDThreads), 0, stream, g);
     *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
     return true;
-  }
-  if constexpr (EPI == EPI_PERM) {
-    if (!whole) {
-      hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI, 1>), dim3(static_cast<unsigned>(grid)),
-                         dim3(kDThreads), 0, stream, g);
-      *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
-      return true;
-    }
   }
   hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI>), dim3(static_cast<unsigned>(grid)),
                      dim3(kDThreads), 0, stream, g);
@@ -273,8 +262,13 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
                 dword_ok<typename Tr::T>(ldb);
   g.band_cols = direct ? kDBN : kBN;
   const int nk = (K + Tr::BK - 1) / Tr::BK;
+  // builds that end in a part of a 16-byte chunk run on the direct kernel's 128 x 256 tiles
+  // (pads or dword loads), where these are not a long serial loop of a few workgroups (W of
+  // o=75 v=7 float32, 49 x 49 x 5625: 320 us, 24 on the register-direct kernel)
+  constexpr bool kRC = LA == RC && LB == RC && EPI == EPI_PERM && Tr::kDirectRC;
   const TilePick pick =
       pick_tiles(dwords    ? (kKC ? kTilesKCDword : kTilesKRDword)
+                 : kRC     ? kTilesKR
                  : !direct ? kTilesStaged
                  : kKC     ? kTilesKC
                            : kTilesKR,
@@ -296,6 +290,10 @@ int launch_gemm(const typename Tr::T* A, long long lda, const typename Tr::T* B,
   if constexpr (LA == RC && LB == RC && (EPI == EPI_PERM || EPI == EPI_PACK) && Tr::kDirectRC) {
     // builds from rows off 16-byte boundaries: dword loads, the order of k of the
     // register-staged kernel
+    if constexpr (kRC) {
+      int rc = CC_LADDER_OK;
+      if (launch_rc_direct<Tr, EPI, false, true>(g, stream, &rc)) return rc;
+    }
     if (dword_ok<typename Tr::T>(lda) && dword_ok<typename Tr::T>(ldb)) {
       int rc = CC_LADDER_OK;
       if (launch_rc_direct<Tr, EPI, true>(g, stream, &rc)) return rc;
