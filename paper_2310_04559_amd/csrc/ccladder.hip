@@ -165,15 +165,20 @@ bool launch_rc_direct(const GemmArgs<typename Tr::T>& g0, hipStream_t stream, in
                        const_cast<int*>(g.row_tiles), g.tiles_m, g.tiles_n, g.v, kDBM, kDBN);
     grid = needed;
   }
-  if (EPI == EPI_PERM && g.sym) grid = sym_tiles_before(g.tiles_m, g.tiles_n);
-  if constexpr (DW || PADS) {
-    hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI, 1, DW>), dim3(static_cast<unsigned>(grid)),
-                       dim3(kDThreads), 0, stream, g);
-    *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
-    return true;
+  constexpr int kMap = DW || PADS ? 1 : 0;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(grid)), dim3(kDThreads), 0, stream, g);
+  };
+  if constexpr (EPI == EPI_PERM) {
+    if (g.sym) {
+      grid = sym_tiles_before(g.tiles_m, g.tiles_n);
+      launch(gemm_rc_direct_kernel<Tr, EPI, kMap, DW, true>);
+    } else {
+      launch(gemm_rc_direct_kernel<Tr, EPI, kMap, DW>);
+    }
+  } else {
+    launch(gemm_rc_direct_kernel<Tr, EPI, kMap, DW>);
   }
-  hipLaunchKernelGGL((gemm_rc_direct_kernel<Tr, EPI>), dim3(static_cast<unsigned>(grid)),
-                     dim3(kDThreads), 0, stream, g);
   *rc = hipGetLastError() == hipSuccess ? CC_LADDER_OK : CC_LADDER_EHIP;
   return true;
 }

@@ -354,14 +354,14 @@ namespace ccl {
 //
 //   C = perm( sum_k A[k*lda + m] B[k*ldb + n] )          (EPI_PERM store in the operand type)
 //
+// Float32 only (float64 builds are faster on the register-staged kernel).
 // Same 128 x 256 tile, 8 waves and 3-stage LDS ring as the K-contiguous kernel.
 // A stage holds BK rows of k: 128 contiguous m of A and 256 contiguous n of B per
 // row, filled 1 KB per wave instruction (lane l writes 16 bytes at +16*l).  An
 // MFMA operand needs one value per lane from one k row, so the rows of the 4 x 4
-// blocks of a wave are interleaved: block i's row r is wave row pos(i, r) with
-// pos = 4r + i (float32) or 32*(i/2) + 2r + (i%2) (float64), making the values a
-// lane needs for all four blocks one 16-byte LDS read (two for float64), the 16
-// lanes of a k row reading 256 contiguous bytes (no bank conflicts, no swizzle).
+// blocks of a wave are interleaved: block i's row r is wave row 4r + i, making the
+// values a lane needs for all four blocks one 16-byte LDS read, the 16 lanes of a k
+// row reading 256 contiguous bytes (no bank conflicts, no swizzle).
 // Columns are interleaved the same way, which also makes the values a lane stores
 // for the four column blocks adjacent in the output: the permuted epilogue writes
 // them with 16-byte stores where they do not wrap around a row (dword-aligned: any v;
@@ -375,11 +375,16 @@ namespace ccl {
 // the register-staged kernel does (slot j of MFMA e in a group of 4*CH takes
 // CH*j + e), so that operands padded for this kernel keep the sums they had there.
 //
-// sym (EPI_PERM, M = N, A = B): the integral (ac|bd) = (bd|ac) of a block that holds
+// SYM (EPI_PERM, M = N, A = B): the integral (ac|bd) = (bd|ac) of a block that holds
 // all virtuals.  Only the tiles that meet n >= m run, on a compact grid, and each
 // value is stored at (m, n) and (n, m): half the multiply-adds for the same bytes.
-// A lane's 4 x CH group of adjacent rows and columns makes both stores 16-byte
-// vectors.  o=40 v=360 P=1200 float32 forward: 728 -> 573 ms.
+// A lane's 4 x 4 group of adjacent rows and columns makes both stores 16-byte
+// vectors.  o=40 v=360 P=1200 float32 forward: 728 -> 573 ms.  (An instantiation of its
+// own: as a branch it cost every other build of this kernel 8 to 10 us a tile.)
+
+// Row (column) of the tile that row r of a wave's block i stands for, in this kernel and
+// for the columns of the mixed one below: 4r + i (float32) or 32*(i/2) + 2r + (i%2)
+// (float64).
 template <class Tr>
 __device__ __forceinline__ int rc_pos(int i, int r) {
   if constexpr (Tr::CH == 4)
@@ -405,15 +410,16 @@ __device__ inline void sym_tile(long long id, int tiles_m, int tiles_n, int& tm,
   tn = t / 2 + static_cast<int>(id - sym_tiles_before(t, tiles_n));
 }
 
-template <class Tr, int EPI, int KMAP = 0, bool DW = false>
+template <class Tr, int EPI, int KMAP = 0, bool DW = false, bool SYM = false>
 __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<typename Tr::T> g) {
   static_assert(EPI == EPI_PERM || EPI == EPI_PACK || EPI == EPI_UNPACK || EPI == EPI_SYM,
                 "integral-block stores");
+  static_assert(Tr::CH == 4 && Tr::kDrain && (!SYM || EPI == EPI_PERM), "float32");
   using T = typename Tr::T;
   using Acc = typename Tr::Acc;
   using Chunk = typename Tr::Chunk;
   constexpr int CH = Tr::CH;
-  constexpr int BK = kDRow / sizeof(T);          // 16 float64 / 32 float32 k rows per stage
+  constexpr int BK = kDRow / sizeof(T);          // 32 k rows per stage
   constexpr int ROWA = kDBM * sizeof(T);         // bytes of one k row of A (128 m)
   constexpr int ROWB = kDBN * sizeof(T);         // bytes of one k row of B (256 n)
   constexpr int A_BYTES = BK * ROWA;             // 16 KB
@@ -444,7 +450,7 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
     }
     tm = lo;
     tn = pack_first_tile(tm, kDBM, kDBN, g.v) + (id - g.row_tiles[tm]);
-  } else if (EPI == EPI_PERM && g.sym) {
+  } else if (SYM) {
     sym_tile(xcd_linear(blockIdx.x, gridDim.x), g.tiles_m, g.tiles_n, tm, tn);
   } else {
     tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.group_m, tm, tn);
@@ -485,7 +491,6 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
       pb[j] = g.B + (long long)rb[j] * g.ldb + n;
     }
   }
-  constexpr bool kSpread = d_spread<T, DW>();
   auto issue_dw = [&](int kt, int q) {
     unsigned char* st = lds + (kt % kDStages) * STAGE;
     const long long ka = (long long)kt * BK * g.lda, kb = (long long)kt * BK * g.ldb;
@@ -571,8 +576,8 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   // pos(., lane % 16) of the four blocks
   const int kr = lane >> 4;
   const int r16 = lane & 15;
-  const int offa = (wm + (CH == 4 ? 4 * r16 : 2 * r16)) * (int)sizeof(T);
-  const int offb = (wn + (CH == 4 ? 4 * r16 : 2 * r16)) * (int)sizeof(T);
+  const int offa = (wm + 4 * r16) * (int)sizeof(T);
+  const int offb = (wn + 4 * r16) * (int)sizeof(T);
   const int nk = (g.K + BK - 1) / BK;
   const int nkf = g.K / BK;
   auto stage_in = [&](int kt) {
@@ -584,57 +589,38 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   stage_in(0);
   if (nk > 1) stage_in(1);
   for (int k0 = 0; k0 < nk;) {
-    const int kend = (Tr::kDrain && k0 + g.drain_steps < nk) ? k0 + g.drain_steps : nk;
+    const int kend = k0 + g.drain_steps < nk ? k0 + g.drain_steps : nk;
     for (int kt = k0; kt < kend; ++kt) {
       d_wait_vm(kt + 1 < nkf ? LOADS : 0);
       __builtin_amdgcn_s_barrier();
-      const bool dw_next = kSpread && kt + 2 < nkf;
-      if (kt + 2 < nk && !dw_next) stage_in(kt + 2);
+      if (kt + 2 < nk) stage_in(kt + 2);
       const unsigned char* st = lds + (kt % kDStages) * STAGE;
 #pragma unroll
       for (int kk = 0; kk < BK / 4; ++kk) {
-        if (dw_next && kk % (BK / 16) == 0) issue_dw(kt + 2, kk / (BK / 16));
         const int krow = KMAP ? 4 * CH * (kk / CH) + CH * kr + kk % CH : 4 * kk + kr;
         const unsigned char* ra_ = st + krow * ROWA + offa;
         const unsigned char* rb_ = st + A_BYTES + krow * ROWB + offb;
-        T fa[4], fb[4];
-        if constexpr (CH == 4) {
-          const Chunk a = *reinterpret_cast<const Chunk*>(ra_);
-          const Chunk b = *reinterpret_cast<const Chunk*>(rb_);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            fa[i] = a[i];
-            fb[i] = b[i];
-          }
-        } else {
-          const Chunk a0 = *reinterpret_cast<const Chunk*>(ra_);
-          const Chunk a1 = *reinterpret_cast<const Chunk*>(ra_ + 32 * sizeof(T));
-          const Chunk b0 = *reinterpret_cast<const Chunk*>(rb_);
-          const Chunk b1 = *reinterpret_cast<const Chunk*>(rb_ + 32 * sizeof(T));
-          fa[0] = a0[0]; fa[1] = a0[1]; fa[2] = a1[0]; fa[3] = a1[1];
-          fb[0] = b0[0]; fb[1] = b0[1]; fb[2] = b1[0]; fb[3] = b1[1];
-        }
+        const Chunk fa = *reinterpret_cast<const Chunk*>(ra_);
+        const Chunk fb = *reinterpret_cast<const Chunk*>(rb_);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[i][j] = Tr::mfma(fa[i], fb[j], acc[i][j]);
       }
     }
-    if (Tr::kDrain) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            acc64[i][j][r] += static_cast<double>(acc[i][j][r]);
-            acc[i][j][r] = 0;
-          }
-    }
+        for (int r = 0; r < 4; ++r) {
+          acc64[i][j][r] += static_cast<double>(acc[i][j][r]);
+          acc[i][j][r] = 0;
+        }
     k0 = kend;
   }
 
-  // epilogue: column groups of CH adjacent n (blocks j = CH*h .. CH*h + CH - 1).
+  // epilogue: a lane's four column blocks are 4 adjacent n.
   // EPI_PERM: m = (a, x), n = (y, d) -> C[(a*(N/v) + y)*ldv + x*v + d];
   // EPI_PACK: m = (a - a0, c), n = (b - a0, d), kept for b >= a, at packed row
   // pair(a, b) - pair(a0, a0): C[row*v^2 + c*v + d];
@@ -643,9 +629,56 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
   const long long v = g.v;
   // vector stores need dword alignment only, so rows of any length take them
   typedef T ChunkU __attribute__((ext_vector_type(CH), aligned(sizeof(T))));
-  constexpr int NG = 4 / CH;  // column groups per lane: 1 (float32) or 2 (float64)
-  auto dst_of = [&](int m, int n) -> long long {  // -1: not stored
-    const int y = n / g.v, d = n - y * g.v;
+  T* C = static_cast<T*>(g.C);
+  const int nb = n0 + wn + 4 * r16;  // first column
+  if (nb >= g.N) return;
+  const int yb = nb / g.v, db = nb - yb * g.v;
+  auto value = [&](int i, int e, int r) { return static_cast<T>(acc64[i][e][r]); };
+  if constexpr (SYM) {
+    // 4 adjacent rows m and columns n: the group on or above the diagonal, and its
+    // mirror with rows and columns exchanged
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int mb = m0 + wm + 4 * Tr::row_of(lane, r);
+      if (mb >= g.M) continue;
+      const int ab = mb / g.v, xb = mb - ab * g.v;
+      if (mb + CH - 1 <= nb && nb + CH <= g.N && db + CH <= g.v && xb + CH <= g.v) {
+        // wholly on or above the diagonal, and in one row of (c, d) either way
+        T* up = C + ab * g.lda_v + yb * g.ldv + (long long)xb * v + db;
+        T* down = C + yb * g.lda_v + ab * g.ldv + (long long)db * v + xb;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+          ChunkU x, y;
+#pragma unroll
+          for (int e = 0; e < CH; ++e) {
+            x[e] = value(i, e, r);
+            y[e] = value(e, i, r);
+          }
+          *reinterpret_cast<ChunkU*>(up + i * v) = x;
+          *reinterpret_cast<ChunkU*>(down + i * v) = y;
+        }
+      } else {
+        // element by element, the indices (a, x) and (y, d) carried along
+        int a = ab, x = xb;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+          int y = yb, d = db;
+#pragma unroll
+          for (int e = 0; e < CH; ++e) {
+            const int m = mb + i, n = nb + e;
+            if (m < g.M && n < g.N && m <= n) {
+              C[a * g.lda_v + y * g.ldv + (long long)x * v + d] = value(i, e, r);
+              C[y * g.lda_v + a * g.ldv + (long long)d * v + x] = value(i, e, r);
+            }
+            if (++d == g.v) { d = 0; ++y; }
+          }
+          if (++x == g.v) { x = 0; ++a; }
+        }
+      }
+    }
+    return;
+  }
+  auto dst_of = [&](int m, int y, int d) -> long long {  // -1: not stored
     if (EPI == EPI_UNPACK) {
       if (m >= g.m_keep) return -1;
       const long long q = pair_prefix_d(g.a0, v) + m;
@@ -659,111 +692,44 @@ __global__ __launch_bounds__(kDThreads, 1) void gemm_rc_direct_kernel(GemmArgs<t
     const long long row = pair_prefix_d(g.a0 + a, v) - pair_prefix_d(g.a0, v) + (y - a);
     return row * v * v + (long long)x * v + d;
   };
+  const bool one_row = nb + CH <= g.N && db + CH <= g.v;  // the 4 columns share y
 #pragma unroll
-  for (int h = 0; h < NG; ++h) {
-    const int nb = n0 + wn + rc_pos<Tr>(CH * h, r16);  // first column of the group
-    if (nb >= g.N) continue;
-    if (EPI == EPI_PERM && g.sym) {
-      // rows of 4 adjacent m per (r), columns of CH adjacent n: the group on or above
-      // the diagonal, and its mirror with rows and columns exchanged
-      T* C = static_cast<T*>(g.C);
-      const int yb = nb / g.v, db = nb - yb * g.v;
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        T val[4][CH];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int e = 0; e < CH; ++e)
-            val[i][e] = static_cast<T>(Tr::kDrain ? acc64[i][CH * h + e][r]
-                                                  : static_cast<double>(acc[i][CH * h + e][r]));
-#pragma unroll
-        for (int q = 0; q < 4 / CH; ++q) {  // CH adjacent rows at a time
-          const int mb = m0 + wm + rc_pos<Tr>(CH * q, Tr::row_of(lane, r));
-          if (mb >= g.M) continue;
-          const int ab = mb / g.v, xb = mb - ab * g.v;
-          if (mb + CH - 1 <= nb && nb + CH <= g.N && db + CH <= g.v && xb + CH <= g.v) {
-            // wholly on or above the diagonal, and in one row of (c, d) either way
-            T* up = C + ab * g.lda_v + yb * g.ldv + (long long)xb * v + db;
-            T* down = C + yb * g.lda_v + ab * g.ldv + (long long)db * v + xb;
-#pragma unroll
-            for (int i = 0; i < CH; ++i) {
-              ChunkU x, y;
-#pragma unroll
-              for (int e = 0; e < CH; ++e) {
-                x[e] = val[CH * q + i][e];
-                y[e] = val[CH * q + e][i];
-              }
-              *reinterpret_cast<ChunkU*>(up + i * v) = x;
-              *reinterpret_cast<ChunkU*>(down + i * v) = y;
-            }
-          } else {
-            // element by element, the indices (a, x) and (y, d) carried along
-            int a = ab, x = xb;
-#pragma unroll
-            for (int i = 0; i < CH; ++i) {
-              int y = yb, d = db;
-#pragma unroll
-              for (int e = 0; e < CH; ++e) {
-                const int m = mb + i, n = nb + e;
-                if (m < g.M && n < g.N && m <= n) {
-                  C[a * g.lda_v + y * g.ldv + (long long)x * v + d] = val[CH * q + i][e];
-                  C[y * g.lda_v + a * g.ldv + (long long)d * v + x] = val[CH * q + i][e];
-                }
-                if (++d == g.v) { d = 0; ++y; }
-              }
-              if (++x == g.v) { x = 0; ++a; }
-            }
-          }
-        }
-      }
-      continue;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + rc_pos<Tr>(i, Tr::row_of(lane, r));
-        if (m >= g.M) continue;
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + wm + 4 * Tr::row_of(lane, r) + i;
+      if (m >= g.M) continue;
+      if constexpr (EPI == EPI_SYM) {
+        // the 4 columns, and their mirrors down one column m
         Chunk val;
 #pragma unroll
-        for (int e = 0; e < CH; ++e) {
-          const double s = Tr::kDrain ? acc64[i][CH * h + e][r]
-                                      : static_cast<double>(acc[i][CH * h + e][r]);
-          val[e] = static_cast<T>(s);
-        }
-        T* C = static_cast<T*>(g.C);
-        if constexpr (EPI == EPI_SYM) {
-          // the group's CH adjacent columns, and their mirrors down one column m
-          if (g.ldc % CH == 0) {
-            *reinterpret_cast<Chunk*>(C + (long long)m * g.ldc + nb) = val;
-          } else {
-#pragma unroll
-            for (int e = 0; e < CH; ++e) C[(long long)m * g.ldc + nb + e] = val[e];
-          }
-#pragma unroll
-          for (int e = 0; e < CH; ++e) C[(long long)(nb + e) * g.ldc + m] = val[e];
-          continue;
-        }
-        if (nb + CH <= g.N && nb % g.v + CH <= g.v) {
-          // the group's CH columns share (y) and are adjacent in d
-          const long long o0 = dst_of(m, nb);
-          if (o0 >= 0) {
-            ChunkU x;
-#pragma unroll
-            for (int e = 0; e < CH; ++e) x[e] = val[e];
-            *reinterpret_cast<ChunkU*>(C + o0) = x;
-          }
+        for (int e = 0; e < CH; ++e) val[e] = value(i, e, r);
+        if (g.ldc % CH == 0) {
+          *reinterpret_cast<Chunk*>(C + (long long)m * g.ldc + nb) = val;
         } else {
 #pragma unroll
-          for (int e = 0; e < CH; ++e) {
-            if (nb + e >= g.N) continue;
-            const long long oe = dst_of(m, nb + e);
-            if (oe >= 0) C[oe] = val[e];
-          }
+          for (int e = 0; e < CH; ++e) C[(long long)m * g.ldc + nb + e] = val[e];
+        }
+#pragma unroll
+        for (int e = 0; e < CH; ++e) C[(long long)(nb + e) * g.ldc + m] = val[e];
+      } else if (one_row) {
+        const long long o0 = dst_of(m, yb, db);
+        if (o0 >= 0) {
+          ChunkU x;
+#pragma unroll
+          for (int e = 0; e < CH; ++e) x[e] = value(i, e, r);
+          *reinterpret_cast<ChunkU*>(C + o0) = x;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < CH; ++e) {
+          if (nb + e >= g.N) continue;
+          const int y = (nb + e) / g.v;
+          const long long oe = dst_of(m, y, nb + e - y * g.v);
+          if (oe >= 0) C[oe] = value(i, e, r);
         }
       }
-  }
+    }
 }
 
 }  // namespace ccl
