@@ -844,14 +844,14 @@ int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ld
   PairPick pick = pick_pair_products(whole, PairExtents{mp, np, mm, nm}, kp, sizeof(T),
                                      Tr::kDrain ? drain : 1, max_splits);
   if (pick.splits == 0) {
-    int rc;
+    int rc = CC_LADDER_EINVAL;
     if (pairs) {
       rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tp, ldp, Vp, ldp, R, v2, mp, np, kp, v, drain, s, o, a0,
                                            nullptr, 0.5, 1, 0, 0, mp, kp);
       if (!rc)
         rc = launch_gemm<Tr, KC, KC, EPI_PM>(Tm, ldm, Vm, ldm, R, v2, mm, nm, km, v, drain, s, o,
                                              a0, nullptr, 0.5, 2, 0, 0, mm, km);
-    } else {
+    } else if constexpr (!Tr::kDrain) {  // (the float32 form folds pairs i <= j only)
       rc = launch_gemm<Tr, KC, KC, EPI_FOLD>(Tp, ldp, Vp, ldp, R, v2, mp, np, kp, v, drain, s, o,
                                              a0, nullptr, 0.5, 1, 0, 0, mp, kp);
       if (!rc)
