@@ -1788,46 +1788,36 @@ int backward_fold(const Plan& pl, const FoldAdjoint& fa, const double* L, const 
   if (rc) return rc;
   if (pl.gsym) rc = build_pair_integral<TrF64>(pl, Lp, G, row_tiles, tr, s);
   if (rc) return rc;
-  for (int blk = 0; blk < f.nb; ++blk) {
-    const int a0 = pair_block_start(v, f.nb, blk);
-    const int na = pair_block_start(v, f.nb, blk + 1) - a0;
-    if (na <= 0) continue;
-    const long long off = (long long)a0 * v;
-    const long long p0 = pair_prefix(a0, v), m0 = pair_prefix(a0, v - 1);  // first pairs
-    const long long np = pair_prefix(a0 + na, v) - p0, nm = np - na;
-    tr(CC_LADDER_PHASE_BUILD, blk, 0);
-    if (pl.gsym) {
-      rc = pm_gather<GATHER_PM>(static_cast<const double*>(G), pl.ldg, np, a0, v, Vp, f.ldp, Vm,
-                                f.ldm, s);
-    } else {
-      rc = launch_gemm<TrF64, RC, RC, EPI_PACK>(L + off, v2, L + off, v2, V, 0, na * v,
-                                                static_cast<int>((long long)(v - a0) * v), P, v, 0,
-                                                s, o, a0, row_tiles, 1.0, 0, 0, 0, iv2, iv2);
-      if (!rc) rc = pm_rows<PM_INTS>(V, np, v, a0, v, Vp, f.ldp, Vm, f.ldm, 2.0, 1.0, s);
-    }
-    tr(CC_LADDER_PHASE_BUILD, blk, 1);
-    if (rc) return rc;
-    // dt over the pairs of c, d, from the block's pairs of a, b (the pads of V+- rows
-    // may be read: their columns are not stored)
-    tr(CC_LADDER_PHASE_DT, blk, 0);
-    const int inp = static_cast<int>(np), inm = static_cast<int>(nm);
-    const int ldp = static_cast<int>(f.ldp), ldm = static_cast<int>(f.ldm);
-    if (pairs) {
-      rc = launch_gemm<TrF64, KC, RC, EPI_PM>(Mp + p0, f.ldp, Vp, f.ldp, dt, v2, mp, kp, inp, v, 0,
-                                              s, o, 0, nullptr, 0.5, 1, 0, 0, 0, 0, ldp);
-      if (!rc)
-        rc = launch_gemm<TrF64, KC, RC, EPI_PM>(Mm + m0, f.ldm, Vm, f.ldm, dt, v2, mm, km, inm, v,
-                                                0, s, o, 0, nullptr, 0.5 * sm, 2, 0, 0, 0, 0, ldm);
-    } else {
-      rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mp + p0, f.ldp, Vp, f.ldp, dt, v2, mp, kp, inp, v, 0,
-                                                s, o, 0, nullptr, 0.5, 1, 0, 0, 0, 0, ldp);
-      if (!rc)
-        rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mm + m0, f.ldm, Vm, f.ldm, dt, v2, mm, km, inm, v,
-                                                  0, s, o, 0, nullptr, 0.5 * sm, 2, 0, 0, 0, 0, ldm);
-    }
-    tr(CC_LADDER_PHASE_DT, blk, 1);
-    if (rc) return rc;
+  tr(CC_LADDER_PHASE_BUILD, 0, 0);
+  if (pl.gsym) {
+    rc = pm_gather<GATHER_PM>(static_cast<const double*>(G), pl.ldg, kp, 0, v, Vp, f.ldp, Vm, f.ldm,
+                              s);
+  } else {
+    rc = launch_gemm<TrF64, RC, RC, EPI_PACK>(L, v2, L, v2, V, 0, iv2, iv2, P, v, 0, s, o, 0,
+                                              row_tiles, 1.0, 0, 0, 0, iv2, iv2);
+    if (!rc) rc = pm_rows<PM_INTS>(V, kp, v, 0, v, Vp, f.ldp, Vm, f.ldm, 2.0, 1.0, s);
   }
+  tr(CC_LADDER_PHASE_BUILD, 0, 1);
+  if (rc) return rc;
+  // dt over the pairs of c, d, from those of a, b (the pads of V+- rows may be read:
+  // their columns are not stored)
+  tr(CC_LADDER_PHASE_DT, 0, 0);
+  const int ldp = static_cast<int>(f.ldp), ldm = static_cast<int>(f.ldm);
+  if (pairs) {
+    rc = launch_gemm<TrF64, KC, RC, EPI_PM>(Mp, f.ldp, Vp, f.ldp, dt, v2, mp, kp, kp, v, 0, s, o, 0,
+                                            nullptr, 0.5, 1, 0, 0, 0, 0, ldp);
+    if (!rc)
+      rc = launch_gemm<TrF64, KC, RC, EPI_PM>(Mm, f.ldm, Vm, f.ldm, dt, v2, mm, km, km, v, 0, s, o, 0,
+                                              nullptr, 0.5 * sm, 2, 0, 0, 0, 0, ldm);
+  } else {
+    rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mp, f.ldp, Vp, f.ldp, dt, v2, mp, kp, kp, v, 0, s, o, 0,
+                                              nullptr, 0.5, 1, 0, 0, 0, 0, ldp);
+    if (!rc)
+      rc = launch_gemm<TrF64, KC, RC, EPI_FOLD>(Mm, f.ldm, Vm, f.ldm, dt, v2, mm, km, km, v, 0, s, o,
+                                                0, nullptr, 0.5 * sm, 2, 0, 0, 0, 0, ldm);
+  }
+  tr(CC_LADDER_PHASE_DT, 0, 1);
+  if (rc) return rc;
   tr(CC_LADDER_PHASE_W, 0, 0);
   rc = launch_gemm<TrF64, RC, RC, EPI_STORE>(Mp, f.ldp, Tp, f.ldp, Wp, f.ldp, kp, kp, mp, v, 0, s);
   if (!rc)

@@ -998,7 +998,9 @@ bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a) {
   // From 64 virtuals on, as the forward: below, the extra launches take what the
   // products save; from 16 for pair-symmetric t and lam, whose direct route has as many
   // launches and K-banded products (o=6 v=33 P=120: 567 -> 93 us).  W is
-  // formed whole, so a plan of several blocks keeps the direct route.
+  // formed whole, so a plan of several blocks keeps the direct route; in a plan of one
+  // block dt's stage is the smaller one (1 v^4 values against W+- and S, 1.5 v^4; with
+  // symmetric vectors G beside it, which the plan holds too).
   if (pl.op != kOpLadder || pl.precision != CC_LADDER_FP64 || !pl.backward || pl.n_a != pl.v ||
       pl.v < (pl.pairsym_adj ? 16 : 64))
     return false;
@@ -1008,39 +1010,35 @@ bool plan_fold_adjoint(const Plan& pl, FoldAdjoint* a) {
   const size_t kp = static_cast<size_t>(v) * (v + 1) / 2;
   // (odd v: with S and a copy of L on padded rows where they fit)
   for (int pad = v % 2; pad >= 0; --pad) {
-    for (int nb = 1; nb <= 4; ++nb) {
-      FoldAdjoint p;
-      p.f = layout_fold(pl, nb);  // t+- first, then the blocks
-      if (!p.f.nb) break;
-      p.lds = static_cast<long long>(v2) + pad;
-      p.copy_L = pad != 0;
-      const size_t ldp = p.f.ldp, ldm = p.f.ldm;
-      // lam+- after t+-; the blocks of dt's stage and W+-, S share what follows
-      size_t cur = p.f.off_V;
-      p.off_Mp = take(&cur, p.f.rows_p * ldp * sizeof(double));
-      p.off_Mm = take(&cur, p.f.rows_m * ldm * sizeof(double));
-      if (pl.gsym) {
-        p.off_Lp = take(&cur, static_cast<size_t>(pl.P) * ldp * sizeof(double));
-        p.off_G = take(&cur, ldp * ldp * sizeof(double));
-      }
-      const size_t shift = cur - p.f.off_V;
-      p.f.off_V += shift;
-      p.f.off_Vp += shift;
-      p.f.off_Vm += shift;
-      p.f.off_tiles += shift;
-      p.f.bytes += shift;
-      // (W+- and S follow lam+-, in the place of the vectors and G as well)
-      cur = p.off_Mm + (p.f.rows_m * ldm * sizeof(double) + kAlign - 1) / kAlign * kAlign;
-      p.off_Wp = take(&cur, kp * ldp * sizeof(double));
-      p.off_Wm = take(&cur, (kp - v) * ldm * sizeof(double));
-      p.off_S = take(&cur, v2 * p.lds * sizeof(double));
-      if (p.copy_L) p.off_L = take(&cur, static_cast<size_t>(pl.P) * p.lds * sizeof(double));
-      p.bytes = cur > p.f.bytes ? cur : p.f.bytes;
-      if (p.bytes <= room) {
-        *a = p;
-        return true;
-      }
-      if (cur > room) break;  // more blocks shrink dt's stage only
+    FoldAdjoint p;
+    p.f = layout_fold(pl, 1);  // t+- first, then the integrals
+    p.lds = static_cast<long long>(v2) + pad;
+    p.copy_L = pad != 0;
+    const size_t ldp = p.f.ldp, ldm = p.f.ldm;
+    // lam+- after t+-; dt's stage (the integrals) and W+-, S share what follows
+    size_t cur = p.f.off_V;
+    p.off_Mp = take(&cur, p.f.rows_p * ldp * sizeof(double));
+    p.off_Mm = take(&cur, p.f.rows_m * ldm * sizeof(double));
+    if (pl.gsym) {
+      p.off_Lp = take(&cur, static_cast<size_t>(pl.P) * ldp * sizeof(double));
+      p.off_G = take(&cur, ldp * ldp * sizeof(double));
+    }
+    const size_t shift = cur - p.f.off_V;
+    p.f.off_V += shift;
+    p.f.off_Vp += shift;
+    p.f.off_Vm += shift;
+    p.f.off_tiles += shift;
+    p.f.bytes += shift;
+    // (W+- and S follow lam+-, in the place of the vectors and G as well)
+    cur = p.off_Mm + (p.f.rows_m * ldm * sizeof(double) + kAlign - 1) / kAlign * kAlign;
+    p.off_Wp = take(&cur, kp * ldp * sizeof(double));
+    p.off_Wm = take(&cur, (kp - v) * ldm * sizeof(double));
+    p.off_S = take(&cur, v2 * p.lds * sizeof(double));
+    if (p.copy_L) p.off_L = take(&cur, static_cast<size_t>(pl.P) * p.lds * sizeof(double));
+    p.bytes = cur > p.f.bytes ? cur : p.f.bytes;
+    if (p.bytes <= room) {
+      *a = p;
+      return true;
     }
   }
   return false;

@@ -202,7 +202,7 @@ bool plan_stacked_i8(const Plan& pl, StackedPlan* q);
 // i <= j (i < j), t's weighted by 2 for i < j where W sums over them; with symmetric
 // vectors (pl.gsym) V+- are gathered from the pair-pair integral.
 struct FoldAdjoint {
-  FoldPlan f;                        // t+-, V, V+- (blocks of dt's stage)
+  FoldPlan f;                        // t+-, V, V+- (one block)
   size_t off_Mp = 0, off_Mm = 0;     // lam+, lam- (strides f.ldp, f.ldm)
   size_t off_Wp = 0, off_Wm = 0;     // W+ [pairs a <= b][f.ldp], W- [pairs a < b][f.ldm]
   size_t off_S = 0;                  // S as rows (a,c), columns (b,d), row stride lds
