@@ -100,9 +100,15 @@ int launch_kc_direct(const GemmArgs<typename Tr::T>& g0, const TilePick& pick, h
   GemmArgs<typename Tr::T> g = g0;
   if ((long long)((g.M + 63) / 64) * ((g.N + 63) / 64) > 0x7fffffffLL) return CC_LADDER_EINVAL;
   if (pick.bm == 160) {
-    if constexpr (!Tr::kDrain && !DW) launch_kc_tiles<Tr, EPI, 160, 256>(g, stream);
+    if constexpr (!Tr::kDrain && !DW)
+      launch_kc_tiles<Tr, EPI, 160, 256>(g, stream);
+    else
+      return CC_LADDER_EINVAL;  // no such kernel
   } else if (pick.bn == 64) {
-    if constexpr (!DW || Tr::kDrain) launch_kc_tiles<Tr, EPI, 64, 64, DW>(g, stream);
+    if constexpr (!DW || Tr::kDrain)
+      launch_kc_tiles<Tr, EPI, 64, 64, DW>(g, stream);
+    else
+      return CC_LADDER_EINVAL;
   } else if (pick.bn == 128) {
     launch_kc_tiles<Tr, EPI, 64, 128, DW>(g, stream);
   } else {
@@ -907,6 +913,8 @@ int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ld
       hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 128, 256>), grid, block, 0, s, g, h, in1);
     else if constexpr (!Tr::kDrain)
       hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 160, 256>), grid, block, 0, s, g, h, in1);
+    else
+      return CC_LADDER_EINVAL;  // no such kernel
     const long long ta = (na + kSwapTile - 1) / kSwapTile, tb = (v - a0 + kSwapTile - 1) / kSwapTile;
     const long long blocks = std::min<long long>(rows * ta * tb, 65536);
     hipLaunchKernelGGL(pm_combine_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s,

@@ -12,7 +12,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 
 @pytest.mark.timeout(300)
-@pytest.mark.parametrize("name", ["route_check"])
+@pytest.mark.parametrize("name", ["route_check", "layout_check"])
 def test_host_program(tmp_path, name):
     gxx = shutil.which("g++")
     if gxx is None:
