@@ -42,12 +42,14 @@ def test_plus_minus_symmetric_vectors(gpu_lib, o, v, P, precision, exchange):
         assert torch.equal(_residual(gpu_lib, Ld, td, precision, a_block=a_block, **kw), one), a_block
 
 
-def _prepares(native, Ld, td, **kw):
-    """Whether the float64 forward prepares amplitudes: the folded route's own phase."""
+def _folded(native, Ld, td, **kw):
+    """Whether the float64 forward is folded: it then prepares amplitudes without being
+    the exchange partner, or runs in other blocks than the plan's."""
     seen = []
-    fn = native.TRACE_FN(lambda user, phase, block, end, stream: seen.append(phase))
+    fn = native.TRACE_FN(lambda user, phase, block, end, stream: seen.append((phase, block)))
     _residual(native, Ld, td, 0, trace=fn, **kw)
-    return 0 in seen
+    blocks = 1 + max(b for p, b in seen if p == 2)
+    return blocks > 1 if kw.get("exchange") else (0, 0) in seen
 
 
 # the float64 forward: folded sizes (46 occupied with 64 virtuals: 2 o^2 > v^2, no room for
@@ -70,7 +72,8 @@ def test_float64_forward(gpu_lib, o, v, P, pairsym, folded, exchange):
     one = _residual(gpu_lib, Ld, td, 0, **kw)
     ref = oracle.exchange_forward(L, t) if exchange else oracle.ladder_forward(L, t)
     assert rel_fro(host(one), ref) < TOL[0]
-    assert exchange or _prepares(gpu_lib, Ld, td, **kw) == folded
+    if folded or not exchange:  # (the swapped copy tips the scales at some of the direct sizes)
+        assert _folded(gpu_lib, Ld, td, **kw) == folded
     for a_block in (1, 7, v // 3, v - 1):
         assert torch.equal(_residual(gpu_lib, Ld, td, 0, a_block=a_block, **kw), one), a_block
     full, _ = gpu_lib.cc_ladder_workspace_query(o, v, P, 0, opts=gpu_lib.make_opts(**kw))
@@ -80,7 +83,7 @@ def test_float64_forward(gpu_lib, o, v, P, pairsym, folded, exchange):
     if folded and not exchange:  # less scratch than the folded route needs: the direct one
         small = _residual(gpu_lib, Ld, td, 0, hbm_budget=least - 1, **kw)
         assert rel_fro(host(small), ref) < TOL[0]
-        assert not _prepares(gpu_lib, Ld, td, hbm_budget=least - 1, **kw)
+        assert not _folded(gpu_lib, Ld, td, hbm_budget=least - 1, **kw)
 
 
 # split-int8 past one chunk of 16384 contracted indices, which the stacked route's swapped
@@ -105,3 +108,27 @@ def test_split_int8_forward(gpu_lib, o, v, P, exchange, slices):
     if o < 20:
         ref = oracle.exchange_forward(L, t) if exchange else oracle.ladder_forward(L, t)
         assert rel_fro(host(one), ref) < (4e-8 if slices == 4 else 1e-9)
+
+
+# the float64 adjoint: folded (amplitudes prepared, nothing swapped back at the end) in a
+# plan of one block, from 64 virtuals on and 16 with pair-symmetric t and lam
+@pytest.mark.parametrize("o,v,P,a_block,pairsym,symv,folded", [
+    (6, 64, 30, 0, False, False, True), (3, 97, 12, 0, False, False, True),
+    (6, 63, 30, 0, False, False, False), (6, 64, 30, 40, False, False, False),
+    (5, 16, 20, 0, True, False, True), (7, 33, 41, 0, True, True, True),
+    (5, 15, 20, 0, True, False, False), (5, 40, 20, 20, True, False, False)])
+@pytest.mark.parametrize("exchange", [False, True])
+def test_adjoint_route(gpu_lib, o, v, P, a_block, pairsym, symv, folded, exchange):
+    import torch
+
+    announce("route-adjoint", o, v, P, a_block, "pairsym", pairsym, "symv", symv, "exchange", exchange)
+    Ld = torch.zeros(P, v, v, dtype=torch.float64, device="cuda")
+    td = torch.zeros(o, o, v, v, dtype=torch.float64, device="cuda")
+    seen = []
+    fn = gpu_lib.TRACE_FN(lambda user, phase, block, end, stream: seen.append((phase, block)))
+    gpu_lib.cc_ladder_backward(
+        Ld, td, td.clone(), torch.zeros_like(Ld), torch.zeros_like(td), 0,
+        opts=gpu_lib.make_opts(a_block=a_block, pair_symmetric=pairsym, symmetric_vectors=symv,
+                               exchange=exchange, trace=fn))
+    torch.cuda.synchronize()
+    assert ((0, 1) not in seen if exchange else (0, 0) in seen) == folded
