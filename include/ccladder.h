@@ -40,6 +40,29 @@
  * - Internal scratch: taken from opts->workspace when given, otherwise
  *   allocated with hipMallocAsync on `stream` and released with hipFreeAsync
  *   on the same stream before return.
+ *
+ * Folded evaluation
+ * -----------------
+ * (ac|bd) = (bd|ac) holds for any vectors, so the ladder splits into parts that are
+ * symmetric and antisymmetric under the exchange of both virtual pairs.  From 64
+ * virtuals on, at sizes where that is faster, the FP64 forward (general and
+ * pair-symmetric) contracts the sums and differences t[i][j][c][d] +- t[i][j][d][c]
+ * with (ac|bd) +- (ad|bc), as CC_LADDER_PLUS_MINUS does; so does the FP64 adjoint
+ * whose plan is one block (pair-symmetric: from 16 virtuals on).  The split-int8
+ * general forward contracts the rows a <= b with t and its swapped copy stacked.
+ * - Which form runs follows from o, v, P and the flags, and from a least scratch
+ *   (about that of t) which every plan includes when the budget holds it.  With less
+ *   the integral blocks are contracted directly.
+ * - The FP64 and split forwards give the same R, bit for bit, however the virtual
+ *   range is cut into blocks (a_block, budget, workspace size), as long as that least
+ *   scratch fits or the direct form is the one chosen; below it the last bits can
+ *   differ.  The order of the adjoint's sums and of the FP32 forms follows the blocks.
+ * - Rounding errors of the folded forms are relative to the larger of R[i][j][a][b]
+ *   and R[i][j][b][a] (dt alike).  Over the whole tensor they are no larger than the
+ *   direct form's; an element far smaller than its partner has fewer correct digits.
+ * - Where the direct form would give an infinity (an infinite element of L, t or lam),
+ *   the folded ones can give NaN.  The elements that are not finite are the same.
+ *   Finite values within a factor 4 of the largest double can overflow.
  */
 #ifndef CCLADDER_H
 #define CCLADDER_H
@@ -155,8 +178,9 @@ typedef enum {
 
 /* Kernel phases reported to an optional trace hook. */
 typedef enum {
-  CC_LADDER_PHASE_PREP = 0,      /* operand conversion / slicing of L, t, lam; the exchange swaps
-                                    (block 1: the adjoint's final swap of dt) */
+  CC_LADDER_PHASE_PREP = 0,      /* operand conversion / slicing of L, t, lam; sums and differences
+                                    of t and lam; the exchange swaps (block 1: the adjoint's final
+                                    swap of dt) */
   CC_LADDER_PHASE_BUILD = 1,     /* integral block V_A (eq. cholesky) */
   CC_LADDER_PHASE_CONTRACT = 2,  /* R += t . V_A (eq. vfunction) */
   CC_LADDER_PHASE_DT = 3,        /* adjoint: dt += lam . V_A */
@@ -167,12 +191,16 @@ typedef enum {
 
 /* Called on the host right before (end = 0) and right after (end = 1) the
  * kernels of one phase of integral block `block` are enqueued on `stream`, so
- * the caller can record events there.  Must not call back into the library. */
+ * the caller can record events there.  The blocks are those that run: the folded and
+ * stacked forms' own where they do.  Must not call back into the library. */
 typedef void (*cc_ladder_trace_fn)(void* user, int phase, int block, int end, hipStream_t stream);
 
 /* Optional controls; a zero-initialised struct (or NULL) selects everything automatically. */
 typedef struct {
-  int    a_block;          /* virtuals per integral block; 0 = largest that fits hbm_budget */
+  int    a_block;          /* virtuals per integral block; 0 = largest that fits hbm_budget.  The
+                              folded and stacked forms cut the virtual range into blocks of
+                              about equal pair counts of their own, as many as the plan's
+                              scratch asks for, whatever a_block is */
   int    split_slices;     /* SPLIT_BF16 slices S in [2, 4]; 0 = 4 (2 = the hi/lo split);
                               SPLIT_INT8 digits in [4, 5]; 0 = 5 */
   int    k_chunk;          /* FP32 drain interval along the contracted index (multiple of 64); 0 = 512 */
@@ -259,7 +287,9 @@ int cc_ladder_reduce(int o, int v, const double* x, const double* y, double* out
  * Host-only planner query (needs no device): the scratch bytes and the
  * integral block (virtuals per block) that cc_ladder_residual (backward = 0)
  * or cc_ladder_backward (backward = 1) would use under `hbm_budget` bytes
- * (0 = no limit, i.e. the whole virtual range in one block).  This is the
+ * (0 = no limit, i.e. the whole virtual range in one block).  The block is that of
+ * the direct forms; folded and stacked ones run in their own blocks inside the same
+ * bytes, which the trace hook numbers.  This is the
  * paper's memory-fit rule for its batches (Sec. "CuPy and batch-wise
  * computations": element counts times element sizes, blocks shrunk until they
  * fit), applied to device-resident data.  `opts` may be NULL; every field that
