@@ -55,7 +55,8 @@
  *   the integral blocks are contracted directly.
  * - The FP64 and split forwards give the same R, bit for bit, however the virtual
  *   range is cut into blocks (a_block, budget, workspace size), as long as that least
- *   scratch fits or the direct form is the one chosen; below it the last bits can
+ *   scratch fits or the direct form is the one chosen (and, with
+ *   CC_LADDER_SYMMETRIC_VECTORS, the pair-pair integral); below it the last bits can
  *   differ.  The order of the adjoint's sums and of the FP32 forms follows the blocks.
  * - Rounding errors of the folded forms are relative to the larger of R[i][j][a][b]
  *   and R[i][j][b][a] (dt alike).  Over the whole tensor they are no larger than the
