@@ -203,6 +203,10 @@ class PhaseTimer:
     def reset(self):
         self.spans = []
 
+    def blocks(self):
+        """Number of integral blocks that were built."""
+        return len({block for name, block, _, _ in self.spans if name == "build"})
+
     def summary(self):
         out = {}
         for name, _, a, b in self.spans:
@@ -236,7 +240,7 @@ def bench_form(native, form, L, t, R, out, ws_bytes, steps, warmup, o, v, P):
     prec = native.PRECISIONS[FORMS[form][0]]
     stream = torch.cuda.current_stream()
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
-    nbytes, n_a = native.cc_ladder_workspace_query(o, v, P, prec, hbm_budget=ws_bytes,
+    nbytes, _ = native.cc_ladder_workspace_query(o, v, P, prec, hbm_budget=ws_bytes,
                                                    opts=form_opts(native, form))
     timer = PhaseTimer(native, stream)
     opts = form_opts(native, form, workspace=ws, trace=timer.fn)
@@ -261,9 +265,10 @@ def bench_form(native, form, L, t, R, out, ws_bytes, steps, warmup, o, v, P):
     ms = evs[0].elapsed_time(evs[-1]) / steps
     per = [evs[k].elapsed_time(evs[k + 1]) for k in range(steps)]
     phases = timer.summary()
+    blocks = timer.blocks()
     del ws
     return {"ms_per_step": ms, "ms_std": statistics.pstdev(per), "ms_min": min(per),
-            "wall_s": wall, "a_block": n_a, "workspace_bytes": nbytes, "phases": phases}
+            "wall_s": wall, "blocks": blocks, "workspace_bytes": nbytes, "phases": phases}
 
 
 def rel_err_form(native, form, L, t, ref, idx_a, idx_b, ws_bytes):
@@ -395,7 +400,7 @@ def bench_adjoint(native, steps, forms=("fp64", "fp32", "fp64_pairsym", "fp32_pa
         ms = e0.elapsed_time(e1) / steps
         executed = adjoint_executed_flops(o, v, P, form.split("_")[0], sym, symv, n_a)
         res[form] = {"ms_per_step": ms, "tflops": flops / (ms * 1e-3) / 1e12,
-                     "tflops_executed": executed / (ms * 1e-3) / 1e12, "a_block": n_a,
+                     "tflops_executed": executed / (ms * 1e-3) / 1e12, "blocks": timer.blocks(),
                      "rel_err_vs_fp64_gpu": err,
                      "phases_ms_per_step": {k: d["ms_total"] / steps for k, d in timer.summary().items()}}
         log(f"adjoint {form}: {ms:.1f} ms {res[form]['tflops']:.1f} TFLOP/s "
@@ -464,7 +469,7 @@ def bench_large(native, forms=("fp64", "split_int8", "split_bf16"), budget_names
             continue
         for form in forms:
             prec, slices = native.PRECISIONS[FORMS[form][0]], FORMS[form][1]
-            nbytes, n_a = native.cc_ladder_workspace_query(
+            nbytes, _ = native.cc_ladder_workspace_query(
                 o, v, P, prec, hbm_budget=budget, opts=native.make_opts(split_slices=slices))
             ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
             timer = PhaseTimer(native, stream)
@@ -481,15 +486,16 @@ def bench_large(native, forms=("fp64", "split_int8", "split_bf16"), budget_names
             ms = timed(lambda: native.cc_ladder_residual(L, t, R, prec, opts=opts), timer, check)
             got = got[0]
             phases = {k: d["ms_total"] for k, d in timer.summary().items()}
+            blocks = timer.blocks()
             # release the workspace (the options hold a reference) before the next plan
             del ws, opts, timer
             torch.cuda.empty_cache()
-            r = {"ms": ms, "tflops": fwd / (ms * 1e-3) / 1e12, "a_block": n_a,
+            r = {"ms": ms, "tflops": fwd / (ms * 1e-3) / 1e12, "blocks": blocks,
                  "workspace_bytes": nbytes,
                  "rel_err_vs_oracle_sampled": float(np.linalg.norm(got - ref) / np.linalg.norm(ref)),
                  "phases_ms": phases}
             res[f"{form}_{bname}"] = r
-            log(f"large {form} budget {bname} ({budget / 2**30:.0f} GiB, a_block {n_a}): "
+            log(f"large {form} budget {bname} ({budget / 2**30:.0f} GiB, {blocks} blocks): "
                 f"{ms:.0f} ms {r['tflops']:.1f} TFLOP/s phases {json.dumps(r['phases_ms'])}")
     del R
     torch.cuda.empty_cache()
@@ -497,16 +503,17 @@ def bench_large(native, forms=("fp64", "split_int8", "split_bf16"), budget_names
         return res
     dL = torch.zeros_like(L)
     dt = torch.zeros_like(t)
-    nbytes, n_a = native.cc_ladder_workspace_query(o, v, P, native.CC_LADDER_FP32, backward=True,
-                                                   hbm_budget=budgets["device"])
+    nbytes, _ = native.cc_ladder_workspace_query(o, v, P, native.CC_LADDER_FP32, backward=True,
+                                                 hbm_budget=budgets["device"])
     ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     timer = PhaseTimer(native, stream)
     opts = native.make_opts(workspace=ws, trace=timer.fn)
     ms = timed(lambda: native.cc_ladder_backward(L, t, lam, dL, dt, native.CC_LADDER_FP32,
                                                  opts=opts), timer)
-    res["adjoint_fp32_device"] = {"ms": ms, "tflops": bwd / (ms * 1e-3) / 1e12, "a_block": n_a,
+    res["adjoint_fp32_device"] = {"ms": ms, "tflops": bwd / (ms * 1e-3) / 1e12,
+                                  "blocks": timer.blocks(),
                                   "phases_ms": {k: d["ms_total"] for k, d in timer.summary().items()}}
-    log(f"large adjoint fp32 (a_block {n_a}): {ms:.0f} ms "
+    log(f"large adjoint fp32 ({timer.blocks()} blocks): {ms:.0f} ms "
         f"{res['adjoint_fp32_device']['tflops']:.1f} TFLOP/s")
     return res
 
@@ -691,8 +698,7 @@ def main():
         r["tolerance"] = TOL[form]
         r["within_tolerance"] = err < TOL[form]
         r["design_bound"] = DESIGN_BOUND[form]
-        n_a = r["a_block"]
-        # dominant kernel: the amplitude contraction, 2 o^2 (n_a v) v^2 flops per full-block launch
+        # dominant kernel: the amplitude contraction, its flops over the blocks that ran
         c = r["phases"].get("contract")
         if c:
             per_step = c["launches"] / args.steps  # launches of the kernel in one step
@@ -714,7 +720,7 @@ def main():
         forms[form] = r
         log(f"{form}: {r['ms_per_step']:.1f} +- {r['ms_std']:.1f} (min {r['ms_min']:.1f}) ms/step "
             f"{r['tflops']:.2f} TFLOP/s err {err:.2e} "
-            f"a_block {n_a} phases {json.dumps(r['phases'])}")
+            f"blocks {r['blocks']} phases {json.dumps(r['phases'])}")
         R.zero_()
 
     head = forms.get(args.precision)
@@ -737,7 +743,7 @@ def main():
         "dtype": DTYPE[args.precision],
         "data": "synthetic",
         "config": {"workload": "ladder residual o=40 v=360 P=1200 (MP2-like amplitudes)",
-                   "o": o, "v": v, "P": P, "a_block": head["a_block"],
+                   "o": o, "v": v, "P": P, "blocks": head["blocks"],
                    "nominal_tflop_per_step": flops / 1e12, "precision": args.precision},
         "roofline": head.get("roofline"),
         "rel_err_vs_oracle": head["rel_err_vs_oracle"],
