@@ -834,8 +834,9 @@ int strict_pairs_before(int r, int o) {
 // run share a launch, K split where their grids leave compute units idle, and one
 // coalesced pass adds both to R.  max_splits 0: one product after the other into R,
 // whose transposed elements are then scattered read-modify-writes of 8 bytes.
-// o=13 v=97, two blocks: 860 -> 395 us; o=9 v=71: 114 -> 57 us; o=40 v=360 forward: 778 ->
-// 768 ms.
+// o=13 v=97, two blocks: 860 -> 395 us; o=9 v=71: 114 -> 58 us; o=40 v=360 forward: 778 ->
+// 768 ms; rows i <= j in three blocks of symmetric vectors 239 -> 235 ms (o=40 v=360), the
+// products there at 57 TFLOP/s on 64 x 128 tiles, and at 66 on 160 x 256 with all rows.
 template <class Tr>
 int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ldp,
                 const typename Tr::T* Tm, const typename Tr::T* Vm, long long ldm, double* R, int o,
@@ -1502,7 +1503,8 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
 // Bound by the matrix cores like the direct route, with half its multiply-adds
 // (P v^4 + o^2 v^4 instead of twice that) for the same bytes: the packed block is
 // written, read and rewritten combined where the direct route writes all of V_A.
-// o=40 v=360 P=1200: 1366 -> 778 ms; o=20 v=180 P=600: 34.2 -> 21.1 ms.
+// o=40 v=360 P=1200: 1365 -> 749 ms (builds 312, V+- 39, products 405); o=20 v=180 P=600:
+// 35.3 -> 20.0 ms.
 int forward_fold(const Plan& pl, const FoldPlan& f, const double* L, const double* t, double* R,
                  char* base, const Tracer& tr, hipStream_t s) {
   const int o = pl.o, v = pl.v, P = pl.P;
@@ -1762,8 +1764,7 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const double* __restrict
 // The float64 adjoint folded over the exchange of both virtual pairs (FoldAdjoint).
 // Matrix-bound: 3 P v^4 + 2 o^2 v^4 multiply-adds instead of the direct route's
 // (4 P + 4 o^2) v^4.  With odd v, dL runs on rows padded to whole 16-byte chunks.
-// o=30 v=300 P=900: 933 -> 608 ms (build 113, combinations 28, dt 120, W 107, S 38, dL
-// 240).
+// o=30 v=300 P=900: 933 -> 623 ms (build 115, V+- 19, dt 120, W 107, S 31, dL 231).
 int backward_fold(const Plan& pl, const FoldAdjoint& fa, const double* L, const double* t,
                   const double* lam, double* dL, double* dt, char* base, const Tracer& tr,
                   hipStream_t s) {
