@@ -830,9 +830,9 @@ int strict_pairs_before(int r, int o) {
 // i <= j and i < j when pairs is set).  `part`: scratch of `room` doubles that holds
 // nothing any more, for up to `max_splits` partials of both products: a number that
 // depends on the sizes alone, like the ranges of K, so that R does not depend on the
-// blocks; the rows are taken in runs whose partials fit the room.  The two products of a
-// run share a launch, K split where their grids leave compute units idle, and one
-// coalesced pass adds both to R.  max_splits 0: one product after the other into R,
+// blocks; the rows are taken in runs whose partials fit the room.  The two products of a run share a launch or (long ones, by the planner) take one
+// each, K split where their grids leave compute units idle, and one coalesced pass adds
+// both to R.  max_splits 0: one product after the other into R,
 // whose transposed elements are then scattered read-modify-writes of 8 bytes.
 // o=13 v=97, two blocks: 860 -> 395 us; o=9 v=71: 114 -> 58 us; o=40 v=360 forward: 778 ->
 // 768 ms; rows i <= j in three blocks of symmetric vectors 239 -> 235 ms (o=40 v=360), the
@@ -869,7 +869,8 @@ int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ld
   }
   constexpr int BK = kDRow / static_cast<int>(sizeof(T));
   const int chunk = Tr::kDrain ? drain : 1;
-  auto args = [&](const T* A, const T* B, long long ld, int M, int N, int K, double* C) {
+  auto args = [&](const T* A, const T* B, long long ld, int M, int N, int K, double* C, int bm,
+                  int bn) {
     GemmArgs<T> g;
     g.A = A; g.lda = ld;
     g.B = B; g.ldb = ld;
@@ -878,13 +879,33 @@ int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ld
     g.v = v; g.o = 0; g.a0 = 0; g.row_tiles = nullptr;
     g.alpha = 1.0;
     g.drain_steps = drain > 0 ? drain : 1;
-    g.tiles_m = (M + pick.bm - 1) / pick.bm;
-    g.tiles_n = (N + pick.bn - 1) / pick.bn;
+    g.tiles_m = (M + bm - 1) / bm;
+    g.tiles_n = (N + bn - 1) / bn;
     g.group_m = g.tiles_m < 16 ? g.tiles_m : 16;
     const int nk = (kp + BK - 1) / BK;  // the longer product's, so both have the same ranges
     g.split_steps = ((nk + pick.splits - 1) / pick.splits + chunk - 1) / chunk * chunk;
     g.part_stride = (long long)M * N;
     return g;
+  };
+  // n1 workgroups of the product g, n2 of h
+  auto launch = [&](int bm, int bn, const GemmArgs<T>& g, const GemmArgs<T>& h, long long n1,
+                    long long n2) {
+    if (n1 + n2 > 0x7fffffffLL) return CC_LADDER_EINVAL;
+    const dim3 grid(static_cast<unsigned>(n1 + n2)), block(kDThreads);
+    const int in1 = static_cast<int>(n1);
+    if (bm == 64 && bn == 64)
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 64>), grid, block, 0, s, g, h, in1);
+    else if (bm == 64 && bn == 128)
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 128>), grid, block, 0, s, g, h, in1);
+    else if (bm == 128 && bn == 256)
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 128, 256>), grid, block, 0, s, g, h, in1);
+    else if constexpr (!Tr::kDrain) {
+      if (bm != 160 || bn != 256) return CC_LADDER_EINVAL;
+      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 160, 256>), grid, block, 0, s, g, h, in1);
+    } else {
+      return CC_LADDER_EINVAL;  // no such kernel
+    }
+    return CC_LADDER_OK;
   };
   // rows of a run: all, or as many as fit the room
   const long long splits = pick.splits;
@@ -899,23 +920,13 @@ int pm_products(const typename Tr::T* Tp, const typename Tr::T* Vp, long long ld
       pick = pick_pair_products(whole, PairExtents{rows, np, rows_m, nm}, kp, sizeof(T), chunk,
                                 max_splits);
     double* Pm = part + splits * rows * np;
-    const GemmArgs<T> g = args(Tp + r0 * ldp, Vp, ldp, rows, np, kp, part);
-    const GemmArgs<T> h = args(Tm + m0 * ldm, Vm, ldm, rows_m, nm, km, Pm);
+    const GemmArgs<T> g = args(Tp + r0 * ldp, Vp, ldp, rows, np, kp, part, pick.bm, pick.bn);
+    const GemmArgs<T> h = args(Tm + m0 * ldm, Vm, ldm, rows_m, nm, km, Pm, pick.bm2, pick.bn2);
     const long long n1 = (long long)g.tiles_m * g.tiles_n * splits;
     const long long n2 = rows_m > 0 && nm > 0 ? (long long)h.tiles_m * h.tiles_n * splits : 0;
-    if (n1 + n2 > 0x7fffffffLL) return CC_LADDER_EINVAL;
-    const dim3 grid(static_cast<unsigned>(n1 + n2)), block(kDThreads);
-    const int in1 = static_cast<int>(n1);
-    if (pick.bn == 64)
-      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 64>), grid, block, 0, s, g, h, in1);
-    else if (pick.bn == 128)
-      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 64, 128>), grid, block, 0, s, g, h, in1);
-    else if (pick.bm == 128)
-      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 128, 256>), grid, block, 0, s, g, h, in1);
-    else if constexpr (!Tr::kDrain)
-      hipLaunchKernelGGL((gemm_kc_two_kernel<Tr, 160, 256>), grid, block, 0, s, g, h, in1);
-    else
-      return CC_LADDER_EINVAL;  // no such kernel
+    int rc = launch(pick.bm, pick.bn, g, h, n1, pick.apart ? 0 : n2);
+    if (!rc && pick.apart && n2 > 0) rc = launch(pick.bm2, pick.bn2, g, h, 0, n2);
+    if (rc) return rc;
     const long long ta = (na + kSwapTile - 1) / kSwapTile, tb = (v - a0 + kSwapTile - 1) / kSwapTile;
     const long long blocks = std::min<long long>(rows * ta * tb, 65536);
     hipLaunchKernelGGL(pm_combine_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s,

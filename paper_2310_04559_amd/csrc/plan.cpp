@@ -715,26 +715,46 @@ PairPick pick_pair_products(const PairExtents& whole, const PairExtents& block, 
   const double kPartial = 16.0 * 0.14e12 / 4e12 * (es == 4 ? 2.0 : 1.0);
   const struct { int bm, bn; double rate; } tiles[] = {
       {160, 256, 0.86}, {128, 256, 0.86}, {64, 128, 0.82}, {64, 64, 0.78}};
-  struct Counts { long long n[4]; double values; };
+  struct Counts { long long p[4], m[4]; double values; };  // tiles of either product
   auto count = [&](const PairExtents& e) {
-    Counts c{{}, static_cast<double>(e.mp) * e.np + static_cast<double>(e.mm) * e.nm};
-    for (int i = 0; i < 4; ++i)
-      c.n[i] = ((e.mp + tiles[i].bm - 1) / tiles[i].bm) * ((e.np + tiles[i].bn - 1) / tiles[i].bn) +
-               ((e.mm + tiles[i].bm - 1) / tiles[i].bm) * ((e.nm + tiles[i].bn - 1) / tiles[i].bn);
+    Counts c{{}, {}, static_cast<double>(e.mp) * e.np + static_cast<double>(e.mm) * e.nm};
+    for (int i = 0; i < 4; ++i) {
+      c.p[i] = ((e.mp + tiles[i].bm - 1) / tiles[i].bm) * ((e.np + tiles[i].bn - 1) / tiles[i].bn);
+      c.m[i] = ((e.mm + tiles[i].bm - 1) / tiles[i].bm) * ((e.nm + tiles[i].bn - 1) / tiles[i].bn);
+    }
     return c;
   };
   auto best_tile = [&](const Counts& c, int s, PairPick* p) {
     double best = 0.0;
     const double steps = static_cast<double>(steps_of(s)) * bk;
+    auto time = [&](long long n, int i) {
+      return static_cast<double>((n * s + 255) / 256) * tiles[i].bm * tiles[i].bn * steps / tiles[i].rate;
+    };
     for (int i = es == 4 ? 1 : 0; i < 4; ++i) {
       const auto& t = tiles[i];
-      const double cost = static_cast<double>((c.n[i] * s + 255) / 256) * t.bm * t.bn * steps / t.rate;
+      const double cost = time(c.p[i] + c.m[i], i);
       if (best == 0.0 || cost < best) {
         best = cost;
-        p->bm = t.bm;
-        p->bn = t.bn;
+        p->bm = p->bm2 = t.bm;
+        p->bn = p->bn2 = t.bn;
+        p->apart = false;
       }
     }
+    // Two launches on tiles of different heights where the rows of both products then
+    // end on whole rounds and a round is long: o=40 v=360, rows 820 and 780 in 7 rounds of
+    // 128 and 5 of 160, 220 -> 211 ms; o=60 v=360 492 -> 465.  Shorter ones leave more idle
+    // between the launches (o=36 v=160 7.0 -> 7.3 ms).
+    if (es == 8 && kp >= 32768)
+      for (int i = 0; i < 2; ++i) {
+        const int j = 1 - i;
+        const double cost = time(c.p[i], i) + time(c.m[j], j);
+        if (cost >= 0.975 * best) continue;
+        best = cost;
+        p->bm = tiles[i].bm;
+        p->bm2 = tiles[j].bm;
+        p->bn = p->bn2 = tiles[i].bn;
+        p->apart = true;
+      }
     return best + c.values * s * kPartial;
   };
   const Counts all = count(whole);

@@ -226,7 +226,7 @@ TilePick pick_part_tiles(long long M, long long N, long long K, int splits, long
 bool split_pays(const TilePick& part, long long M, long long N, long long K, int splits,
                 long long units, int es);
 
-// The two products of a +- contraction in one launch of float64 partials that a
+// The two products of a +- contraction as float64 partials, in one launch, that a
 // pass combines into R: K cut into `splits` ranges of whole drain chunks (`chunk`
 // K-steps; 1 in float64), tiles of bm x bn.
 constexpr int kPairSplits = 16;  // at most
@@ -234,7 +234,9 @@ struct PairExtents {
   long long mp = 0, np = 0, mm = 0, nm = 0;  // rows and columns of the + and - products
 };
 struct PairPick {
-  int bm = 0, bn = 0;
+  int bm = 0, bn = 0;    // tiles of the + product
+  int bm2 = 0, bn2 = 0;  // and of the - product: the same, or
+  bool apart = false;    // ... each product a launch of its own, on its own tiles
   int splits = 0;  // 0: no room for one partial of each
   double cost = 0.0;  // time of the block's launch, as TilePick's times K
 };

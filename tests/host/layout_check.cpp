@@ -179,8 +179,11 @@ static void picks(std::mt19937_64& rng) {
     const PairExtents e{M, N, M - 1, N - 1};
     const PairPick r = pick_pair_products(e, e, K, es, es == 4 ? 16 : 1, rng() % 20);
     CHECK(r.splits >= 0 && r.splits <= kPairSplits);
-    CHECK(!r.splits || (r.bn == 256 && (r.bm == 128 || (r.bm == 160 && es == 8))) ||
-          (r.bm == 64 && (r.bn == 128 || r.bn == 64)));
+    auto tile = [&](int bm, int bn) {
+      return (bn == 256 && (bm == 128 || (bm == 160 && es == 8))) || (bm == 64 && (bn == 128 || bn == 64));
+    };
+    CHECK(!r.splits || (tile(r.bm, r.bn) && tile(r.bm2, r.bn2)));
+    CHECK(r.apart || (r.bm == r.bm2 && r.bn == r.bn2));
   }
 }
 

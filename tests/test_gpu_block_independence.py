@@ -42,6 +42,27 @@ def test_plus_minus_symmetric_vectors(gpu_lib, o, v, P, precision, exchange):
         assert torch.equal(_residual(gpu_lib, Ld, td, precision, a_block=a_block, **kw), one), a_block
 
 
+# long rows: the two products of one block in a launch each, on tiles of 160 and 128 rows,
+# against blocks in one launch
+@pytest.mark.parametrize("o,v,P,symv", [(16, 256, 3, False)])
+def test_plus_minus_long_rows(gpu_lib, o, v, P, symv):
+    import torch
+
+    announce("blocks-pm-long", o, v, P, "symv", symv)
+    L, t, _ = random_general(o, v, P, 6050 + o + v)
+    L = 0.5 * (L + L.transpose(0, 2, 1))
+    t = 0.5 * (t + t.transpose(1, 0, 3, 2))
+    Ld, td = dev(L), dev(t)
+    kw = dict(pair_symmetric=True, plus_minus=True, symmetric_vectors=symv)
+    one = _residual(gpu_lib, Ld, td, 0, **kw)
+    pairs = [(0, 0), (v - 1, v - 1), (0, v - 1), (v - 1, 0), (127, 128), (v // 2, 3), (31, 32), (200, 77)]
+    ref = np.stack(list(oracle.ladder_pairs(L, t, pairs)))
+    got = one[:, :, [a for a, _ in pairs], [b for _, b in pairs]].permute(2, 0, 1)
+    assert rel_fro(host(got), ref) < TOL[0]
+    for a_block in (v - 1, v // 2, v // 3):
+        assert torch.equal(_residual(gpu_lib, Ld, td, 0, a_block=a_block, **kw), one), a_block
+
+
 def _folded(native, Ld, td, **kw):
     """Whether the float64 forward is folded: it then prepares amplitudes without being
     the exchange partner, or runs in other blocks than the plan's."""
