@@ -1491,10 +1491,34 @@ int forward_blocks_pm(const Plan& pl, const typename Tr::T* L, const typename Tr
       if (pl.nblocks == 1)
         room = static_cast<long long>(pl.off_G - pl.off_Lp) / 8 + pl.ldg * pl.ldg * es / 8;
     }
+    const int kp = static_cast<int>((long long)v * (v + 1) / 2), mp = o * (o + 1) / 2, mm = mp - o;
+    const PairExtents all{mp, kp, mm, kp - v};
+    auto pick = [&](const PairExtents& e) {
+      return pick_pair_products(all, e, kp, es, Tr::kDrain ? drain : 1, splits);
+    };
+    const long long ranges = pick(all).splits;
     for (int c0 = a0; !rc && c0 < a0 + na;) {
-      // the block's virtuals, or (few vectors) as many as leave a row room
       int nc = a0 + na - c0;
       auto pairs = [&](int n) { return pair_prefix(c0 + n, v) - pair_prefix(c0, v); };
+      auto extents = [&](int n) { return PairExtents{mp, pairs(n), mm, pairs(n) - n}; };
+      // the block's virtuals, or as many as leave all rows room, by the time that all take:
+      // a launch holds the same number of tiles whatever is cut, and only columns are fine
+      // enough to end on whole rounds (o=44 v=400 P=444, two blocks: 598 ms in runs of
+      // rows, 540 so) ...
+      if (ranges * (mp * pairs(nc) + mm * (pairs(nc) - nc)) > room) {
+        double best = 0.0;
+        int cut = 0;
+        for (int n = 1; n < nc && ranges * (mp * pairs(n) + mm * (pairs(n) - n)) <= room; ++n) {
+          const long long full = pairs(nc) / pairs(n), rest = pairs(nc) % pairs(n);
+          double cost = full * (pick(extents(n)).cost + 10e-6 * 0.14e12);  // (10 us of launches)
+          if (rest) cost += pick(PairExtents{mp, rest, mm, rest}).cost;
+          if (cut && cost > best) continue;
+          best = cost;
+          cut = n;
+        }
+        if (cut && pairs(cut) >= 512) nc = cut;
+      }
+      // ... or (few vectors) as many as leave a row room
       while (nc > 1 && std::min<long long>(splits, kPairSplits) * 2 * pairs(nc) > room) nc = (nc + 1) / 2;
       const long long before = pair_prefix(c0, v) - pair_prefix(a0, v);
       rc = pm_products<Tr>(Tp, Vp + before * pl.ldp, pl.ldp, Tm, Vm + (before - (c0 - a0)) * pl.ldm,

@@ -43,8 +43,9 @@ def test_plus_minus_symmetric_vectors(gpu_lib, o, v, P, precision, exchange):
 
 
 # long rows: the two products of one block in a launch each, on tiles of 160 and 128 rows,
-# against blocks in one launch
-@pytest.mark.parametrize("o,v,P,symv", [(16, 256, 3, False)])
+# against blocks in one launch; and, of few vectors in several blocks, cut once more into
+# virtuals whose partial sums the packed vectors' room holds
+@pytest.mark.parametrize("o,v,P,symv", [(16, 256, 3, False), (16, 261, 40, True), (25, 256, 30, True)])
 def test_plus_minus_long_rows(gpu_lib, o, v, P, symv):
     import torch
 
